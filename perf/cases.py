@@ -13,6 +13,7 @@ from __future__ import annotations
 import math
 
 import torch
+import torch.nn.functional as F
 
 import paper_2508_11584_amd as vpe
 import vpe_inputs as vi
@@ -205,6 +206,18 @@ def _dpt_std(name, shape):
     return math.sqrt(2.0 / (shape[0] if name.startswith("up") else math.prod(shape[1:])))
 
 
+def _blobs(case):
+    """The weights of the case's configuration: one blob per head, and the backbone's (in fp32, on the host)."""
+    s = _spec(case)
+    gen = torch.Generator("cuda").manual_seed(1000 + s.dim)
+    quantize = s.dtype == "bf16"
+    heads = []
+    for kind in _heads(case):
+        layout = vi.head_layout(s, HEAD_KIND[kind])
+        heads.append(_weights(layout, gen, quantize, _dpt_std) if kind == "dpt" else _weights(layout, gen, quantize))
+    return heads, _weights(vi.backbone_layout(s), gen, quantize)
+
+
 _kept = {}
 
 
@@ -214,20 +227,16 @@ def _engine(case):
     if key not in _kept:
         _kept.clear()
         s, kinds = _spec(case), _heads(case)
-        gen = torch.Generator("cuda").manual_seed(1000 + s.dim)
-        quantize = s.dtype == "bf16"
-        cfgs = []
-        for kind, n in zip(kinds, _every(case)):
-            layout = vi.head_layout(s, HEAD_KIND[kind])
-            blob = _weights(layout, gen, quantize, _dpt_std) if kind == "dpt" else _weights(layout, gen, quantize)
-            cfgs.append(vpe.HeadCfg(kind=HEAD_KIND[kind], weights=blob, every_n=n, channels=0 if kind == "seg" else s.head_ch,
-                                    classes={"seg": s.seg_classes, "det": s.det_classes}.get(kind, 0)))
+        blobs, backbone = _blobs(case)
+        cfgs = [vpe.HeadCfg(kind=HEAD_KIND[kind], weights=blob, every_n=n, channels=0 if kind == "seg" else s.head_ch,
+                            classes={"seg": s.seg_classes, "det": s.det_classes}.get(kind, 0))
+                for kind, blob, n in zip(kinds, blobs, _every(case))]
         lanes = case["lanes"]
         engine = vpe.Engine(dim=s.dim, depth=s.depth, heads=s.heads, mlp_hidden=s.mlp_hidden, mlp_kind=s.mlp_kind,
                             registers=s.registers, img_h=s.img_h, img_w=s.img_w, batch=s.batch,
-                            dtype=vpe.VPE_BF16 if quantize else vpe.VPE_F32, taps=s.taps, ring_slots=lanes + 1,
+                            dtype=vpe.VPE_BF16 if s.dtype == "bf16" else vpe.VPE_F32, taps=s.taps, ring_slots=lanes + 1,
                             encoder_lanes=lanes, flags=vpe.VPE_FLAG_GRAPHS if case["graphs"] else 0,
-                            weights=_weights(vi.backbone_layout(s), gen, quantize), head_cfgs=cfgs)
+                            weights=backbone, head_cfgs=cfgs)
         # the head's results stay in buffers of the engine: views of them are taken once
         views = {"%d_%s%d" % (i, kind, which): engine.head_output(i, which)
                  for i, kind in enumerate(kinds) for which in range(2 if kind in ("seg", "det") else 1)}
@@ -290,3 +299,115 @@ def run(state):
         for h in state["heads"]:
             engine.run_head(h, frame)
     return {"features": [engine.feat_view(frame, k) for k in range(4)], **state["views"]}
+
+
+# ------------------------------------------------------------------ the same in 64 bits, in plain torch
+def _named(layout, blob):
+    x, at, out = torch.from_numpy(blob).cuda().double(), 0, {}
+    for name, shape in layout:
+        n = math.prod(shape)
+        out[name] = x[at:at + n].view(shape)
+        at += n
+    return out
+
+
+def _resized(x, size, aligned=False):
+    return F.interpolate(x.permute(0, 3, 1, 2), size=size, mode="bilinear", align_corners=aligned).permute(0, 2, 3, 1)
+
+
+def _conv3(x, w, b=None, stride=1):
+    """3x3, padding 1, of channels-last maps: the nine taps as matrix products."""
+    p = F.pad(x, (0, 0, 1, 1, 1, 1))
+    H, W = x.shape[1], x.shape[2]
+    y = sum(p[:, dy:dy + H:stride, dx:dx + W:stride] @ w[:, :, dy, dx].T.contiguous() for dy in range(3) for dx in range(3))
+    return y if b is None else y + b
+
+
+def _encoded(s, w, image):
+    """The four feature maps of one image [3][H][W]."""
+    D, heads, eps = s.dim, s.heads, s.ln_eps
+    cells = F.unfold(image[None], 14, stride=14)[0].T                   # [P][3 * 14 * 14]
+    x = torch.cat((w["cls"][None] + w["pos"][:1], w["reg"], cells @ w["patch_w"].view(D, -1).T + w["patch_b"] + w["pos"][1:]))
+    maps = []
+    for l in range(s.depth):
+        p = {k: w["blk%d.%s" % (l, k)] for k in ("ln1_g", "ln1_b", "qkv_w", "qkv_b", "proj_w", "proj_b", "ls1", "ln2_g",
+                                                 "ln2_b", "fc1_w", "fc1_b", "fc2_w", "fc2_b", "ls2")}
+        u = F.layer_norm(x, (D,), p["ln1_g"], p["ln1_b"], eps) @ p["qkv_w"] + p["qkv_b"]
+        q, k, v = (t.contiguous() for t in u.view(-1, 3, heads, 64).permute(1, 2, 0, 3))
+        a = torch.cat([torch.softmax(q[h] @ k[h].T * 0.125, -1) @ v[h] for h in range(heads)], 1)
+        x = x + p["ls1"] * (a @ p["proj_w"] + p["proj_b"])
+        u = F.layer_norm(x, (D,), p["ln2_g"], p["ln2_b"], eps) @ p["fc1_w"] + p["fc1_b"]
+        u = F.silu(u[:, :s.mlp_hidden]) * u[:, s.mlp_hidden:] if s.mlp_kind == vi.MLP_SWIGLU else F.gelu(u)
+        x = x + p["ls2"] * (u @ p["fc2_w"] + p["fc2_b"])
+        if l + 1 in s.taps:
+            maps.append(F.layer_norm(x, (D,), w["norm_g"], w["norm_b"], eps))
+    return maps
+
+
+def _head_exact(s, kind, w, maps):
+    """A head's first output from the patch grids [B][gh][gw][D] of the four maps."""
+    gh, gw, H, W = s.gh, s.gw, s.img_h, s.img_w
+    if kind == "seg":
+        return maps[3] @ w["seg_w"].T + w["seg_b"]
+    if kind == "det":
+        towers = [F.relu(_conv3(maps[3], w[t + "_tower_w"], w[t + "_tower_b"])) for t in ("cls", "box")]
+        return torch.cat((towers[0] @ w["cls_w"].T + w["cls_b"], towers[1] @ w["box_w"].T + w["box_b"]), -1)
+    if kind == "depth":
+        y = 0.0
+        for k in range(4):
+            size = (gh << k, gw << k)
+            z = _resized(maps[3 - k] @ w["proj%d_w" % k].T + w["proj%d_b" % k], size) + y
+            z = F.relu(_conv3(z, w["fuse%d_w" % k], w["fuse%d_b" % k]))
+            y = _resized(z, (2 * size[0], 2 * size[1])) if k < 3 else _resized(z @ w["out_w"].T, (2 * size[0], 2 * size[1]))
+        return F.relu(_resized(y + w["out_b"], (H, W)))[..., 0]
+    levels = []
+    for i in range(4):
+        r = maps[i] @ w["proj%d_w" % i].T + w["proj%d_b" % i]
+        if i < 2:                                                        # transposed convolution, kernel = stride = k
+            k = 4 >> i
+            r = torch.einsum("bhwc,coyx->bhywxo", r, w["up%d_w" % i]).reshape(r.shape[0], gh * k, gw * k, -1) + w["up%d_b" % i]
+        elif i == 3:
+            r = _conv3(r, w["down3_w"], w["down3_b"], 2)
+        levels.append(_conv3(r, w["rn%d_w" % i]))
+    unit = lambda x, n: x + _conv3(F.relu(_conv3(F.relu(x), w[n + "_c1_w"], w[n + "_c1_b"])), w[n + "_c2_w"], w[n + "_c2_b"])  # noqa: E731
+    path = None
+    for k in (3, 2, 1, 0):
+        y = levels[k] if path is None else path + unit(levels[k], "fuse%d_a" % k)
+        y = unit(y, "fuse%d_b" % k)
+        size = levels[k - 1].shape[1:3] if k else (2 * y.shape[1], 2 * y.shape[2])
+        path = _resized(y, tuple(size), True) @ w["fuse%d_out_w" % k].T + w["fuse%d_out_b" % k]
+    u = _resized(_conv3(path, w["head1_w"], w["head1_b"]), (H, W), True)
+    u = F.relu(_conv3(u, w["head2_w"], w["head2_b"]))
+    return F.relu(u @ w["head3_w"].T + w["head3_b"])[..., 0]
+
+
+def exact(case, seed):
+    """What `run` leaves behind, in 64 bits (class maps have no such value).  A camera's frame is resized and normalised in
+    64 bits as well; weights are those of the engine, in bf16 where it holds them so."""
+    mean, std = (torch.tensor(v, dtype=torch.float64, device="cuda").view(3, 1, 1) for v in (vi.CAMERA_MEAN, vi.CAMERA_STD))
+
+    def transformed(frames):
+        x = F.interpolate(frames.permute(0, 3, 1, 2).double() / 255.0, size=(case["h"], case["w"]), mode="bilinear", align_corners=False)
+        return (x - mean) / std
+
+    gen = torch.Generator("cuda").manual_seed(seed)
+    if case["kind"] == "transform":
+        return transformed(_camera_frames(gen, case["batch"], case["src_h"], case["src_w"])[0])
+    s, kinds = _spec(case), _heads(case)
+    if case["camera"]:
+        images = [transformed(x) for x in _camera_frames(gen, case["batch"], 1080, 1920, case["frames"])]
+    else:
+        x = _field(gen, case["batch"], case["h"], case["w"], case["frames"])
+        images = [i.double() for i in (x - x.mean((3, 4), keepdim=True)) / x.std((3, 4), keepdim=True)]
+    blobs, backbone = _blobs(case)
+    w = _named(vi.backbone_layout(s), backbone)
+    last = len(images) - 1
+    frames = {last - last % n for n in _every(case)} | {last}          # the frames that the outputs belong to
+    maps = {f: [torch.stack(m) for m in zip(*(_encoded(s, w, image) for image in images[f]))] for f in frames}
+    out = {"features": maps[last]}
+    for i, (kind, blob, n) in enumerate(zip(kinds, blobs, _every(case))):
+        grids = [m[:, 1 + s.registers:].reshape(s.batch, s.gh, s.gw, s.dim) for m in maps[last - last % n]]
+        out["%d_%s0" % (i, kind)] = _head_exact(s, kind, _named(vi.head_layout(s, HEAD_KIND[kind]), blob), grids)
+        if kind in ("seg", "det"):
+            out["%d_%s1" % (i, kind)] = None
+    return out
