@@ -200,21 +200,72 @@ __device__ __forceinline__ void store8(float* dst, const float* v) {
     *reinterpret_cast<f32x4*>(dst + 4) = f32x4{v[4], v[5], v[6], v[7]};
 }
 
-// Epilogue of one row chunk: columns c .. c + 7 of logical row r (r < M, c < N, c % 8 == 0), the raw
-// accumulators in v.  Full, aligned chunks go out as 16-byte stores; ragged ones element by element.
-template <typename T>
-__device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, int r, int c, float* v) {
-    const int nv = p.N - c < 8 ? p.N - c : 8;
+// Epilogue of row chunks: a lane keeps eight consecutive columns and visits several rows.  What it needs of the columns is
+// loaded once (EpiCols); what it needs of a row (residual values, positional row, added maps: EpiRow) is loaded for a
+// whole batch of rows before the first of them is stored.  Taken row by row -- the compiler cannot move a row's loads
+// above the previous row's stores -- every row pays a memory latency: a 256 x 256 tile spent 21 us on its 16 dependent
+// rows per lane (bias, LayerScale and the residual values fetched behind each other), a 64 x 128 tile 3.5 us.
+struct EpiCols { f32x4 b0, b1, g0, g1; int c, nv; };      // nv: columns of the chunk that exist (8, fewer at a ragged edge, <= 0: none)
+struct EpiRow { int orow; f32x4 a0, a1; float lev; };
+
+__device__ __forceinline__ EpiCols epilogue_cols(const GemmArgs& p, int c) {
+    EpiCols k;
+    k.c = c;
+    k.nv = p.N - c < 8 ? p.N - c : 8;
+    k.b0 = k.b1 = k.g0 = k.g1 = f32x4{0, 0, 0, 0};
     if (p.bias) {
-        if (nv == 8) {
-            const f32x4 b0 = *reinterpret_cast<const f32x4*>(p.bias + c), b1 = *reinterpret_cast<const f32x4*>(p.bias + c + 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { v[i] += b0[i]; v[4 + i] += b1[i]; }
+        if (k.nv == 8) {
+            k.b0 = *reinterpret_cast<const f32x4*>(p.bias + c);
+            k.b1 = *reinterpret_cast<const f32x4*>(p.bias + c + 4);
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) if (i < nv) v[i] += p.bias[c + i];
+            for (int i = 0; i < 4; ++i) {
+                if (i < k.nv) k.b0[i] = p.bias[c + i];
+                if (4 + i < k.nv) k.b1[i] = p.bias[c + 4 + i];
+            }
         }
     }
+    if (p.epi == EPI_RESID && k.nv == 8) {
+        k.g0 = *reinterpret_cast<const f32x4*>(p.gamma + c);
+        k.g1 = *reinterpret_cast<const f32x4*>(p.gamma + c + 4);
+    }
+    return k;
+}
+
+// Row r of the output: its place under the row map and the operands of its chunk (loads only; ok: r < M and the chunk exists).
+__device__ __forceinline__ EpiRow epilogue_row_operands(const GemmArgs& p, const EpiCols& k, int r, bool ok) {
+    EpiRow e;
+    e.orow = r;
+    e.a0 = e.a1 = f32x4{0, 0, 0, 0};
+    e.lev = 0.0f;
+    if (!ok) return e;
+    const float* src = nullptr;
+    if (p.epi == EPI_STORE) {
+        // (the plain map, one run of rows, needs no division)
+        e.orow = p.o_rpi >= p.M ? p.o_off + r : (r / p.o_rpi) * p.o_istride + p.o_off + r % p.o_rpi;
+        if (p.add1) src = p.add1 + (int64_t)e.orow * p.ldo + k.c;
+    } else if (p.epi == EPI_RESID) {
+        src = reinterpret_cast<const float*>(p.out) + (int64_t)e.orow * p.ldo + k.c;
+    } else if (p.epi == EPI_PATCH) {
+        const int b = r / p.o_rpi, pp = r - b * p.o_rpi;
+        e.orow = b * p.o_istride + p.o_off + pp;
+        src = p.pos + (int64_t)pp * p.N + k.c;
+    }
+    if (src) {
+        e.a0 = *reinterpret_cast<const f32x4*>(src);
+        e.a1 = *reinterpret_cast<const f32x4*>(src + 4);
+    }
+    if (p.xb_level) e.lev = p.xb_level[e.orow];
+    return e;
+}
+
+// Columns k.c .. of the row of `e`, the raw accumulators in v.  Full, aligned chunks go out as 16-byte stores; ragged
+// ones element by element.  RESID / PATCH leave the updated residual values in v.
+template <typename T>
+__device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, const EpiCols& k, const EpiRow& e, float* v) {
+    const int nv = k.nv;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[i] += k.b0[i]; v[4 + i] += k.b1[i]; }
     if (p.epi == EPI_STORE) {
         if (p.act == ACT_RELU) {
 #pragma unroll
@@ -223,15 +274,12 @@ __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, int r, int c, 
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = gelu_for<T>(v[i]);
         }
-        const int64_t orow = (int64_t)(r / p.o_rpi) * p.o_istride + p.o_off + r % p.o_rpi;
         if (p.add1) {
-            const float* a = p.add1 + orow * p.ldo + c;
-            const f32x4 a0 = *reinterpret_cast<const f32x4*>(a), a1 = *reinterpret_cast<const f32x4*>(a + 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { v[i] += a0[i]; v[4 + i] += a1[i]; }
+            for (int i = 0; i < 4; ++i) { v[i] += e.a0[i]; v[4 + i] += e.a1[i]; }
         }
         if (p.add2) {
-            const float* a = p.add2 + orow * p.ldo + c;
+            const float* a = p.add2 + (int64_t)e.orow * p.ldo + k.c;
             const f32x4 a0 = *reinterpret_cast<const f32x4*>(a), a1 = *reinterpret_cast<const f32x4*>(a + 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[i] += a0[i]; v[4 + i] += a1[i]; }
@@ -240,17 +288,17 @@ __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, int r, int c, 
             float t[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) t[i] = p.twin_relu ? fmaxf(v[i], 0.0f) : v[i];
-            store8(reinterpret_cast<T*>(p.twin) + orow * p.ldo + c, t);
+            store8(reinterpret_cast<T*>(p.twin) + (int64_t)e.orow * p.ldo + k.c, t);
         }
         if (p.out_f32) {
-            float* dst = reinterpret_cast<float*>(p.out) + orow * p.ldo + c;
+            float* dst = reinterpret_cast<float*>(p.out) + (int64_t)e.orow * p.ldo + k.c;
             if (nv == 8 && (p.ldo & 3) == 0) store8(dst, v);
             else {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) if (i < nv) dst[i] = v[i];
             }
         } else {
-            T* dst = reinterpret_cast<T*>(p.out) + orow * p.ldo + c;
+            T* dst = reinterpret_cast<T*>(p.out) + (int64_t)e.orow * p.ldo + k.c;
             if (nv == 8 && (p.ldo & 7) == 0) store8(dst, v);
             else {
 #pragma unroll
@@ -259,25 +307,22 @@ __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, int r, int c, 
         }
     } else if (p.epi == EPI_RESID || p.epi == EPI_PATCH) {
         // fp32 residual stream, N = ldo = model width (multiple of 64): always full aligned chunks
-        int64_t orow = r;
         if (p.epi == EPI_PATCH) {
-            const int b = r / p.o_rpi, pp = r % p.o_rpi;
-            orow = (int64_t)b * p.o_istride + p.o_off + pp;
-            const float* ps = p.pos + (int64_t)pp * p.N + c;
-            const f32x4 p0 = *reinterpret_cast<const f32x4*>(ps), p1 = *reinterpret_cast<const f32x4*>(ps + 4);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { v[i] += p0[i]; v[4 + i] += p1[i]; }
-        }
-        float* x = reinterpret_cast<float*>(p.out) + orow * p.ldo + c;
-        if (p.epi == EPI_RESID) {
-            const f32x4 g0 = *reinterpret_cast<const f32x4*>(p.gamma + c), g1 = *reinterpret_cast<const f32x4*>(p.gamma + c + 4);
-            const f32x4 x0 = *reinterpret_cast<const f32x4*>(x), x1 = *reinterpret_cast<const f32x4*>(x + 4);
+            for (int i = 0; i < 4; ++i) { v[i] += e.a0[i]; v[4 + i] += e.a1[i]; }
+        } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { v[i] = x0[i] + g0[i] * v[i]; v[4 + i] = x1[i] + g1[i] * v[4 + i]; }
+            for (int i = 0; i < 4; ++i) { v[i] = e.a0[i] + k.g0[i] * v[i]; v[4 + i] = e.a1[i] + k.g1[i] * v[4 + i]; }
         }
-        store8(x, v);
+        store8(reinterpret_cast<float*>(p.out) + (int64_t)e.orow * p.ldo + k.c, v);
+        if (p.xb_out) {
+            float rel[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) rel[i] = v[i] - e.lev;
+            store8(reinterpret_cast<T*>(p.xb_out) + (int64_t)e.orow * p.ldo + k.c, rel);
+        }
     } else {   // EPI_QKV, query / key columns
-        store8(reinterpret_cast<T*>(p.out) + (int64_t)r * p.ldo + c, v);
+        store8(reinterpret_cast<T*>(p.out) + (int64_t)e.orow * p.ldo + k.c, v);
     }
 }
 
@@ -302,7 +347,7 @@ __device__ __forceinline__ float rowdot_chunk(const GemmArgs& p, int c, const fl
 // (or the end of the matrix) goes element by element.
 template <typename T>
 __device__ __forceinline__ void store_tokens8(const GemmArgs& p, T* vt, int r, int c2, const float* v) {
-    const int b = r / p.ntok, n = r - b * p.ntok;
+    const int b = p.M <= p.ntok ? 0 : r / p.ntok, n = r - b * p.ntok;     // (one image: no division)
     T* dst = vt + ((int64_t)b * p.dim + c2) * p.npad + n;
     if (n + 8 <= p.ntok && r + 8 <= p.M) {
         if ((n & 7) == 0) {
@@ -356,56 +401,57 @@ __device__ __forceinline__ void ln_row_stats(const GemmArgs& p, int r, float& me
     rstd = 1.0f / sqrtf(m2 / (64.0f * G) + p.ln_eps);
 }
 
-// Consumer prologue, one thread per tile row: (mean relative to the level A was stored against, rstd) into
-// lnrow, and the row's mean handed on as the next level by the first column block's tiles.
-__device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, int t, float* lnrow) {
+// Consumer prologue, one thread per tile row: the row's mean relative to the level A was stored against and its rstd;
+// the mean itself is handed on as the next level by the first column block's tiles.
+__device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, int t, float& mean, float& rstd) {
     const bool real = m0 + t < p.M;
     const int r = real ? m0 + t : p.M - 1;
-    float mean, rstd;
     ln_row_stats(p, r, mean, rstd);
-    lnrow[2 * t] = mean - (p.ln_level ? p.ln_level[r] : 0.0f);
-    lnrow[2 * t + 1] = rstd;
     if (p.ln_level_out && n0 == 0 && real) p.ln_level_out[r] = mean;
+    if (p.ln_level) mean -= p.ln_level[r];
+}
+__device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, int t, float* lnrow) {
+    float mean, rstd;
+    ln_tile_row(p, m0, n0, t, mean, rstd);
+    lnrow[2 * t] = mean;
+    lnrow[2 * t + 1] = rstd;
 }
 
-// RESID / PATCH chunk with the producer-side extras.  Called by all 8 lanes that hold the 8 chunks of one
-// 64-column group of a row (consecutive lanes, chunk index = lane % 8); `active` is the same for all of them.
+// The value of the lane 1, 2 or (for values equal within every four lanes) 4 away among eight consecutive lanes, on the
+// vector ALU (row permutations; an exchange through the LDS crossbar takes ~100 clocks, six of them in a row per chunk).
+template <int O>
+__device__ __forceinline__ float lane_across(float v) {
+    static_assert(O == 1 || O == 2 || O == 4, "");
+    constexpr int ctrl = O == 1 ? 0xB1 : O == 2 ? 0x4E : 0x141;     // quad_perm [1,0,3,2], [2,3,0,1]; mirror within eight
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, true));
+}
+
+// Statistics (mean, sum of squared deviations) of a 64-column group of the row of `e`, for the LayerNorm that follows.
+// Called by all 8 lanes that hold the group's chunks (consecutive lanes, chunk index = lane % 8).  Each lane takes its
+// eight values around the first of them, then the lanes' means and sums are merged pairwise: only differences are
+// squared, so the level of the data cancels.
 template <typename T>
-__device__ __forceinline__ void resid_stats_chunk(const GemmArgs& p, int r, int c, float* v, bool active, int lane8) {
-    int64_t orow = r;
-    if (active) {
-        epilogue_chunk<T>(p, r, c, v);         // leaves the updated residual values in v
-        if (p.epi == EPI_PATCH) orow = (int64_t)(r / p.o_rpi) * p.o_istride + p.o_off + r % p.o_rpi;
-        if (p.xb_out) {
-            const float lev = p.xb_level ? p.xb_level[orow] : 0.0f;
-            float rel[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) rel[i] = v[i] - lev;
-            store8(reinterpret_cast<T*>(p.xb_out) + orow * p.ldo + c, rel);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = 0.0f;
-    }
+__device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k, const EpiRow& e, const float* v, bool active, int lane8) {
     if (!p.st_out) return;
-    // group statistics around the group's first element (broadcast from the group's first lane), so that the
-    // level of the data cancels before squaring: mean_g = v0 + s1 / 64, M2_g = s2 - s1^2 / 64
-    const float v0 = __shfl(v[0], (int)(__lane_id() & ~7u));
     float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float d = v[i] - v0;
+    for (int i = 1; i < 8; ++i) {
+        const float d = v[i] - v[0];
         s1 += d;
         s2 += d * d;
     }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-        s1 += __shfl_xor(s1, o);
-        s2 += __shfl_xor(s2, o);
-    }
+    float mean = v[0] + s1 * 0.125f, m2 = fmaxf(s2 - s1 * s1 * 0.125f, 0.0f);
+    float d = lane_across<1>(mean) - mean;
+    m2 += lane_across<1>(m2) + 4.0f * d * d;
+    mean += 0.5f * d;
+    d = lane_across<2>(mean) - mean;
+    m2 += lane_across<2>(m2) + 8.0f * d * d;
+    mean += 0.5f * d;
+    d = lane_across<4>(mean) - mean;
+    m2 += lane_across<4>(m2) + 16.0f * d * d;
+    mean += 0.5f * d;
     if (active && lane8 == 0)
-        *reinterpret_cast<f32x2*>(p.st_out + (orow * (p.N >> 6) + (c >> 6)) * 2) =
-            f32x2{v0 + s1 * (1.0f / 64.0f), fmaxf(s2 - s1 * s1 * (1.0f / 64.0f), 0.0f)};
+        *reinterpret_cast<f32x2*>(p.st_out + ((int64_t)e.orow * (p.N >> 6) + (k.c >> 6)) * 2) = f32x2{mean, m2};
 }
 
 // Block-level epilogue shared by the register-staged kernels.  The accumulators go through LDS
@@ -414,8 +460,9 @@ __device__ __forceinline__ void resid_stats_chunk(const GemmArgs& p, int r, int 
 // coalesced global accesses per chunk instead of 64 scattered 2-byte stores per lane.
 // accumulator element v of lane (g, li) in block (i, j): row = 32 i + 8 (v / 4) + 4 g + v % 4, col = 32 j + li
 // KG > 1: the workgroup holds KG groups of WGM x WGN waves, each with the partial sums of its share of the k
-// range for the same tile; they are added in LDS in a fixed order (group 0, then 1, ...), and all KG groups'
-// threads share the chunk work below.
+// range for the same tile; each leaves them in a tile of its own in LDS (KG * BM * BN * 4 bytes), they are added in a
+// fixed order (group 0, then 1, ...) where they are read, and all KG groups' threads share the chunk work below.  (Added
+// into one tile group by group, with a barrier each, four groups cost 1.3 us more than two at 64 x 64.)
 template <typename T, int BM, int BN, int WGM, int WGN, int KG = 1>
 __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32],
                                                char* smem, const float* lnrow, const float* lncs, int m0, int n0) {
@@ -441,41 +488,67 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
                 for (int j = 0; j < NI; ++j) acc[i][j][v] = st[1] * (acc[i][j][v] - mean * lncs[j]);
             }
     }
+    // the lane's columns for the row-chunk paths, and its first rows' operands: on their way while the tile is staged
+    constexpr int CG = BN / 8, RPASS = NT / CG, PASSES = BM / RPASS, NB = PASSES < 4 ? PASSES : 4;
+    static_assert(BM % RPASS == 0 && PASSES % NB == 0, "whole passes over the tile's rows");
+    const int cg = tid % CG, rr0 = tid / CG;
+    const bool chunks = p.epi != EPI_SWIGLU && p.epi != EPI_ROWDOT && !(p.epi == EPI_QKV && n0 >= 2 * p.dim);
+    EpiCols cols;
+    EpiRow rows[NB];
+    if (chunks) {
+        cols = epilogue_cols(p, n0 + cg * 8);
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {
-        if (kg == k) {
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        float* dst = sC + (wm * WM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3)) * BN + wn * WN + j * 32 + li;
-                        *dst = k == 0 ? acc[i][j][v] : *dst + acc[i][j][v];
-                    }
+        for (int n = 0; n < NB; ++n) {
+            const int r = m0 + rr0 + n * RPASS;
+            rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
         }
-        __syncthreads();
     }
+    // 4-column groups of a row are stored exchanged by the row's 8-row block (as the column reads of the transposed value
+    // store need it: eight lanes read one column of eight blocks, all on one bank otherwise)
+    auto at = [&](int row, int col) { return row * BN + (col ^ (((row >> 3) & 7) << 2)); };
+    {
+        float* own = sC + kg * BM * BN;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) own[at(wm * WM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3), wn * WN + j * 32 + li)] = acc[i][j][v];
+    }
+    __syncthreads();
+    auto tile8 = [&](int row, int col, float* v) {           // columns col .. col + 7 of a tile row, the groups' partial sums added in order
+#pragma unroll
+        for (int k = 0; k < KG; ++k) {
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + k * BM * BN + at(row, col));
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + k * BM * BN + at(row, col + 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = k == 0 ? lo[e] : v[e] + lo[e];
+                v[4 + e] = k == 0 ? hi[e] : v[4 + e] + hi[e];
+            }
+        }
+    };
 
     if (p.epi == EPI_SWIGLU) {
         // physical columns come in groups of 64: 32 gate columns, then their 32 linear partners;
         // a thread takes 8 gate columns and their partners and writes 8 hidden units
-        constexpr int CG = BN / 16, RPASS = NT / CG;
-        const int cg = tid % CG, grp = cg >> 2, j0 = (cg & 3) * 8;
+        constexpr int GG = BN / 16, GPASS = NT / GG;
+        const int gg = tid % GG, grp = gg >> 2, j0 = (gg & 3) * 8;
         const int ca = n0 + grp * 64 + j0;            // physical gate column
         if (ca + 40 <= p.N) {
             const int oc = (ca >> 6) * 32 + j0;       // hidden unit index
             T* out = reinterpret_cast<T*>(p.out);
-            for (int rr = tid / CG; rr < BM; rr += RPASS) {
+            float ba[8], bb[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { ba[i] = p.bias[ca + i]; bb[i] = p.bias[ca + 32 + i]; }
+            for (int rr = tid / GG; rr < BM; rr += GPASS) {
                 const int r = m0 + rr;
                 if (r >= p.M) break;
-                const float* src = sC + rr * BN + grp * 64 + j0;
-                float h[8];
+                float va[8], vb[8], h[8];
+                tile8(rr, grp * 64 + j0, va);
+                tile8(rr, grp * 64 + j0 + 32, vb);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float a = src[i] + p.bias[ca + i], b = src[32 + i] + p.bias[ca + 32 + i];
-                    h[i] = swiglu_for<T>(a, b);
-                }
+                for (int i = 0; i < 8; ++i) h[i] = swiglu_for<T>(va[i] + ba[i], vb[i] + bb[i]);
                 store8(out + (int64_t)r * p.ldo + oc, h);
             }
         }
@@ -490,45 +563,31 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
         for (int it = tid; it < BN * RGN; it += NT) {
             const int cc = it / RGN, rr = (it % RGN) * 8;
             const int r = m0 + rr, c2 = n0 + cc - 2 * p.dim;
-            if (r >= p.M) continue;
+            if (r >= p.M || n0 + cc >= p.N) continue;     // (128-column tiles: the last one of an odd multiple of 64 is half empty)
             const float bias = p.bias[n0 + cc];
             float v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = sC[(rr + k) * BN + cc] + bias;
-            store_tokens8<T>(p, vt, r, c2, v);
-        }
-        return;
-    }
-    if ((p.epi == EPI_RESID || p.epi == EPI_PATCH) && (p.st_out || p.xb_out)) {
-        constexpr int CG = BN / 8, RPASS = NT / CG;
-        const int cg = tid % CG, c = n0 + cg * 8;
-        for (int rr = tid / CG; rr < BM; rr += RPASS) {
-            const int r = m0 + rr;
-            const bool active = r < p.M && c < p.N;
-            float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (active) {
-                const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8);
-                const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8 + 4);
-                v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
-                v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
+            for (int k = 0; k < 8; ++k) {
+                v[k] = sC[at(rr + k, cc)];
+#pragma unroll
+                for (int q = 1; q < KG; ++q) v[k] += sC[q * BM * BN + at(rr + k, cc)];
+                v[k] += bias;
             }
-            resid_stats_chunk<T>(p, r, c, v, active, cg & 7);
+            store_tokens8<T>(p, vt, r, c2, v);
         }
         return;
     }
     if (p.epi == EPI_ROWDOT) {
         // 8 consecutive lanes hold the 8 chunks of one 64-column group of a row: every lane takes part in
         // the exchange (out-of-range rows / columns contribute zero), the first lane of a group writes
-        constexpr int CG = BN / 8, RPASS = NT / CG;
-        const int cg = tid % CG, c = n0 + cg * 8;
+        const int c = n0 + cg * 8;
         float* out = reinterpret_cast<float*>(p.out);
-        for (int rr = tid / CG; rr < BM; rr += RPASS) {
+        for (int rr = rr0; rr < BM; rr += RPASS) {
             const int r = m0 + rr;
             float sum = 0.0f;
             if (r < p.M && c < p.N) {
-                const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8);
-                const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8 + 4);
-                const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                float v[8];
+                tile8(rr, cg * 8, v);
                 sum = rowdot_chunk(p, c, v);
             }
             sum += __shfl_xor(sum, 1);
@@ -538,18 +597,26 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
         }
         return;
     }
-    {
-        constexpr int CG = BN / 8, RPASS = NT / CG;
-        const int cg = tid % CG, c = n0 + cg * 8;
-        if (c < p.N) {
-            for (int rr = tid / CG; rr < BM; rr += RPASS) {
-                const int r = m0 + rr;
-                if (r >= p.M) break;
-                const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8);
-                const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * BN + cg * 8 + 4);
-                float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                epilogue_chunk<T>(p, r, c, v);
+#pragma unroll 1
+    for (int b = 0; b < PASSES; b += NB) {
+        EpiRow now[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) now[n] = rows[n];
+        if (b + NB < PASSES) {                           // the next batch's operands, ahead of this batch's stores
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const int r = m0 + rr0 + (b + NB + n) * RPASS;
+                rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
             }
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const int rr = rr0 + (b + n) * RPASS;
+            const bool active = m0 + rr < p.M && cols.nv > 0;
+            float v[8];
+            tile8(rr, cg * 8, v);
+            if (active) epilogue_chunk<T>(p, cols, now[n], v);
+            if (p.epi == EPI_RESID || p.epi == EPI_PATCH) group_stats<T>(p, cols, now[n], v, active, cg & 7);
         }
     }
 }
@@ -884,7 +951,7 @@ __global__ __launch_bounds__(64 * KG * WGM * WGN, KG * WGM * WGN / 4) void gemm_
         __syncthreads();
     }
 
-    static_assert(BM * BN * 4 <= 2 * STAGE, "accumulator tile must fit the stage buffers");
+    static_assert(KG * BM * BN * 4 <= KG * 2 * STAGE, "accumulator tiles must fit the stage buffers");
     block_epilogue<T, BM, BN, WGM, WGN, KG>(p, acc, smem_all, lnrow, lncs, m0, n0);
 }
 

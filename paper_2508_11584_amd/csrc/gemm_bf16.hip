@@ -13,23 +13,26 @@ namespace {
 //     t [us] = alpha * max(r, 1) + beta * r * (bm * bn * K / 1e6),     r = ceil(tiles / 256) / held,
 // r being the number of "rounds" on the busiest of the 256 CUs (it gets ceil(tiles / 256) tiles and works on
 // `held` of them at a time); alpha is the cost a workgroup pays whatever its size (first loads, epilogue), not
-// discounted on a partly filled chip.  Fitted (relative least squares) to 28 measured shapes x 8 tilings on
-// MI355X with random bf16 data: the QKV / proj / fc1 / fc2 GEMMs of ViT-S, -B, -L (batch 4) and -g (batch 8),
-// the heads' 1x1 projections, and the 3x3 convolutions at 34x45 ... 296x296 grids (batch 1 and 4).  The
-// model's pick is the measured best on 23 of them, within 8 % on four and 15 % on one (0.4 % in total time).
+// discounted on a partly filled chip.  Fitted (relative least squares, 9-11 % rms per tiling) to 66 measured shapes on
+// MI355X with random bf16 data and the layers' own epilogues: the QKV / proj / fc1 / fc2 GEMMs of ViT-S (257, 900, 1531, 4097,
+// 12000 tokens), -B (1370, 1572, 4110), -L (300, 1374, 2748, 5496) and -g (1374, 4122, 10992), and 3x3 convolutions at
+// 34x45 ... 136x180 grids.  The model's pick costs 0.9 % more than the measured best in total time; it is within 5 %
+// of it on all but three shapes (8-9 %).
 // Tuning aids, read from the environment when an engine is created (configure_gemm_bf16), never per launch:
-// VPE_GEMM_TILE forces a tiling, VPE_NO_SMALL_DMA leaves the two small direct-to-LDS shapes out, VPE_NO_SPLITK
-// the split-k kernel, VPE_NO_STRIP the strip convolution, VPE_NO_ROW_SPLIT the two-launch form of a GEMM whose tile
+// VPE_GEMM_TILE forces a tiling, VPE_NO_SMALL_DMA leaves the two small one-group direct-to-LDS shapes out, VPE_NO_SPLITK
+// the shapes with several wave groups, VPE_NO_STRIP the strip convolution, VPE_NO_ROW_SPLIT the two-launch form of a GEMM whose tile
 // count is just above a whole number of rounds.
 int g_forced_tile = 0;
 bool g_no_small = false, g_no_splitk = false, g_no_strip = false, g_no_split = false;
 struct Cand { int kind, bm, bn, held; float alpha, beta; bool dma; };
 constexpr Cand kCands[] = {
-    {128, 256, 128, 2, 5.16f, 1.055f, true},    // direct-to-LDS, 8 waves, 64 x 64 wave tiles
-    {256, 256, 256, 1, 11.96f, 0.332f, true},   // direct-to-LDS, 8 waves, 64 x 128 wave tiles
-    {384, 384, 256, 1, 15.66f, 0.361f, true},   // direct-to-LDS, 8 waves, 96 x 128 wave tiles
-    {65, 64, 128, 3, 5.13f, 1.828f, true},      // direct-to-LDS, 4 waves, 32 x 64 wave tiles
-    {64, 64, 64, 4, 4.55f, 2.909f, true},       // direct-to-LDS, 4 waves, 32 x 32 wave tiles
+    {256, 256, 256, 1, 15.83f, 0.300f, true},   // direct-to-LDS (launch_gemm_dma_bf16 describes the shapes)
+    {384, 384, 256, 1, 22.58f, 0.344f, true},
+    {128, 256, 128, 1, 10.33f, 0.406f, true},
+    {65, 64, 128, 3, 6.58f, 2.001f, true},
+    {64, 64, 64, 4, 5.28f, 3.287f, true},
+    {5, 64, 128, 2, 5.87f, 1.222f, true},
+    {4, 64, 64, 2, 4.79f, 1.411f, true},
     {1, 128, 128, 2, 7.72f, 1.120f, false},     // register-staged (any operand size)
     {2, 64, 128, 3, 5.96f, 1.972f, false},
     {3, 64, 64, 4, 4.88f, 3.153f, false},
@@ -43,16 +46,15 @@ static int pick_tile(const GemmArgs& a, bool fits, float& best_cost) {
     const bool no_small = g_no_small;
     const int rows = a.M - a.m_begin;
     for (const Cand& c : kCands) {
-        if (c.dma && !fits) continue;
+        if (c.dma != fits && !(fits && no_small)) continue;     // register staging: operands past the 32-bit offsets
         if (no_small && (c.kind == 64 || c.kind == 65)) continue;
-        if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;        // needs 64-column wave tiles
+        if (g_no_splitk && (c.kind == 4 || c.kind == 5)) continue;
+        if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;        // gate and linear partner are 64 physical columns of one wave's tile
         const int64_t tiles = (int64_t)cdiv(rows, c.bm) * cdiv(a.N, c.bn) * (a.nz > 1 ? a.nz : 1);
-        // Inside the engine (not in the calibration harness) the small direct-to-LDS shapes lose to their
-        // register-staged counterparts when there is less than one tile per CU (ViT-S proj / fc2 with 144 tiles:
-        // 12.7 against 11.7 us; 3x3 convolutions on the 34x45 and 68x90 grids: 24.0 against 20.7, 27.8 against
-        // 25.9 us) and win above that (QKV 8.3 against 9.1, fc1 11.3 against 12.0, the 136x180 convolution 43.8
-        // against 47.4 us)
-        if ((c.kind == 64 || c.kind == 65) && tiles < 256) continue;
+        // Two workgroups of 64 x 64 with four wave groups share a CU like four of one group do; with a short k loop that is
+        // where their partial sums cost more than the groups gain (432 tiles at K = 384: 8.2 against 7.7 us, 264 at K = 768:
+        // 9.7 against 9.3; 352 at K = 1024: 11.4 against 11.3, 264 at K = 3072: 23.2 against 26.3)
+        if (c.kind == 4 && tiles > 256 && a.K < 1024) continue;
         const float r = (float)cdiv(tiles, 256) / c.held;
         const float cost = c.alpha * (r > 1.0f ? r : 1.0f) + c.beta * r * (1e-6f * c.bm * c.bn * a.K);
         if (best_cost == 0.0f || cost < best_cost) { best_cost = cost; best = c.kind; }
@@ -110,17 +112,6 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best, bool fits) {
     const int forced = g_forced_tile;
-    const int rows = a.M - a.m_begin;
-    // A 64 x 64 tiling with at most one tile per CU and at least 4 k-tiles: two wave groups per tile, each over
-    // half of the k range (in-engine: ViT-S fc2 14.4 -> 12.5 us, the 3x3 convolution on the 34x45 grid 20.7 -> 17.5,
-    // the detection towers 26.9 -> 23.8; ViT-S 476x630 frame latency 1.13 -> 1.08 ms, sequential baseline 396 -> 418
-    // frames/s, pipelined rate +0.5 %; with the threshold at 16 k-tiles 1.10 ms / 408 / +0 %).
-    // VPE_NO_SPLITK in the environment switches it off (a tuning aid).  A limit of 288 tiles, which takes in the
-    // ViT-B proj / fc2 GEMMs (264 tiles), brings that model's frame latency from 1.79 to 1.70 ms but costs 1.5 % of its
-    // pipelined rate with three encoder lanes.  Four wave groups for the heads' long k loops on few tiles (3x3 convolutions
-    // on the patch grid, 36 and 54 k-tiles on 96 and 192 tiles): frame latency 1.084 -> 1.081 ms, pipelined rate -1 %.
-    const bool no_splitk = g_no_splitk;
-    if (!no_splitk && best == 3 && a.K >= 256 && (int64_t)cdiv(rows, 64) * cdiv(a.N, 64) * (a.nz > 1 ? a.nz : 1) <= 256) best = 4;
     // 3x3 convolutions: the strip kernel (conv_strip.h) where its 384 x 256 tiles make one well-filled round of the
     // 256 CUs (measured on 272 x 360 x 256 -> 256, 256 tiles: 128 against 144 us for the generic 384 x 256 kernel on the
     // same box; with several rounds -- 4 x 296 x 296: 477 against 443 us -- the generic kernels stay ahead).
@@ -129,20 +120,19 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
         const int shape = conv_strip_shape(a, forced == 9, nullptr);
         if (shape) return launch_conv_strip_bf16(shape, a, s);
     }
-    if ((forced == 384 || forced == 256 || forced == 128 || forced == 65) && fits) best = forced;
-    if (forced == 4) best = a.epi == EPI_SWIGLU ? 2 : 4;
+    if ((forced == 384 || forced == 256 || forced == 128 || forced == 65 || forced == 5) && fits) best = forced;
+    if (forced == 4 && fits) best = a.epi == EPI_SWIGLU ? 5 : 4;
     if (forced == 64 && fits) best = a.epi == EPI_SWIGLU ? 65 : 64;
     if (forced == 1) best = a.epi == EPI_SWIGLU ? 2 : 3;
     switch (best) {
-        case 64: case 65: case 128: case 256: case 384: return launch_gemm_dma_bf16(best, a, amode, s);
+        case 4: case 5: case 64: case 65: case 128: case 256: case 384: return launch_gemm_dma_bf16(best, a, amode, s);
         case 1: return launch_tile<bf16, 128, 128, 2, 2>(a, amode, s);
         case 2: return launch_tile<bf16, 64, 128, 2, 2>(a, amode, s);
-        case 4: return launch_tile_splitk<bf16, 64, 64, 2, 2, 2>(a, amode, s);
         default: return launch_tile<bf16, 64, 64, 2, 2>(a, amode, s);
     }
 }
 
-// LDS opt-in of the split-k kernel; called once at engine creation, outside any stream capture.
+// Reads the tuning aids; called at engine creation, outside any stream capture.
 hipError_t configure_gemm_bf16() {
     const char* env = getenv("VPE_GEMM_TILE");
     g_forced_tile = env ? atoi(env) : 0;
@@ -150,7 +140,6 @@ hipError_t configure_gemm_bf16() {
     g_no_splitk = getenv("VPE_NO_SPLITK") != nullptr;
     g_no_strip = getenv("VPE_NO_STRIP") != nullptr;
     g_no_split = getenv("VPE_NO_ROW_SPLIT") != nullptr;
-    GemmArgs a{};
-    return launch_tile_splitk<bf16, 64, 64, 2, 2, 2>(a, A_PLAIN, nullptr, true);
+    return hipSuccess;
 }
 }  // namespace vpe

@@ -26,6 +26,19 @@ namespace vpe {
 // expcnt 6:4 and lgkmcnt 11:8 left at their maxima)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
+// Workgroup barrier of the load pipelines: this wave's LDS reads are done (lgkmcnt 0) and all but its N youngest
+// direct-to-LDS loads have landed, then s_barrier.  __syncthreads() would not do: its fence waits for vmcnt(0), so every
+// barrier drains the loads still in flight and any number of LDS stages works like two (measured: 8 waves streaming
+// 32 KB stages of 128-byte rows, operands in the memory-side cache: 1360 clocks a stage with __syncthreads at one, two or
+// three stages in flight; 794 / 715 at two / three without the drain).
+template <int N>
+__device__ __forceinline__ void pipeline_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(N) & ~0x0F00);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
 // 32 x WN fp32 block of LDS (the operand buffers are free by now; the caller has put a barrier behind its last
 // read of them) and leaves with 8-column chunks per lane.  lnrow: (mean, rstd) per tile row for GEMMs with a
@@ -90,8 +103,14 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
         rd_w0 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c);
         rd_w1 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c + 4);
     }
-    // one pass per 32-row block of the wave tile; the block index is a compile-time constant of each pass (a
-    // loop that the optimizer declines to unroll would turn the accumulators into an indexed array in scratch)
+    // The row-chunk paths: a lane keeps one 8-column chunk (64 is a multiple of the chunks per row) for all its rows
+    // (96 x 128 wave tiles have registers for two rows at a time, and none for the columns while all blocks wait)
+    constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < 4 ? ITS : 4;
+    static_assert(64 % CG == 0 && ITS % NB == 0, "a lane keeps its column chunk");
+    // One pass per 32-row block of the wave tile; the block index is a compile-time constant of each pass (a loop over the
+    // blocks turns the accumulators into an indexed array in scratch, or spills them).
+    // (rows without operands of their own go one by one: nothing to wait for, and the short loop keeps its code small)
+    const bool batched = p.epi == EPI_RESID || p.epi == EPI_PATCH || (p.epi == EPI_STORE && p.add1);
     auto pass = [&](auto I) {
         constexpr int i = decltype(I)::value;
         if (p.ln_stats) {
@@ -117,25 +136,29 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
         const int rblk = wrow0 + i * 32;
         if (p.epi == EPI_SWIGLU) {
             // groups of 64 physical columns: 32 gate columns, then their 32 linear partners
-            constexpr int CG = WN / 16;                  // 8-wide gate chunks per row
+            constexpr int GG = WN / 16;                  // 8-wide gate chunks per row
             T* out = reinterpret_cast<T*>(p.out);
-            for (int it = lane; it < 32 * CG; it += 64) {
-                const int rr = it / CG, cg = it % CG, grp = cg >> 2, j0 = (cg & 3) * 8;
-                const int r = epilogue_row<PADDED>(p, rblk + rr), ca = wcol0 + grp * 64 + j0;
+            const int gg = lane % GG, grp = gg >> 2, j0 = (gg & 3) * 8, ca = wcol0 + grp * 64 + j0;
+            float ba[8], bb[8];
+            if (ca + 40 <= p.N) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { ba[e] = p.bias[ca + e]; bb[e] = p.bias[ca + 32 + e]; }
+            }
+#pragma unroll 1
+            for (int rr = lane / GG; rr < 32; rr += 64 / GG) {
+                const int r = epilogue_row<PADDED>(p, rblk + rr);
                 if (r < p.M && ca + 40 <= p.N) {
                     const float* src = sC + rr * WN + grp * 64 + j0;
                     float h[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float a = src[e] + p.bias[ca + e], b = src[32 + e] + p.bias[ca + 32 + e];
-                        h[e] = swiglu_for<T>(a, b);
-                    }
+                    for (int e = 0; e < 8; ++e) h[e] = swiglu_for<T>(src[e] + ba[e], src[32 + e] + bb[e]);
                     store8(out + (int64_t)r * p.ldo + (ca >> 6) * 32 + j0, h);
                 }
             }
         } else if (p.epi == EPI_QKV && wcol0 >= 2 * p.dim) {
             // value columns, written transposed: one column and 8 consecutive tokens per lane
             T* vt = reinterpret_cast<T*>(p.out2);
+#pragma unroll 2
             for (int it = lane; it < WN * 4; it += 64) {
                 const int cc = it >> 2, rr = (it & 3) * 8;      // 4 lanes = 32 consecutive tokens of a column
                 const int r = epilogue_row<PADDED>(p, rblk + rr), c2 = wcol0 + cc - 2 * p.dim;
@@ -147,32 +170,11 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                     store_tokens8<T>(p, vt, r, c2, v);
                 }
             }
-        } else if ((p.epi == EPI_RESID || p.epi == EPI_PATCH) && (p.st_out || p.xb_out)) {
-            // 8 consecutive lanes hold the 8 chunks of one 64-column statistics group of a row
-            if constexpr (WN % 64 == 0) {
-                constexpr int CG = WN / 8;
-#pragma unroll
-                for (int it = lane; it < 32 * CG; it += 64) {
-                    const int rr = it / CG, cg = it % CG;
-                    const int r = epilogue_row<PADDED>(p, rblk + rr), c = wcol0 + cg * 8;
-                    const bool active = r < p.M && c < p.N;
-                    float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                    if (active) {
-                        const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + cg * 8);
-                        const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + cg * 8 + 4);
-                        v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
-                        v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
-                    }
-                    resid_stats_chunk<T>(p, r, c, v, active, cg & 7);
-                }
-            }
         } else if (p.epi == EPI_ROWDOT) {
             // 8 consecutive lanes hold the 8 chunks of one 64-column projection group of a row
             if constexpr (WN % 64 == 0) {
-                constexpr int CG = RD_CG;
-                static_assert(64 % CG == 0, "a lane keeps its column chunk");
                 float* out = reinterpret_cast<float*>(p.out);
-#pragma unroll
+#pragma unroll 2
                 for (int n = 0; n < 32 * CG / 64; ++n) {
                     const int rr = lane / CG + n * (64 / CG);
                     const int r = rd_rows.row(p);
@@ -192,16 +194,39 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                     if ((lane & 7) == 0 && r < p.M && rd_c < p.N) out[(int64_t)r * p.ldo + (rd_c >> 6)] = sum;
                 }
             }
-        } else {
-            constexpr int CG = WN / 8;
-            for (int it = lane; it < 32 * CG; it += 64) {
-                const int rr = it / CG, cg = it % CG;
-                const int r = epilogue_row<PADDED>(p, rblk + rr), c = wcol0 + cg * 8;
-                if (r < p.M && c < p.N) {
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + cg * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + cg * 8 + 4);
+        } else if (batched) {
+            const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
+#pragma unroll 1
+            for (int b = 0; b < ITS; b += NB) {
+                EpiRow rows[NB];
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    const int r = epilogue_row<PADDED>(p, rblk + lane / CG + (b + n) * (64 / CG));
+                    rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
+                }
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    const int rr = lane / CG + (b + n) * (64 / CG);
+                    const bool active = epilogue_row<PADDED>(p, rblk + rr) < p.M && cols.nv > 0;
+                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
+                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
                     float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    epilogue_chunk<T>(p, r, c, v);
+                    if (active) epilogue_chunk<T>(p, cols, rows[n], v);
+                    if constexpr (WN % 64 == 0) {        // (8 consecutive lanes hold the 8 chunks of a 64-column statistics group)
+                        if (p.epi == EPI_RESID || p.epi == EPI_PATCH) group_stats<T>(p, cols, rows[n], v, active, lane & 7);
+                    }
+                }
+            }
+        } else {
+            const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
+#pragma unroll 1
+            for (int rr = lane / CG; rr < 32; rr += 64 / CG) {
+                const int r = epilogue_row<PADDED>(p, rblk + rr);
+                if (r < p.M && cols.nv > 0) {
+                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
+                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
+                    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    epilogue_chunk<T>(p, cols, epilogue_row_operands(p, cols, r, true), v);
                 }
             }
         }
@@ -275,16 +300,20 @@ __device__ __forceinline__ void rowdot_epilogue_transposed(const GemmArgs& p, f3
 }
 
 // RD: the instantiation for EPI_ROWDOT alone (MFMAs with the W operand first, projection epilogue without LDS staging).
-template <int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int BM_ = 256, bool RD = false>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_kernel(const GemmArgs args) {
+// KG: groups of WGM x WGN waves that share the tile's loads and take KS / KG of the k-steps of every k-tile each; their
+// partial sums are added in LDS in a fixed order by the block-level epilogue.
+// RING: the operand tiles of a k-tile are units of their own in a ring of five (A0 B0 A1 B1 A2 ...), see the main loop.
+template <int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int BM_ = 256, bool RD = false, int KG = 1, bool RING = false>
+__global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void gemm_dma_kernel(const GemmArgs args) {
     const GemmArgs p = select_problem(args);
     typedef bf16 T;
-    constexpr int BM = BM_, CE = 8, NW = WGN * WGM;
+    constexpr int BM = BM_, CE = 8, NW = WGN * WGM * KG;
     static_assert((BM * BK * 2) % (1024 * NW) == 0 && (BN * BK * 2) % (1024 * NW) == 0 && BM % (32 * WGM) == 0, "loader / wave tiling");
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
     constexpr int ROWB = BK * 2, CPR = BK / 8, RPI = 64 / CPR;   // row bytes, chunks per row, rows per DMA instruction
-    constexpr int KS = BK / 16;
+    constexpr int KS = BK / 16 / KG;                    // k-steps of a k-tile that a wave takes
     constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB, STAGE = A_BYTES + B_BYTES;
+    static_assert((BK / 16) % KG == 0 && (!RING || (A_BYTES == B_BYTES && KG == 1 && S == 2)), "k-step groups / ring units");
     constexpr int A_SLOTS = A_BYTES / (1024 * NW), B_SLOTS = B_BYTES / (1024 * NW);   // 1 KB DMA instructions per wave per k-tile
     constexpr int PD = S - 1;
     // chunk swizzle: 256 bytes of LDS (64 banks) hold 2 rows of 128 bytes or 4 rows of 64 bytes
@@ -292,16 +321,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int kg = KG > 1 ? wave / (WGM * WGN) : 0;
+    const int wm = (KG > 1 ? wave % (WGM * WGN) : wave) / WGN, wn = wave % WGN;
     const int g = lane >> 5, li = lane & 31;
 
     int tm, tn;
     tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
     const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
 
-    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers
-    constexpr int EPI_BYTES = NW * 32 * WN * 4;
-    float* lnrow = reinterpret_cast<float*>(smem + (S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
+    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (RING, whose stages take
+    // the whole LDS: behind the staging blocks, written when the k loop is done)
+    constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : NW * 32 * WN * 4;
+    float* lnrow = reinterpret_cast<float*>(smem + (!RING && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
 
     const char* __restrict__ A = reinterpret_cast<const char*>(p.A);
     const char* __restrict__ W = reinterpret_cast<const char*>(p.W);
@@ -338,11 +369,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
     }
     const char* zptr = reinterpret_cast<const char*>(p.zeros);
 
-    auto dma = [&](int stage, int kt) {
-        char* sA = smem + stage * STAGE;
-        char* sB = sA + A_BYTES;
-        const int k0 = kt * BK;
+    auto dma_a = [&](char* sA, int kt) {
         if (AMODE == A_PLAIN) {
+            const int k0 = kt * BK;
 #pragma unroll
             for (int s = 0; s < A_SLOTS; ++s)
                 __builtin_amdgcn_global_load_lds(VPE_GPTR(A + aoff[s] + k0 * 2), VPE_LPTR(sA + (wave + NW * s) * 1024), 16, 0, 0);
@@ -360,10 +389,16 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
                 __builtin_amdgcn_global_load_lds(VPE_GPTR(addr), VPE_LPTR(sA + (wave + NW * s) * 1024), 16, 0, 0);
             }
         }
-        const int kw = AMODE == A_PLAIN ? k0 : (kt % 9) * p.cC + (kt / 9) * BK;   // weight column of this k-tile
+    };
+    auto dma_b = [&](char* sB, int kt) {
+        const int kw = AMODE == A_PLAIN ? kt * BK : (kt % 9) * p.cC + (kt / 9) * BK;   // weight column of this k-tile
 #pragma unroll
         for (int s = 0; s < B_SLOTS; ++s)
             __builtin_amdgcn_global_load_lds(VPE_GPTR(W + boff[s] + kw * 2), VPE_LPTR(sB + (wave + NW * s) * 1024), 16, 0, 0);
+    };
+    auto dma = [&](int stage, int kt) {
+        dma_a(smem + stage * STAGE, kt);
+        dma_b(smem + stage * STAGE + A_BYTES, kt);
     };
 
     f32x16 acc[MI][NI];
@@ -382,19 +417,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
     // flight during the MFMAs of step ks); larger wave tiles have no registers for the second set and read
     // each step's fragments just before its MFMAs (two waves per SIMD cover for each other).
     constexpr bool FRAG_DB = MI + NI <= 6;
-    auto compute = [&](int stage) {
-        const char* sA = smem + stage * STAGE + arow0 * ROWB;
-        const char* sB = smem + stage * STAGE + A_BYTES + brow0 * ROWB;
+    const int ks0 = kg * KS;                                        // first k-step of this wave's group
+    auto compute = [&](const char* tile_a, const char* tile_b, auto&& between) {
+        const char* sA = tile_a + arow0 * ROWB;
+        const char* sB = tile_b + brow0 * ROWB;
         if constexpr (FRAG_DB) {
             bf16x8 fa[2][MI], fb[2][NI];
+            const int ca0 = ((2 * ks0 + g) ^ asw) * 16, cb0 = ((2 * ks0 + g) ^ bsw) * 16;
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ((g ^ asw) * 16));
+            for (int i = 0; i < MI; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca0);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + ((g ^ bsw) * 16));
+            for (int j = 0; j < NI; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + cb0);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
+                if (RING && ks == 1) between();
                 if (ks + 1 < KS) {
-                    const int ca = ((2 * (ks + 1) + g) ^ asw) * 16, cb = ((2 * (ks + 1) + g) ^ bsw) * 16;
+                    const int ca = ((2 * (ks0 + ks + 1) + g) ^ asw) * 16, cb = ((2 * (ks0 + ks + 1) + g) ^ bsw) * 16;
 #pragma unroll
                     for (int i = 0; i < MI; ++i) fa[(ks + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca);
 #pragma unroll
@@ -427,7 +465,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
         } else {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const int ca = ((2 * ks + g) ^ asw) * 16, cb = ((2 * ks + g) ^ bsw) * 16;
+                const int ca = ((2 * (ks0 + ks) + g) ^ asw) * 16, cb = ((2 * (ks0 + ks) + g) ^ bsw) * 16;
                 bf16x8 fa[MI], fb[NI];
 #pragma unroll
                 for (int i = 0; i < MI; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca);
@@ -450,31 +488,67 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
     // iteration kt - 1 is free), issue the loads of tile kt + S - 1 into that free stage, multiply
     // tile kt.  Prefetches are unconditional (clamped index): every path has the same loads in flight.
     const int KT = p.K / BK;
+    auto last = [&](int kt) { return kt < KT ? kt : KT - 1; };
+    if constexpr (RING) {
+        // Two whole stages of a 256 x 256 tile leave 32 KB of the LDS unused and give a load one tile time to arrive (about
+        // 2100 clocks, as long as the loads of a tile take by themselves).  Five units of 32 KB instead: during tile kt the A
+        // operand of tile kt + 1 is already on its way when B's is issued, then A's of tile kt + 2 between the MFMAs.
+        char* unit[5] = {smem, smem + A_BYTES, smem + 2 * A_BYTES, smem + 3 * A_BYTES, smem + 4 * A_BYTES};
+        dma_a(unit[0], 0);
+        dma_b(unit[1], 0);
+        dma_a(unit[2], last(1));
+        float mean = 0.0f, rstd = 0.0f;
+        if (p.ln_stats && tid < BM) ln_tile_row(p, m0, n0, tid, mean, rstd);
+        for (int kt = 0; kt < KT; ++kt) {
+            pipeline_barrier<A_SLOTS>();                      // A and B of tile kt are here; A of kt + 1 may be on its way
+            dma_b(unit[3], last(kt + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            compute(unit[0], unit[1], [&] {
+                __builtin_amdgcn_sched_barrier(0);
+                dma_a(unit[4], last(kt + 2));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            char* const u0 = unit[0];
+            char* const u1 = unit[1];
+            unit[0] = unit[2]; unit[1] = unit[3]; unit[2] = unit[4]; unit[3] = u0; unit[4] = u1;
+        }
+        pipeline_barrier<0>();                                // drain the clamped tail prefetches before LDS is reused
+        if (p.ln_stats) {
+            if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+            __syncthreads();
+        }
+    } else {
 #pragma unroll
-    for (int s = 0; s < PD; ++s) dma(s, s < KT ? s : KT - 1);
-    // behind the first tile loads, ordered before the epilogue by the loop's barriers
-    if (p.ln_stats && tid < BM) ln_tile_row(p, m0, n0, tid, lnrow);
-    for (int kt = 0; kt < KT; ++kt) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((PD - 1) * (A_SLOTS + B_SLOTS)));
-        __syncthreads();
-        dma((kt + PD) % S, kt + PD < KT ? kt + PD : KT - 1);
-        __builtin_amdgcn_sched_barrier(0);
-        compute(kt % S);
+        for (int s = 0; s < PD; ++s) dma(s, last(s));
+        // behind the first tile loads, ordered before the epilogue by the loop's barriers
+        if (p.ln_stats && tid < BM) {
+            float mean, rstd;
+            ln_tile_row(p, m0, n0, tid, mean, rstd);
+            *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+        }
+        int cur = 0, nxt = PD;                                // stages of tiles kt and kt + PD
+        for (int kt = 0; kt < KT; ++kt) {
+            pipeline_barrier<(PD - 1) * (A_SLOTS + B_SLOTS)>();
+            dma(nxt, last(kt + PD));
+            __builtin_amdgcn_sched_barrier(0);
+            compute(smem + cur * STAGE, smem + cur * STAGE + A_BYTES, [] {});
+            cur = cur + 1 == S ? 0 : cur + 1;
+            nxt = nxt + 1 == S ? 0 : nxt + 1;
+        }
+        pipeline_barrier<0>();                                // drain the clamped tail prefetches before LDS is reused
     }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // drain the clamped tail prefetches before LDS is reused
-    __syncthreads();
 
-    if constexpr (WN % 64 != 0) {
+    if constexpr (WN % 64 != 0 || KG > 1) {
         // Small tiles (32-column wave tiles): a wave does not hold whole 64-column groups, so the tile leaves
         // through the block-level epilogue of the register-staged kernels (whole tile staged in LDS).
-        static_assert(BM * BN * 4 <= S * STAGE, "accumulator tile must fit the stage buffers");
+        static_assert(KG > 1 || BM * BN * 4 <= S * STAGE, "accumulator tile must fit the stage buffers");
         float lncs[NI];
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int c = n0 + wn * WN + j * 32 + li;
             lncs[j] = p.ln_stats && c < p.N ? p.ln_colsum[c] : 0.0f;
         }
-        block_epilogue<T, BM, BN, WGM, WGN>(p, acc, smem, lnrow, lncs, m0, n0);
+        block_epilogue<T, BM, BN, WGM, WGN, KG>(p, acc, smem, lnrow, lncs, m0, n0);
         return;
     }
 
@@ -482,19 +556,21 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void gemm_dma_
     else wave_tile_epilogue<MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
 }
 
-template <int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false>
+template <int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
-    constexpr int stage_b = S * (BM + BN) * BK * 2, epi_b = WGM * WGN * 32 * (BN / WGN) * 4;
-    constexpr int lds = (stage_b > epi_b ? stage_b : epi_b) + BM * 8;     // + (mean, rstd) of the tile's rows
-    static_assert(lds * OCC <= 160 * 1024, "LDS budget of one CU");
+    constexpr int nt = 64 * WGM * WGN * KG;
+    constexpr int stage_b = RING ? 5 * BM * BK * 2 : S * (BM + BN) * BK * 2;
+    constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
+    constexpr int ln_b = BM * 8;                                          // (mean, rstd) of the tile's rows
+    constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
+    static_assert(lds * OCC <= 160 * 1024 && nt <= 1024, "LDS budget of one CU, workgroup size");
+    auto plain = &gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
+    auto conv = &gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
     static bool configured = false;
     if (!configured) {
         hipError_t rc = hipSuccess;
-        if (!RD) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (rc == hipSuccess)
-            rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (!RD) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(plain), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (rc == hipSuccess) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(conv), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc != hipSuccess) return rc;
         configured = true;
     }
@@ -502,9 +578,8 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     // the projection-only instantiation exists for convolutions (the only users of that epilogue on these tiles)
     if (RD && (amode != A_CONV3 || a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
     const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN), nz = a.nz > 1 ? a.nz : 1;
-    if (RD) hipLaunchKernelGGL((gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD>), dim3(tiles, nz), dim3(64 * WGM * WGN), lds, s, a);
-    else if (amode == A_PLAIN) hipLaunchKernelGGL((gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false>), dim3(tiles, nz), dim3(64 * WGM * WGN), lds, s, a);
-    else hipLaunchKernelGGL((gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, false>), dim3(tiles, nz), dim3(64 * WGM * WGN), lds, s, a);
+    if (!RD && amode == A_PLAIN) hipLaunchKernelGGL(plain, dim3(tiles, nz), dim3(nt), lds, s, a);
+    else hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
     return hipGetLastError();
 }
 

@@ -5,22 +5,33 @@
 #include "gemm_dma.h"
 #include "kernels.h"
 namespace vpe {
-// Measured on MI355X, 3x3 conv 256->256 (K = 2304) with real data, TFLOP/s at whole rounds of workgroups:
-//   128: 256 x 128 tile, 32-deep k-tiles, 8 waves (64 x 64 wave tiles), two workgroups per CU      820-850
-//   256: 256 x 256 tile, 64-deep k-tiles, 8 waves (64 x 128 wave tiles), one workgroup per CU       975
-//   384: 384 x 256 tile, 32-deep k-tiles, 8 waves (96 x 128 wave tiles), one workgroup per CU       995
-// and two small shapes for small problems (4 waves, 64-deep k-tiles), faster than their register-staged
-// counterparts by 8-14 % on the ViT-S / ViT-B GEMMs and the small convolutions:
-//    64: 64 x 64 tile (32 x 32 wave tiles, block-level epilogue), 65: 64 x 128 tile (32 x 64 wave tiles)
+// Tilings, all with 64-deep k-tiles (128-byte rows: a k-tile of 64-byte rows loads at half the rate, 20 against 43 bytes
+// per clock and CU in a load-only probe) but for 384, whose two 64-deep stages would not fit the LDS:
+//   384: 384 x 256, 32-deep k-tiles, 8 waves (96 x 128 wave tiles), one workgroup per CU
+//   256: 256 x 256, 8 waves (64 x 128), operand tiles in a ring of five units, one workgroup per CU
+//   128: 256 x 128, 8 waves (64 x 64), three stages, one workgroup per CU
+//    65:  64 x 128, 4 waves (32 x 64),  two stages, two workgroups per CU;  64: 64 x 64, 4 waves (32 x 32), two stages
+//     5:  64 x 128, 8 waves in two groups that halve the k-steps of every k-tile (32 x 64 wave tiles), three stages
+//     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages
+// 4 and 5 are for problems with few tiles per CU, where a workgroup's own loop is the time: what it waits for is the LDS
+// (operand reads + landing loads) and the loads in flight.  Two groups at 64 x 64 read 32 KB of fragments per 16 KB k-tile, four
+// groups of twice as wide wave tiles 24 KB.  Against the register-staged two-group kernel that served these problems (us, its
+// old / new): ViT-S 1531 tokens fc2 12.2 / 8.4, out-projection 6.8 / 5.6; 257 tokens QKV 6.1 / 5.6, fc2 11.3 / 7.5; 3x3 convolutions
+// 34 x 45 256 -> 256 17.3 / 15.3, towers 24.3 / 21.2.  5 against the register-staged 64 x 128 tiles: ViT-B 1370 tokens fc2
+// 30.4 / 20.8, ViT-L 1374 tokens fc2 38.2 / 27.1; against 64: 68 x 90 convolution 23.7 / 20.4.
 // The one-per-CU shapes run in lockstep rounds, so they pay for a partly filled last round in full; which
 // shape wins depends on how the tile count divides by the 256 CUs (see launch_gemm_bf16).
 hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStream_t s) {
-    if (kind == 64) return launch_gemm_dma<64, 64, 2, 2, 2, 2, 64>(a, amode, s);
-    if (kind == 65) return launch_gemm_dma<128, 64, 2, 2, 2, 2, 64>(a, amode, s);
     const bool rd = amode == A_CONV3 && a.epi == EPI_ROWDOT && !a.ln_stats;   // projection epilogue from transposed accumulators
-    if (kind == 384) return rd ? launch_gemm_dma<256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<256, 32, 2, 4, 2, 1, 384>(a, amode, s);
-    if (kind == 256) return rd ? launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true>(a, amode, s) : launch_gemm_dma<256, 64, 2, 4, 2, 1>(a, amode, s);
-    return launch_gemm_dma<128, 32, 2, 4, 2, 2>(a, amode, s);
+    switch (kind) {
+        case 4: return launch_gemm_dma<64, 64, 4, 1, 2, 2, 64, false, 4>(a, amode, s);
+        case 5: return launch_gemm_dma<128, 64, 3, 2, 2, 2, 64, false, 2>(a, amode, s);
+        case 64: return launch_gemm_dma<64, 64, 2, 2, 2, 2, 64>(a, amode, s);
+        case 65: return launch_gemm_dma<128, 64, 2, 2, 2, 2, 64>(a, amode, s);
+        case 384: return rd ? launch_gemm_dma<256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<256, 32, 2, 4, 2, 1, 384>(a, amode, s);
+        case 256: return rd ? launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, amode, s) : launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, amode, s);
+        default: return launch_gemm_dma<128, 64, 3, 4, 2, 1>(a, amode, s);
+    }
 }
 // 3x3 convolution from an input strip in LDS (conv_strip.h), 96 x 128 wave tiles: 768 x 128 tiles (eight waves on top
 // of each other; per 16-channel chunk a tile loads a strip of 768 + 2 (W + 1) + 2 positions and 128 x 9 weight rows: at
@@ -61,10 +72,12 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, false>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<256, 32, 2, 4, 2, 1, 384>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<256, 32, 2, 4, 2, 1, 384, true>(a, A_CONV3, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true>(a, A_CONV3, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, A_CONV3, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<64, 64, 4, 1, 2, 2, 64, false, 4>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<128, 64, 3, 2, 2, 2, 64, false, 2>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<128, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1>(a, A_PLAIN, nullptr, true);
-    return rc != hipSuccess ? rc : launch_gemm_dma<128, 32, 2, 4, 2, 2>(a, A_PLAIN, nullptr, true);
+    return rc != hipSuccess ? rc : launch_gemm_dma<128, 64, 3, 4, 2, 1>(a, A_PLAIN, nullptr, true);
 }
 }  // namespace vpe

@@ -214,6 +214,16 @@ def test_direct_to_lds_gemm_variant(tile, monkeypatch):
     check_all(spec, 103, 203)
 
 
+@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
+def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
+    # one k-tile (width 64), three (MLP of 192) and nine (3x3 convolutions of 64 channels): pipelines whose first loads
+    # already run past the last k-tile; 35 + 3 tokens a view, so that tiles and 8-row groups straddle two views.  The
+    # gates of check_all are those of every bf16 model
+    monkeypatch.setenv("VPE_GEMM_TILE", tile)
+    check_all(vi.ModelSpec("short_k_tile" + tile, dtype="bf16", dim=64, depth=4, heads=1, mlp_hidden=192, registers=2, batch=2,
+                           img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 141, 241)
+
+
 @pytest.mark.parametrize("shape", ["1", "2"])
 def test_strip_convolution_kernel(shape, monkeypatch):
     # the 3x3 convolution that forms its nine taps from one input strip in LDS, in both of its tile shapes (1: 384 x 256,
