@@ -1,13 +1,12 @@
 // Tiled MFMA GEMM for gfx950:  C[M][N] = A[M][K] * W^T  with W stored [N][K] (K contiguous),
-// fp32 accumulation, and the layer's epilogue applied to the accumulators in registers.
+// fp32 accumulation, and the layer's epilogue applied to the accumulators: the arguments, the tile order and the
+// epilogues.  The kernel is gemm_dma_kernel (gemm_dma.h).
 //
-// One kernel serves every dense contraction of the encoder and the heads (ViT blocks: fused
+// It serves every dense contraction of the encoder and the heads (ViT blocks: fused
 // QKV, out-projection, MLP; patch embedding after im2col; the heads' 1x1 and 3x3 convolutions):
 //   * A operand: plain rows (optionally re-mapped so that only patch tokens of each image are
 //     read) or an implicit im2col of a channels-last grid for 3x3 / pad 1 convolutions.
-//   * operands in bf16 (v_mfma_f32_32x32x16_bf16) or fp32 (v_mfma_f32_32x32x2_f32).
-//   * LDS: two stages of (BM + BN) rows x 128 bytes, 16-byte chunks XOR-swizzled by row.
-//   * global -> register -> LDS software pipeline two k-tiles deep, one barrier per k-tile.
+//   * operands in bf16, or fp32 split into three bf16 terms each; v_mfma_f32_32x32x16_bf16 either way.
 #pragma once
 #include "common.h"
 
@@ -88,39 +87,6 @@ __device__ __forceinline__ GemmArgs select_problem(const GemmArgs& in) {
     return p;
 }
 
-
-template <typename T> struct Mma;
-
-template <> struct Mma<bf16> {
-    static constexpr int KS = 4;   // MFMA k-steps per 64-element k-tile
-    typedef bf16x8 Frag;
-    // lane half g supplies k elements 16 ks + 8 g .. + 7 of its row
-    static __device__ __forceinline__ Frag load(const char* tile, int row, int ks, int g) {
-        return *reinterpret_cast<const Frag*>(tile + (row * 8 + swz(row, 2 * ks + g)) * 16);
-    }
-    static __device__ __forceinline__ void mma(f32x16& c, const Frag& a, const Frag& b) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-    }
-};
-
-template <> struct Mma<float> {
-    static constexpr int KS = 2;   // macro k-steps (16 elements) per 32-element k-tile
-    struct Frag { f32x4 lo, hi; };
-    // lane half g supplies k elements 16 ks + 8 g .. + 7 of its row; the 8 MFMAs of a macro
-    // step pair element kk of A with element kk of B, so the k order only has to agree.
-    static __device__ __forceinline__ Frag load(const char* tile, int row, int ks, int g) {
-        Frag f;
-        f.lo = *reinterpret_cast<const f32x4*>(tile + (row * 8 + swz(row, 4 * ks + 2 * g)) * 16);
-        f.hi = *reinterpret_cast<const f32x4*>(tile + (row * 8 + swz(row, 4 * ks + 2 * g + 1)) * 16);
-        return f;
-    }
-    static __device__ __forceinline__ void mma(f32x16& c, const Frag& a, const Frag& b) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.lo[i], b.lo[i], c, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.hi[i], b.hi[i], c, 0, 0, 0);
-    }
-};
 
 // GELU in its exact (erf) form.  erf by the Abramowitz-Stegun 7.1.26 rational approximation
 // (|error| <= 1.5e-7, i.e. fp32 rounding level): one reciprocal, one exponential and six FMAs
@@ -454,7 +420,7 @@ __device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k,
         *reinterpret_cast<f32x2*>(p.st_out + ((int64_t)e.orow * (p.N >> 6) + (k.c >> 6)) * 2) = f32x2{mean, m2};
 }
 
-// Block-level epilogue shared by the register-staged kernels.  The accumulators go through LDS
+// Block-level epilogue of the tiles whose waves hold less than whole 64-column groups or partial sums.  The accumulators go through LDS
 // (`smem`, free after the k loop, at least BM * BN * 4 bytes) as a row-major fp32 tile, so that
 // each thread then owns 8 consecutive columns of a row: one row-index computation and 16-byte
 // coalesced global accesses per chunk instead of 64 scattered 2-byte stores per lane.
@@ -619,384 +585,6 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
             if (p.epi == EPI_RESID || p.epi == EPI_PATCH) group_stats<T>(p, cols, now[n], v, active, cg & 7);
         }
     }
-}
-
-template <typename T, int BM, int BN, int WGM, int WGN, int AMODE>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_kernel(const GemmArgs args) {
-    const GemmArgs p = select_problem(args);
-    constexpr int NT = 64 * WGM * WGN;
-    constexpr int CE = Elem<T>::CE;
-    constexpr int BK = 8 * CE;
-    constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int RPP = NT / 8;
-    constexpr int A_IT = BM / RPP, B_IT = BN / RPP;
-    static_assert(BM % RPP == 0 && BN % RPP == 0, "tile rows must be a multiple of the loader pass");
-    constexpr int STAGE = (BM + BN) * 128;
-    __shared__ __attribute__((aligned(16))) char smem[2 * STAGE];
-    __shared__ __attribute__((aligned(8))) float lnrow[2 * BM];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int g = lane >> 5, li = lane & 31;
-    const int lrow = tid >> 3, lchunk = tid & 7;
-
-    int tm, tn;
-    tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
-    const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
-
-
-    const T* __restrict__ A = reinterpret_cast<const T*>(p.A);
-    const T* __restrict__ W = reinterpret_cast<const T*>(p.W);
-
-    // per-thread A row state.  Loads carry neither branches nor selects on the loaded value (either
-    // would make the wave wait for the load right where it is issued): rows past M re-read row
-    // M - 1 (their accumulators are never stored) and out-of-image conv taps read a page of zeros.
-    const T* aptr[A_IT];
-    int ay[A_IT], ax[A_IT];
-#pragma unroll
-    for (int i = 0; i < A_IT; ++i) {
-        int r = m0 + lrow + i * RPP;
-        r = r < p.M ? r : p.M - 1;
-        ay[i] = ax[i] = 0;
-        if (AMODE == A_PLAIN) {
-            const int64_t ar = (int64_t)(r / p.a_rpi) * p.a_istride + p.a_off + r % p.a_rpi;
-            aptr[i] = A + ar * p.lda + lchunk * CE;
-        } else {
-            const int hw = p.cH * p.cW;
-            const int b = r / hw, pix = r % hw;
-            ay[i] = pix / p.cW;
-            ax[i] = pix % p.cW;
-            aptr[i] = A + ((int64_t)b * p.a_istride + p.a_off + pix) * p.lda + lchunk * CE;
-        }
-    }
-    const T* wptr = W + (int64_t)(n0 + lrow) * p.K + lchunk * CE;
-    const T* zptr = reinterpret_cast<const T*>(p.zeros);
-
-    // two register sets: the loads of k-tile kt + 2 are issued while tile kt is multiplied and tile
-    // kt + 1 waits in the other set, so a global load has two tile times to arrive
-    u32x4 ra[2][A_IT], rb[2][B_IT];
-    auto gload = [&](int set, int kt) {
-        const int k0 = kt * BK;
-        if (AMODE == A_PLAIN) {
-#pragma unroll
-            for (int i = 0; i < A_IT; ++i) ra[set][i] = ld_global_16(aptr[i] + k0);
-        } else {
-            // k-tile order: channel chunk outer, tap inner -- the 9 taps of a chunk re-read the same
-            // 128-byte slices of neighbouring pixels, which keeps a workgroup's L2 footprint small
-            const int cc = kt / 9, tap = kt - cc * 9, c0 = cc * BK;
-            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-            const int64_t shift = (int64_t)(dy * p.cW + dx) * p.lda + c0;
-#pragma unroll
-            for (int i = 0; i < A_IT; ++i) {
-                const int yy = ay[i] + dy, xx = ax[i] + dx;
-                const bool ok = yy >= 0 && yy < p.cH && xx >= 0 && xx < p.cW;
-                // bitwise pointer select: a ternary here is compiled to a branch around the address math
-                const uint64_t mask = ok ? ~uint64_t(0) : uint64_t(0);
-                const uint64_t addr = (reinterpret_cast<uint64_t>(aptr[i] + shift) & mask) |
-                                      (reinterpret_cast<uint64_t>(zptr) & ~mask);
-                ra[set][i] = ld_global_16(reinterpret_cast<const void*>(addr));
-            }
-        }
-        const int kw = AMODE == A_PLAIN ? k0 : (kt % 9) * p.cC + (kt / 9) * BK;   // weight column of this k-tile
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i) rb[set][i] = ld_global_16(wptr + (int64_t)i * RPP * p.K + kw);
-    };
-    auto sstore = [&](int set, int buf) {
-        char* sA = smem + buf * STAGE;
-        char* sB = sA + BM * 128;
-#pragma unroll
-        for (int i = 0; i < A_IT; ++i) {
-            const int r = lrow + i * RPP;
-            *reinterpret_cast<u32x4*>(sA + (r * 8 + swz(r, lchunk)) * 16) = ra[set][i];
-        }
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i) {
-            const int r = lrow + i * RPP;
-            *reinterpret_cast<u32x4*>(sB + (r * 8 + swz(r, lchunk)) * 16) = rb[set][i];
-        }
-    };
-
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    // fragments of k-step ks + 1 are read from LDS before the MFMAs of step ks are issued
-    auto compute = [&](int buf) {
-        const char* sA = smem + buf * STAGE;
-        const char* sB = sA + BM * 128;
-        typename Mma<T>::Frag fa[2][MI], fb[2][NI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) fa[0][i] = Mma<T>::load(sA, wm * WM + i * 32 + li, 0, g);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) fb[0][j] = Mma<T>::load(sB, wn * WN + j * 32 + li, 0, g);
-#pragma unroll
-        for (int ks = 0; ks < Mma<T>::KS; ++ks) {
-            if (ks + 1 < Mma<T>::KS) {
-#pragma unroll
-                for (int i = 0; i < MI; ++i) fa[(ks + 1) & 1][i] = Mma<T>::load(sA, wm * WM + i * 32 + li, ks + 1, g);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) fb[(ks + 1) & 1][j] = Mma<T>::load(sB, wn * WN + j * 32 + li, ks + 1, g);
-            }
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j) Mma<T>::mma(acc[i][j], fa[ks & 1][i], fb[ks & 1][j]);
-        }
-    };
-
-    // The prefetches are unconditional (tile index clamped to the last tile) so that the number of
-    // loads in flight is the same on every path: with a conditional prefetch the compiler has to
-    // assume it was skipped and waits for the newest loads before storing the older set.
-    const int KT = p.K / BK;
-    const int klast = KT - 1;
-    gload(0, 0);
-    gload(1, klast < 1 ? klast : 1);
-    // folded LayerNorm: statistics of this tile's rows, read by the epilogue (the k loop's barriers order
-    // them); placed behind the first tile loads so that it does not delay them
-    float lncs[NI];
-#pragma unroll
-    for (int j = 0; j < NI; ++j) lncs[j] = 0.0f;
-    if (p.ln_stats) {
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int c = n0 + wn * WN + j * 32 + li;
-            if (c < p.N) lncs[j] = p.ln_colsum[c];
-        }
-        if (tid < BM) ln_tile_row(p, m0, n0, tid, lnrow);
-    }
-    sstore(0, 0);
-    __syncthreads();
-    for (int kt = 0; kt < KT; kt += 2) {
-        gload(0, kt + 2 < klast ? kt + 2 : klast);
-        compute(0);
-        sstore(1, 1);
-        __syncthreads();
-        if (kt + 1 >= KT) break;
-        gload(1, kt + 3 < klast ? kt + 3 : klast);
-        compute(1);
-        sstore(0, 0);
-        __syncthreads();
-    }
-
-    static_assert(BM * BN * 4 <= 2 * STAGE, "accumulator tile must fit the stage buffers");
-    block_epilogue<T, BM, BN, WGM, WGN>(p, acc, smem, lnrow, lncs, m0, n0);
-}
-
-// The same tile computed by KG groups of WGM x WGN waves, each over 1 / KG of the k range (group g the k-tiles
-// [g ceil(KT / KG), (g + 1) ceil(KT / KG))), with its own pair of LDS buffers; the partial sums are added in
-// LDS in a fixed order by the epilogue.  For problems with less than one tile per CU and a long k loop (the
-// ViT-S fc2 GEMM, the 3x3 convolutions on the patch grid): such a loop is a serial chain of load, barrier, LDS
-// read and MFMA in one wave per SIMD, and the second group's chain runs in the gaps of the first.
-// Dynamic LDS: 2 KG * STAGE + 8 * BM bytes.
-template <typename T, int BM, int BN, int WGM, int WGN, int AMODE, int KG>
-__global__ __launch_bounds__(64 * KG * WGM * WGN, KG * WGM * WGN / 4) void gemm_splitk_kernel(const GemmArgs args) {
-    const GemmArgs p = select_problem(args);
-    constexpr int NTG = 64 * WGM * WGN;
-    constexpr int CE = Elem<T>::CE;
-    constexpr int BK = 8 * CE;
-    constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int RPP = NTG / 8;
-    constexpr int A_IT = BM / RPP, B_IT = BN / RPP;
-    static_assert(BM % RPP == 0 && BN % RPP == 0, "tile rows must be a multiple of the loader pass");
-    constexpr int STAGE = (BM + BN) * 128;
-    extern __shared__ __attribute__((aligned(16))) char smem_all[];
-    float* lnrow = reinterpret_cast<float*>(smem_all + KG * 2 * STAGE);
-
-    const int tid = threadIdx.x, kg = tid / NTG, gt = tid % NTG;
-    char* smem = smem_all + kg * 2 * STAGE;
-    const int lane = gt & 63, wave = gt >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int g = lane >> 5, li = lane & 31;
-    const int lrow = gt >> 3, lchunk = gt & 7;
-
-    int tm, tn;
-    tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
-    const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
-
-    const T* __restrict__ A = reinterpret_cast<const T*>(p.A);
-    const T* __restrict__ W = reinterpret_cast<const T*>(p.W);
-
-    // loader state as in gemm_kernel: no branches or selects on loaded values, rows past M re-read row M - 1,
-    // out-of-image taps read the page of zeros
-    const T* aptr[A_IT];
-    int ay[A_IT], ax[A_IT];
-#pragma unroll
-    for (int i = 0; i < A_IT; ++i) {
-        int r = m0 + lrow + i * RPP;
-        r = r < p.M ? r : p.M - 1;
-        ay[i] = ax[i] = 0;
-        if (AMODE == A_PLAIN) {
-            const int64_t ar = (int64_t)(r / p.a_rpi) * p.a_istride + p.a_off + r % p.a_rpi;
-            aptr[i] = A + ar * p.lda + lchunk * CE;
-        } else {
-            const int hw = p.cH * p.cW;
-            const int b = r / hw, pix = r % hw;
-            ay[i] = pix / p.cW;
-            ax[i] = pix % p.cW;
-            aptr[i] = A + ((int64_t)b * p.a_istride + p.a_off + pix) * p.lda + lchunk * CE;
-        }
-    }
-    const T* wptr = W + (int64_t)(n0 + lrow) * p.K + lchunk * CE;
-    const T* zptr = reinterpret_cast<const T*>(p.zeros);
-
-    // this group's k-tiles: [kbeg, kbeg + kcnt) of the KT tiles; all groups run ceil(KT / KG) iterations (the
-    // barriers are common), a group with fewer tiles re-loads its last one and skips the multiply
-    const int KT = p.K / BK, KH = (KT + KG - 1) / KG;
-    const int kbeg = kg * KH;
-    const int kcnt = KT - kbeg < KH ? (KT - kbeg > 0 ? KT - kbeg : 0) : KH;
-    auto tile_of = [&](int local) {
-        const int t = kbeg + (local < kcnt ? local : kcnt - 1);
-        return t < 0 ? 0 : (t < KT ? t : KT - 1);
-    };
-
-    u32x4 ra[2][A_IT], rb[2][B_IT];
-    auto gload = [&](int set, int local) {
-        const int kt = tile_of(local);
-        const int k0 = kt * BK;
-        if (AMODE == A_PLAIN) {
-#pragma unroll
-            for (int i = 0; i < A_IT; ++i) ra[set][i] = ld_global_16(aptr[i] + k0);
-        } else {
-            const int cc = kt / 9, tap = kt - cc * 9, c0 = cc * BK;
-            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-            const int64_t shift = (int64_t)(dy * p.cW + dx) * p.lda + c0;
-#pragma unroll
-            for (int i = 0; i < A_IT; ++i) {
-                const int yy = ay[i] + dy, xx = ax[i] + dx;
-                const bool ok = yy >= 0 && yy < p.cH && xx >= 0 && xx < p.cW;
-                const uint64_t mask = ok ? ~uint64_t(0) : uint64_t(0);
-                const uint64_t addr = (reinterpret_cast<uint64_t>(aptr[i] + shift) & mask) |
-                                      (reinterpret_cast<uint64_t>(zptr) & ~mask);
-                ra[set][i] = ld_global_16(reinterpret_cast<const void*>(addr));
-            }
-        }
-        const int kw = AMODE == A_PLAIN ? k0 : (kt % 9) * p.cC + (kt / 9) * BK;
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i) rb[set][i] = ld_global_16(wptr + (int64_t)i * RPP * p.K + kw);
-    };
-    auto sstore = [&](int set, int buf) {
-        char* sA = smem + buf * STAGE;
-        char* sB = sA + BM * 128;
-#pragma unroll
-        for (int i = 0; i < A_IT; ++i) {
-            const int r = lrow + i * RPP;
-            *reinterpret_cast<u32x4*>(sA + (r * 8 + swz(r, lchunk)) * 16) = ra[set][i];
-        }
-#pragma unroll
-        for (int i = 0; i < B_IT; ++i) {
-            const int r = lrow + i * RPP;
-            *reinterpret_cast<u32x4*>(sB + (r * 8 + swz(r, lchunk)) * 16) = rb[set][i];
-        }
-    };
-
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    auto compute = [&](int buf) {
-        const char* sA = smem + buf * STAGE;
-        const char* sB = sA + BM * 128;
-        typename Mma<T>::Frag fa[2][MI], fb[2][NI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) fa[0][i] = Mma<T>::load(sA, wm * WM + i * 32 + li, 0, g);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) fb[0][j] = Mma<T>::load(sB, wn * WN + j * 32 + li, 0, g);
-#pragma unroll
-        for (int ks = 0; ks < Mma<T>::KS; ++ks) {
-            if (ks + 1 < Mma<T>::KS) {
-#pragma unroll
-                for (int i = 0; i < MI; ++i) fa[(ks + 1) & 1][i] = Mma<T>::load(sA, wm * WM + i * 32 + li, ks + 1, g);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) fb[(ks + 1) & 1][j] = Mma<T>::load(sB, wn * WN + j * 32 + li, ks + 1, g);
-            }
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j) Mma<T>::mma(acc[i][j], fa[ks & 1][i], fb[ks & 1][j]);
-        }
-    };
-
-    gload(0, 0);
-    gload(1, 1);
-    float lncs[NI];
-#pragma unroll
-    for (int j = 0; j < NI; ++j) lncs[j] = 0.0f;
-    if (p.ln_stats) {
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int c = n0 + wn * WN + j * 32 + li;
-            if (c < p.N) lncs[j] = p.ln_colsum[c];
-        }
-        if (tid < BM) ln_tile_row(p, m0, n0, tid, lnrow);
-    }
-    sstore(0, 0);
-    __syncthreads();
-    for (int kt = 0; kt < KH; kt += 2) {
-        gload(0, kt + 2);
-        if (kt < kcnt) compute(0);              // uniform per wave
-        sstore(1, 1);
-        __syncthreads();
-        if (kt + 1 >= KH) break;
-        gload(1, kt + 3);
-        if (kt + 1 < kcnt) compute(1);
-        sstore(0, 0);
-        __syncthreads();
-    }
-
-    static_assert(KG * BM * BN * 4 <= KG * 2 * STAGE, "accumulator tiles must fit the stage buffers");
-    block_epilogue<T, BM, BN, WGM, WGN, KG>(p, acc, smem_all, lnrow, lncs, m0, n0);
-}
-
-template <typename T, int BM, int BN, int WGM, int WGN, int KG>
-static inline hipError_t launch_tile_splitk(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
-    constexpr int lds = KG * 2 * (BM + BN) * 128 + 8 * BM;
-    static_assert(lds <= 160 * 1024 && 64 * KG * WGM * WGN <= 1024, "LDS and workgroup size limits");
-    static_assert(BM <= 64 * WGM * WGN, "the row statistics are taken by the first BM threads (group 0)");
-    static bool configured = false;
-    if (!configured) {
-        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_splitk_kernel<T, BM, BN, WGM, WGN, A_PLAIN, KG>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (rc == hipSuccess)
-            rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_splitk_kernel<T, BM, BN, WGM, WGN, A_CONV3, KG>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (rc != hipSuccess) return rc;
-        configured = true;
-    }
-    if (configure_only) return hipSuccess;
-    const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN);
-    dim3 grid(tiles, a.nz > 1 ? a.nz : 1), block(64 * KG * WGM * WGN);
-    if (amode == A_PLAIN) hipLaunchKernelGGL((gemm_splitk_kernel<T, BM, BN, WGM, WGN, A_PLAIN, KG>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((gemm_splitk_kernel<T, BM, BN, WGM, WGN, A_CONV3, KG>), grid, block, lds, s, a);
-    return hipGetLastError();
-}
-
-template <typename T, int BM, int BN, int WGM, int WGN>
-static inline hipError_t launch_tile(const GemmArgs& a, int amode, hipStream_t s) {
-    const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN);
-    dim3 grid(tiles, a.nz > 1 ? a.nz : 1), block(64 * WGM * WGN);
-    if (amode == A_PLAIN) hipLaunchKernelGGL((gemm_kernel<T, BM, BN, WGM, WGN, A_PLAIN>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((gemm_kernel<T, BM, BN, WGM, WGN, A_CONV3>), grid, block, 0, s, a);
-    return hipGetLastError();
-}
-
-// Tile choice: the largest tile that still yields about two workgroups per CU; SwiGLU needs
-// wave tiles of 64 columns (gate and linear partner in the same lane).
-template <typename T>
-static inline hipError_t launch_gemm_t(const GemmArgs& a, int amode, hipStream_t s) {
-    const int nz = a.nz > 1 ? a.nz : 1;
-    const int64_t t128 = (int64_t)cdiv(a.M, 128) * cdiv(a.N, 128) * nz;
-    const int64_t t64x128 = (int64_t)cdiv(a.M, 64) * cdiv(a.N, 128) * nz;
-    if (t128 >= 384) return launch_tile<T, 128, 128, 2, 2>(a, amode, s);
-    if (t64x128 >= 384 || a.epi == EPI_SWIGLU) return launch_tile<T, 64, 128, 2, 2>(a, amode, s);
-    return launch_tile<T, 64, 64, 2, 2>(a, amode, s);
 }
 
 }  // namespace vpe

@@ -1,5 +1,4 @@
-// bf16-operand instantiations of the register-staged MFMA GEMM, and the choice between them and
-// the large-tile direct-to-LDS kernel.
+// The choice of tiling for the bf16 GEMMs.
 #include <cstdlib>
 
 #include "kernels.h"
@@ -24,29 +23,25 @@ namespace {
 // count is just above a whole number of rounds.
 int g_forced_tile = 0;
 bool g_no_small = false, g_no_splitk = false, g_no_strip = false, g_no_split = false;
-struct Cand { int kind, bm, bn, held; float alpha, beta; bool dma; };
+struct Cand { int kind, bm, bn, held; float alpha, beta; };
 constexpr Cand kCands[] = {
-    {256, 256, 256, 1, 15.83f, 0.300f, true},   // direct-to-LDS (launch_gemm_dma_bf16 describes the shapes)
-    {384, 384, 256, 1, 22.58f, 0.344f, true},
-    {128, 256, 128, 1, 10.33f, 0.406f, true},
-    {65, 64, 128, 3, 6.58f, 2.001f, true},
-    {64, 64, 64, 4, 5.28f, 3.287f, true},
-    {5, 64, 128, 2, 5.87f, 1.222f, true},
-    {4, 64, 64, 2, 4.79f, 1.411f, true},
-    {1, 128, 128, 2, 7.72f, 1.120f, false},     // register-staged (any operand size)
-    {2, 64, 128, 3, 5.96f, 1.972f, false},
-    {3, 64, 64, 4, 4.88f, 3.153f, false},
+    {256, 256, 256, 1, 15.83f, 0.300f},   // direct-to-LDS (launch_gemm_dma_bf16 describes the shapes)
+    {384, 384, 256, 1, 22.58f, 0.344f},
+    {128, 256, 128, 1, 10.33f, 0.406f},
+    {65, 64, 128, 3, 6.58f, 2.001f},
+    {64, 64, 64, 4, 5.28f, 3.287f},
+    {5, 64, 128, 2, 5.87f, 1.222f},
+    {4, 64, 64, 2, 4.79f, 1.411f},
 };
 }  // namespace
 
 // The model's pick for rows m_begin .. M - 1 of `a` and its predicted time in us.
-static int pick_tile(const GemmArgs& a, bool fits, float& best_cost) {
-    int best = 3;
+static int pick_tile(const GemmArgs& a, float& best_cost) {
+    int best = 128;
     best_cost = 0.0f;
     const bool no_small = g_no_small;
     const int rows = a.M - a.m_begin;
     for (const Cand& c : kCands) {
-        if (c.dma != fits && !(fits && no_small)) continue;     // register staging: operands past the 32-bit offsets
         if (no_small && (c.kind == 64 || c.kind == 65)) continue;
         if (g_no_splitk && (c.kind == 4 || c.kind == 5)) continue;
         if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;        // gate and linear partner are 64 physical columns of one wave's tile
@@ -62,23 +57,19 @@ static int pick_tile(const GemmArgs& a, bool fits, float& best_cost) {
     return best;
 }
 
-static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best, bool fits);
+static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best);
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
-    // the direct-to-LDS loader keeps byte offsets in 32-bit ints
-    const int64_t a_rows = amode == A_PLAIN ? (int64_t)(a.M / a.a_rpi + 1) * (a.a_istride > a.a_rpi ? a.a_istride : a.a_rpi)
-                                            : (int64_t)(a.M / (a.cH * a.cW) + 1) * a.a_istride;
-    const bool fits = a_rows * a.lda * 2 < (int64_t(1) << 31) && (int64_t)(a.N + 256) * a.K * 2 < (int64_t(1) << 31);
     float whole_cost;
-    const int whole = pick_tile(a, fits, whole_cost);
+    const int whole = pick_tile(a, whole_cost);
     // The one-per-CU tiles run in lockstep rounds of 256 and pay for a partly filled last round in full (ViT-g, 8
     // views: fc2 and the out-projection have 43 x 6 = 258 tiles of 256 x 256, QKV 774).  Two launches instead: whole
     // rounds of the large tile over the leading rows, then the remaining rows with whatever the model picks for them.
-    if (g_forced_tile == 0 && !g_no_split && fits && a.nz <= 1 && a.m_begin == 0) {
+    if (g_forced_tile == 0 && !g_no_split && a.nz <= 1 && a.m_begin == 0) {
         float split_cost = whole_cost;
         int split_kind = 0, split_rows = 0;
         for (const Cand& c : kCands) {
-            if (!c.dma || c.held != 1) continue;
+            if (c.held != 1) continue;
             const int tn = cdiv(a.N, c.bn), tm = cdiv(a.M, c.bm);
             const int64_t tiles = (int64_t)tm * tn;
             const int rounds = (int)(tiles / 256);
@@ -90,7 +81,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
             GemmArgs tail = a;
             tail.m_begin = tm_main * c.bm;
             float tail_cost;
-            pick_tile(tail, fits, tail_cost);
+            pick_tile(tail, tail_cost);
             if (main_cost + tail_cost < 0.93f * split_cost) {   // a second launch costs a few us the model does not see
                 split_cost = main_cost + tail_cost;
                 split_kind = c.kind;
@@ -104,13 +95,13 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
             hipError_t rc = launch_gemm_dma_bf16(split_kind, main, amode, s);
             if (rc != hipSuccess) return rc;
             float unused;
-            return launch_picked(tail, amode, s, pick_tile(tail, fits, unused), fits);
+            return launch_picked(tail, amode, s, pick_tile(tail, unused));
         }
     }
-    return launch_picked(a, amode, s, whole, fits);
+    return launch_picked(a, amode, s, whole);
 }
 
-static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best, bool fits) {
+static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best) {
     const int forced = g_forced_tile;
     // 3x3 convolutions: the strip kernel (conv_strip.h) where its 384 x 256 tiles make one well-filled round of the
     // 256 CUs (measured on 272 x 360 x 256 -> 256, 256 tiles: 128 against 144 us for the generic 384 x 256 kernel on the
@@ -120,16 +111,10 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
         const int shape = conv_strip_shape(a, forced == 9, nullptr);
         if (shape) return launch_conv_strip_bf16(shape, a, s);
     }
-    if ((forced == 384 || forced == 256 || forced == 128 || forced == 65 || forced == 5) && fits) best = forced;
-    if (forced == 4 && fits) best = a.epi == EPI_SWIGLU ? 5 : 4;
-    if (forced == 64 && fits) best = a.epi == EPI_SWIGLU ? 65 : 64;
-    if (forced == 1) best = a.epi == EPI_SWIGLU ? 2 : 3;
-    switch (best) {
-        case 4: case 5: case 64: case 65: case 128: case 256: case 384: return launch_gemm_dma_bf16(best, a, amode, s);
-        case 1: return launch_tile<bf16, 128, 128, 2, 2>(a, amode, s);
-        case 2: return launch_tile<bf16, 64, 128, 2, 2>(a, amode, s);
-        default: return launch_tile<bf16, 64, 64, 2, 2>(a, amode, s);
-    }
+    if (forced == 384 || forced == 256 || forced == 128 || forced == 65 || forced == 5) best = forced;
+    if (forced == 4) best = a.epi == EPI_SWIGLU ? 5 : 4;
+    if (forced == 64) best = a.epi == EPI_SWIGLU ? 65 : 64;
+    return launch_gemm_dma_bf16(best, a, amode, s);
 }
 
 // Reads the tuning aids; called at engine creation, outside any stream capture.

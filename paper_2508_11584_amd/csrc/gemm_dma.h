@@ -1,17 +1,13 @@
-// Large-tile MFMA GEMM for gfx950 with direct global->LDS loads (global_load_lds_dwordx4).
+// MFMA GEMM for gfx950 with direct global->LDS loads (global_load_lds_dwordx4).
 //
-// Why a second kernel: on MI355X the register-staged 128 x 128 tiles stop at 750-840 TFLOP/s: the
-// LDS write path (ds_write_b128 at ~80 bytes per clock per CU) and the global-load issue rate of
-// 8 waves cannot keep four MFMA pipes fed at 64 FLOP per loaded byte.  Here a workgroup owns a
-// 256 x BN tile (BN = 128 or 256), operands go from global memory straight into the swizzled LDS
-// tile (global_load_lds_dwordx4: no VGPR staging, no ds_write), the next k-tile's loads are issued
-// before the current tile's MFMAs, the LDS reads of k-step s + 1 are interleaved with the MFMAs of
-// step s (sched_group_barrier), and the accumulators leave through a per-wave LDS staging block
-// with 16-byte coalesced stores.  Measured: with the loads switched off the loop runs at 88 % of
-// the MFMA rate; the loads are the limit, and their rate grows with the number of waves issuing
-// them (4 waves: 670, 8 waves: 880, 16 waves per CU: 910-970 TFLOP/s on the 3x3 conv).
+// Operands go from global memory straight into the swizzled LDS tile (no VGPR staging, no ds_write: on MI355X register
+// staging stops at 750-840 TFLOP/s with 128 x 128 tiles, its LDS write path and load issue cannot keep four MFMA pipes fed),
+// later k-tiles' loads are in flight during the current tile's MFMAs, the LDS reads of k-step s + 1 are interleaved with the
+// MFMAs of step s (sched_group_barrier), and the accumulators leave through LDS with 16-byte coalesced stores.
+// A CU draws at most 56 bytes per clock through this path (load-only probe, 128-byte rows, operands in L2; 40-45 from
+// the memory-side cache with two 32 KB stages in flight).
 //
-// Same operands, A modes and epilogues as gemm_kernel (see gemm.h); bf16 only.
+// bf16, and fp32 on the bf16 instructions (Split3).  A modes and epilogues: gemm.h.
 #pragma once
 #include <type_traits>
 
@@ -37,6 +33,43 @@ __device__ __forceinline__ void pipeline_barrier() {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(N) & ~0x0F00);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// fp32 products on the bf16 matrix instructions.  A value is the sum of three bf16 terms, each the rounded rest of the
+// one before (8 + 8 + 8 significant bits; the rests are exact), and six of the nine products of the terms are taken: the
+// three left out are at most 2^-27 of the product.  The instruction multiplies exactly and accumulates in fp32, so what
+// remains is the rounding of the accumulation, once per 16 k elements and product where v_mfma_f32_32x32x2_f32 rounds
+// once per 2.  Six bf16 instructions take 192 clocks for a 32 x 32 x 16 block, eight of the fp32 ones 512.
+// (An infinite or NaN operand gives NaN.)
+struct Split3 { bf16x8 t[3]; };
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ Split3 split3(const f32x4& lo, const f32x4& hi) {
+    // the rest x - term of the lower / upper element of a pair in one instruction, v_dot2c_f32_bf16: (term0, term1) . (-1, 0) + x
+    // (the constants are kept in registers: as an inline constant -1.0 stands for the upper element)
+    uint32_t c0 = 0x0000BF80u, c1 = 0xBF800000u;
+    asm("" : "+s"(c0), "+s"(c1));
+    const bf16x2 m0 = __builtin_bit_cast(bf16x2, c0), m1 = __builtin_bit_cast(bf16x2, c1);
+    Split3 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x0 = e < 2 ? lo[2 * e] : hi[2 * e - 4], x1 = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const bf16x2 p = {(bf16)x0, (bf16)x1};
+            r.t[k][2 * e] = p[0];
+            r.t[k][2 * e + 1] = p[1];
+            if (k < 2) {
+                x0 = __builtin_amdgcn_fdot2_f32_bf16(p, m0, x0, false);
+                x1 = __builtin_amdgcn_fdot2_f32_bf16(p, m1, x1, false);
+            }
+        }
+    }
+    return r;
+}
+// Product t of six (small ones first) of two split operands.
+__device__ __forceinline__ f32x16 split_mma(int t, const Split3& a, const Split3& b, f32x16 c) {
+    const int ia = t == 0 ? 2 : t == 1 ? 0 : t == 2 ? 1 : t == 3 ? 1 : 0, ib = t == 0 ? 0 : t == 1 ? 2 : t == 2 ? 1 : t == 3 ? 0 : t == 4 ? 1 : 0;
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.t[ia], b.t[ib], c, 0, 0, 0);
 }
 
 // Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
@@ -84,10 +117,9 @@ struct EpilogueRows {
     }
 };
 
-template <int MI, int NI, int WM, int WN, bool PADDED = false>
+template <typename T, int MI, int NI, int WM, int WN, bool PADDED = false>
 __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, const float* lnrow,
                                                    int wave, int wm, int wn, int lane, int m0, int n0) {
-    typedef bf16 T;
     const int g = lane >> 5, li = lane & 31;
     float* sC = reinterpret_cast<float*>(smem) + wave * (32 * WN);
     const int wrow0 = m0 + wm * WM, wcol0 = n0 + wn * WN;
@@ -303,21 +335,21 @@ __device__ __forceinline__ void rowdot_epilogue_transposed(const GemmArgs& p, f3
 // KG: groups of WGM x WGN waves that share the tile's loads and take KS / KG of the k-steps of every k-tile each; their
 // partial sums are added in LDS in a fixed order by the block-level epilogue.
 // RING: the operand tiles of a k-tile are units of their own in a ring of five (A0 B0 A1 B1 A2 ...), see the main loop.
-template <int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int BM_ = 256, bool RD = false, int KG = 1, bool RING = false>
+template <typename T, int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int BM_ = 256, bool RD = false, int KG = 1, bool RING = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void gemm_dma_kernel(const GemmArgs args) {
     const GemmArgs p = select_problem(args);
-    typedef bf16 T;
-    constexpr int BM = BM_, CE = 8, NW = WGN * WGM * KG;
-    static_assert((BM * BK * 2) % (1024 * NW) == 0 && (BN * BK * 2) % (1024 * NW) == 0 && BM % (32 * WGM) == 0, "loader / wave tiling");
+    constexpr int BM = BM_, CE = Elem<T>::CE, ESZ = sizeof(T), NW = WGN * WGM * KG;
+    static_assert((BM * BK * ESZ) % (1024 * NW) == 0 && (BN * BK * ESZ) % (1024 * NW) == 0 && BM % (32 * WGM) == 0, "loader / wave tiling");
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
-    constexpr int ROWB = BK * 2, CPR = BK / 8, RPI = 64 / CPR;   // row bytes, chunks per row, rows per DMA instruction
+    constexpr int ROWB = BK * ESZ, CPR = BK / CE, RPI = 64 / CPR;   // row bytes, chunks per row, rows per DMA instruction
     constexpr int KS = BK / 16 / KG;                    // k-steps of a k-tile that a wave takes
     constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB, STAGE = A_BYTES + B_BYTES;
     static_assert((BK / 16) % KG == 0 && (!RING || (A_BYTES == B_BYTES && KG == 1 && S == 2)), "k-step groups / ring units");
     constexpr int A_SLOTS = A_BYTES / (1024 * NW), B_SLOTS = B_BYTES / (1024 * NW);   // 1 KB DMA instructions per wave per k-tile
     constexpr int PD = S - 1;
-    // chunk swizzle: 256 bytes of LDS (64 banks) hold 2 rows of 128 bytes or 4 rows of 64 bytes
-    constexpr int SW_SHIFT = BK == 64 ? 1 : 2, SW_MASK = CPR - 1;
+    constexpr bool LN_LATE = RING;
+    // chunk swizzle: 256 bytes of LDS (64 banks) hold one row of 256 bytes, 2 rows of 128 or 4 rows of 64
+    constexpr int SW_SHIFT = ROWB == 256 ? 0 : ROWB == 128 ? 1 : 2, SW_MASK = CPR - 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -329,17 +361,23 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
     const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
 
-    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (RING, whose stages take
-    // the whole LDS: behind the staging blocks, written when the k loop is done)
-    constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : NW * 32 * WN * 4;
-    float* lnrow = reinterpret_cast<float*>(smem + (!RING && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
-
-    const char* __restrict__ A = reinterpret_cast<const char*>(p.A);
-    const char* __restrict__ W = reinterpret_cast<const char*>(p.W);
+    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (LN_LATE, where the stages leave
+    // no room: behind the staging blocks, written when the k loop is done)
+    constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : WN % 64 ? BM * BN * 4 : NW * 32 * WN * 4;
+    float* lnrow = reinterpret_cast<float*>(smem + (!LN_LATE && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
 
     // --- loader state.  DMA instruction `slot` of this wave fills 1 KB of LDS = RPI consecutive rows of
     // the A (or B) tile, row group rg = wave + NW slot: lane l lands on row rg*RPI + l/CPR, physical
-    // chunk l%CPR, so it must fetch the logical chunk (l%CPR) ^ swizzle(row) of that row.
+    // chunk l%CPR, so it must fetch the logical chunk (l%CPR) ^ swizzle(row) of that row.  Byte offsets are 32-bit, from
+    // the tile's first row (whose place in the tensor is a 64-bit one).
+    const int hw = p.cH * p.cW;
+    auto a_row = [&](int r) -> int64_t {        // row of A that row r of the problem reads (conv: centre pixel)
+        if (AMODE == A_PLAIN) return p.a_rpi >= p.M ? (int64_t)p.a_off + r : (int64_t)(r / p.a_rpi) * p.a_istride + p.a_off + r % p.a_rpi;
+        return (int64_t)(r / hw) * p.a_istride + p.a_off + r % hw;
+    };
+    const int64_t a_first = a_row(m0 < p.M ? m0 : p.M - 1);
+    const char* __restrict__ A = reinterpret_cast<const char*>(p.A) + a_first * p.lda * ESZ;
+    const char* __restrict__ W = reinterpret_cast<const char*>(p.W) + (int64_t)n0 * p.K * ESZ;
     int aoff[A_SLOTS];          // byte offset of the lane's chunk from A (k = 0; conv: centre pixel)
     int ay[A_SLOTS], ax[A_SLOTS];
     int boff[B_SLOTS];
@@ -350,22 +388,18 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         int r = m0 + row;
         r = r < p.M ? r : p.M - 1;
         ay[s] = ax[s] = 0;
-        if (AMODE == A_PLAIN) {
-            const int64_t ar = (int64_t)(r / p.a_rpi) * p.a_istride + p.a_off + r % p.a_rpi;
-            aoff[s] = (int)((ar * p.lda + c * CE) * 2);
-        } else {
-            const int hw = p.cH * p.cW;
-            const int b = r / hw, pix = r % hw;
+        aoff[s] = (int)(((a_row(r) - a_first) * p.lda + c * CE) * ESZ);
+        if (AMODE == A_CONV3) {
+            const int pix = r % hw;
             ay[s] = pix / p.cW;
             ax[s] = pix % p.cW;
-            aoff[s] = (int)((((int64_t)b * p.a_istride + p.a_off + pix) * p.lda + c * CE) * 2);
         }
     }
 #pragma unroll
     for (int s = 0; s < B_SLOTS; ++s) {
         const int row = (wave + NW * s) * RPI + lane / CPR;
         const int c = (lane % CPR) ^ ((row >> SW_SHIFT) & SW_MASK);
-        boff[s] = (int)(((int64_t)(n0 + row) * p.K + c * CE) * 2);
+        boff[s] = (row * p.K + c * CE) * ESZ;
     }
     const char* zptr = reinterpret_cast<const char*>(p.zeros);
 
@@ -374,11 +408,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             const int k0 = kt * BK;
 #pragma unroll
             for (int s = 0; s < A_SLOTS; ++s)
-                __builtin_amdgcn_global_load_lds(VPE_GPTR(A + aoff[s] + k0 * 2), VPE_LPTR(sA + (wave + NW * s) * 1024), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(VPE_GPTR(A + aoff[s] + k0 * ESZ), VPE_LPTR(sA + (wave + NW * s) * 1024), 16, 0, 0);
         } else {
             const int cc = kt / 9, tap = kt - cc * 9, c0 = cc * BK;    // chunk-major, tap-minor k order
             const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-            const int shift = ((dy * p.cW + dx) * (int)p.lda + c0) * 2;
+            const int shift = ((dy * p.cW + dx) * (int)p.lda + c0) * ESZ;
 #pragma unroll
             for (int s = 0; s < A_SLOTS; ++s) {
                 const int yy = ay[s] + dy, xx = ax[s] + dx;
@@ -394,7 +428,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         const int kw = AMODE == A_PLAIN ? kt * BK : (kt % 9) * p.cC + (kt / 9) * BK;   // weight column of this k-tile
 #pragma unroll
         for (int s = 0; s < B_SLOTS; ++s)
-            __builtin_amdgcn_global_load_lds(VPE_GPTR(W + boff[s] + kw * 2), VPE_LPTR(sB + (wave + NW * s) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(VPE_GPTR(W + boff[s] + kw * ESZ), VPE_LPTR(sB + (wave + NW * s) * 1024), 16, 0, 0);
     };
     auto dma = [&](int stage, int kt) {
         dma_a(smem + stage * STAGE, kt);
@@ -421,7 +455,35 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     auto compute = [&](const char* tile_a, const char* tile_b, auto&& between) {
         const char* sA = tile_a + arow0 * ROWB;
         const char* sB = tile_b + brow0 * ROWB;
-        if constexpr (FRAG_DB) {
+        if constexpr (ESZ == 4) {
+            // fp32: a lane's eight k elements of a step are two chunks of its row
+            auto chunk = [&](const char* base, int ks, int sw, int half) {
+                return *reinterpret_cast<const f32x4*>(base + ((4 * (ks0 + ks) + 2 * g + half) ^ sw) * 16);
+            };
+            f32x4 ra[MI][2], rb[NI][2];
+            auto read = [&](int ks) {
+#pragma unroll
+                for (int i = 0; i < MI; ++i) { ra[i][0] = chunk(sA + i * 32 * ROWB, ks, asw, 0); ra[i][1] = chunk(sA + i * 32 * ROWB, ks, asw, 1); }
+#pragma unroll
+                for (int j = 0; j < NI; ++j) { rb[j][0] = chunk(sB + j * 32 * ROWB, ks, bsw, 0); rb[j][1] = chunk(sB + j * 32 * ROWB, ks, bsw, 1); }
+            };
+            read(0);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                Split3 fa[MI], fb[NI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) fa[i] = split3(ra[i][0], ra[i][1]);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) fb[j] = split3(rb[j][0], rb[j][1]);
+                if (ks + 1 < KS) read(ks + 1);
+#pragma unroll
+                for (int t = 0; t < 6; ++t)
+#pragma unroll
+                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) acc[i][j] = split_mma(t, fa[i], fb[j], acc[i][j]);
+            }
+        } else if constexpr (FRAG_DB) {
             bf16x8 fa[2][MI], fb[2][NI];
             const int ca0 = ((2 * ks0 + g) ^ asw) * 16, cb0 = ((2 * ks0 + g) ^ bsw) * 16;
 #pragma unroll
@@ -489,6 +551,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     // tile kt.  Prefetches are unconditional (clamped index): every path has the same loads in flight.
     const int KT = p.K / BK;
     auto last = [&](int kt) { return kt < KT ? kt : KT - 1; };
+    float mean = 0.0f, rstd = 0.0f;
     if constexpr (RING) {
         // Two whole stages of a 256 x 256 tile leave 32 KB of the LDS unused and give a load one tile time to arrive (about
         // 2100 clocks, as long as the loads of a tile take by themselves).  Five units of 32 KB instead: during tile kt the A
@@ -497,7 +560,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         dma_a(unit[0], 0);
         dma_b(unit[1], 0);
         dma_a(unit[2], last(1));
-        float mean = 0.0f, rstd = 0.0f;
         if (p.ln_stats && tid < BM) ln_tile_row(p, m0, n0, tid, mean, rstd);
         for (int kt = 0; kt < KT; ++kt) {
             pipeline_barrier<A_SLOTS>();                      // A and B of tile kt are here; A of kt + 1 may be on its way
@@ -512,19 +574,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             char* const u1 = unit[1];
             unit[0] = unit[2]; unit[1] = unit[3]; unit[2] = unit[4]; unit[3] = u0; unit[4] = u1;
         }
-        pipeline_barrier<0>();                                // drain the clamped tail prefetches before LDS is reused
-        if (p.ln_stats) {
-            if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
-            __syncthreads();
-        }
     } else {
 #pragma unroll
         for (int s = 0; s < PD; ++s) dma(s, last(s));
         // behind the first tile loads, ordered before the epilogue by the loop's barriers
         if (p.ln_stats && tid < BM) {
-            float mean, rstd;
             ln_tile_row(p, m0, n0, tid, mean, rstd);
-            *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+            if (!LN_LATE) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
         }
         int cur = 0, nxt = PD;                                // stages of tiles kt and kt + PD
         for (int kt = 0; kt < KT; ++kt) {
@@ -535,12 +591,16 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             cur = cur + 1 == S ? 0 : cur + 1;
             nxt = nxt + 1 == S ? 0 : nxt + 1;
         }
-        pipeline_barrier<0>();                                // drain the clamped tail prefetches before LDS is reused
+    }
+    pipeline_barrier<0>();                                    // drain the clamped tail prefetches before LDS is reused
+    if (LN_LATE && p.ln_stats) {
+        if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+        __syncthreads();
     }
 
     if constexpr (WN % 64 != 0 || KG > 1) {
         // Small tiles (32-column wave tiles): a wave does not hold whole 64-column groups, so the tile leaves
-        // through the block-level epilogue of the register-staged kernels (whole tile staged in LDS).
+        // through the block-level epilogue (whole tile staged in LDS).
         static_assert(KG > 1 || BM * BN * 4 <= S * STAGE, "accumulator tile must fit the stage buffers");
         float lncs[NI];
 #pragma unroll
@@ -553,19 +613,20 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     }
 
     if constexpr (RD) rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
-    else wave_tile_epilogue<MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
+    else wave_tile_epilogue<T, MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
 }
 
-template <int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
+template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     constexpr int nt = 64 * WGM * WGN * KG;
-    constexpr int stage_b = RING ? 5 * BM * BK * 2 : S * (BM + BN) * BK * 2;
-    constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
+    constexpr bool late = RING;
+    constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
+    constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : BN / WGN % 64 ? BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
     constexpr int ln_b = BM * 8;                                          // (mean, rstd) of the tile's rows
-    constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
+    constexpr int lds = late ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024, "LDS budget of one CU, workgroup size");
-    auto plain = &gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
-    auto conv = &gemm_dma_kernel<BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
+    auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
+    auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
     static bool configured = false;
     if (!configured) {
         hipError_t rc = hipSuccess;

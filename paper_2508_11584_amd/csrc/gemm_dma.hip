@@ -24,13 +24,13 @@ namespace vpe {
 hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStream_t s) {
     const bool rd = amode == A_CONV3 && a.epi == EPI_ROWDOT && !a.ln_stats;   // projection epilogue from transposed accumulators
     switch (kind) {
-        case 4: return launch_gemm_dma<64, 64, 4, 1, 2, 2, 64, false, 4>(a, amode, s);
-        case 5: return launch_gemm_dma<128, 64, 3, 2, 2, 2, 64, false, 2>(a, amode, s);
-        case 64: return launch_gemm_dma<64, 64, 2, 2, 2, 2, 64>(a, amode, s);
-        case 65: return launch_gemm_dma<128, 64, 2, 2, 2, 2, 64>(a, amode, s);
-        case 384: return rd ? launch_gemm_dma<256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<256, 32, 2, 4, 2, 1, 384>(a, amode, s);
-        case 256: return rd ? launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, amode, s) : launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, amode, s);
-        default: return launch_gemm_dma<128, 64, 3, 4, 2, 1>(a, amode, s);
+        case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, false, 4>(a, amode, s);
+        case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, amode, s);
+        case 64: return launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, amode, s);
+        case 65: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, amode, s);
+        case 384: return rd ? launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s);
+        case 256: return rd ? launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, amode, s);
+        default: return launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, amode, s);
     }
 }
 // 3x3 convolution from an input strip in LDS (conv_strip.h), 96 x 128 wave tiles: 768 x 128 tiles (eight waves on top
@@ -70,14 +70,14 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_conv_strip<384, 256, 4, 2, 1, false>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, true>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, false>(a, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 32, 2, 4, 2, 1, 384>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 32, 2, 4, 2, 1, 384, true>(a, A_CONV3, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, A_CONV3, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<64, 64, 4, 1, 2, 2, 64, false, 4>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<128, 64, 3, 2, 2, 2, 64, false, 2>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<128, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
-    return rc != hipSuccess ? rc : launch_gemm_dma<128, 64, 3, 4, 2, 1>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, A_CONV3, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, A_CONV3, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, false, 4>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
+    return rc != hipSuccess ? rc : launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, A_PLAIN, nullptr, true);
 }
 }  // namespace vpe

@@ -224,6 +224,15 @@ def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
                            img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 141, 241)
 
 
+@pytest.mark.parametrize("width", [64, 128, 192])
+def test_fp32_products_on_short_and_ragged_shapes(width):
+    # fp32 operands as three bf16 terms: one to three k-tiles, 38 tokens a view (tiles and 8-row groups straddle two views),
+    # a last 128-column tile that is half empty, convolutions from 5 x 7 up to 40 x 56 (one and several tiles per CU);
+    # the gates are those of every fp32 model (1e-4)
+    check_all(vi.ModelSpec("short_f32_%d" % width, dtype="f32", dim=width, depth=4, heads=width // 64, mlp_hidden=3 * width, registers=2,
+                           batch=2, img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=2 * width), 142, 242)
+
+
 @pytest.mark.parametrize("shape", ["1", "2"])
 def test_strip_convolution_kernel(shape, monkeypatch):
     # the 3x3 convolution that forms its nine taps from one input strip in LDS, in both of its tile shapes (1: 384 x 256,
