@@ -13,6 +13,7 @@
 #pragma once
 #include "common.h"
 #include "gemm.h"
+#include "split3.h"
 
 namespace vpe {
 
@@ -51,18 +52,11 @@ template <> struct AttnMma<bf16> {
     static constexpr int QF = 4;                  // q fragments per lane (4 k-steps of 16 over dh = 64)
     typedef bf16x8 QFrag;
     static constexpr int ROWB = 128;              // bytes per 64-element row
+    static __device__ __forceinline__ int chunk_at(int row, int chunk) { return swz(row, chunk); }   // where a row's chunk is stored
     static __device__ __forceinline__ QFrag load_q(const bf16* qrow, int ks, int g) {
         return *reinterpret_cast<const QFrag*>(qrow + 16 * ks + 8 * g);
     }
     static __device__ __forceinline__ QFrag zero_q() { return QFrag{0, 0, 0, 0, 0, 0, 0, 0}; }
-    // S^T block (32 keys x 32 queries) += K[keys][dh] Q^T
-    static __device__ __forceinline__ void qk(f32x16& s, const char* sK, int krow, const QFrag* q, int g) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(sK + (krow * 8 + swz(krow, 2 * ks + g)) * 16);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q[ks], s, 0, 0, 0);
-        }
-    }
     // Both 32-key blocks of a tile at once: S0^T, S1^T = K[0..31], K[32..63] times Q^T.  The two accumulation chains
     // alternate (consecutive MFMAs are independent) and the K fragments of k-step ks + 1 are read while the MFMAs of
     // step ks run, instead of read - wait - multiply eight times in a row.
@@ -146,59 +140,57 @@ template <> struct AttnMma<bf16> {
     }
 };
 
+// fp32: every operand as three bf16 terms (Split3), six MFMAs per product block.  Queries are split once, keys and values by
+// each wave as it reads them, probabilities in registers.  The score block's rows are permuted as in the bf16 form, so a
+// lane's eight probabilities of a k-step are eight consecutive keys here too.  With v_mfma_f32_32x32x2_f32 a 64-key tile
+// is 8192 clocks of a wave's matrix pipe, split 3072 and about 750 vector instructions.
 template <> struct AttnMma<float> {
-    static constexpr int QF = 4;                  // 4 macro steps of 16 dh
-    struct QFrag { f32x4 lo, hi; };
+    static constexpr int QF = 4;                  // 4 steps of 16 dh
+    typedef Split3 QFrag;
     static constexpr int ROWB = 256;
-    static __device__ __forceinline__ QFrag load_q(const float* qrow, int ks, int g) {
-        QFrag f;
-        f.lo = *reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g);
-        f.hi = *reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g + 4);
-        return f;
+    // a row covers all 64 banks: 16 rows of one logical chunk fall on 16 different 16-byte groups
+    static __device__ __forceinline__ int chunk_at(int row, int chunk) { return chunk ^ (row & 15); }
+    static __device__ __forceinline__ Split3 load_split(const char* tile, int row, int chunk) {
+        return split3(*reinterpret_cast<const f32x4*>(tile + (row * 16 + chunk_at(row, chunk)) * 16),
+                      *reinterpret_cast<const f32x4*>(tile + (row * 16 + chunk_at(row, chunk + 1)) * 16));
     }
-    static __device__ __forceinline__ QFrag zero_q() { return QFrag{{0, 0, 0, 0}, {0, 0, 0, 0}}; }
-    static __device__ __forceinline__ void qk(f32x16& s, const char* sK, int krow, const QFrag* q, int g) {
+    static __device__ __forceinline__ QFrag load_q(const float* qrow, int ks, int g) {
+        return split3(*reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g), *reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g + 4));
+    }
+    static __device__ __forceinline__ QFrag zero_q() { return split3(f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}); }
+    static __device__ __forceinline__ void qk2(f32x16& s0, f32x16& s1, const char* sK, int li, const QFrag* q, int g) {
+        const int kr = (li & 0x13) | ((li & 8) >> 1) | ((li & 4) << 1);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(sK + (krow * 16 + swz(krow, 4 * ks + 2 * g)) * 16);
-            const f32x4 hi = *reinterpret_cast<const f32x4*>(sK + (krow * 16 + swz(krow, 4 * ks + 2 * g + 1)) * 16);
+            const Split3 a0 = load_split(sK, kr, 4 * ks + 2 * g), a1 = load_split(sK, kr + 32, 4 * ks + 2 * g);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(lo[i], q[ks].lo[i], s, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(hi[i], q[ks].hi[i], s, 0, 0, 0);
+            for (int t = 0; t < 6; ++t) {
+                s0 = split_mma(t, a0, q[ks], s0);
+                s1 = split_mma(t, a1, q[ks], s1);
+            }
         }
     }
-    static __device__ __forceinline__ void qk2(f32x16& s0, f32x16& s1, const char* sK, int li, const QFrag* q, int g) {
-        qk(s0, sK, li, q, g);
-        qk(s1, sK, 32 + li, q, g);
-    }
-    static __device__ __forceinline__ int key_of(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
+    static __device__ __forceinline__ int key_of(int v, int g) { return 16 * (v >> 3) + 8 * g + (v & 7); }
+    static constexpr bool MFMA_ROWSUM = false;
     template <bool LM>
     static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, f32x16&, float& psum, const char* sV, int li,
                                                    f32x16* sc, float scale, float ref, int g) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int st = 0; st < 4; ++st) {
+            f32x4 p[2];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                sc[kb][v] = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], scale, -ref));
-                psum += sc[kb][v];
+            for (int kk = 0; kk < 8; ++kk) {
+                const float e = __builtin_amdgcn_exp2f(fmaf(sc[st >> 1][8 * (st & 1) + kk], scale, -ref));
+                psum += e;
+                p[kk >> 2][kk & 3] = e;
             }
+            const Split3 b = split3(p[0], p[1]);
+            const Split3 a0 = load_split(sV, li, 4 * st + 2 * g), a1 = load_split(sV, li + 32, 4 * st + 2 * g);
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            pv(o0, sV, li, kb, sc[kb], g);
-            pv(o1, sV, 32 + li, kb, sc[kb], g);
-        }
-    }
-    // one MFMA per score element index v: k slot g is key 8 (v / 4) + 4 g + v % 4 of the block
-    static constexpr bool MFMA_ROWSUM = false;
-    static __device__ __forceinline__ void pv(f32x16& o, const char* sV, int drow, int kb, const f32x16& p, int g) {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            // keys 32 kb + 8 q4 + 4 g .. + 3  -> float chunk index (32 kb + 8 q4 + 4 g) / 4
-            const int c = 8 * kb + 2 * q4 + g;
-            const f32x4 a = *reinterpret_cast<const f32x4*>(sV + (drow * 16 + swz(drow, c)) * 16);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], p[4 * q4 + i], o, 0, 0, 0);
+            for (int t = 0; t < 6; ++t) {
+                o0 = split_mma(t, a0, b, o0);
+                o1 = split_mma(t, a1, b, o1);
+            }
         }
     }
 };
@@ -313,8 +305,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         for (int i = 0; i < (DB ? 0 : CH); ++i) {
             const int idx = (tid + i * NT) / CPR;
             const int row = idx & 63;
-            const int phys = (lchunk & ~7) | swz(row, lchunk & 7);
-            *reinterpret_cast<u32x4*>(base + (idx >> 6) * TILE + (row * CPR + phys) * 16) = rg[i];
+            *reinterpret_cast<u32x4*>(base + (idx >> 6) * TILE + (row * CPR + AttnMma<T>::chunk_at(row, lchunk)) * 16) = rg[i];
         }
     };
 
@@ -329,7 +320,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     constexpr int NDMA = KW * 2 * G / NW;              // instructions per wave per iteration
     static_assert(!DB || (G % NW == 0 && (NW * RPI) % 16 == 0) || NW == G, "loader mapping of the direct-to-LDS path");
     const int drow = wave * RPI + lane / CPR;
-    const int dlc = ((lane % CPR) & ~7) | (((lane % CPR) & 7) ^ ((drow >> 1) & 7));
+    const int dlc = AttnMma<T>::chunk_at(drow, lane % CPR);          // (exclusive or with the row's term: its own inverse)
     const T* kdma = kbase + (int64_t)drow * ld + dlc * CE;
     const T* vdma = vt + (int64_t)drow * p.npad + dlc * CE;
     auto dma = [&](char* base, int it) {               // tiles of iteration `it` into the stage at `base`

@@ -10,12 +10,12 @@ static hipError_t launch_variant(int variant, const AttnArgs& a, hipStream_t s, 
     switch (variant) {
         case 114: return launch_attention_variant<T, 1, 1, 4>(a, s, cfg);
         case 141: return launch_attention_variant<T, 1, 4, 1>(a, s, cfg);
+        case 122: return launch_attention_variant<T, 1, 2, 2>(a, s, cfg);
         default: break;
     }
     if constexpr (sizeof(T) == 2) {
         switch (variant) {
             case 214: return launch_attention_variant<T, 2, 1, 4>(a, s, cfg);
-            case 122: return launch_attention_variant<T, 1, 2, 2>(a, s, cfg);
             case 124: return launch_attention_variant<T, 1, 2, 4>(a, s, cfg);
             case 224: return launch_attention_variant<T, 2, 2, 4>(a, s, cfg);
             default: break;
@@ -37,9 +37,11 @@ hipError_t configure_attention() {
         hipError_t rc = launch_variant<bf16>(v, a, nullptr, true);
         if (rc != hipSuccess) return rc;
     }
-    hipError_t rc = launch_variant<float>(114, a, nullptr, true);
-    if (rc != hipSuccess) return rc;
-    return launch_variant<float>(141, a, nullptr, true);
+    for (int v : {114, 122, 141}) {
+        hipError_t rc = launch_variant<float>(v, a, nullptr, true);
+        if (rc != hipSuccess) return rc;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
@@ -61,6 +63,13 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     const int64_t qblocks = (int64_t)cdiv(a.N, 32) * a.B * a.heads;
     int variant = qblocks >= 2048 ? 141 : (qblocks >= 400 || a.shared_gpu) ? 122 : 124;
     if (forced) variant = forced;
-    return dtype ? launch_variant<bf16>(variant, a, s) : launch_variant<float>(forced == 141 || qblocks >= 2048 ? 141 : 114, a, s);
+    if (dtype) return launch_variant<bf16>(variant, a, s);
+    // fp32: a workgroup of any shape fills a CU's LDS, or half of it with (1,4,1), so what counts is whole rounds of the 256 CUs.
+    // us, the kernel on fp32 instructions / (1,1,4) (1,2,2) (1,4,1) here:
+    //   54 pairs (ViT-S 224x224)  15.8 / 14.1 15.2 20.9      288 (ViT-S 476x630) 79.0 / 66.9 51.1 86.2
+    //   516 (ViT-B 518x518)      116.3 / 100.5 91.1 84.5    1032 (ViT-S 518x518 x4) 192 / 167 139 143     2064 (ViT-B x4) 280 / 293 237 215
+    int v32 = qblocks <= 256 ? 114 : qblocks <= 512 ? 122 : 141;
+    if (forced == 114 || forced == 122 || forced == 141) v32 = forced;
+    return launch_variant<float>(v32, a, s);
 }
 }  // namespace vpe

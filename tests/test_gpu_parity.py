@@ -224,6 +224,16 @@ def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
                            img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 141, 241)
 
 
+@pytest.mark.parametrize("variant", ["114", "122", "141"])
+def test_fp32_attention_shapes(variant, monkeypatch):
+    # every workgroup shape of the fp32 attention: 38 tokens a view (one ragged key tile, fewer than the key waves), and 166
+    # (three tiles, the last of 38 keys: key waves with unequal numbers of tiles); fp32 gates
+    monkeypatch.setenv("VPE_ATTN_VARIANT", variant)
+    check_all(vi.ModelSpec("attn_f32_" + variant, dtype="f32", **MEDIUM), 143, 243, kinds=("seg",))
+    check_all(vi.ModelSpec("attn_f32_short_" + variant, dtype="f32", **{**MEDIUM, "registers": 2, "batch": 2, "img_h": 70, "img_w": 98}),
+              144, 244, kinds=("seg",))
+
+
 @pytest.mark.parametrize("width", [64, 128, 192])
 def test_fp32_products_on_short_and_ragged_shapes(width):
     # fp32 operands as three bf16 terms: one to three k-tiles, 38 tokens a view (tiles and 8-row groups straddle two views),
