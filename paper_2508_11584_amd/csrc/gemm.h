@@ -103,24 +103,28 @@ __device__ __forceinline__ float gelu_erf(float v) {
     return 0.5f * v * (1.0f + copysignf(erf_abs, v));
 }
 
-// The same function for results that are rounded to bf16: v / 2 + |v| h(|v|) with h(u) = erf(u / sqrt 2) / 2 = u P(u^2) on
-// |v| <= 3 sqrt 2, P of degree 9 (least-squares fit at Chebyshev nodes, the fp32 coefficients then searched for the smallest error of the
-// fp32 evaluation, 8.5e-6 of h; beyond, the value at the end), Horner in fp32: 14 instructions, no reciprocal and no exponential (18 with erf, its sign and the product
-// with v one after the other; 23 issue slots of the form above).  The vector pipe is what the GELU epilogue of a large tile
-// waits for (fc1 with 384 x 256 tiles: ViT-L x 4 74.9 -> 72.7 us, ViT-B 52.6 -> 50.6; 64 x 64: ViT-S 9.8 -> 9.7).  The result differs from the exact form by at most 0.9e-5 |v| -- 1/400 of a bf16 rounding step.
+// The same function for results that are rounded to bf16: erf(x) = x P(x^2) on |x| <= 3, P of degree 9 (least-squares fit
+// at Chebyshev nodes, |error of erf| <= 2.1e-5; beyond 3 the value at 3, 0.99998), Horner in fp32: 18 instructions, no
+// reciprocal and no exponential (two quarter-rate instructions of the form above, 23 issue slots).  The result differs from
+// the exact form by at most 1.04e-5 |v| (rms, before rounding: 4.2e-6 on 2 < |v| < 3, 6.5e-6 up to 3.5, 1.0e-5 up to 4.25).
+// For positive v that is below 1/380 of a bf16 rounding step; for v < -3, where the result is far smaller than |v|, it is
+// the larger error: 1 % of the result at -3.5, 8 % at -4, and from about -4.4 on the result is 1e-5 v instead of almost nothing.
+// (Folding the sign and both products into a last FMA saves four instructions, 1-3 % of fc1, but the fits of that form
+// with this error in the tail are 2.4 times worse on 3 < |v| < 3.5, and -inf gives NaN.)
 __device__ __forceinline__ float gelu_erf_bf16(float v) {
-    const float u = fminf(fabsf(v), 4.242640687f);
-    const float t = u * u;
-    float p = fmaf(-3.086643788e-12f, t, 3.179433938e-10f);
-    p = fmaf(p, t, -1.470189481e-08f);
-    p = fmaf(p, t, 4.085038654e-07f);
-    p = fmaf(p, t, -7.744979484e-06f);
-    p = fmaf(p, t, 1.082136150e-04f);
-    p = fmaf(p, t, -1.169088297e-03f);
-    p = fmaf(p, t, 9.949631989e-03f);
-    p = fmaf(p, t, -6.647815555e-02f);
-    p = fmaf(p, t, 3.989412785e-01f);
-    return fmaf(fabsf(v), u * p, 0.5f * v);
+    const float x = fminf(fabsf(v) * 0.70710678118654752f, 3.0f);
+    const float t = x * x;
+    float p = fmaf(-4.469939086e-09f, t, 2.302152922e-07f);
+    p = fmaf(p, t, -5.322654488e-06f);
+    p = fmaf(p, t, 7.394709974e-05f);
+    p = fmaf(p, t, -7.009955007e-04f);
+    p = fmaf(p, t, 4.897189327e-03f);
+    p = fmaf(p, t, -2.645343542e-02f);
+    p = fmaf(p, t, 1.125671491e-01f);
+    p = fmaf(p, t, -3.760564327e-01f);
+    p = fmaf(p, t, 1.128376126e+00f);
+    const float erf_abs = fminf(p * x, 1.0f);
+    return 0.5f * v * (1.0f + copysignf(erf_abs, v));
 }
 template <typename T>
 __device__ __forceinline__ float gelu_for(float v) { return sizeof(T) == 2 ? gelu_erf_bf16(v) : gelu_erf(v); }

@@ -7,6 +7,8 @@ Depth maps: the same measure; both it and the error relative to the map before i
 and a map that the ReLU clips (its maximum below a quarter of the pre-ReLU magnitude: with random weights
 that happens) is held to the second form instead (helpers.depth_gate).
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -380,3 +382,36 @@ def test_attention_with_peaked_softmax(dtype, variant, scale, monkeypatch):
     spec = vi.ModelSpec(f"sharp_{dtype}_{variant or 'auto'}", dtype=dtype, **SHARP)
     rep = check_all(spec, 141, 241, kinds=("seg",), weights_edit=_sharpen(scale))
     assert rep["b0.feat3"] > 0.0
+
+
+# ---------------------------------------------------------------- GELU of bf16 results
+def _gelu_exact(v):
+    return np.array([0.5 * x * math.erfc(-x / math.sqrt(2.0)) for x in np.asarray(v, dtype=np.float64)])
+
+
+@pytest.mark.parametrize("lo,hi,gate", [(-3.5, -3.0, 1.1e-5), (-4.2, -3.5, 1.3e-5)])
+def test_gelu_of_bf16_results_where_it_is_nearly_zero(lo, hi, gate):
+    # One block whose second MLP product is the identity, fed by biases alone: the residual stream is GELU(v) of 256 known
+    # v, beside 256 exact anchors between 0 and -0.005 whose straight-line fit undoes the final LayerNorm.  Gate: rms error of
+    # the rounded value.  Its polynomial gives 6.5e-6 and 1.0e-5, rounding to bf16 3.6e-6 and 0.6e-6, the features' own
+    # rounding (2^-9 / sqrt 3 of values up to 2e-3 from the mean) up to 2e-6: 7.7e-6 and 1.05e-5 together.  A fit with the
+    # same largest error over all v that is worse on these intervals gave 1.8e-5 on both.
+    D = 512
+    spec = vi.ModelSpec("gelu_tail", dtype="bf16", dim=D, depth=4, heads=8, mlp_hidden=D, img_h=14, img_w=14, taps=(1, 2, 3, 4))
+    w = vi.make_backbone_weights(spec, 1)
+    v, anchors = np.linspace(lo, hi, 256).astype(np.float32), np.linspace(0.0, -0.005, 256).astype(np.float32)
+    for name in w:
+        w[name][...] = 0.0
+    w["norm_g"][...] = 1.0
+    w["blk0.fc1_b"][:256] = v
+    w["blk0.fc2_w"][...] = np.eye(D, dtype=np.float32)
+    w["blk0.fc2_b"][256:] = anchors
+    w["blk0.ls2"][...] = 1024.0                                  # (so that LayerNorm's epsilon does not count)
+    eng, _, _ = make_engine(spec, 1, kinds=("seg",), weights=w)
+    _, feats = run_gpu(eng, np.zeros((1, 3, 14, 14), np.float32), 0)
+    eng.close()
+    y = feats[0][0, 1].astype(np.float64)
+    err = np.polyval(np.polyfit(y[256:], anchors, 1), y[:256]) - _gelu_exact(v)
+    rms = float(np.sqrt(np.mean(err ** 2)))
+    print("gelu", lo, hi, "rms", rms, "max", float(np.max(np.abs(err))), flush=True)
+    assert rms <= gate
