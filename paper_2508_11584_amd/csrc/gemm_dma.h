@@ -329,6 +329,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     // no room: behind the staging blocks, written when the k loop is done)
     constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : WN % 64 ? BM * BN * 4 : NW * 32 * WN * 4;
     float* lnrow = reinterpret_cast<float*>(smem + (!LN_LATE && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
+    int* redo_flags = reinterpret_cast<int*>(lnrow + 2 * BM);            // fp32: one per wave, behind them
 
     // --- loader state.  DMA instruction `slot` of this wave fills 1 KB of LDS = RPI consecutive rows of
     // the A (or B) tile, row group rg = wave + NW slot: lane l lands on row rg*RPI + l/CPR, physical
@@ -416,14 +417,34 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     // each step's fragments just before its MFMAs (two waves per SIMD cover for each other).
     constexpr bool FRAG_DB = MI + NI <= 6;
     const int ks0 = kg * KS;                                        // first k-step of this wave's group
+    // fp32: a lane's eight k elements of a step are two chunks of its row
+    auto chunk = [&](const char* base, int ks, int sw, int half) {
+        return *reinterpret_cast<const f32x4*>(base + ((4 * (ks0 + ks) + 2 * g + half) ^ sw) * 16);
+    };
+    auto compute_f32 = [&](const char* tile_a, const char* tile_b) {       // on v_mfma_f32_32x32x2_f32
+        const char* sA = tile_a + arow0 * ROWB;
+        const char* sB = tile_b + brow0 * ROWB;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                f32x4 ra[MI], rb[NI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) ra[i] = chunk(sA + i * 32 * ROWB, ks, asw, half);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) rb[j] = chunk(sB + j * 32 * ROWB, ks, bsw, half);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[i][e], rb[j][e], acc[i][j], 0, 0, 0);
+            }
+    };
     auto compute = [&](const char* tile_a, const char* tile_b, auto&& between) {
         const char* sA = tile_a + arow0 * ROWB;
         const char* sB = tile_b + brow0 * ROWB;
         if constexpr (ESZ == 4) {
-            // fp32: a lane's eight k elements of a step are two chunks of its row
-            auto chunk = [&](const char* base, int ks, int sw, int half) {
-                return *reinterpret_cast<const f32x4*>(base + ((4 * (ks0 + ks) + 2 * g + half) ^ sw) * 16);
-            };
             f32x4 ra[MI][2], rb[NI][2];
             auto read = [&](int ks) {
 #pragma unroll
@@ -556,7 +577,42 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             nxt = nxt + 1 == S ? 0 : nxt + 1;
         }
     }
+    if constexpr (ESZ == 4) {
+        float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};                // NaN if any of the lane's sums is infinite or NaN
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t[v & 3] = fmaf(acc[i][j][v], 0.0f, t[v & 3]);
+        const float all = (t[0] + t[1]) + (t[2] + t[3]);
+        const int any = __any(all != all);
+        if (lane == 0) redo_flags[wave] = any;
+    }
     pipeline_barrier<0>();                                    // drain the clamped tail prefetches before LDS is reused
+    if constexpr (ESZ == 4) {
+        // The split holds neither infinities nor finite values above 3.396e38 (they round to infinity in bf16): their rests, and
+        // with them every sum that they enter, are NaN.  A tile with such a sum is computed again on the fp32
+        // instructions, without prefetching: infinities, NaN and overflow come out as those instructions give them.  The check
+        // costs 0.4 us a launch (ViT-S 224x224: 926 -> 945 us a frame, 476x630: 2519 -> 2537-2568).
+        int redo = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) redo |= redo_flags[w];
+        if (__builtin_amdgcn_readfirstlane(redo)) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int kt = 0; kt < KT; ++kt) {
+                dma(0, kt);
+                pipeline_barrier<0>();
+                compute_f32(smem, smem + A_BYTES);
+                pipeline_barrier<0>();
+            }
+        }
+    }
     if (LN_LATE && p.ln_stats) {
         if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
         __syncthreads();
@@ -586,9 +642,9 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     constexpr bool late = RING;
     constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
     constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : BN / WGN % 64 ? BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
-    constexpr int ln_b = BM * 8;                                          // (mean, rstd) of the tile's rows
+    constexpr int ln_b = BM * 8 + (sizeof(T) == 4 ? 64 : 0);              // (mean, rstd) of the tile's rows; fp32: a flag per wave
     constexpr int lds = late ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
-    static_assert(lds * OCC <= 160 * 1024 && nt <= 1024, "LDS budget of one CU, workgroup size");
+    static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
     auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
     auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
     static bool configured = false;

@@ -9,7 +9,9 @@ namespace vpe {
 // three left out are at most 2^-27 of the product.  The instruction multiplies exactly and accumulates in fp32, so what
 // remains is the rounding of the accumulation, once per 16 k elements and product where v_mfma_f32_32x32x2_f32 rounds
 // once per 2.  Six bf16 instructions take 192 clocks for a 32 x 32 x 16 block, eight of the fp32 ones 512.
-// (An infinite or NaN operand gives NaN.)
+// An infinite operand, or a finite one above 3.396e38 (it rounds to infinity in bf16), has NaN among its terms and makes every
+// sum that it enters NaN: users look for infinite and NaN sums and compute those again on the fp32 instructions.  Terms
+// below 1e-38 may be lost, so operands smaller than about 1e-33 keep fewer bits (the absolute error stays below 1e-38).
 struct Split3 { bf16x8 t[3]; };
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ Split3 split3(const f32x4& lo, const f32x4& hi) {

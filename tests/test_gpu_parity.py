@@ -415,3 +415,42 @@ def test_gelu_of_bf16_results_where_it_is_nearly_zero(lo, hi, gate):
     rms = float(np.sqrt(np.mean(err ** 2)))
     print("gelu", lo, hi, "rms", rms, "max", float(np.max(np.abs(err))), flush=True)
     assert rms <= gate
+
+
+# ---------------------------------------------------------------- fp32 operands that bf16 terms cannot hold
+BIG = np.float32(3.4e38)          # finite in fp32, rounds to infinity in bf16
+
+
+def test_fp32_head_weights_beyond_the_range_of_bf16(monkeypatch):
+    # features within +-1 (a small final LayerNorm gain), so that a weight of 3.4e38 gives finite sums; an infinite one gives
+    # infinities of the feature's sign, and the detection tower's ReLU has to keep them and the large values apart from 0
+    spec = vi.ModelSpec("f32_range", dtype="f32", **MEDIUM)
+    backbone = vi.make_backbone_weights(spec, 151)
+    backbone["norm_g"][...] = 0.1
+    backbone["norm_b"][...] = 0.0
+
+    def edited(spec_, kind, seed, make=vi.make_head_weights):
+        hw = make(spec_, kind, seed)
+        if kind == vi.HEAD_SEG:
+            hw["seg_w"][:2] = 0.0
+            hw["seg_w"][0, 5], hw["seg_w"][1, 70] = BIG, np.inf
+        else:
+            hw["cls_tower_w"][0] = 0.0
+            hw["cls_tower_w"][0, 5, 1, 1] = BIG
+            hw["cls_w"][:, 0] = np.where(np.arange(spec_.det_classes) % 2, 1e-36, -1e-36)
+        return hw
+
+    monkeypatch.setattr(vi, "make_head_weights", edited)
+    eng, w, hw = make_engine(spec, 151, kinds=("seg", "det"), weights=backbone)
+    images = vi.make_batch(spec, 251)
+    _, feats = run_gpu(eng, images, 2)
+    outs = head_outputs(eng, ("seg", "det"))
+    eng.close()
+    f = feats[3][0, 1:].reshape(spec.gh, spec.gw, spec.dim).astype(np.float64)
+    logits = outs[0][0][0]
+    assert np.max(np.abs(f)) < 1.0
+    np.testing.assert_allclose(logits[..., 0], f[..., 5] * float(BIG) + hw[0]["seg_b"][0], rtol=1e-6)
+    assert np.array_equal(logits[..., 1], np.inf * np.sign(f[..., 70]))
+    assert relerr(logits[..., 2:], f @ hw[0]["seg_w"][2:].T.astype(np.float64) + hw[0]["seg_b"][2:]) <= TOL["f32"]
+    o = model.det_head(spec, hw[1], model.encode_image(spec, w, images[0]))
+    assert relerr(outs[1][0][0][..., :spec.det_classes].transpose(2, 0, 1), o["logits"]) <= TOL["f32"]
