@@ -195,6 +195,46 @@ template <> struct AttnMma<float> {
     }
 };
 
+// The same blocks on v_mfma_f32_32x32x2_f32, one instruction per k element of a lane half: for workgroups whose values the
+// split does not hold.
+struct AttnMmaF32 : AttnMma<float> {
+    struct QFrag { f32x4 c[2]; };
+    static __device__ __forceinline__ f32x4 load_chunk(const char* tile, int row, int chunk) {
+        return *reinterpret_cast<const f32x4*>(tile + (row * 16 + chunk_at(row, chunk)) * 16);
+    }
+    static __device__ __forceinline__ QFrag load_q(const float* qrow, int ks, int g) {
+        return {{*reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g), *reinterpret_cast<const f32x4*>(qrow + 16 * ks + 8 * g + 4)}};
+    }
+    static __device__ __forceinline__ QFrag zero_q() { return {{f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}}}; }
+    static __device__ __forceinline__ void qk2(f32x16& s0, f32x16& s1, const char* sK, int li, const QFrag* q, int g) {
+        const int kr = (li & 0x13) | ((li & 8) >> 1) | ((li & 4) << 1);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const f32x4 a0 = load_chunk(sK, kr, 4 * (c >> 1) + 2 * g + (c & 1)), a1 = load_chunk(sK, kr + 32, 4 * (c >> 1) + 2 * g + (c & 1));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], q[c >> 1].c[c & 1][e], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], q[c >> 1].c[c & 1][e], s1, 0, 0, 0);
+            }
+        }
+    }
+    template <bool LM>
+    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, f32x16&, float& psum, const char* sV, int li,
+                                                   f32x16* sc, float scale, float ref, int g) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const f32x4 a0 = load_chunk(sV, li, 4 * (c >> 1) + 2 * g + (c & 1)), a1 = load_chunk(sV, li + 32, 4 * (c >> 1) + 2 * g + (c & 1));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float pe = __builtin_amdgcn_exp2f(fmaf(sc[c >> 2][4 * (c & 3) + e], scale, -ref));
+                psum += pe;
+                o0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[e], pe, o0, 0, 0, 0);
+                o1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[e], pe, o1, 0, 0, 0);
+            }
+        }
+    }
+};
+
 // Workgroup shape: QW x KW waves.  Wave (qw, kw) owns QB blocks of 32 queries (query group qw) and
 // the key tiles t with t % KW == kw.  Each iteration stages KW key tiles and KW value tiles in LDS,
 // loaded by all threads; waves of the same kw share their tile across query groups.  At the end
@@ -209,6 +249,13 @@ template <> struct AttnMma<float> {
 // shapes would spill under the bound and keep the old one.
 template <typename T, int KW>
 constexpr bool attn_double_buffered() { return 2 * KW * 2 * 64 * AttnMma<T>::ROWB <= 128 * 1024; }
+
+// LDS of the tiles or, when they are done with, of the merge; fp32 shapes have a flag per wave behind it.
+template <typename T, int QB, int QW, int KW>
+constexpr int attn_lds() {
+    constexpr int kv = (attn_double_buffered<T, KW>() ? 2 : 1) * KW * 2 * 64 * AttnMma<T>::ROWB, red = KW > 1 ? KW * QW * QB * 34 * 64 * 4 : 0;
+    return kv > red ? kv : red;
+}
 
 template <typename T, int QB, int QW, int KW>
 constexpr int attn_min_waves() { return (QW * KW == 4 && (QB == 2 || (sizeof(T) == 4 && KW == 4))) ? 1 : 2; }
@@ -244,34 +291,12 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     const T* __restrict__ kbase = qk + p.dim;
     const T* __restrict__ vt = reinterpret_cast<const T*>(p.vt) + ((int64_t)b * p.dim + h * 64) * p.npad;
 
-    typename AttnMma<T>::QFrag q[QB][4];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int qi = q0 + qb * 32 + li;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            q[qb][ks] = qi < p.N ? AttnMma<T>::load_q(qk + (int64_t)qi * ld, ks, g) : AttnMma<T>::zero_q();
-    }
-
     // denominators: on the matrix pipe where the type and the register budget allow it (complete sums, every
     // accumulator row the same), else per lane half in l_run
     constexpr bool LMFMA = AttnMma<T>::MFMA_ROWSUM && QB == 1;
     f32x16 lacc[LMFMA ? QB : 1];
     f32x16 o[QB][2];
     float m_run[QB], l_run[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = -INFINITY;
-        l_run[qb] = 0.0f;
-        if (LMFMA) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) lacc[qb][v] = 0.0f;
-        }
-#pragma unroll
-        for (int d = 0; d < 2; ++d)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[qb][d][v] = 0.0f;
-    }
 
     const int KT = p.npad / 64;
     const int NIT = (KT + KW - 1) / KW;
@@ -338,82 +363,131 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     // in iteration it - 1, and one barrier per iteration is enough (everyone has finished reading buffer b, and the
     // loads into buffer b ^ 1 have landed).  Shapes whose two buffers would not fit the CU's LDS keep one buffer,
     // register staging and two barriers.
-    if constexpr (DB) {
-        dma(smem, 0);
-        __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the loads into LDS have landed
-        __syncthreads();
-    } else {
-        gload();
-    }
-    for (int it = 0; it < NIT; ++it) {
-        const char* stage = smem;
-        if constexpr (DB) {
-            if (it + 1 < NIT) dma(smem + ((it + 1) & 1) * STAGE, it + 1);
-            stage = smem + (it & 1) * STAGE;
-        } else {
-            __syncthreads();           // everyone is done reading the previous tiles
-            sstore(smem);
-            __syncthreads();
-            if (it + 1 < NIT) gload();
+    // All tiles from the start: scores, softmax and values with the product blocks of M.
+    auto sweep = [&](auto mma) {
+        using M = decltype(mma);
+        typename M::QFrag q[QB][4];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const int qi = q0 + qb * 32 + li;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                q[qb][ks] = qi < p.N ? M::load_q(qk + (int64_t)qi * ld, ks, g) : M::zero_q();
         }
-        const int t = it * KW + kw;
-        if (t < KT) {                  // (a wave without a tile in the last iteration still takes part in the barriers)
-            const char* sK = stage + (kw * 2) * TILE;
-            const char* sV = sK + TILE;
-            const bool last = t == KT - 1;     // keys past N only exist in the last tile
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                f32x16 s[2];
+        for (int qb = 0; qb < QB; ++qb) {
+            m_run[qb] = -INFINITY;
+            l_run[qb] = 0.0f;
+            if (LMFMA) {
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int v = 0; v < 16; ++v) lacc[qb][v] = 0.0f;
+            }
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
-                AttnMma<T>::qk2(s[0], s[1], sK, li, q[qb], g);
-                if (last) {
+            for (int d = 0; d < 2; ++d)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[qb][d][v] = 0.0f;
+        }
+        kadv = vadv = 0;
+        if constexpr (DB) {
+            dma(smem, 0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the loads into LDS have landed
+            __syncthreads();
+        } else {
+            gload();
+        }
+        for (int it = 0; it < NIT; ++it) {
+            const char* stage = smem;
+            if constexpr (DB) {
+                if (it + 1 < NIT) dma(smem + ((it + 1) & 1) * STAGE, it + 1);
+                stage = smem + (it & 1) * STAGE;
+            } else {
+                __syncthreads();           // everyone is done reading the previous tiles
+                sstore(smem);
+                __syncthreads();
+                if (it + 1 < NIT) gload();
+            }
+            const int t = it * KW + kw;
+            if (t < KT) {                  // (a wave without a tile in the last iteration still takes part in the barriers)
+                const char* sK = stage + (kw * 2) * TILE;
+                const char* sV = sK + TILE;
+                const bool last = t == KT - 1;     // keys past N only exist in the last tile
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    f32x16 s[2];
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int key = t * 64 + kb * 32 + AttnMma<T>::key_of(v, g);
-                            if (key >= p.N) s[kb][v] = -INFINITY;
-                        }
-                }
-                float mx = s[0][0];
+                        for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
+                    M::qk2(s[0], s[1], sK, li, q[qb], g);
+                    if (last) {
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
-                mx = halves_max(mx);
-                // Lazy rescaling: m_run is the reference the exponentials are taken against (in log2 units), not
-                // necessarily the running maximum.  It only moves when a query's maximum has grown by more than 8
-                // (probabilities stay <= 2^8, exact in fp32 and harmless in bf16), which after the first tile is
-                // rare -- and then the whole wave skips the 32 multiplications of the accumulator.  On the first
-                // tile the reference is -inf, alpha = 0 and the (zero) accumulators are overwritten.
-                const float mxs = mx * p.scale_log2e;
-                const bool grow = mxs > m_run[qb] + 8.0f;
-                if (__any(grow)) {
-                    const float m_new = grow ? mxs : m_run[qb];
-                    const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-                    l_run[qb] *= alpha;
-                    m_run[qb] = m_new;
-                    if (LMFMA) {
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) lacc[qb][v] *= alpha;
+                            for (int v = 0; v < 16; ++v) {
+                                const int key = t * 64 + kb * 32 + M::key_of(v, g);
+                                if (key >= p.N) s[kb][v] = -INFINITY;
+                            }
                     }
+                    float mx = s[0][0];
 #pragma unroll
-                    for (int d = 0; d < 2; ++d)
+                    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) o[qb][d][v] *= alpha;
+                        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
+                    mx = halves_max(mx);
+                    // Lazy rescaling: m_run is the reference the exponentials are taken against (in log2 units), not
+                    // necessarily the running maximum.  It only moves when a query's maximum has grown by more than 8
+                    // (probabilities stay <= 2^8, exact in fp32 and harmless in bf16), which after the first tile is
+                    // rare -- and then the whole wave skips the 32 multiplications of the accumulator.  On the first
+                    // tile the reference is -inf, alpha = 0 and the (zero) accumulators are overwritten.
+                    const float mxs = mx * p.scale_log2e;
+                    const bool grow = mxs > m_run[qb] + 8.0f;
+                    if (__any(grow)) {
+                        const float m_new = grow ? mxs : m_run[qb];
+                        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+                        l_run[qb] *= alpha;
+                        m_run[qb] = m_new;
+                        if (LMFMA) {
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) lacc[qb][v] *= alpha;
+                        }
+#pragma unroll
+                        for (int d = 0; d < 2; ++d)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) o[qb][d][v] *= alpha;
+                    }
+                    float psum = 0.0f;
+                    M::template pv_tile<LMFMA>(o[qb][0], o[qb][1], lacc[LMFMA ? qb : 0], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
+                    if (!LMFMA) l_run[qb] += psum;
                 }
-                float psum = 0.0f;
-                AttnMma<T>::template pv_tile<LMFMA>(o[qb][0], o[qb][1], lacc[LMFMA ? qb : 0], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
-                if (!LMFMA) l_run[qb] += psum;
+            }
+            if constexpr (DB) {
+                __builtin_amdgcn_s_waitcnt(0x0F70);
+                __syncthreads();
             }
         }
-        if constexpr (DB) {
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            __syncthreads();
+    };
+    sweep(AttnMma<T>{});
+    if constexpr (sizeof(T) == 4) {
+        // The split holds neither infinities nor finite values above 3.396e38: NaN among their terms, and with them in the sums.
+        // A workgroup with an infinite or NaN sum starts again on the fp32 instructions (the check: ViT-S 224x224 13.6 -> 14.1 us
+        // a launch, 476x630 and larger no difference).
+        float t = 0.0f;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            t = fmaf(l_run[qb], 0.0f, t);
+#pragma unroll
+            for (int d = 0; d < 2; ++d)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) t = fmaf(o[qb][d][v], 0.0f, t);
         }
+        const int any = __any(t != t);
+        int* flags = reinterpret_cast<int*>(smem + attn_lds<T, QB, QW, KW>());
+        if (lane == 0) flags[wave] = any;
+        __syncthreads();
+        int redo = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) redo |= flags[w];
+        if (__builtin_amdgcn_readfirstlane(redo)) sweep(AttnMmaF32{});
     }
 
     if (LMFMA) {
@@ -536,9 +610,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
 
 template <typename T, int QB, int QW, int KW>
 static inline hipError_t launch_attention_variant(const AttnArgs& a, hipStream_t s, bool configure_only) {
-    constexpr int TILE = 64 * AttnMma<T>::ROWB;
-    constexpr int kv = (attn_double_buffered<T, KW>() ? 2 : 1) * KW * 2 * TILE, red = KW > 1 ? KW * QW * QB * 34 * 64 * 4 : 0;
-    constexpr int lds = kv > red ? kv : red;
+    constexpr int lds = attn_lds<T, QB, QW, KW>() + (sizeof(T) == 4 ? 64 : 0);
     static bool configured = false;       // opt in to more than 64 KB of LDS once per instantiation
     if (!configured) {
         hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<T, QB, QW, KW>),

@@ -454,3 +454,16 @@ def test_fp32_head_weights_beyond_the_range_of_bf16(monkeypatch):
     assert relerr(logits[..., 2:], f @ hw[0]["seg_w"][2:].T.astype(np.float64) + hw[0]["seg_b"][2:]) <= TOL["f32"]
     o = model.det_head(spec, hw[1], model.encode_image(spec, w, images[0]))
     assert relerr(outs[1][0][0][..., :spec.det_classes].transpose(2, 0, 1), o["logits"]) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("variant", ["114", "122", "141"])
+def test_fp32_attention_keys_beyond_the_range_of_bf16(variant, monkeypatch):
+    # one channel of every key at 3.4e38 against 1e-37 in the queries: the same 4.25 in every score, which the softmax does not see
+    monkeypatch.setenv("VPE_ATTN_VARIANT", variant)
+    D = MEDIUM["dim"]
+
+    def edit(w):
+        for c, value in ((3, np.float32(1e-37)), (D + 3, BIG)):
+            w["blk1.qkv_w"][:, c] = 0.0
+            w["blk1.qkv_b"][c] = value
+    check_all(vi.ModelSpec("f32_keys_" + variant, dtype="f32", **MEDIUM), 152, 252, kinds=("seg",), weights_edit=edit)
