@@ -335,10 +335,13 @@ __device__ __forceinline__ void store_tokens8(const GemmArgs& p, T* vt, int r, i
             for (int k = 0; k < 8; ++k) dst[k] = from_f32<T>(v[k]);
         }
     } else {
+        // (an image's end or the matrix's: the place moves on by comparison, not by a division per token)
+        int image = b, at = n;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int rk = r + k;
-            if (rk < p.M) vt[((int64_t)(rk / p.ntok) * p.dim + c2) * p.npad + rk % p.ntok] = from_f32<T>(v[k]);
+            if (at == p.ntok) { at = 0; ++image; }
+            if (r + k < p.M) vt[((int64_t)image * p.dim + c2) * p.npad + at] = from_f32<T>(v[k]);
+            ++at;
         }
     }
 }
