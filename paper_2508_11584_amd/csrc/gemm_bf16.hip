@@ -12,11 +12,15 @@ namespace {
 //     t [us] = alpha * max(r, 1) + beta * r * (bm * bn * K / 1e6),     r = ceil(tiles / 256) / held,
 // r being the number of "rounds" on the busiest of the 256 CUs (it gets ceil(tiles / 256) tiles and works on
 // `held` of them at a time); alpha is the cost a workgroup pays whatever its size (first loads, epilogue), not
-// discounted on a partly filled chip.  Fitted (relative least squares, 9-11 % rms per tiling) to 66 measured shapes on
-// MI355X with random bf16 data and the layers' own epilogues: the QKV / proj / fc1 / fc2 GEMMs of ViT-S (257, 900, 1531, 4097,
-// 12000 tokens), -B (1370, 1572, 4110), -L (300, 1374, 2748, 5496) and -g (1374, 4122, 10992), and 3x3 convolutions at
-// 34x45 ... 136x180 grids.  The model's pick costs 0.9 % more than the measured best in total time; it is within 5 %
-// of it on all but three shapes (8-9 %).
+// discounted on a partly filled chip.  Fitted (relative least squares) to 66 measured shapes on MI355X with random bf16 data and
+// the layers' own epilogues: the QKV / proj / fc1 / fc2 GEMMs of ViT-S (257, 900, 1531, 4097, 12000 tokens), -B (1370, 1572, 4110),
+// -L (300, 1374, 2748, 5496) and -g (1374, 4122, 10992), and 3x3 convolutions at 34x45 ... 136x180 grids.
+// Over 264 shapes of those layers (17 token counts, 145 to 10992) the picks cost 1.1 % more than the measured best in the geometric
+// mean, more than 5 % on 24 of them and 14 % at most.  Predictions near the best are within 4-12 % rms, except that one
+// alpha for all epilogues is 16-22 % low for the one-per-CU tiles with GELU or the residual epilogue (ViT-L x 4 fc1 on
+// 384 x 256: 57 us predicted, 73 measured).  Coefficients per epilogue predict those to 8 % and pick within 0.4 % of the
+// best, and frames got slower with them (ViT-g, 663 tokens: 4404 -> 4638 us with QKV and fc1 on 64 x 128; ViT-L x 4 on two lanes
+// 6370 -> 6680 with fc2 on 64 x 128 in two groups): a shape timed over and over has its weights in the caches and the chip to itself.
 // Tuning aids, read from the environment when an engine is created (configure_gemm_bf16), never per launch:
 // VPE_GEMM_TILE forces a tiling, VPE_NO_SMALL_DMA leaves the two small one-group direct-to-LDS shapes out, VPE_NO_SPLITK
 // the shapes with several wave groups, VPE_NO_STRIP the strip convolution, VPE_NO_ROW_SPLIT the two-launch form of a GEMM whose tile
@@ -33,16 +37,50 @@ constexpr Cand kCands[] = {
     {5, 64, 128, 2, 5.87f, 1.222f},
     {4, 64, 64, 2, 4.79f, 1.411f},
 };
+// 3x3 convolutions have long k loops, where a CU's rounds are told apart better than by r: with q = ceil(tiles / 256) tiles on the
+// busiest CU, floor(q / held) full rounds and one of the q % held tiles that are left, a round of n tiles taking
+//     t(n) [us] = alpha + next (n - 1) + K max(chain, rate n)
+// (next: what a further workgroup adds to the fixed time; chain: one workgroup's own time per k; rate: the CU's time per k and tile
+// when its workgroups share it).  Fitted to 126 convolutions (64-512 channels on 16x16 ... 296x296 grids, detection towers of
+// 384-1536 channels), 2-10 % rms per tiling.  Under the model above 64 x 64 tiles in four groups were taken for 257-768
+// tiles, up to 31 % slower than 64 x 128 in two (us): 512 -> 512 on 68x90 64.8 / 52.3, 256 -> 256 on 96x96 34.7 / 26.9, ViT-S
+// towers on 74x74 49.5 / 38.0, ViT-g towers there 171 / 126; the picks cost 2.7 % over the measured best, now 0.3 % (0.1 % without
+// kConvShared).
+struct ConvCand { int kind, bm, bn, held; float alpha, next, chain, rate; };
+constexpr ConvCand kConvCands[] = {
+    {256, 256, 256, 1, 18.99f, 0.0f, 0.02160f, 0.0f},
+    {384, 384, 256, 1, 27.00f, 0.0f, 0.03675f, 0.0f},
+    {128, 256, 128, 1, 10.96f, 0.0f, 0.01561f, 0.0f},
+    {65, 64, 128, 3, 4.49f, 1.32f, 0.00859f, 0.00522f},
+    {64, 64, 64, 4, 4.84f, 0.03f, 0.00593f, 0.00365f},
+    {5, 64, 128, 2, 5.31f, 2.02f, 0.00615f, 0.00444f},
+    {4, 64, 64, 4, 4.59f, 1.73f, 0.00458f, 0.00362f},
+};
+// What a tiling with several workgroups per CU has to be faster by, alone, to be taken over one that holds a CU: a head's
+// convolutions run beside encoder kernels, where operand traffic costs more than the time alone shows.  256 -> 256 on
+// 136x180: 46.6 us with 64 x 128 tiles, 50.4 with 256 x 128, but a ViT-S 476x630 frame takes 856 us with the first and 848 with
+// the second, and 631 and 620 as a stream of two lanes.
+constexpr float kConvShared = 1.1f;
+
+float predicted(const Cand& c, int64_t tiles, int K) {
+    const float r = (float)cdiv(tiles, 256) / c.held;
+    return c.alpha * (r > 1.0f ? r : 1.0f) + c.beta * r * (1e-6f * c.bm * c.bn * K);
+}
+float predicted(const ConvCand& c, int64_t tiles, int K) {
+    auto round = [&](int n) { return n == 0 ? 0.0f : c.alpha + c.next * (n - 1) + K * (c.chain > c.rate * n ? c.chain : c.rate * n); };
+    const int q = cdiv(tiles, 256);
+    return (c.held > 1 ? kConvShared : 1.0f) * ((float)(q / c.held) * round(c.held) + round(q % c.held));
+}
 }  // namespace
 
 // The model's pick for rows m_begin .. M - 1 of `a` and its predicted time in us.
-static int pick_tile(const GemmArgs& a, float& best_cost) {
+template <typename C, int NC>
+static int pick_tile(const C (&cands)[NC], const GemmArgs& a, float& best_cost) {
     int best = 128;
     best_cost = 0.0f;
-    const bool no_small = g_no_small;
     const int rows = a.M - a.m_begin;
-    for (const Cand& c : kCands) {
-        if (no_small && (c.kind == 64 || c.kind == 65)) continue;
+    for (const C& c : cands) {
+        if (g_no_small && (c.kind == 64 || c.kind == 65)) continue;
         if (g_no_splitk && (c.kind == 4 || c.kind == 5)) continue;
         if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;        // gate and linear partner are 64 physical columns of one wave's tile
         const int64_t tiles = (int64_t)cdiv(rows, c.bm) * cdiv(a.N, c.bn) * (a.nz > 1 ? a.nz : 1);
@@ -50,8 +88,7 @@ static int pick_tile(const GemmArgs& a, float& best_cost) {
         // where their partial sums cost more than the groups gain (432 tiles at K = 384: 8.2 against 7.7 us, 264 at K = 768:
         // 9.7 against 9.3; 352 at K = 1024: 11.4 against 11.3, 264 at K = 3072: 23.2 against 26.3)
         if (c.kind == 4 && tiles > 256 && a.K < 1024) continue;
-        const float r = (float)cdiv(tiles, 256) / c.held;
-        const float cost = c.alpha * (r > 1.0f ? r : 1.0f) + c.beta * r * (1e-6f * c.bm * c.bn * a.K);
+        const float cost = predicted(c, tiles, a.K);
         if (best_cost == 0.0f || cost < best_cost) { best_cost = cost; best = c.kind; }
     }
     return best;
@@ -59,16 +96,17 @@ static int pick_tile(const GemmArgs& a, float& best_cost) {
 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best);
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
+template <typename C, int NC>
+static hipError_t launch_chosen(const C (&cands)[NC], const GemmArgs& a, int amode, hipStream_t s) {
     float whole_cost;
-    const int whole = pick_tile(a, whole_cost);
+    const int whole = pick_tile(cands, a, whole_cost);
     // The one-per-CU tiles run in lockstep rounds of 256 and pay for a partly filled last round in full (ViT-g, 8
     // views: fc2 and the out-projection have 43 x 6 = 258 tiles of 256 x 256, QKV 774).  Two launches instead: whole
     // rounds of the large tile over the leading rows, then the remaining rows with whatever the model picks for them.
     if (g_forced_tile == 0 && !g_no_split && a.nz <= 1 && a.m_begin == 0) {
         float split_cost = whole_cost;
         int split_kind = 0, split_rows = 0;
-        for (const Cand& c : kCands) {
+        for (const C& c : cands) {
             if (c.held != 1) continue;
             const int tn = cdiv(a.N, c.bn), tm = cdiv(a.M, c.bm);
             const int64_t tiles = (int64_t)tm * tn;
@@ -76,12 +114,11 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
             if (rounds < 1 || tiles % 256 == 0) continue;
             const int tm_main = rounds * 256 / tn;              // whole tile rows in `rounds` rounds
             if (tm_main < 1 || tm_main >= tm) continue;
-            const float main_rounds = (float)cdiv((int64_t)tm_main * tn, 256);
-            const float main_cost = (c.alpha + c.beta * (1e-6f * c.bm * c.bn * a.K)) * main_rounds;
+            const float main_cost = predicted(c, (int64_t)tm_main * tn, a.K);
             GemmArgs tail = a;
             tail.m_begin = tm_main * c.bm;
             float tail_cost;
-            pick_tile(tail, tail_cost);
+            pick_tile(cands, tail, tail_cost);
             if (main_cost + tail_cost < 0.93f * split_cost) {   // a second launch costs a few us the model does not see
                 split_cost = main_cost + tail_cost;
                 split_kind = c.kind;
@@ -95,10 +132,14 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
             hipError_t rc = launch_gemm_dma_bf16(split_kind, main, amode, s);
             if (rc != hipSuccess) return rc;
             float unused;
-            return launch_picked(tail, amode, s, pick_tile(tail, unused));
+            return launch_picked(tail, amode, s, pick_tile(cands, tail, unused));
         }
     }
     return launch_picked(a, amode, s, whole);
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
+    return amode == A_CONV3 ? launch_chosen(kConvCands, a, amode, s) : launch_chosen(kCands, a, amode, s);
 }
 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best) {
