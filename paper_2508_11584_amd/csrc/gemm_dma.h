@@ -575,7 +575,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         char* unit[5] = {smem, smem + A_BYTES, smem + 2 * A_BYTES, smem + 3 * A_BYTES, smem + 4 * A_BYTES};
         dma_a(unit[0], 0);
         dma_b(unit[1], 0);
+        __builtin_amdgcn_sched_barrier(0);                    // (the counted waits go by the order of issue)
         dma_a(unit[2], last(1));
+        __builtin_amdgcn_sched_barrier(0);
         if (p.ln_stats && tid < BM) ln_tile_row(p, m0, n0, tid, mean, rstd);
         for (int kt = 0; kt < KT; ++kt) {
             pipeline_barrier<A_SLOTS>();                      // A and B of tile kt are here; A of kt + 1 may be on its way
@@ -592,7 +594,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         }
     } else {
 #pragma unroll
-        for (int s = 0; s < PD; ++s) dma(s, last(s));
+        for (int s = 0; s < PD; ++s) {
+            dma(s, last(s));
+            __builtin_amdgcn_sched_barrier(0);                // (the counted waits go by the order of issue)
+        }
         // behind the first tile loads, ordered before the epilogue by the loop's barriers
         if (p.ln_stats && tid < BM) {
             ln_tile_row(p, m0, n0, tid, mean, rstd);
