@@ -21,12 +21,12 @@ struct GemmArgs {
     int64_t lda;         // elements between consecutive A rows (PLAIN) / pixels (CONV3)
     const void* W;       // T [N rounded up to 256][K]
     const float* bias;   // [N] in the physical column order of W, may be null
-    int M, N, K;         // K multiple of 64 (bf16) / 32 (fp32)
+    int M, N, K;         // K multiple of 64 (k-tiles are whole; anything else is refused)
     int m_begin;         // a launch covers rows m_begin .. M - 1 (row indices stay those of the whole problem)
     // PLAIN: logical row r reads A row (r / a_rpi) * a_istride + a_off + r % a_rpi
     // CONV3: pixel (b, y, x) is A row b * a_istride + a_off + y * cW + x
     int a_rpi, a_istride, a_off;
-    int cH, cW, cC;      // CONV3 grid and channels (K = 9 cC, cC multiple of the k-tile)
+    int cH, cW, cC;      // CONV3 grid and channels (K = 9 cC, cC multiple of 64)
     const void* zeros;   // CONV3: >= 16 bytes of zeros, read in place of out-of-image taps
     int epi, act, out_f32;
     void* out;           // T or float (out_f32); RESID/PATCH: float residual stream

@@ -1,0 +1,40 @@
+"""Host-side checks of the GEMM launcher: sizes that its kernels' k loops cannot do are refused before anything is launched."""
+import os
+import subprocess
+
+import paper_2508_11584_amd as vpe
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2508_11584_amd")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace vpe;
+int main() {
+    struct { int amode, K, cC; } refused[] = {{A_PLAIN, 32, 0}, {A_PLAIN, 96, 0}, {A_PLAIN, 0, 0}, {A_PLAIN, 608, 0},
+                                              {A_CONV3, 9 * 32, 32}, {A_CONV3, 9 * 96, 96}, {A_CONV3, 576, 128}, {A_CONV3, 576, 32}};
+    int bad = 0;
+    for (auto& r : refused)
+        for (int dtype = 0; dtype < 2; ++dtype) {
+            GemmArgs a{};
+            a.M = a.N = 64;
+            a.K = r.K; a.cC = r.cC; a.cH = a.cW = 8;
+            a.lda = a.ldo = 64; a.a_rpi = a.o_rpi = 64; a.nz = 1;
+            const hipError_t rc = launch_gemm(dtype, a, r.amode, nullptr);
+            if (rc != hipErrorInvalidValue) { printf("dtype %d mode %d K %d cC %d: %d\n", dtype, r.amode, r.K, r.cC, (int)rc); ++bad; }
+        }
+    return bad;
+}
+"""
+
+
+def test_gemm_launcher_refuses_k_extents_that_are_not_whole_tiles(tmp_path):
+    vpe.load_library()                                   # (built already, or an error that says so)
+    src, exe = tmp_path / "contract.cpp", tmp_path / "contract"
+    src.write_text(PROGRAM)
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O0", "-w", "-I" + os.path.join(PKG, "csrc"), str(src),
+                    "-x", "none", os.path.join(PKG, "libvpe.so"), "-Wl,-rpath," + PKG, "-o", str(exe)], check=True, capture_output=True)
+    # no device: the refusal must come from the arguments alone, with a device as without one
+    r = subprocess.run([str(exe)], capture_output=True, text=True, env={**os.environ, "HIP_VISIBLE_DEVICES": ""})
+    assert r.returncode == 0, r.stdout + r.stderr
