@@ -161,7 +161,8 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
 // Reads the tuning aids; called at engine creation, outside any stream capture.
 hipError_t configure_gemm_bf16() {
     const char* env = getenv("VPE_GEMM_TILE");
-    g_forced_tile = env ? atoi(env) : 0;
+    g_forced_tile = 0;
+    for (int kind : {384, 256, 128, 65, 64, 5, 4, 9}) if (env && atoi(env) == kind) g_forced_tile = kind;      // (anything else: no tile forced)
     g_no_small = getenv("VPE_NO_SMALL_DMA") != nullptr;
     g_no_splitk = getenv("VPE_NO_SPLITK") != nullptr;
     g_no_strip = getenv("VPE_NO_STRIP") != nullptr;

@@ -1,5 +1,7 @@
-// fp32 GEMMs (on the bf16 matrix instructions, Split3 in gemm_dma.h): instantiations and choice of tiling, plus the dtype
+// fp32 GEMMs (on the bf16 matrix instructions, Split3 in split3.h): instantiations and choice of tiling, plus the dtype
 // dispatch.
+#include <cstdlib>
+
 #include "gemm_dma.h"
 #include "kernels.h"
 namespace vpe {
@@ -17,6 +19,10 @@ namespace {
 // out-projection 12.8 / 10.2, fc1 29.0 / 24.8, fc2 36.1 / 25.0; ViT-B 1370 tokens fc2 103 / 70; 3x3 convolutions 256 -> 256 on
 // 34 x 45 55 / 39, 136 x 180 307 / 207, 272 x 360 901 / 642 (180 TFLOP/s, 6 x that on the matrix pipes: 1.08 PFLOP/s, near what
 // the card sustains on bf16 operands; the fp32 instructions reach 128 there).
+// Tuning aids, read when an engine is created: VPE_GEMM_TILE_F32 = 0 ... 3 forces a tiling, VPE_NO_SPLITK leaves those with
+// several wave groups out.
+int g_forced_tile_f32 = -1;
+bool g_no_splitk_f32 = false;
 struct Cand { int bm, bn, held; float alpha, beta; };
 constexpr Cand kCands[] = {{64, 64, 2, 5.25f, 6.325f}, {64, 128, 1, 6.75f, 2.649f}, {64, 128, 2, 7.78f, 5.883f}, {128, 128, 2, 10.01f, 5.504f}};
 
@@ -34,20 +40,24 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, int amode, hipStream_t s) {
     // the k loops have no remainder, and a k-tile of a convolution belongs to one tap
     if (a.K < 64 || a.K % 64 || (amode == A_CONV3 && (a.cC % 64 || a.K != 9 * a.cC))) return hipErrorInvalidValue;
     if (dtype) return launch_gemm_bf16(a, amode, s);
-    int best = 0;
+    int best = 3;
     float best_cost = 0.0f;
     for (int k = 0; k < 4; ++k) {
+        if (g_no_splitk_f32 && k != 3) continue;
         const Cand& c = kCands[k];
         const int64_t tiles = (int64_t)cdiv(a.M, c.bm) * cdiv(a.N, c.bn) * (a.nz > 1 ? a.nz : 1);
         const float r = (float)cdiv(tiles, 256) / c.held;
         const float cost = c.alpha * (r > 1.0f ? r : 1.0f) + c.beta * r * (1e-6f * c.bm * c.bn * a.K);
-        if (k == 0 || cost < best_cost) { best_cost = cost; best = k; }
+        if (best_cost == 0.0f || cost < best_cost) { best_cost = cost; best = k; }
     }
-    return launch_f32(best, a, amode, s);
+    return launch_f32(g_forced_tile_f32 >= 0 ? g_forced_tile_f32 : best, a, amode, s);
 }
 
-// LDS opt-in of the fp32 tilings; called once at engine creation, outside any stream capture.
+// LDS opt-in of the fp32 tilings and the tuning aids; called at engine creation, outside any stream capture.
 hipError_t configure_gemm_f32() {
+    const char* env = getenv("VPE_GEMM_TILE_F32");
+    g_forced_tile_f32 = env && env[0] >= '0' && env[0] <= '3' && !env[1] ? env[0] - '0' : -1;
+    g_no_splitk_f32 = getenv("VPE_NO_SPLITK") != nullptr;
     GemmArgs a{};
     for (int k = 0; k < 4; ++k) {
         const hipError_t rc = launch_f32(k, a, A_PLAIN, nullptr, true);

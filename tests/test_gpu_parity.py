@@ -245,6 +245,22 @@ def test_fp32_products_on_short_and_ragged_shapes(width):
                            batch=2, img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=2 * width), 142, 242)
 
 
+@pytest.mark.parametrize("tile", ["0", "1", "2", "3"])
+def test_fp32_gemm_tilings(tile, monkeypatch):
+    # each fp32 tiling (0: 64 x 64 in four wave groups, 1: 64 x 128 in four, 2: 64 x 128 in two with three stages, 3: 128 x 128, whose
+    # waves leave by themselves) forced for every GEMM, through every epilogue: folded LayerNorm + QKV with transposed values,
+    # LayerScale residual with row statistics, GELU and SwiGLU, patch embedding, 1x1 and 3x3 convolutions, the fused 1-channel
+    # projection, the full DPT head's adds and ReLU copies; 166 tokens, then 38 + 38 (tiles and 8-row groups straddle two views) at
+    # one and three k-tiles of 64 and with a half-empty last 128-column tile.  The gates are those of every fp32 model (1e-4)
+    monkeypatch.setenv("VPE_GEMM_TILE_F32", tile)
+    small = {"registers": 2, "batch": 2, "img_h": 70, "img_w": 98}
+    check_all(vi.ModelSpec("medium_f32_tile" + tile, dtype="f32", **MEDIUM), 145, 245)
+    check_all(vi.ModelSpec("swiglu_f32_tile" + tile, dtype="f32", **{**MEDIUM, **small, "mlp_kind": vi.MLP_SWIGLU}), 146, 246, kinds=("seg", "dpt"))
+    for width in (64, 192):
+        check_all(vi.ModelSpec("short_f32_tile%s_%d" % (tile, width), dtype="f32", **{**MEDIUM, **small, "dim": width, "heads": width // 64,
+                                                                                      "mlp_hidden": 192}), 147, 247)
+
+
 @pytest.mark.parametrize("shape", ["1", "2"])
 def test_strip_convolution_kernel(shape, monkeypatch):
     # the 3x3 convolution that forms its nine taps from one input strip in LDS, in both of its tile shapes (1: 384 x 256,
@@ -421,9 +437,12 @@ def test_gelu_of_bf16_results_where_it_is_nearly_zero(lo, hi, gate):
 BIG = np.float32(3.4e38)          # finite in fp32, rounds to infinity in bf16
 
 
-def test_fp32_head_weights_beyond_the_range_of_bf16(monkeypatch):
+@pytest.mark.parametrize("tile", ["", "0", "1", "2", "3"])
+def test_fp32_head_weights_beyond_the_range_of_bf16(tile, monkeypatch):
     # features within +-1 (a small final LayerNorm gain), so that a weight of 3.4e38 gives finite sums; an infinite one gives
     # infinities of the feature's sign, and the detection tower's ReLU has to keep them and the large values apart from 0
+    if tile:
+        monkeypatch.setenv("VPE_GEMM_TILE_F32", tile)
     spec = vi.ModelSpec("f32_range", dtype="f32", **MEDIUM)
     backbone = vi.make_backbone_weights(spec, 151)
     backbone["norm_g"][...] = 0.1
