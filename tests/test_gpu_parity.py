@@ -203,10 +203,10 @@ def test_cfg2_in_the_pipelined_configuration_the_benchmark_times():
     check_all(spec, *vi.SEEDS["cfg2"], flags=vpe.VPE_FLAG_GRAPHS, lead_frames=6, ring_slots=4, encoder_lanes=3)
 
 
-@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "4"])
+@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_variant(tile, monkeypatch):
-    # each direct-to-LDS GEMM shape (384 x 256, 256 x 256, 256 x 128, 64 x 128, 64 x 64 tiles) and the split-k 64 x 64
-    # shape ("4": two wave groups over halves of the k range, odd and even k-tile counts), forced for every GEMM of the model,
+    # each bf16 GEMM shape (384 x 256, 256 x 256, 256 x 128, 64 x 128, 64 x 64 tiles; "5" and "4": 64 x 128 and 64 x 64 whose two and
+    # four wave groups share the k-steps of every k-tile), forced for every GEMM of the model,
     # through every epilogue: folded LayerNorm + QKV with transposed values, LayerScale residual with row
     # statistics, GELU and SwiGLU, patch embedding, 1x1 and 3x3 convolutions, the fused 1-channel projection
     monkeypatch.setenv("VPE_GEMM_TILE", tile)
@@ -219,7 +219,8 @@ def test_direct_to_lds_gemm_variant(tile, monkeypatch):
 @pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
     # one k-tile (width 64), three (MLP of 192) and nine (3x3 convolutions of 64 channels): pipelines whose first loads
-    # already run past the last k-tile; 35 + 3 tokens a view, so that tiles and 8-row groups straddle two views.  The
+    # already run past the last k-tile; 35 + 3 tokens a view, so that tiles and 8-row groups straddle two views; QKV width
+    # 192, so that a 128-column tile of value columns is half empty (its other half is the next view's place).  The
     # gates of check_all are those of every bf16 model
     monkeypatch.setenv("VPE_GEMM_TILE", tile)
     check_all(vi.ModelSpec("short_k_tile" + tile, dtype="bf16", dim=64, depth=4, heads=1, mlp_hidden=192, registers=2, batch=2,
@@ -275,6 +276,25 @@ def test_strip_convolution_kernel(shape, monkeypatch):
     # one row of patches (every pixel on the top and bottom edge) and a single patch
     check_all(vi.ModelSpec("strip_conv_row", dtype="bf16", **{**MEDIUM, "head_ch": 256, "img_h": 14, "img_w": 14 * 9}), 109, 209)
     check_all(vi.ModelSpec("strip_conv_1x1", dtype="bf16", **{**MEDIUM, "head_ch": 256, "img_h": 14, "img_w": 14}), 110, 210)
+
+
+@pytest.mark.parametrize("dtype,batch", [("f32", 104), ("bf16", 208)])
+def test_operands_larger_than_two_gib(dtype, batch):
+    # convolution inputs of 2.25 GB (11 x 15 patches, 88 x 120 pixels of 512 channels per view): byte offsets from the first view
+    # do not fit 32 bits, those from a tile's own first row do.  Three different views in turn, so a wrapped offset meets
+    # other data; every view against the same view in an engine of three, by the gates of its type
+    spec = vi.ModelSpec("large_" + dtype, dtype=dtype, **{**MEDIUM, "head_ch": 512, "batch": 3})
+    views = vi.make_batch(spec, 260)
+    results = []
+    for n in (3, batch):
+        eng, _, _ = make_engine(vi.with_(spec, batch=n), 160, kinds=("depth", "seg"))
+        _, feats = run_gpu(eng, np.ascontiguousarray(views[np.arange(n) % 3]), 2)
+        results.append([feats[3], eng.head_output(0, 0).cpu().numpy().copy(), eng.head_output(1, 0).cpu().numpy().copy()])
+        eng.close()
+    for small, large in zip(*results):
+        err = max(relerr(large[b], small[b % 3]) for b in range(batch))
+        print("large", dtype, small.shape, err, flush=True)
+        assert err <= TOL[dtype]
 
 
 # ---------------------------------------------------------------- full DPT head
@@ -386,7 +406,7 @@ def _sharpen(scale):
 @pytest.mark.parametrize("dtype,variant,scale", [("bf16", "124", 16.0), ("bf16", "224", 16.0), ("bf16", "141", 16.0),
                                                  ("bf16", "114", 16.0), ("bf16", "214", 16.0), ("bf16", "122", 16.0),
                                                  ("bf16", "", 16.0),
-                                                 ("f32", "114", 32.0), ("f32", "141", 32.0)])
+                                                 ("f32", "114", 32.0), ("f32", "122", 32.0), ("f32", "141", 32.0)])
 def test_attention_with_peaked_softmax(dtype, variant, scale, monkeypatch):
     # 361 tokens = six key tiles of 64 (the last with 41 keys): with four key waves two of them own two tiles.
     # With the benchmark's weights every score lies within a fraction of a unit of the others, so the running
