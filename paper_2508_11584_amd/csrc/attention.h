@@ -238,9 +238,9 @@ struct AttnMmaF32 : AttnMma<float> {
 // Workgroup shape: QW x KW waves.  Wave (qw, kw) owns QB blocks of 32 queries (query group qw) and
 // the key tiles t with t % KW == kw.  Each iteration stages KW key tiles and KW value tiles in LDS,
 // loaded by all threads; waves of the same kw share their tile across query groups.  At the end
-// the KW partial results of a query group are merged in LDS by its kw = 0 wave (fixed order, so
-// results are deterministic).  KW > 1 gives small problems enough waves to fill 1024 SIMDs;
-// QW > 1 and QB = 2 cut the L2 -> LDS traffic per query on large ones.
+// the KW partial results of a query group are merged in LDS (fixed order, so results are
+// deterministic): by its kw = 0 wave for two, a share by each wave for four.  KW > 1 gives small problems
+// enough waves to fill 1024 SIMDs; QW > 1 and QB = 2 cut the L2 -> LDS traffic per query on large ones.
 // Launch bound: at least two waves per SIMD wherever the kernel fits 256 registers.  Besides the occupancy, this
 // is what makes the compiler keep the MFMA accumulators in ordinary vector registers: with up to 512 registers
 // allowed it places them in the accumulation-register file, and since the softmax works on the scores with
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     }
 
     if constexpr (KW == 2) {
-        // two triples: the second wave's through LDS, merged and stored by the first (shared as below: ViT-B 20.0 against 19.7 us)
+        // two triples: the second wave's through LDS, merged and stored by the first (shared as above: ViT-B 20.0 against 19.7 us)
         constexpr int PER = QB * (32 + 2) * 64;          // floats per wave: O (32 per lane), m, l
         float* red = reinterpret_cast<float*>(smem);
         __syncthreads();

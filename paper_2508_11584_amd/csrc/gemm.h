@@ -383,12 +383,6 @@ __device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, i
     if (p.ln_level_out && n0 == 0 && real) p.ln_level_out[r] = mean;
     if (p.ln_level) mean -= p.ln_level[r];
 }
-__device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, int t, float* lnrow) {
-    float mean, rstd;
-    ln_tile_row(p, m0, n0, t, mean, rstd);
-    lnrow[2 * t] = mean;
-    lnrow[2 * t + 1] = rstd;
-}
 
 // The value of the lane 1, 2 or (for values equal within every four lanes) 4 away among eight consecutive lanes, on the
 // vector ALU (row permutations; an exchange through the LDS crossbar takes ~100 clocks, six of them in a row per chunk).

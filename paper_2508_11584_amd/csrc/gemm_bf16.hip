@@ -82,7 +82,9 @@ static int pick_tile(const C (&cands)[NC], const GemmArgs& a, float& best_cost) 
     for (const C& c : cands) {
         if (g_no_small && (c.kind == 64 || c.kind == 65)) continue;
         if (g_no_splitk && (c.kind == 4 || c.kind == 5)) continue;
-        if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;        // gate and linear partner are 64 physical columns of one wave's tile
+        // 64-column tiles can do SwiGLU (gate and partner columns meet in the block-level epilogue) but were slower wherever they were
+        // timed (ViT-g fc1, us, 64 x 64 in one and four groups against 64 x 128: 400 tokens 23.5, 27.0 / 20.4, 900 45.4, 52.2 / 41.1)
+        if (c.bn == 64 && a.epi == EPI_SWIGLU) continue;
         const int64_t tiles = (int64_t)cdiv(rows, c.bm) * cdiv(a.N, c.bn) * (a.nz > 1 ? a.nz : 1);
         // Two workgroups of 64 x 64 with four wave groups share a CU like four of one group do; with a short k loop that is
         // where their partial sums cost more than the groups gain (432 tiles at K = 384: 8.2 against 7.7 us, 264 at K = 768:

@@ -36,10 +36,6 @@ __device__ __forceinline__ void pipeline_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
-// 32 x WN fp32 block of LDS (the operand buffers are free by now; the caller has put a barrier behind its last
-// read of them) and leaves with 8-column chunks per lane.  lnrow: (mean, rstd) per tile row for GEMMs with a
-// folded LayerNorm (ignored otherwise).
 // Row index of a tile row in the output.  PADDED (the strip convolution): tile rows run over the padded pixel index
 // ((image (H + 1) + y + 1) (W + 1) + x: one zero column behind every image row, one zero row between images); pad
 // positions have no output (returned as a row past M).
@@ -81,6 +77,10 @@ struct EpilogueRows {
     }
 };
 
+// Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
+// 32 x WN fp32 block of LDS (the operand buffers are free by now; the caller has put a barrier behind its last
+// read of them) and leaves with 8-column chunks per lane.  lnrow: (mean, rstd) per tile row for GEMMs with a
+// folded LayerNorm (ignored otherwise).
 template <typename T, int MI, int NI, int WM, int WN, bool PADDED = false>
 __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, const float* lnrow,
                                                    int wave, int wm, int wn, int lane, int m0, int n0) {
@@ -255,11 +255,6 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
     static_assert(MI <= 4, "passes are written out up to four row blocks");
 }
 
-// BK = 64 or 32 elements per k-tile (LDS rows of 128 or 64 bytes), S LDS stages: the loads of tile
-// kt + S - 1 are in flight while tile kt is multiplied, so a load has S - 1 tile times to arrive.
-// OCC workgroups per CU (the launch bound is given in waves per SIMD: OCC * waves / 4).
-// WGM x 2 waves: WGM = 2 gives 128-row wave tiles (256 accumulator registers, one wave per SIMD),
-// WGM = 4 gives 64-row wave tiles and two waves per SIMD, i.e. twice as many waves issuing loads.
 // Sum of a value over the two halves of a wave (lane l and lane l ^ 32), in both.
 __device__ __forceinline__ float wave_halves_sum(float v) {
     const uint32_t u = __float_as_uint(v);
@@ -316,6 +311,9 @@ __device__ __forceinline__ void rowdot_epilogue_transposed(const GemmArgs& p, f3
     }
 }
 
+// BM x BN tiles, BK elements per k-tile (LDS rows of 64, 128 or 256 bytes), S LDS stages: the loads of tile kt + S - 1 are
+// in flight while tile kt is multiplied, so a load has S - 1 tile times to arrive.  WGM x WGN waves share a tile (BM / WGM
+// rows and BN / WGN columns each); OCC workgroups per CU (the launch bound is in waves per SIMD: OCC * waves / 4).
 // RD: the instantiation for EPI_ROWDOT alone (MFMAs with the W operand first, projection epilogue without LDS staging).
 // KG: groups of WGM x WGN waves that share the tile's loads and take KS / KG of the k-steps of every k-tile each; their
 // partial sums are added in LDS in a fixed order by the block-level epilogue.
@@ -332,7 +330,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     static_assert((BK / 16) % KG == 0 && (!RING || (A_BYTES == B_BYTES && KG == 1 && S == 2)), "k-step groups / ring units");
     constexpr int A_SLOTS = A_BYTES / (1024 * NW), B_SLOTS = B_BYTES / (1024 * NW);   // 1 KB DMA instructions per wave per k-tile
     constexpr int PD = S - 1;
-    constexpr bool LN_LATE = RING;
     // chunk swizzle: 256 bytes of LDS (64 banks) hold one row of 256 bytes, 2 rows of 128 or 4 rows of 64
     constexpr int SW_SHIFT = ROWB == 256 ? 0 : ROWB == 128 ? 1 : 2, SW_MASK = CPR - 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -346,10 +343,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
     const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
 
-    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (LN_LATE, where the stages leave
-    // no room: behind the staging blocks, written when the k loop is done)
+    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (the ring leaves no room there:
+    // behind the staging blocks, written when the k loop is done)
     constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : WN % 64 ? BM * BN * 4 : NW * 32 * WN * 4;
-    float* lnrow = reinterpret_cast<float*>(smem + (!LN_LATE && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
+    float* lnrow = reinterpret_cast<float*>(smem + (!RING && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
     int* redo_flags = reinterpret_cast<int*>(lnrow + 2 * BM);            // fp32: one per wave, behind them
 
     // --- loader state.  DMA instruction `slot` of this wave fills 1 KB of LDS = RPI consecutive rows of
@@ -601,7 +598,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         // behind the first tile loads, ordered before the epilogue by the loop's barriers
         if (p.ln_stats && tid < BM) {
             ln_tile_row(p, m0, n0, tid, mean, rstd);
-            if (!LN_LATE) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+            *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
         }
         int cur = 0, nxt = PD;                                // stages of tiles kt and kt + PD
         for (int kt = 0; kt < KT; ++kt) {
@@ -649,7 +646,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             }
         }
     }
-    if (LN_LATE && p.ln_stats) {
+    if (RING && p.ln_stats) {
         if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
         __syncthreads();
     }
@@ -667,11 +664,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
 template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     constexpr int nt = 64 * WGM * WGN * KG;
-    constexpr bool late = RING;
     constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
     constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : BN / WGN % 64 ? BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
     constexpr int ln_b = BM * 8 + (sizeof(T) == 4 ? 64 : 0);              // (mean, rstd) of the tile's rows; fp32: a flag per wave
-    constexpr int lds = late ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
+    constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
     auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
     auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
