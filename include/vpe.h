@@ -24,12 +24,12 @@
  *   - an engine may be driven from one host thread at a time.
  *
  * Throughput.  With the defaults (encoder_lanes = 1) frames pass through the encoder one after another and a
- * ViT-S pass leaves most of the 256 compute units idle (about 1000 frames/s at 476x630 with three heads).  The
- * pipelined rate the benchmark reports (about 1800 frames/s) needs encoder_lanes = 3 and ring_slots = 4 (lanes + 1),
+ * ViT-S pass leaves most of the 256 compute units idle (about 1100 frames/s at 476x630 with three heads).  The
+ * pipelined rate the benchmark reports (about 2100 frames/s) needs encoder_lanes = 3 and ring_slots = 4 (lanes + 1),
  * which makes the engine use 3 encoder streams + 1 head stream, AND a process that may use five hardware queues:
  * export GPU_MAX_HW_QUEUES=5 before the HIP runtime initialises (the runtime's default of 4 leaves three for the
  * engine beside the default stream's, and the fourth engine stream then shares a queue and serialises; with the
- * default limit the best choice is encoder_lanes = 2, ring_slots = 3: about 1450 frames/s).  The batched
+ * default limit the best choice is encoder_lanes = 2, ring_slots = 3: about 1650 frames/s).  The batched
  * configurations (4 or 8 views per step) want encoder_lanes = 2, ring_slots = 3.
  */
 #ifndef VPE_H
