@@ -41,26 +41,26 @@ constexpr Cand kCands[] = {
 // busiest CU, floor(q / held) full rounds and one of the q % held tiles that are left, a round of n tiles taking
 //     t(n) [us] = alpha + next (n - 1) + K max(chain, rate n)
 // (next: what a further workgroup adds to the fixed time; chain: one workgroup's own time per k; rate: the CU's time per k and tile
-// when its workgroups share it).  Fitted to 126 convolutions (64-512 channels on 16x16 ... 296x296 grids, detection towers of
-// 384-1536 channels), 2-10 % rms per tiling.  Under the model above 64 x 64 tiles in four groups were taken for 257-768
+// when its workgroups share it).  Fitted to 174 convolutions (64-512 channels on 16x16 ... 600x600 grids, detection towers of
+// 384-1536 channels), 3-8 % rms per tiling.  Under the model above 64 x 64 tiles in four groups were taken for 257-768
 // tiles, up to 31 % slower than 64 x 128 in two (us): 512 -> 512 on 68x90 64.8 / 52.3, 256 -> 256 on 96x96 34.7 / 26.9, ViT-S
-// towers on 74x74 49.5 / 38.0, ViT-g towers there 171 / 126; the picks cost 2.7 % over the measured best, now 0.3 % (0.1 % without
-// kConvShared).
+// towers on 74x74 49.5 / 38.0, ViT-g towers there 171 / 126; the picks cost 2.7 % over the measured best, now 0.2 %.
 struct ConvCand { int kind, bm, bn, held; float alpha, next, chain, rate; };
 constexpr ConvCand kConvCands[] = {
-    {256, 256, 256, 1, 18.99f, 0.0f, 0.02160f, 0.0f},
-    {384, 384, 256, 1, 27.00f, 0.0f, 0.03675f, 0.0f},
-    {128, 256, 128, 1, 10.96f, 0.0f, 0.01561f, 0.0f},
-    {65, 64, 128, 3, 4.49f, 1.32f, 0.00859f, 0.00522f},
-    {64, 64, 64, 4, 4.84f, 0.03f, 0.00593f, 0.00365f},
-    {5, 64, 128, 2, 5.31f, 2.02f, 0.00615f, 0.00444f},
-    {4, 64, 64, 4, 4.59f, 1.73f, 0.00458f, 0.00362f},
+    {256, 256, 256, 1, 19.79f, 0.0f, 0.02239f, 0.0f},
+    {384, 384, 256, 1, 24.60f, 0.0f, 0.03818f, 0.0f},
+    {128, 256, 128, 1, 10.87f, 0.0f, 0.01573f, 0.0f},
+    {129, 256, 128, 2, 10.50f, 2.24f, 0.01760f, 0.01570f},
+    {65, 64, 128, 3, 4.50f, 0.56f, 0.00829f, 0.00535f},
+    {64, 64, 64, 4, 4.88f, 0.0f, 0.00585f, 0.00352f},
+    {5, 64, 128, 2, 5.33f, 1.59f, 0.00617f, 0.00453f},
+    {4, 64, 64, 4, 4.68f, 1.54f, 0.00458f, 0.00362f},
 };
-// What a tiling with several workgroups per CU has to be faster by, alone, to be taken over one that holds a CU: a head's
+// What a tile of 64 rows has to be faster by, alone, to be taken over one of 256 or more: a head's
 // convolutions run beside encoder kernels, where operand traffic costs more than the time alone shows.  256 -> 256 on
 // 136x180: 46.6 us with 64 x 128 tiles, 50.4 with 256 x 128, but a ViT-S 476x630 frame takes 856 us with the first and 848 with
 // the second, and 631 and 620 as a stream of two lanes.
-constexpr float kConvShared = 1.1f;
+constexpr float kConvShared = 1.12f;
 
 float predicted(const Cand& c, int64_t tiles, int K) {
     const float r = (float)cdiv(tiles, 256) / c.held;
@@ -69,7 +69,7 @@ float predicted(const Cand& c, int64_t tiles, int K) {
 float predicted(const ConvCand& c, int64_t tiles, int K) {
     auto round = [&](int n) { return n == 0 ? 0.0f : c.alpha + c.next * (n - 1) + K * (c.chain > c.rate * n ? c.chain : c.rate * n); };
     const int q = cdiv(tiles, 256);
-    return (c.held > 1 ? kConvShared : 1.0f) * ((float)(q / c.held) * round(c.held) + round(q % c.held));
+    return (c.bm == 64 ? kConvShared : 1.0f) * ((float)(q / c.held) * round(c.held) + round(q % c.held));
 }
 }  // namespace
 
@@ -155,6 +155,7 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
         if (shape) return launch_conv_strip_bf16(shape, a, s);
     }
     if (forced == 384 || forced == 256 || forced == 128 || forced == 65 || forced == 5) best = forced;
+    if (forced == 129) best = amode == A_CONV3 ? 129 : 128;
     if (forced == 4) best = a.epi == EPI_SWIGLU ? 5 : 4;
     if (forced == 64) best = a.epi == EPI_SWIGLU ? 65 : 64;
     return launch_gemm_dma_bf16(best, a, amode, s);
@@ -164,7 +165,7 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
 hipError_t configure_gemm_bf16() {
     const char* env = getenv("VPE_GEMM_TILE");
     g_forced_tile = 0;
-    for (int kind : {384, 256, 128, 65, 64, 5, 4, 9}) if (env && atoi(env) == kind) g_forced_tile = kind;      // (anything else: no tile forced)
+    for (int kind : {384, 256, 128, 129, 65, 64, 5, 4, 9}) if (env && atoi(env) == kind) g_forced_tile = kind;      // (anything else: no tile forced)
     g_no_small = getenv("VPE_NO_SMALL_DMA") != nullptr;
     g_no_splitk = getenv("VPE_NO_SPLITK") != nullptr;
     g_no_strip = getenv("VPE_NO_STRIP") != nullptr;

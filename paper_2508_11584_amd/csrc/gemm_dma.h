@@ -80,8 +80,8 @@ struct EpilogueRows {
 // Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
 // 32 x WN fp32 block of LDS (the operand buffers are free by now; the caller has put a barrier behind its last
 // read of them) and leaves with 8-column chunks per lane.  lnrow: (mean, rstd) per tile row for GEMMs with a
-// folded LayerNorm (ignored otherwise).
-template <typename T, int MI, int NI, int WM, int WN, bool PADDED = false>
+// folded LayerNorm (ignored otherwise).  CONV: only the epilogues of convolutions (store, projection); BATCH: rows at a time.
+template <typename T, int MI, int NI, int WM, int WN, bool CONV = false, bool PADDED = false, int BATCH = 4>
 __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, const float* lnrow,
                                                    int wave, int wm, int wn, int lane, int m0, int n0) {
     const int g = lane >> 5, li = lane & 31;
@@ -93,23 +93,25 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
     f32x4 rd_b0 = {0, 0, 0, 0}, rd_b1 = rd_b0, rd_w0 = rd_b0, rd_w1 = rd_b0;
     EpilogueRows<PADDED> rd_rows(p, wrow0 + lane / RD_CG);
     const int rd_c = wcol0 + (lane % RD_CG) * 8;
-    if (p.epi == EPI_ROWDOT && rd_c < p.N) {
+    auto rd_columns = [&] {
+        if (rd_c >= p.N) return;
         rd_b0 = *reinterpret_cast<const f32x4*>(p.bias + rd_c);
         rd_b1 = *reinterpret_cast<const f32x4*>(p.bias + rd_c + 4);
         rd_w0 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c);
         rd_w1 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c + 4);
-    }
+    };
+    if (BATCH > 1 && p.epi == EPI_ROWDOT) rd_columns();        // (one row at a time: no registers to keep them in)
     // The row-chunk paths: a lane keeps one 8-column chunk (64 is a multiple of the chunks per row) for all its rows
     // (96 x 128 wave tiles have registers for two rows at a time, and none for the columns while all blocks wait)
-    constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < 4 ? ITS : 4;
+    constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < BATCH ? ITS : BATCH;
     static_assert(64 % CG == 0 && ITS % NB == 0, "a lane keeps its column chunk");
     // One pass per 32-row block of the wave tile; the block index is a compile-time constant of each pass (a loop over the
     // blocks turns the accumulators into an indexed array in scratch, or spills them).
     // (rows without operands of their own go one by one: nothing to wait for, and the short loop keeps its code small)
-    const bool batched = p.epi == EPI_RESID || p.epi == EPI_PATCH || (p.epi == EPI_STORE && p.add1);
+    const bool batched = (!CONV && (p.epi == EPI_RESID || p.epi == EPI_PATCH)) || (p.epi == EPI_STORE && p.add1);
     auto pass = [&](auto I) {
         constexpr int i = decltype(I)::value;
-        if (p.ln_stats) {
+        if (!CONV && p.ln_stats) {
             // (column sums are loaded here, not before the k loop: this kernel has no registers to spare)
             float lncs[NI];
 #pragma unroll
@@ -130,7 +132,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
 #pragma unroll
             for (int v = 0; v < 16; ++v) sC[(8 * (v >> 2) + 4 * g + (v & 3)) * WN + j * 32 + li] = acc[i][j][v];
         const int rblk = wrow0 + i * 32;
-        if (p.epi == EPI_SWIGLU) {
+        if (!CONV && p.epi == EPI_SWIGLU) {
             // groups of 64 physical columns: 32 gate columns, then their 32 linear partners
             constexpr int GG = WN / 16;                  // 8-wide gate chunks per row
             T* out = reinterpret_cast<T*>(p.out);
@@ -151,7 +153,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                     store8(out + (int64_t)r * p.ldo + (ca >> 6) * 32 + j0, h);
                 }
             }
-        } else if (!PADDED && p.epi == EPI_QKV && wcol0 >= 2 * p.dim) {
+        } else if (!CONV && p.epi == EPI_QKV && wcol0 >= 2 * p.dim) {
             // value columns, written transposed: one column and 8 consecutive tokens per lane.  All rows and columns of the QKV
             // epilogue are written out and the biases fetched first: it has no arithmetic to hide a round's LDS and
             // store latency behind (over 66 QKV shapes 256 x 256 and 384 x 256 tiles 6 % faster, 64 x 128 3 %)
@@ -177,6 +179,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
             // 8 consecutive lanes hold the 8 chunks of one 64-column projection group of a row
             if constexpr (WN % 64 == 0) {
                 float* out = reinterpret_cast<float*>(p.out);
+                if (BATCH == 1) rd_columns();
 #pragma unroll 2
                 for (int n = 0; n < 32 * CG / 64; ++n) {
                     const int rr = lane / CG + n * (64 / CG);
@@ -197,7 +200,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                     if ((lane & 7) == 0 && r < p.M && rd_c < p.N) out[(int64_t)r * p.ldo + (rd_c >> 6)] = sum;
                 }
             }
-        } else if (!PADDED && p.epi == EPI_QKV) {
+        } else if (!CONV && p.epi == EPI_QKV) {
             const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
 #pragma unroll
             for (int n = 0; n < ITS; ++n) {
@@ -230,7 +233,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                     float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                     if (active) epilogue_chunk<T>(p, cols, rows[n], v);
                     if constexpr (WN % 64 == 0) {        // (8 consecutive lanes hold the 8 chunks of a 64-column statistics group)
-                        if (p.epi == EPI_RESID || p.epi == EPI_PATCH) group_stats<T>(p, cols, rows[n], v, active, lane & 7);
+                        if (!CONV && (p.epi == EPI_RESID || p.epi == EPI_PATCH)) group_stats<T>(p, cols, rows[n], v, active, lane & 7);
                     }
                 }
             }
@@ -658,10 +661,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     }
 
     if constexpr (RD) rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
-    else wave_tile_epilogue<T, MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
+    else wave_tile_epilogue<T, MI, NI, WM, WN, AMODE == A_CONV3, false, (OCC * NW > 8 ? 1 : 4)>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
 }
 
-template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
+template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false,
+          bool CONV_ONLY = RD>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     constexpr int nt = 64 * WGM * WGN * KG;
     constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
@@ -669,22 +673,23 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     constexpr int ln_b = BM * 8 + (sizeof(T) == 4 ? 64 : 0);              // (mean, rstd) of the tile's rows; fp32: a flag per wave
     constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
-    auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
     auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
     static bool configured = false;
     if (!configured) {
         hipError_t rc = hipSuccess;
-        if (!RD) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(plain), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if constexpr (!CONV_ONLY) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc == hipSuccess) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(conv), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc != hipSuccess) return rc;
         configured = true;
     }
     if (configure_only) return hipSuccess;
     // the projection-only instantiation exists for convolutions (the only users of that epilogue on these tiles)
-    if (RD && (amode != A_CONV3 || a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
+    if (RD && (a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
+    if (CONV_ONLY && amode != A_CONV3) return hipErrorInvalidValue;
     const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN), nz = a.nz > 1 ? a.nz : 1;
-    if (!RD && amode == A_PLAIN) hipLaunchKernelGGL(plain, dim3(tiles, nz), dim3(nt), lds, s, a);
-    else hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
+    if (amode == A_CONV3) hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
+    else if constexpr (!CONV_ONLY) hipLaunchKernelGGL((gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>), dim3(tiles, nz), dim3(nt), lds, s, a);
     return hipGetLastError();
 }
 

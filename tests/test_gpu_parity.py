@@ -203,7 +203,7 @@ def test_cfg2_in_the_pipelined_configuration_the_benchmark_times():
     check_all(spec, *vi.SEEDS["cfg2"], flags=vpe.VPE_FLAG_GRAPHS, lead_frames=6, ring_slots=4, encoder_lanes=3)
 
 
-@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
+@pytest.mark.parametrize("tile", ["384", "256", "128", "129", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_variant(tile, monkeypatch):
     # each bf16 GEMM shape (384 x 256, 256 x 256, 256 x 128, 64 x 128, 64 x 64 tiles; "5" and "4": 64 x 128 and 64 x 64 whose two and
     # four wave groups share the k-steps of every k-tile), forced for every GEMM of the model,
@@ -216,7 +216,7 @@ def test_direct_to_lds_gemm_variant(tile, monkeypatch):
     check_all(spec, 103, 203)
 
 
-@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
+@pytest.mark.parametrize("tile", ["384", "256", "128", "129", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
     # one k-tile (width 64), three (MLP of 192) and nine (3x3 convolutions of 64 channels): pipelines whose first loads
     # already run past the last k-tile; 35 + 3 tokens a view, so that tiles and 8-row groups straddle two views; QKV width
