@@ -32,6 +32,7 @@ constexpr Cand kCands[] = {
     {256, 256, 256, 1, 15.83f, 0.300f},   // direct-to-LDS (launch_gemm_dma_bf16 describes the shapes)
     {384, 384, 256, 1, 22.58f, 0.344f},
     {128, 256, 128, 1, 10.33f, 0.406f},
+    {129, 256, 128, 2, 12.91f, 0.924f},   // (fitted to 158 shapes of 40 ... 33000 tokens, times 0.98: picked from 20000 on)
     {65, 64, 128, 3, 6.58f, 2.001f},
     {64, 64, 64, 4, 5.28f, 3.287f},
     {5, 64, 128, 2, 5.87f, 1.222f},
@@ -154,8 +155,7 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
         const int shape = conv_strip_shape(a, forced == 9, nullptr);
         if (shape) return launch_conv_strip_bf16(shape, a, s);
     }
-    if (forced == 384 || forced == 256 || forced == 128 || forced == 65 || forced == 5) best = forced;
-    if (forced == 129) best = amode == A_CONV3 ? 129 : 128;
+    if (forced == 384 || forced == 256 || forced == 128 || forced == 129 || forced == 65 || forced == 5) best = forced;
     if (forced == 4) best = a.epi == EPI_SWIGLU ? 5 : 4;
     if (forced == 64) best = a.epi == EPI_SWIGLU ? 65 : 64;
     return launch_gemm_dma_bf16(best, a, amode, s);

@@ -664,8 +664,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     else wave_tile_epilogue<T, MI, NI, WM, WN, AMODE == A_CONV3, false, (OCC * NW > 8 ? 1 : 4)>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
 }
 
-template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false,
-          bool CONV_ONLY = RD>
+template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     constexpr int nt = 64 * WGM * WGN * KG;
     constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
@@ -673,23 +672,22 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     constexpr int ln_b = BM * 8 + (sizeof(T) == 4 ? 64 : 0);              // (mean, rstd) of the tile's rows; fp32: a flag per wave
     constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
+    auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
     auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
     static bool configured = false;
     if (!configured) {
         hipError_t rc = hipSuccess;
-        if constexpr (!CONV_ONLY) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (!RD) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(plain), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc == hipSuccess) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(conv), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc != hipSuccess) return rc;
         configured = true;
     }
     if (configure_only) return hipSuccess;
     // the projection-only instantiation exists for convolutions (the only users of that epilogue on these tiles)
-    if (RD && (a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
-    if (CONV_ONLY && amode != A_CONV3) return hipErrorInvalidValue;
+    if (RD && (amode != A_CONV3 || a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
     const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN), nz = a.nz > 1 ? a.nz : 1;
-    if (amode == A_CONV3) hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
-    else if constexpr (!CONV_ONLY) hipLaunchKernelGGL((gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>), dim3(tiles, nz), dim3(nt), lds, s, a);
+    if (!RD && amode == A_PLAIN) hipLaunchKernelGGL(plain, dim3(tiles, nz), dim3(nt), lds, s, a);
+    else hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
     return hipGetLastError();
 }
 

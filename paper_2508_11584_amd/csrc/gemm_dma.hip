@@ -10,9 +10,10 @@ namespace vpe {
 //   384: 384 x 256, 32-deep k-tiles, 8 waves (96 x 128 wave tiles), one workgroup per CU
 //   256: 256 x 256, 8 waves (64 x 128), operand tiles in a ring of five units, one workgroup per CU
 //   128: 256 x 128, 8 waves (64 x 64), three stages, one workgroup per CU
-//   129: the same for convolutions with 32-deep k-tiles, two workgroups per CU: a large convolution of 128 channels has no wider tile to
-//        fall back on, and one workgroup's epilogue has the other's k loop beside it (us, 128 / 129: 128 -> 128 on 320x320 57.8 / 50.6,
-//        on 480x520 118.7 / 100.2; with more columns 256 and 384 are ahead of both)
+//   129: the same with 32-deep k-tiles, two workgroups per CU: a large convolution of 128 channels has no wider tile to fall back on,
+//        and products of many rows with short k loops are mostly epilogue, which has the other workgroup's k loop beside it (us, best
+//        of the others / 129: 128 -> 128 on 320x320 57.8 / 50.6, on 480x520 118.7 / 100.2; ViT-S 25000 tokens fc1 78 / 71,
+//        33000 QKV 61 / 54, out-projection 37 / 34.5)
 //    65:  64 x 128, 4 waves (32 x 64),  two stages, two workgroups per CU;  64: 64 x 64, 4 waves (32 x 32), two stages
 //     5:  64 x 128, 8 waves in two groups that halve the k-steps of every k-tile (32 x 64 wave tiles), three stages
 //     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages
@@ -31,7 +32,7 @@ hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStrea
         case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, amode, s);
         case 64: return launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, amode, s);
         case 65: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, amode, s);
-        case 129: return launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2, 256, false, 1, false, true>(a, amode, s);
+        case 129: return launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, amode, s);
         case 384: return rd ? launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s);
         case 256: return rd ? launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, amode, s);
         default: return launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, amode, s);
@@ -78,7 +79,7 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, A_CONV3, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, A_CONV3, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2, 256, false, 1, false, true>(a, A_CONV3, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, false, 4>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
