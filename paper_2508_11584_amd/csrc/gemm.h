@@ -28,7 +28,7 @@ struct GemmArgs {
     int a_rpi, a_istride, a_off;
     int cH, cW, cC;      // CONV3 grid and channels (K = 9 cC, cC multiple of 64)
     const void* zeros;   // CONV3: >= 16 bytes of zeros, read in place of out-of-image taps
-    int epi, act, out_f32;
+    int epi, act, out_f32;         // (CONV3: STORE or ROWDOT, without a folded LayerNorm)
     void* out;           // T or float (out_f32); RESID/PATCH: float residual stream
     int64_t ldo;
     int o_rpi, o_istride, o_off;   // output row map, as for A

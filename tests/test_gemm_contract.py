@@ -1,4 +1,5 @@
-"""Host-side checks of the GEMM launcher: sizes that its kernels' k loops cannot do are refused before anything is launched."""
+"""Host-side checks of the GEMM launcher: k extents that its kernels' loops cannot do, and epilogues that its convolution kernels do
+not carry, are refused before anything is launched."""
 import os
 import subprocess
 
@@ -24,12 +25,20 @@ int main() {
             const hipError_t rc = launch_gemm(dtype, a, r.amode, nullptr);
             if (rc != hipErrorInvalidValue) { printf("dtype %d mode %d K %d cC %d: %d\n", dtype, r.amode, r.K, r.cC, (int)rc); ++bad; }
         }
+    for (int epi : {EPI_RESID, EPI_SWIGLU, EPI_QKV, EPI_PATCH}) {
+        GemmArgs a{};
+        a.M = a.N = 64;
+        a.cC = 64; a.K = 9 * a.cC; a.cH = a.cW = 8;
+        a.lda = a.ldo = 64; a.a_rpi = a.o_rpi = 64; a.nz = 1; a.epi = epi;
+        const hipError_t rc = launch_gemm(1, a, A_CONV3, nullptr);
+        if (rc != hipErrorInvalidValue) { printf("convolution with epilogue %d: %d\n", epi, (int)rc); ++bad; }
+    }
     return bad;
 }
 """
 
 
-def test_gemm_launcher_refuses_k_extents_that_are_not_whole_tiles(tmp_path):
+def test_gemm_launcher_refuses_what_its_kernels_do_not_have(tmp_path):
     vpe.load_library()                                   # (built already, or an error that says so)
     src, exe = tmp_path / "contract.cpp", tmp_path / "contract"
     src.write_text(PROGRAM)
