@@ -40,12 +40,11 @@ constexpr int STRIP_MAX_SLOTS = 7;        // strip load instructions per wave an
 // this range: the leading pad row and whatever follows the last pixel are nobody's output).
 static inline int64_t strip_positions(int images, int H, int W) { return ((int64_t)(images - 1) * (H + 1) + H) * (W + 1) - 1; }
 
-// ROWDOT = true: the instantiation for EPI_ROWDOT alone.  Its MFMAs take the weights as the first operand, so a
-// lane's accumulators are one pixel's channels (pixel = lane % 32, channel 8 (v / 4) + 4 (lane / 32) + v % 4 of the
-// 32-channel block) and the projection over channels is a sum inside the lane plus one exchange between the lane
-// halves (rowdot_epilogue_transposed).
+// The MFMAs take the weights as the first operand, so a lane's accumulators are one pixel's channels (pixel = lane % 32, channel
+// 8 (v / 4) + 4 (lane / 32) + v % 4 of the 32-channel block).  ROWDOT: the instantiation for EPI_ROWDOT, whose projection over channels is
+// then a sum inside the lane plus one exchange between the lane halves (rowdot_epilogue_transposed); else EPI_STORE.
 template <int BM, int BN, int WGM, int WGN, int OCC, bool ROWDOT>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_strip_kernel(const GemmArgs args, int sp_rows, int tiles_m) {
+__global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_strip_kernel(const GemmArgs args, int sp_rows) {
     const GemmArgs p = select_problem(args);
     constexpr int NW = WGM * WGN;
     static_assert(NW == 8 && BN % 32 == 0, "loader mapping: eight waves; a weight load instruction takes 32 rows of a tap");
@@ -61,7 +60,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_stri
     const int images = p.M / (p.cH * p.cW);
 
     int tm, tn;
-    tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), tiles_m, (p.N + BN - 1) / BN, tm, tn);
+    tile_coords(blockIdx.x, p.map, tm, tn);
     const int m0 = Wp + tm * BM, n0 = tn * BN;            // position W + 1 is pixel (0, 0) of the first image
 
     const int strip_bytes = sp_rows * 32;
@@ -163,8 +162,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_stri
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int nj = 0; nj < NI; ++nj) {
-                    acc[mi][nj] = ROWDOT ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[nj], fa[cur], acc[mi][nj], 0, 0, 0)
-                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur], fb[nj], acc[mi][nj], 0, 0, 0);
+                    acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[nj], fa[cur], acc[mi][nj], 0, 0, 0);
                     if (mi == MI - 1 && i < 2) fb[nj] = *reinterpret_cast<const bf16x8*>(sb + (i + 1) * WTAP + nj * 1024);
                     if (last && more) fb[nj] = *reinterpret_cast<const bf16x8*>(nb + nj * 1024);
                 }
@@ -225,7 +223,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_stri
     if constexpr (ROWDOT) {
         rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, true>(p, acc, smem, wm, wn, tid, m0, n0);
     } else {
-        wave_tile_epilogue<bf16, MI, NI, WM, WN, true, true>(p, acc, smem, nullptr, wave, wm, wn, lane, m0, n0);
+        wave_tile_epilogue<bf16, EPI_STORE, BM, MI, NI, WM, WN, true>(p, acc, smem, nullptr, wave, wm, wn, tid, m0, n0);
     }
 }
 
@@ -264,8 +262,9 @@ static inline hipError_t launch_conv_strip(const GemmArgs& a, hipStream_t s, boo
     const int lds = ops_b > epi_b ? ops_b : epi_b;
     if (lds > max_lds) return hipErrorInvalidValue;
     const int tiles_m = (int)((strip_positions(a.M / (a.cH * a.cW), a.cH, a.cW) + BM - 1) / BM);
-    const int tiles = tiles_m * cdiv(a.N, BN), nz = a.nz > 1 ? a.nz : 1;
-    hipLaunchKernelGGL((conv_strip_kernel<BM, BN, WGM, WGN, OCC, ROWDOT>), dim3(tiles, nz), dim3(64 * WGM * WGN), lds, s, a, sp, tiles_m);
+    GemmArgs args = a;
+    args.map = TileMap::make(tiles_m, cdiv(a.N, BN));
+    hipLaunchKernelGGL((conv_strip_kernel<BM, BN, WGM, WGN, OCC, ROWDOT>), dim3(args.map.tiles, a.nz > 1 ? a.nz : 1), dim3(64 * WGM * WGN), lds, s, args, sp);
     return hipGetLastError();
 }
 

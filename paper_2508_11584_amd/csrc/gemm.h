@@ -16,6 +16,21 @@ enum AMode { A_PLAIN = 0, A_CONV3 = 1 };
 enum Epi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3, EPI_PATCH = 4, EPI_ROWDOT = 5 };
 enum Act { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
 
+// Where the tiles of a launch lie, worked out on the host (TileMap::make): the kernel's divisions by these numbers are products
+// with their reciprocals.  (The prologue of a 64 x 64 workgroup was 290 instructions, four divisions among them.)
+struct TileMap {
+    int tiles, tiles_m, per_group;       // workgroups per problem, tile rows, tiles in a group of GM tile rows
+    uint32_t inv_group, inv_last;        // ceil(2^32 / d) for d = per_group and the rows of the last group (0: divide)
+    static constexpr int GM = 8;
+    static uint32_t reciprocal(int64_t d, int64_t most) { return d > 1 && d * most < (int64_t(1) << 32) ? (uint32_t)(((uint64_t(1) << 32) + d - 1) / d) : 0; }
+    static TileMap make(int tiles_m, int tiles_n) {
+        TileMap t{tiles_m * tiles_n, tiles_m, GM * tiles_n, 0, 0};
+        t.inv_group = reciprocal(t.per_group, t.tiles);
+        t.inv_last = reciprocal(tiles_m % GM, t.per_group);
+        return t;
+    }
+};
+
 struct GemmArgs {
     const void* A;       // T
     int64_t lda;         // elements between consecutive A rows (PLAIN) / pixels (CONV3)
@@ -23,6 +38,8 @@ struct GemmArgs {
     const float* bias;   // [N] in the physical column order of W, may be null
     int M, N, K;         // K multiple of 64 (k-tiles are whole; anything else is refused)
     int m_begin;         // a launch covers rows m_begin .. M - 1 (row indices stay those of the whole problem)
+    int nz;              // problems of a batched launch (see z_a below)
+    TileMap map;         // (filled in by the launchers)
     // PLAIN: logical row r reads A row (r / a_rpi) * a_istride + a_off + r % a_rpi
     // CONV3: pixel (b, y, x) is A row b * a_istride + a_off + y * cW + x
     int a_rpi, a_istride, a_off;
@@ -69,7 +86,6 @@ struct GemmArgs {
     // batch of nz independent problems of the same shape in one launch (blockIdx.y = z): problem z uses
     // A + z * z_a, W + z * z_w, out + z * z_out (byte strides, may be negative) and bias + z * z_bias (elements);
     // with z_inner > 0 the output alone is addressed in two levels, out + (z % z_inner) * z_out + (z / z_inner) * z_out2
-    int nz;
     int64_t z_a, z_w, z_out, z_bias;
     int z_inner;
     int64_t z_out2;
@@ -78,6 +94,7 @@ struct GemmArgs {
 // The arguments of problem blockIdx.y of a batched launch (a plain copy when the launch is not batched).
 __device__ __forceinline__ GemmArgs select_problem(const GemmArgs& in) {
     GemmArgs p = in;
+    if (in.nz <= 1) return p;
     const int64_t z = blockIdx.y;
     p.A = reinterpret_cast<const char*>(in.A) + z * in.z_a;
     p.W = reinterpret_cast<const char*>(in.W) + z * in.z_w;
@@ -148,14 +165,15 @@ __device__ __forceinline__ int xcd_contiguous(int bid, int nb) {
 // k-slice fetched into that XCD's L2 serves 32 / GM workgroups and each W k-slice GM of them.
 // (Measured on the large tiles: with row-major order the loads ran at the XCD <-> memory-side
 // fabric rate, about 13 TB/s in aggregate, not at the L2 rate.)
-__device__ __forceinline__ void tile_coords(int lin, int tiles_m, int tiles_n, int& tm, int& tn) {
-    constexpr int GM = 8;
-    const int per_group = GM * tiles_n;
-    const int group = lin / per_group, rem = lin - group * per_group;
+__device__ __forceinline__ uint32_t quotient(uint32_t x, uint32_t d, uint32_t inv) { return inv ? __umulhi(x, inv) : x / d; }
+__device__ __forceinline__ void tile_coords(int bid, const TileMap& t, int& tm, int& tn) {
+    constexpr int GM = TileMap::GM;
+    const int lin = xcd_contiguous(bid, t.tiles);
+    const int group = quotient(lin, t.per_group, t.inv_group), rem = lin - group * t.per_group;
     const int first = group * GM;
-    const int gsz = tiles_m - first < GM ? tiles_m - first : GM;
-    tm = first + rem % gsz;
-    tn = rem / gsz;
+    const int rows = t.tiles_m - first;
+    tn = rows >= GM ? rem / GM : rows == 1 ? rem : quotient(rem, rows, t.inv_last);
+    tm = first + rem - tn * (rows >= GM ? GM : rows);
 }
 
 // 8 consecutive values of T (16 bytes of bf16, 32 bytes of fp32) to global memory.
@@ -175,34 +193,41 @@ __device__ __forceinline__ void store8(float* dst, const float* v) {
 // whole batch of rows before the first of them is stored.  Taken row by row -- the compiler cannot move a row's loads
 // above the previous row's stores -- every row pays a memory latency: a 256 x 256 tile spent 21 us on its 16 dependent
 // rows per lane (bias, LayerScale and the residual values fetched behind each other), a 64 x 128 tile 3.5 us.
-struct EpiCols { f32x4 b0, b1, g0, g1; int c, nv; };      // nv: columns of the chunk that exist (8, fewer at a ragged edge, <= 0: none)
+struct EpiCols { f32x4 b0, b1, g0, g1; int c, nv; };      // bias; LayerScale (RESID) or the folded LayerNorm's column sums; nv: columns
+                                                          // of the chunk that exist (8, fewer at a ragged edge, <= 0: none)
 struct EpiRow { int orow; f32x4 a0, a1; float lev; };
 
+__device__ __forceinline__ void load_columns(const float* src, int c, int nv, f32x4& lo, f32x4& hi) {
+    lo = hi = f32x4{0, 0, 0, 0};
+    if (!src) return;
+    if (nv == 8) {
+        lo = *reinterpret_cast<const f32x4*>(src + c);
+        hi = *reinterpret_cast<const f32x4*>(src + c + 4);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i < nv) lo[i] = src[c + i];
+            if (4 + i < nv) hi[i] = src[c + 4 + i];
+        }
+    }
+}
+template <int EPI>
 __device__ __forceinline__ EpiCols epilogue_cols(const GemmArgs& p, int c) {
     EpiCols k;
     k.c = c;
     k.nv = p.N - c < 8 ? p.N - c : 8;
-    k.b0 = k.b1 = k.g0 = k.g1 = f32x4{0, 0, 0, 0};
-    if (p.bias) {
-        if (k.nv == 8) {
-            k.b0 = *reinterpret_cast<const f32x4*>(p.bias + c);
-            k.b1 = *reinterpret_cast<const f32x4*>(p.bias + c + 4);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (i < k.nv) k.b0[i] = p.bias[c + i];
-                if (4 + i < k.nv) k.b1[i] = p.bias[c + 4 + i];
-            }
-        }
-    }
-    if (p.epi == EPI_RESID && k.nv == 8) {
-        k.g0 = *reinterpret_cast<const f32x4*>(p.gamma + c);
-        k.g1 = *reinterpret_cast<const f32x4*>(p.gamma + c + 4);
-    }
+    load_columns(p.bias, c, k.nv, k.b0, k.b1);
+    load_columns(EPI == EPI_RESID ? p.gamma : EPI != EPI_PATCH && p.ln_stats ? p.ln_colsum : nullptr, c, k.nv, k.g0, k.g1);
     return k;
+}
+// The folded LayerNorm on eight columns of a row: st = (mean, rstd), cs the column sums.
+__device__ __forceinline__ void ln_apply(const f32x2& st, const f32x4& cs0, const f32x4& cs1, float* v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[i] = st[1] * (v[i] - st[0] * cs0[i]); v[4 + i] = st[1] * (v[4 + i] - st[0] * cs1[i]); }
 }
 
 // Row r of the output: its place under the row map and the operands of its chunk (loads only; ok: r < M and the chunk exists).
+template <int EPI>
 __device__ __forceinline__ EpiRow epilogue_row_operands(const GemmArgs& p, const EpiCols& k, int r, bool ok) {
     EpiRow e;
     e.orow = r;
@@ -210,13 +235,13 @@ __device__ __forceinline__ EpiRow epilogue_row_operands(const GemmArgs& p, const
     e.lev = 0.0f;
     if (!ok) return e;
     const float* src = nullptr;
-    if (p.epi == EPI_STORE) {
+    if (EPI == EPI_STORE) {
         // (the plain map, one run of rows, needs no division)
         e.orow = p.o_rpi >= p.M ? p.o_off + r : (r / p.o_rpi) * p.o_istride + p.o_off + r % p.o_rpi;
         if (p.add1) src = p.add1 + (int64_t)e.orow * p.ldo + k.c;
-    } else if (p.epi == EPI_RESID) {
+    } else if (EPI == EPI_RESID) {
         src = reinterpret_cast<const float*>(p.out) + (int64_t)e.orow * p.ldo + k.c;
-    } else if (p.epi == EPI_PATCH) {
+    } else if (EPI == EPI_PATCH) {
         const int b = r / p.o_rpi, pp = r - b * p.o_rpi;
         e.orow = b * p.o_istride + p.o_off + pp;
         src = p.pos + (int64_t)pp * p.N + k.c;
@@ -231,12 +256,12 @@ __device__ __forceinline__ EpiRow epilogue_row_operands(const GemmArgs& p, const
 
 // Columns k.c .. of the row of `e`, the raw accumulators in v.  Full, aligned chunks go out as 16-byte stores; ragged
 // ones element by element.  RESID / PATCH leave the updated residual values in v.
-template <typename T>
+template <typename T, int EPI>
 __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, const EpiCols& k, const EpiRow& e, float* v) {
     const int nv = k.nv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) { v[i] += k.b0[i]; v[4 + i] += k.b1[i]; }
-    if (p.epi == EPI_STORE) {
+    if (EPI == EPI_STORE) {
         if (p.act == ACT_RELU) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.0f);
@@ -275,9 +300,9 @@ __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, const EpiCols&
                 for (int i = 0; i < 8; ++i) if (i < nv) dst[i] = from_f32<T>(v[i]);
             }
         }
-    } else if (p.epi == EPI_RESID || p.epi == EPI_PATCH) {
+    } else if (EPI == EPI_RESID || EPI == EPI_PATCH) {
         // fp32 residual stream, N = ldo = model width (multiple of 64): always full aligned chunks
-        if (p.epi == EPI_PATCH) {
+        if (EPI == EPI_PATCH) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[i] += e.a0[i]; v[4 + i] += e.a1[i]; }
         } else {
@@ -346,43 +371,61 @@ __device__ __forceinline__ void store_tokens8(const GemmArgs& p, T* vt, int r, i
     }
 }
 
-// (mean, rstd) of row r from its group statistics (mean_g, M2_g = sum of squared deviations from mean_g, of
-// each 64-column group).  Groups are merged around the first group's mean, so a level common to the whole row
-// cancels before anything is squared:
+// (mean, rstd) of a row from its group statistics (mean_g, M2_g = sum of squared deviations from mean_g, of
+// each 64-column group), one thread per tile row.  Groups are merged around the first group's mean, so a level common to
+// the whole row cancels before anything is squared:
 //   mean = m_0 + avg_g (m_g - m_0),   M2 = sum_g M2_g + 64 (sum_g (m_g - m_0)^2 - G (mean - m_0)^2).
-// All loads are independent 16-byte loads of two groups each.
-__device__ __forceinline__ void ln_row_stats(const GemmArgs& p, int r, float& mean, float& rstd) {
-    const float* st = p.ln_stats + (int64_t)r * p.ln_groups * 2;
-    const float m0 = st[0];
-    float sd = 0.0f, sdd = 0.0f, sm2 = 0.0f;
-    int g = 0;
-#pragma unroll 4
-    for (; g + 2 <= p.ln_groups; g += 2) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(st + 2 * g);
-        const float d0 = v[0] - m0, d1 = v[2] - m0;
-        sd += d0 + d1;
-        sdd += d0 * d0 + d1 * d1;
-        sm2 += v[1] + v[3];
-    }
-    if (g < p.ln_groups) {
-        const float d = st[2 * g] - m0;
-        sd += d; sdd += d * d; sm2 += st[2 * g + 1];
-    }
-    const float G = (float)p.ln_groups, dm = sd / G;
-    mean = m0 + dm;
-    const float m2 = sm2 + 64.0f * fmaxf(sdd - G * dm * dm, 0.0f);
-    rstd = 1.0f / sqrtf(m2 / (64.0f * G) + p.ln_eps);
-}
+// In two parts, so that the loads are under way while the accumulators are staged: `fetch` asks for the statistics, `merge`
+// uses them.  Both belong to the epilogue: while loads into LDS are in flight the compiler waits for all of them before it
+// uses any other loaded value, so in front of the k loop the statistics cost a drained pipeline (us before the first
+// barrier with / without them, ViT-S 1.9 / 1.0, ViT-g 3.7 / 1.3).
+// Rows of up to 24 groups (width 1536) go in one batch; more follow in `merge`.
+struct LnRow {
+    f32x4 v[12];                    // two groups each
+    float odd_mean, odd_m2, level;  // the last group of an odd number; what A was stored against
 
-// Consumer prologue, one thread per tile row: the row's mean relative to the level A was stored against and its rstd;
-// the mean itself is handed on as the next level by the first column block's tiles.
-__device__ __forceinline__ void ln_tile_row(const GemmArgs& p, int m0, int n0, int t, float& mean, float& rstd) {
-    const bool real = m0 + t < p.M;
-    const int r = real ? m0 + t : p.M - 1;
-    ln_row_stats(p, r, mean, rstd);
-    if (p.ln_level_out && n0 == 0 && real) p.ln_level_out[r] = mean;
-    if (p.ln_level) mean -= p.ln_level[r];
-}
+    template <int N>
+    __device__ __forceinline__ void fetch_pairs(const float* st, int pairs) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = *reinterpret_cast<const f32x4*>(st + 4 * (k < pairs ? k : 0));
+    }
+    __device__ __forceinline__ void fetch(const GemmArgs& p, int r) {
+        const float* st = p.ln_stats + (int64_t)r * p.ln_groups * 2;
+        const int pairs = p.ln_groups >> 1;
+        odd_mean = st[2 * (p.ln_groups - 1)];
+        odd_m2 = st[2 * (p.ln_groups - 1) + 1];
+        level = p.ln_level ? p.ln_level[r] : 0.0f;
+        if (pairs == 0) v[0] = f32x4{odd_mean, 0.0f, 0.0f, 0.0f};
+        else if (pairs <= 3) fetch_pairs<3>(st, pairs);
+        else if (pairs <= 6) fetch_pairs<6>(st, pairs);
+        else if (pairs <= 8) fetch_pairs<8>(st, pairs);
+        else fetch_pairs<12>(st, pairs);
+    }
+    __device__ __forceinline__ void merge(const GemmArgs& p, int r, float& mean, float& rstd) const {
+        const float m0 = v[0][0];
+        float sd = 0.0f, sdd = 0.0f, sm2 = 0.0f;
+        auto add = [&](const f32x4& u) {
+            const float d0 = u[0] - m0, d1 = u[2] - m0;
+            sd += d0 + d1;
+            sdd += d0 * d0 + d1 * d1;
+            sm2 += u[1] + u[3];
+        };
+        const int pairs = p.ln_groups >> 1;
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+            if (k < pairs) add(v[k]);
+        const float* st = p.ln_stats + (int64_t)r * p.ln_groups * 2;
+        for (int k = 12; k < pairs; ++k) add(*reinterpret_cast<const f32x4*>(st + 4 * k));
+        if (p.ln_groups & 1) {
+            const float d = odd_mean - m0;
+            sd += d; sdd += d * d; sm2 += odd_m2;
+        }
+        const float G = (float)p.ln_groups, dm = sd / G;
+        mean = m0 + dm;
+        const float m2 = sm2 + 64.0f * fmaxf(sdd - G * dm * dm, 0.0f);
+        rstd = 1.0f / sqrtf(m2 / (64.0f * G) + p.ln_eps);
+    }
+};
 
 // The value of the lane 1, 2 or (for values equal within every four lanes) 4 away among eight consecutive lanes, on the
 // vector ALU (row permutations; an exchange through the LDS crossbar takes ~100 clocks, six of them in a row per chunk).
@@ -421,18 +464,39 @@ __device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k,
         *reinterpret_cast<f32x2*>(p.st_out + ((int64_t)e.orow * (p.N >> 6) + (k.c >> 6)) * 2) = f32x2{mean, m2};
 }
 
+// The folded LayerNorm's (mean, rstd) of the tile's rows into lnrow[2 row] (LDS), one thread per row: `ask` in front of other
+// epilogue work, `leave` behind it and in front of a barrier.  The means are relative to the level A was stored against; the
+// means themselves are handed on as the next level by the first column block's tiles.
+template <int BM>
+struct LnTile {
+    LnRow row;
+    __device__ __forceinline__ int place(const GemmArgs& p, int m0, int tid) const { return m0 + tid < p.M ? m0 + tid : p.M - 1; }
+    __device__ __forceinline__ void ask(const GemmArgs& p, int m0, int tid) {
+        if (tid < BM) row.fetch(p, place(p, m0, tid));
+    }
+    __device__ __forceinline__ void leave(const GemmArgs& p, float* lnrow, int m0, int n0, int tid) const {
+        if (tid >= BM) return;
+        float mean, rstd;
+        row.merge(p, place(p, m0, tid), mean, rstd);
+        if (p.ln_level_out && n0 == 0 && m0 + tid < p.M) p.ln_level_out[m0 + tid] = mean;
+        *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean - row.level, rstd};
+    }
+};
+
 // Block-level epilogue of the tiles whose waves hold less than whole 64-column groups or partial sums.  The accumulators go through LDS
 // (`smem`, free after the k loop, at least BM * BN * 4 bytes) as a row-major fp32 tile, so that
 // each thread then owns 8 consecutive columns of a row: one row-index computation and 16-byte
-// coalesced global accesses per chunk instead of 64 scattered 2-byte stores per lane.
-// accumulator element v of lane (g, li) in block (i, j): row = 32 i + 8 (v / 4) + 4 g + v % 4, col = 32 j + li
+// coalesced global accesses per chunk.  The MFMAs took the W operand first, so a lane holds one tile row and of every block of
+// 32 columns four runs of four: accumulator element v of lane (g, li) in block (i, j) is row 32 i + li, column
+// 32 j + 8 (v / 4) + 4 g + v % 4, and the tile is written 16 bytes at a time.
 // KG > 1: the workgroup holds KG groups of WGM x WGN waves, each with the partial sums of its share of the k
 // range for the same tile; each leaves them in a tile of its own in LDS (KG * BM * BN * 4 bytes), they are added in a
 // fixed order (group 0, then 1, ...) where they are read, and all KG groups' threads share the chunk work below.  (Added
-// into one tile group by group, with a barrier each, four groups cost 1.3 us more than two at 64 x 64.)
-template <typename T, int BM, int BN, int WGM, int WGN, int KG = 1>
+// into one tile group by group, with a barrier each, four groups cost 1.3 us more than two at 64 x 64.)  The folded
+// LayerNorm is applied to the sums: on the partial sums it was done once per group and element.
+template <typename T, int EPI, int BM, int BN, int WGM, int WGN, int KG = 1>
 __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[BM / WGM / 32][BN / WGN / 32],
-                                               char* smem, const float* lnrow, const float* lncs, int m0, int n0) {
+                                               char* smem, float* lnrow, int m0, int n0) {
     constexpr int NTG = 64 * WGM * WGN, NT = NTG * KG;
     constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid % NTG) >> 6;
@@ -440,39 +504,28 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
     const int wm = wave / WGN, wn = wave % WGN;
     const int g = lane >> 5, li = lane & 31;
     float* sC = reinterpret_cast<float*>(smem);
-    if (p.ln_stats) {
-        // folded LayerNorm: lnrow[2 row] = mean, lnrow[2 row + 1] = rstd of the tile's rows
-        // lncs[j]: column sum of this lane's column in block j, loaded before the k loop
-        // (the mean term belongs to the whole sum: only group 0 subtracts it)
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = wm * WM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                const f32x2 st = *reinterpret_cast<const f32x2*>(lnrow + 2 * row);
-                const float mean = kg == 0 ? st[0] : 0.0f;
-#pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j][v] = st[1] * (acc[i][j][v] - mean * lncs[j]);
-            }
-    }
+    const bool has_ln = EPI != EPI_RESID && EPI != EPI_PATCH && EPI != EPI_ROWDOT && p.ln_stats;
+    LnTile<BM> ln;
+    if (has_ln) ln.ask(p, m0, tid);
     // the lane's columns for the row-chunk paths, and its first rows' operands: on their way while the tile is staged
     constexpr int CG = BN / 8, RPASS = NT / CG, PASSES = BM / RPASS, NB = PASSES < 4 ? PASSES : 4;
     static_assert(BM % RPASS == 0 && PASSES % NB == 0, "whole passes over the tile's rows");
     const int cg = tid % CG, rr0 = tid / CG;
-    const bool chunks = p.epi != EPI_SWIGLU && p.epi != EPI_ROWDOT && !(p.epi == EPI_QKV && n0 >= 2 * p.dim);
+    const bool values = EPI == EPI_QKV && n0 >= 2 * p.dim;            // value columns of QKV
+    const bool chunks = EPI != EPI_SWIGLU && EPI != EPI_ROWDOT && !values;
     EpiCols cols;
     EpiRow rows[NB];
     if (chunks) {
-        cols = epilogue_cols(p, n0 + cg * 8);
+        cols = epilogue_cols<EPI>(p, n0 + cg * 8);
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
             const int r = m0 + rr0 + n * RPASS;
-            rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
+            rows[n] = epilogue_row_operands<EPI>(p, cols, r, r < p.M && cols.nv > 0);
         }
     }
-    // 4-column groups of a row are stored exchanged by the row's 8-row block (as the column reads of the transposed value
-    // store need it: eight lanes read one column of eight blocks, all on one bank otherwise)
-    auto at = [&](int row, int col) { return row * BN + (col ^ (((row >> 3) & 7) << 2)); };
+    // 4-column groups of a row are exchanged by the row: 16 consecutive rows writing one group, and eight lanes reading one
+    // column of eight 8-row blocks (the transposed value store), fall on different banks
+    auto at = [&](int row, int col) { return row * BN + (col ^ (((row ^ (row >> 3)) & 15) << 2)); };
     {
         float* own = sC + kg * BM * BN;
 #pragma unroll
@@ -480,8 +533,11 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) own[at(wm * WM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3), wn * WN + j * 32 + li)] = acc[i][j][v];
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4*>(own + at(wm * WM + i * 32 + li, wn * WN + j * 32 + 8 * q + 4 * g)) =
+                        f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
     }
+    if (has_ln) ln.leave(p, lnrow, m0, n0, tid);
     __syncthreads();
     auto tile8 = [&](int row, int col, float* v) {           // columns col .. col + 7 of a tile row, the groups' partial sums added in order
 #pragma unroll
@@ -495,8 +551,9 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
             }
         }
     };
+    auto row_stats = [&](int row) { return *reinterpret_cast<const f32x2*>(lnrow + 2 * row); };
 
-    if (p.epi == EPI_SWIGLU) {
+    if constexpr (EPI == EPI_SWIGLU) {
         // physical columns come in groups of 64: 32 gate columns, then their 32 linear partners;
         // a thread takes 8 gate columns and their partners and writes 8 hidden units
         constexpr int GG = BN / 16, GPASS = NT / GG;
@@ -505,23 +562,29 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
         if (ca + 40 <= p.N) {
             const int oc = (ca >> 6) * 32 + j0;       // hidden unit index
             T* out = reinterpret_cast<T*>(p.out);
-            float ba[8], bb[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) { ba[i] = p.bias[ca + i]; bb[i] = p.bias[ca + 32 + i]; }
+            const EpiCols ka = epilogue_cols<EPI>(p, ca), kb = epilogue_cols<EPI>(p, ca + 32);
             for (int rr = tid / GG; rr < BM; rr += GPASS) {
                 const int r = m0 + rr;
                 if (r >= p.M) break;
                 float va[8], vb[8], h[8];
                 tile8(rr, grp * 64 + j0, va);
                 tile8(rr, grp * 64 + j0 + 32, vb);
+                if (has_ln) {
+                    const f32x2 st = row_stats(rr);
+                    ln_apply(st, ka.g0, ka.g1, va);
+                    ln_apply(st, kb.g0, kb.g1, vb);
+                }
 #pragma unroll
-                for (int i = 0; i < 8; ++i) h[i] = swiglu_for<T>(va[i] + ba[i], vb[i] + bb[i]);
+                for (int i = 0; i < 4; ++i) {
+                    h[i] = swiglu_for<T>(va[i] + ka.b0[i], vb[i] + kb.b0[i]);
+                    h[4 + i] = swiglu_for<T>(va[4 + i] + ka.b1[i], vb[4 + i] + kb.b1[i]);
+                }
                 store8(out + (int64_t)r * p.ldo + oc, h);
             }
         }
         return;
     }
-    if (p.epi == EPI_QKV && n0 >= 2 * p.dim) {
+    if (EPI == EPI_QKV && values) {
         // value columns: written transposed, vt[(b dim + c)][token].  A thread takes one column and 8
         // consecutive tokens (one 16-byte store); consecutive threads take consecutive token groups of
         // the same column, so a column's BM tokens leave as one contiguous run.
@@ -531,20 +594,24 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
             const int cc = it / RGN, rr = (it % RGN) * 8;
             const int r = m0 + rr, c2 = n0 + cc - 2 * p.dim;
             if (r >= p.M || n0 + cc >= p.N) continue;     // (128-column tiles: the last one of an odd multiple of 64 is half empty)
-            const float bias = p.bias[n0 + cc];
+            const float bias = p.bias[n0 + cc], cs = has_ln ? p.ln_colsum[n0 + cc] : 0.0f;
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 v[k] = sC[at(rr + k, cc)];
 #pragma unroll
                 for (int q = 1; q < KG; ++q) v[k] += sC[q * BM * BN + at(rr + k, cc)];
+                if (has_ln) {
+                    const f32x2 st = row_stats(rr + k);
+                    v[k] = st[1] * (v[k] - st[0] * cs);
+                }
                 v[k] += bias;
             }
             store_tokens8<T>(p, vt, r, c2, v);
         }
         return;
     }
-    if (p.epi == EPI_ROWDOT) {
+    if constexpr (EPI == EPI_ROWDOT) {
         // 8 consecutive lanes hold the 8 chunks of one 64-column group of a row: every lane takes part in
         // the exchange (out-of-range rows / columns contribute zero), the first lane of a group writes
         const int c = n0 + cg * 8;
@@ -573,7 +640,7 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 const int r = m0 + rr0 + (b + NB + n) * RPASS;
-                rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
+                rows[n] = epilogue_row_operands<EPI>(p, cols, r, r < p.M && cols.nv > 0);
             }
         }
 #pragma unroll
@@ -582,8 +649,9 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
             const bool active = m0 + rr < p.M && cols.nv > 0;
             float v[8];
             tile8(rr, cg * 8, v);
-            if (active) epilogue_chunk<T>(p, cols, now[n], v);
-            if (p.epi == EPI_RESID || p.epi == EPI_PATCH) group_stats<T>(p, cols, now[n], v, active, cg & 7);
+            if (has_ln) ln_apply(row_stats(rr), cols.g0, cols.g1, v);
+            if (active) epilogue_chunk<T, EPI>(p, cols, now[n], v);
+            if (EPI == EPI_RESID || EPI == EPI_PATCH) group_stats<T>(p, cols, now[n], v, active, cg & 7);
         }
     }
 }

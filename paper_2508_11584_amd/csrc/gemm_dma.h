@@ -79,28 +79,35 @@ struct EpilogueRows {
 
 // Epilogue of the wave-tiled kernels: each wave stages its MI x NI accumulator blocks 32 rows at a time in its own
 // 32 x WN fp32 block of LDS (the operand buffers are free by now; the caller has put a barrier behind its last
-// read of them) and leaves with 8-column chunks per lane.  lnrow: (mean, rstd) per tile row for GEMMs with a
-// folded LayerNorm (ignored otherwise).  CONV: only the epilogues of convolutions (store, projection); BATCH: rows at a time.
-template <typename T, int MI, int NI, int WM, int WN, bool CONV = false, bool PADDED = false, int BATCH = 4>
-__device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, const float* lnrow,
-                                                   int wave, int wm, int wn, int lane, int m0, int n0) {
-    const int g = lane >> 5, li = lane & 31;
+// read of them) and leaves with 8-column chunks per lane.  The MFMAs took the W operand first: a lane holds one row of
+// each block (row lane % 32, columns 8 (v / 4) + 4 (lane / 32) + v % 4 of every 32), so a block is staged with 16-byte writes, a quarter of
+// the instructions of a layout with a column per lane, and the folded LayerNorm is applied where the chunks are read.
+// lnrow: LDS for (mean, rstd) per tile row.
+template <typename T, int EPI, int BM, int MI, int NI, int WM, int WN, bool PADDED = false, int BATCH = 4>
+__device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, float* lnrow,
+                                                   int wave, int wm, int wn, int tid, int m0, int n0) {
+    const int lane = tid & 63, g = lane >> 5, li = lane & 31;
     float* sC = reinterpret_cast<float*>(smem) + wave * (32 * WN);
     const int wrow0 = m0 + wm * WM, wcol0 = n0 + wn * WN;
-    // ROWDOT: a lane keeps one 8-column chunk (lane % CG) for all its rows -- its bias and projection values are
-    // loaded once -- and visits rows lane / CG, + 64 / CG, ... of the wave tile in order, across the passes
-    constexpr int RD_CG = WN / 8;
-    f32x4 rd_b0 = {0, 0, 0, 0}, rd_b1 = rd_b0, rd_w0 = rd_b0, rd_w1 = rd_b0;
-    EpilogueRows<PADDED> rd_rows(p, wrow0 + lane / RD_CG);
-    const int rd_c = wcol0 + (lane % RD_CG) * 8;
-    auto rd_columns = [&] {
-        if (rd_c >= p.N) return;
-        rd_b0 = *reinterpret_cast<const f32x4*>(p.bias + rd_c);
-        rd_b1 = *reinterpret_cast<const f32x4*>(p.bias + rd_c + 4);
-        rd_w0 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c);
-        rd_w1 = *reinterpret_cast<const f32x4*>(p.gamma + rd_c + 4);
+    const bool has_ln = EPI != EPI_RESID && EPI != EPI_PATCH && p.ln_stats;
+    // 4-column groups of a row are exchanged by the row: 16 consecutive rows writing one group, and the four 8-row blocks
+    // that a transposed value read takes at once, fall on different banks
+    auto at = [&](int row, int col) { return row * WN + (col ^ ((((row & 15) ^ ((row >> 3) << 2)) & 15) << 2)); };
+    auto stage = [&](auto I) {
+        constexpr int i = decltype(I)::value;
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(sC + at(li, j * 32 + 8 * q + 4 * g)) =
+                    f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
     };
-    if (BATCH > 1 && p.epi == EPI_ROWDOT) rd_columns();        // (one row at a time: no registers to keep them in)
+    auto chunk8 = [&](int row, int col, float* v) {
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + at(row, col)), hi = *reinterpret_cast<const f32x4*>(sC + at(row, col + 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
+    };
+    auto row_stats = [&](int row) { return *reinterpret_cast<const f32x2*>(lnrow + 2 * row); };     // (of a tile row)
     // The row-chunk paths: a lane keeps one 8-column chunk (64 is a multiple of the chunks per row) for all its rows
     // (96 x 128 wave tiles have registers for two rows at a time, and none for the columns while all blocks wait)
     constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < BATCH ? ITS : BATCH;
@@ -108,153 +115,123 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
     // One pass per 32-row block of the wave tile; the block index is a compile-time constant of each pass (a loop over the
     // blocks turns the accumulators into an indexed array in scratch, or spills them).
     // (rows without operands of their own go one by one: nothing to wait for, and the short loop keeps its code small)
-    const bool batched = (!CONV && (p.epi == EPI_RESID || p.epi == EPI_PATCH)) || (p.epi == EPI_STORE && p.add1);
-    auto pass = [&](auto I) {
-        constexpr int i = decltype(I)::value;
-        if (!CONV && p.ln_stats) {
-            // (column sums are loaded here, not before the k loop: this kernel has no registers to spare)
-            float lncs[NI];
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int c = wcol0 + j * 32 + li;
-                lncs[j] = c < p.N ? p.ln_colsum[c] : 0.0f;
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = wm * WM + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                const f32x2 st = *reinterpret_cast<const f32x2*>(lnrow + 2 * row);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j][v] = st[1] * (acc[i][j][v] - st[0] * lncs[j]);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sC[(8 * (v >> 2) + 4 * g + (v & 3)) * WN + j * 32 + li] = acc[i][j][v];
-        const int rblk = wrow0 + i * 32;
-        if (!CONV && p.epi == EPI_SWIGLU) {
+    const bool batched = EPI == EPI_RESID || EPI == EPI_PATCH || (EPI == EPI_STORE && p.add1);
+    auto pass = [&](int i) {
+        const int rblk = wrow0 + i * 32, tblk = wm * WM + i * 32;
+        if constexpr (EPI == EPI_SWIGLU) {
             // groups of 64 physical columns: 32 gate columns, then their 32 linear partners
             constexpr int GG = WN / 16;                  // 8-wide gate chunks per row
             T* out = reinterpret_cast<T*>(p.out);
             const int gg = lane % GG, grp = gg >> 2, j0 = (gg & 3) * 8, ca = wcol0 + grp * 64 + j0;
-            float ba[8], bb[8];
             if (ca + 40 <= p.N) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { ba[e] = p.bias[ca + e]; bb[e] = p.bias[ca + 32 + e]; }
-            }
+                const EpiCols ka = epilogue_cols<EPI>(p, ca), kb = epilogue_cols<EPI>(p, ca + 32);
 #pragma unroll 1
-            for (int rr = lane / GG; rr < 32; rr += 64 / GG) {
-                const int r = epilogue_row<PADDED>(p, rblk + rr);
-                if (r < p.M && ca + 40 <= p.N) {
-                    const float* src = sC + rr * WN + grp * 64 + j0;
-                    float h[8];
+                for (int rr = lane / GG; rr < 32; rr += 64 / GG) {
+                    const int r = epilogue_row<PADDED>(p, rblk + rr);
+                    float va[8], vb[8], h[8];
+                    chunk8(rr, grp * 64 + j0, va);
+                    chunk8(rr, grp * 64 + j0 + 32, vb);
+                    if (has_ln) {
+                        const f32x2 st = row_stats(tblk + rr);
+                        ln_apply(st, ka.g0, ka.g1, va);
+                        ln_apply(st, kb.g0, kb.g1, vb);
+                    }
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) h[e] = swiglu_for<T>(src[e] + ba[e], src[32 + e] + bb[e]);
-                    store8(out + (int64_t)r * p.ldo + (ca >> 6) * 32 + j0, h);
+                    for (int e = 0; e < 4; ++e) {
+                        h[e] = swiglu_for<T>(va[e] + ka.b0[e], vb[e] + kb.b0[e]);
+                        h[4 + e] = swiglu_for<T>(va[4 + e] + ka.b1[e], vb[4 + e] + kb.b1[e]);
+                    }
+                    if (r < p.M) store8(out + (int64_t)r * p.ldo + (ca >> 6) * 32 + j0, h);
                 }
             }
-        } else if (!CONV && p.epi == EPI_QKV && wcol0 >= 2 * p.dim) {
+        } else if (EPI == EPI_QKV && wcol0 >= 2 * p.dim) {
             // value columns, written transposed: one column and 8 consecutive tokens per lane.  All rows and columns of the QKV
             // epilogue are written out and the biases fetched first: it has no arithmetic to hide a round's LDS and
             // store latency behind (over 66 QKV shapes 256 x 256 and 384 x 256 tiles 6 % faster, 64 x 128 3 %)
             T* vt = reinterpret_cast<T*>(p.out2);
-            float bias[WN / 16];
+            float bias[WN / 16], cs[WN / 16];
 #pragma unroll
             for (int n = 0; n < WN / 16; ++n) {
                 const int c = wcol0 + (lane >> 2) + 16 * n;
                 bias[n] = c < p.N ? p.bias[c] : 0.0f;
+                cs[n] = has_ln && c < p.N ? p.ln_colsum[c] : 0.0f;
             }
             const int rr = (lane & 3) * 8, r = epilogue_row<PADDED>(p, rblk + rr);      // 4 lanes = 32 consecutive tokens of a column
+            f32x2 st[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) st[k] = has_ln ? row_stats(tblk + rr + k) : f32x2{0.0f, 1.0f};
 #pragma unroll
             for (int n = 0; n < WN / 16; ++n) {
                 const int cc = (lane >> 2) + 16 * n;
                 if (r < p.M && wcol0 + cc < p.N) {
                     float v[8];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = sC[(rr + k) * WN + cc] + bias[n];
+                    for (int k = 0; k < 8; ++k) v[k] = st[k][1] * (sC[at(rr + k, cc)] - st[k][0] * cs[n]) + bias[n];
                     store_tokens8<T>(p, vt, r, wcol0 + cc - 2 * p.dim, v);
                 }
             }
-        } else if (p.epi == EPI_ROWDOT) {
-            // 8 consecutive lanes hold the 8 chunks of one 64-column projection group of a row
-            if constexpr (WN % 64 == 0) {
-                float* out = reinterpret_cast<float*>(p.out);
-                if (BATCH == 1) rd_columns();
-#pragma unroll 2
-                for (int n = 0; n < 32 * CG / 64; ++n) {
-                    const int rr = lane / CG + n * (64 / CG);
-                    const int r = rd_rows.row(p);
-                    rd_rows.advance(64 / CG);
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
-                    float sum = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float a = lo[e] + rd_b0[e], b = hi[e] + rd_b1[e];
-                        if (p.act == ACT_RELU) { a = fmaxf(a, 0.0f); b = fmaxf(b, 0.0f); }
-                        sum += a * rd_w0[e] + b * rd_w1[e];
-                    }
-                    sum += __shfl_xor(sum, 1);
-                    sum += __shfl_xor(sum, 2);
-                    sum += __shfl_xor(sum, 4);
-                    if ((lane & 7) == 0 && r < p.M && rd_c < p.N) out[(int64_t)r * p.ldo + (rd_c >> 6)] = sum;
-                }
-            }
-        } else if (!CONV && p.epi == EPI_QKV) {
-            const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
+        } else if constexpr (EPI == EPI_QKV) {
+            const EpiCols cols = epilogue_cols<EPI>(p, wcol0 + (lane % CG) * 8);
 #pragma unroll
             for (int n = 0; n < ITS; ++n) {
                 const int rr = lane / CG + n * (64 / CG), r = epilogue_row<PADDED>(p, rblk + rr);
-                if (r < p.M && cols.nv > 0) {
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
-                    float v[8];
+                float v[8];
+                chunk8(rr, (lane % CG) * 8, v);
+                if (has_ln) ln_apply(row_stats(tblk + rr), cols.g0, cols.g1, v);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) { v[i] = lo[i] + cols.b0[i]; v[4 + i] = hi[i] + cols.b1[i]; }
-                    store8(reinterpret_cast<T*>(p.out) + (int64_t)r * p.ldo + cols.c, v);
-                }
+                for (int e = 0; e < 4; ++e) { v[e] += cols.b0[e]; v[4 + e] += cols.b1[e]; }
+                if (r < p.M && cols.nv > 0) store8(reinterpret_cast<T*>(p.out) + (int64_t)r * p.ldo + cols.c, v);
             }
         } else if (batched) {
-            const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
+            const EpiCols cols = epilogue_cols<EPI>(p, wcol0 + (lane % CG) * 8);
 #pragma unroll 1
             for (int b = 0; b < ITS; b += NB) {
                 EpiRow rows[NB];
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
                     const int r = epilogue_row<PADDED>(p, rblk + lane / CG + (b + n) * (64 / CG));
-                    rows[n] = epilogue_row_operands(p, cols, r, r < p.M && cols.nv > 0);
+                    rows[n] = epilogue_row_operands<EPI>(p, cols, r, r < p.M && cols.nv > 0);
                 }
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
                     const int rr = lane / CG + (b + n) * (64 / CG);
                     const bool active = epilogue_row<PADDED>(p, rblk + rr) < p.M && cols.nv > 0;
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
-                    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    if (active) epilogue_chunk<T>(p, cols, rows[n], v);
+                    float v[8];
+                    chunk8(rr, (lane % CG) * 8, v);
+                    if (has_ln) ln_apply(row_stats(tblk + rr), cols.g0, cols.g1, v);
+                    if (active) epilogue_chunk<T, EPI>(p, cols, rows[n], v);
                     if constexpr (WN % 64 == 0) {        // (8 consecutive lanes hold the 8 chunks of a 64-column statistics group)
-                        if (!CONV && (p.epi == EPI_RESID || p.epi == EPI_PATCH)) group_stats<T>(p, cols, rows[n], v, active, lane & 7);
+                        if (EPI == EPI_RESID || EPI == EPI_PATCH) group_stats<T>(p, cols, rows[n], v, active, lane & 7);
                     }
                 }
             }
         } else {
-            const EpiCols cols = epilogue_cols(p, wcol0 + (lane % CG) * 8);
+            const EpiCols cols = epilogue_cols<EPI>(p, wcol0 + (lane % CG) * 8);
 #pragma unroll 1
             for (int rr = lane / CG; rr < 32; rr += 64 / CG) {
                 const int r = epilogue_row<PADDED>(p, rblk + rr);
                 if (r < p.M && cols.nv > 0) {
-                    const f32x4 lo = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8);
-                    const f32x4 hi = *reinterpret_cast<const f32x4*>(sC + rr * WN + (lane % CG) * 8 + 4);
-                    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    epilogue_chunk<T>(p, cols, epilogue_row_operands(p, cols, r, true), v);
+                    float v[8];
+                    chunk8(rr, (lane % CG) * 8, v);
+                    if (has_ln) ln_apply(row_stats(tblk + rr), cols.g0, cols.g1, v);
+                    epilogue_chunk<T, EPI>(p, cols, epilogue_row_operands<EPI>(p, cols, r, true), v);
                 }
             }
         }
     };
-    pass(std::integral_constant<int, 0>{});
-    if constexpr (MI > 1) pass(std::integral_constant<int, 1>{});
-    if constexpr (MI > 2) pass(std::integral_constant<int, 2>{});
-    if constexpr (MI > 3) pass(std::integral_constant<int, 3>{});
+    if (has_ln) {
+        LnTile<BM> ln;
+        ln.ask(p, m0, tid);
+        stage(std::integral_constant<int, 0>{});
+        ln.leave(p, lnrow, m0, n0, tid);
+        __syncthreads();
+    } else {
+        stage(std::integral_constant<int, 0>{});
+    }
+    pass(0);
+    if constexpr (MI > 1) { stage(std::integral_constant<int, 1>{}); pass(1); }
+    if constexpr (MI > 2) { stage(std::integral_constant<int, 2>{}); pass(2); }
+    if constexpr (MI > 3) { stage(std::integral_constant<int, 3>{}); pass(3); }
     static_assert(MI <= 4, "passes are written out up to four row blocks");
 }
 
@@ -265,7 +242,7 @@ __device__ __forceinline__ float wave_halves_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Projection epilogue (EPI_ROWDOT) of a wave tile whose MFMAs took the W operand first: a lane's accumulators are
+// Projection epilogue (EPI_ROWDOT) of a wave tile: a lane's accumulators are
 // one tile row's columns (row = lane % 32 of a 32-row block, column 8 (v / 4) + 4 (lane / 32) + v % 4 of a 32-column
 // block), so out[r][c / 64] = sum over the 64 columns of act(acc + bias) * w is a sum inside the lane plus one
 // exchange between the lane halves, and the accumulators never go through LDS (staging a 384 x 256 tile there and
@@ -317,11 +294,11 @@ __device__ __forceinline__ void rowdot_epilogue_transposed(const GemmArgs& p, f3
 // BM x BN tiles, BK elements per k-tile (LDS rows of 64, 128 or 256 bytes), S LDS stages: the loads of tile kt + S - 1 are
 // in flight while tile kt is multiplied, so a load has S - 1 tile times to arrive.  WGM x WGN waves share a tile (BM / WGM
 // rows and BN / WGN columns each); OCC workgroups per CU (the launch bound is in waves per SIMD: OCC * waves / 4).
-// RD: the instantiation for EPI_ROWDOT alone (MFMAs with the W operand first, projection epilogue without LDS staging).
+// EPI: one instantiation per epilogue (with all of them behind run-time branches the kernels were two to four times as large).
 // KG: groups of WGM x WGN waves that share the tile's loads and take KS / KG of the k-steps of every k-tile each; their
 // partial sums are added in LDS in a fixed order by the block-level epilogue.
 // RING: the operand tiles of a k-tile are units of their own in a ring of five (A0 B0 A1 B1 A2 ...), see the main loop.
-template <typename T, int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int BM_ = 256, bool RD = false, int KG = 1, bool RING = false>
+template <typename T, int BN, int BK, int S, int WGM, int WGN, int OCC, int AMODE, int EPI, int BM_ = 256, int KG = 1, bool RING = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void gemm_dma_kernel(const GemmArgs args) {
     const GemmArgs p = select_problem(args);
     constexpr int BM = BM_, CE = Elem<T>::CE, ESZ = sizeof(T), NW = WGN * WGM * KG;
@@ -337,20 +314,20 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     constexpr int SW_SHIFT = ROWB == 256 ? 0 : ROWB == 128 ? 1 : 2, SW_MASK = CPR - 1;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = KG > 1 ? wave / (WGM * WGN) : 0;
     const int wm = (KG > 1 ? wave % (WGM * WGN) : wave) / WGN, wn = wave % WGN;
     const int g = lane >> 5, li = lane & 31;
 
     int tm, tn;
-    tile_coords(xcd_contiguous(blockIdx.x, gridDim.x), (p.M - p.m_begin + BM - 1) / BM, (p.N + BN - 1) / BN, tm, tn);
+    tile_coords(blockIdx.x, p.map, tm, tn);
     const int m0 = p.m_begin + tm * BM, n0 = tn * BN;
 
-    // folded LayerNorm: (mean, rstd) of this tile's rows live behind the stage / staging buffers (the ring leaves no room there:
-    // behind the staging blocks, written when the k loop is done)
+    // folded LayerNorm: (mean, rstd) of this tile's rows, written and read in the epilogue, live behind its staging blocks
     constexpr int EPI_BYTES = KG > 1 ? KG * BM * BN * 4 : WN % 64 ? BM * BN * 4 : NW * 32 * WN * 4;
-    float* lnrow = reinterpret_cast<float*>(smem + (!RING && S * STAGE > EPI_BYTES ? S * STAGE : EPI_BYTES));
-    int* redo_flags = reinterpret_cast<int*>(lnrow + 2 * BM);            // fp32: one per wave, behind them
+    float* lnrow = reinterpret_cast<float*>(smem + EPI_BYTES);
+    constexpr int OPERANDS = RING ? 5 * A_BYTES : S * STAGE;
+    int* redo_flags = reinterpret_cast<int*>(smem + (OPERANDS > EPI_BYTES + BM * 8 ? OPERANDS : EPI_BYTES + BM * 8));    // fp32: one per wave, behind both
 
     // --- loader state.  DMA instruction `slot` of this wave fills 1 KB of LDS = RPI consecutive rows of
     // the A (or B) tile, row group rg = wave + NW slot: lane l lands on row rg*RPI + l/CPR, physical
@@ -436,7 +413,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     // Wave tiles of up to 6 fragments per k-step keep two fragment sets (the reads of step ks + 1 are in
     // flight during the MFMAs of step ks); larger wave tiles have no registers for the second set and read
     // each step's fragments just before its MFMAs (two waves per SIMD cover for each other).
-    constexpr bool FRAG_DB = MI + NI <= 6;
+    constexpr bool FRAG_DB = ESZ == 2 && MI + NI <= 6;
     const int ks0 = kg * KS;                                        // first k-step of this wave's group
     // fp32: a lane's eight k elements of a step are two chunks of its row
     auto chunk = [&](const char* base, int ks, int sw, int half) {
@@ -459,156 +436,199 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
 #pragma unroll
                     for (int i = 0; i < MI; ++i)
 #pragma unroll
-                        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[i][e], rb[j][e], acc[i][j], 0, 0, 0);
+                        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(rb[j][e], ra[i][e], acc[i][j], 0, 0, 0);
             }
     };
-    auto compute = [&](const char* tile_a, const char* tile_b, auto&& between) {
+    // Fragments of k-step ks of a tile into set `set` (fp32: one set of raw values, split before the next read overwrites it).
+    bf16x8 fa[FRAG_DB ? 2 : 1][MI], fb[FRAG_DB ? 2 : 1][NI];
+    f32x4 ra[ESZ == 4 ? MI : 1][2], rb[ESZ == 4 ? NI : 1][2];
+    auto fetch = [&](const char* tile_a, const char* tile_b, int ks, int set) {
         const char* sA = tile_a + arow0 * ROWB;
         const char* sB = tile_b + brow0 * ROWB;
         if constexpr (ESZ == 4) {
-            f32x4 ra[MI][2], rb[NI][2];
-            auto read = [&](int ks) {
 #pragma unroll
-                for (int i = 0; i < MI; ++i) { ra[i][0] = chunk(sA + i * 32 * ROWB, ks, asw, 0); ra[i][1] = chunk(sA + i * 32 * ROWB, ks, asw, 1); }
+            for (int i = 0; i < MI; ++i) { ra[i][0] = chunk(sA + i * 32 * ROWB, ks, asw, 0); ra[i][1] = chunk(sA + i * 32 * ROWB, ks, asw, 1); }
 #pragma unroll
-                for (int j = 0; j < NI; ++j) { rb[j][0] = chunk(sB + j * 32 * ROWB, ks, bsw, 0); rb[j][1] = chunk(sB + j * 32 * ROWB, ks, bsw, 1); }
-            };
-            read(0);
+            for (int j = 0; j < NI; ++j) { rb[j][0] = chunk(sB + j * 32 * ROWB, ks, bsw, 0); rb[j][1] = chunk(sB + j * 32 * ROWB, ks, bsw, 1); }
+        } else {
+            const int ca = ((2 * (ks0 + ks) + g) ^ asw) * 16, cb = ((2 * (ks0 + ks) + g) ^ bsw) * 16;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                Split3 fa[MI], fb[NI];
+            for (int i = 0; i < MI; ++i) fa[set][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca);
 #pragma unroll
-                for (int i = 0; i < MI; ++i) fa[i] = split3(ra[i][0], ra[i][1]);
+            for (int j = 0; j < NI; ++j) fb[set][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + cb);
+        }
+    };
+    auto multiply = [&](int set) {
 #pragma unroll
-                for (int j = 0; j < NI; ++j) fb[j] = split3(rb[j][0], rb[j][1]);
-                if (ks + 1 < KS) read(ks + 1);
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+    };
+    // One k-tile.  The fragments of a step are read during the step before it, across the tile boundary too, so no step begins
+    // with an LDS latency.  The tile's one barrier stands in front of its LAST step: by then every wave has read
+    // all of the tile (its stage is free for the loads of a later one) and the next tile has landed, so the last step's MFMAs run
+    // beside the first reads of the next tile and the issue of the loads.  `turn` does that: waits, barrier, loads, and then the
+    // reads it is given.  PAR: the set of the first step.
+    constexpr bool SMALL = MI * NI <= 2;
+    auto k_tile = [&](const char* tile_a, const char* tile_b, const char* next_a, const char* next_b, auto PAR, auto&& between, auto&& turn) {
+        constexpr int par = decltype(PAR)::value;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int cur = (par + ks) & 1;
+            if constexpr (ESZ == 4) {
+                Split3 sa[MI], sb[NI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) sa[i] = split3(ra[i][0], ra[i][1]);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) sb[j] = split3(rb[j][0], rb[j][1]);
+                if (ks + 1 < KS) {
+                    fetch(tile_a, tile_b, ks + 1, 0);
+                } else {
+                    turn([&] { fetch(next_a, next_b, 0, 0); });
+                    __builtin_amdgcn_sched_barrier(0);
+                }
 #pragma unroll
                 for (int t = 0; t < 6; ++t)
 #pragma unroll
                     for (int i = 0; i < MI; ++i)
 #pragma unroll
-                        for (int j = 0; j < NI; ++j) acc[i][j] = split_mma(t, fa[i], fb[j], acc[i][j]);
-            }
-        } else if constexpr (FRAG_DB) {
-            bf16x8 fa[2][MI], fb[2][NI];
-            const int ca0 = ((2 * ks0 + g) ^ asw) * 16, cb0 = ((2 * ks0 + g) ^ bsw) * 16;
-#pragma unroll
-            for (int i = 0; i < MI; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca0);
-#pragma unroll
-            for (int j = 0; j < NI; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + cb0);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+                        for (int j = 0; j < NI; ++j) acc[i][j] = split_mma(t, sb[j], sa[i], acc[i][j]);
+            } else {
                 if (RING && ks == 1) between();
                 if (ks + 1 < KS) {
-                    const int ca = ((2 * (ks0 + ks + 1) + g) ^ asw) * 16, cb = ((2 * (ks0 + ks + 1) + g) ^ bsw) * 16;
-#pragma unroll
-                    for (int i = 0; i < MI; ++i) fa[(ks + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca);
-#pragma unroll
-                    for (int j = 0; j < NI; ++j) fb[(ks + 1) & 1][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + cb);
-                }
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-                        acc[i][j] = RD ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks & 1][j], fa[ks & 1][i], acc[i][j], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks & 1][i], fb[ks & 1][j], acc[i][j], 0, 0, 0);
-                // Issue order for the scheduler: the LDS reads of step ks + 1 are spread between the MFMAs
-                // of step ks (one read per two MFMAs), so the only wave on this SIMD never waits on LDS
-                // with an empty matrix pipe.  0x100 = DS read, 0x008 = MFMA.
-                if (ks == 0) __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
-                if (ks + 1 < KS) {
-                    constexpr int PER = (MI * NI) / (MI + NI) > 0 ? (MI * NI) / (MI + NI) : 1;
-                    constexpr int GROUPS = (MI * NI) / PER < MI + NI ? (MI * NI) / PER : MI + NI;
-#pragma unroll
-                    for (int n = 0; n < GROUPS; ++n) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x100, MI + NI - GROUPS, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - GROUPS * PER, 0);
+                    fetch(tile_a, tile_b, ks + 1, cur ^ 1);
                 } else {
-                    __builtin_amdgcn_sched_group_barrier(0x008, MI * NI, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    turn([&] { fetch(next_a, next_b, 0, cur ^ 1); });
+                    if (SMALL) __builtin_amdgcn_sched_barrier(0);
                 }
+                multiply(cur);
+                if (SMALL && ks + 1 == KS) { __builtin_amdgcn_sched_barrier(0); continue; }
+                // Issue order for the scheduler: the reads of the next step are spread between the MFMAs of this one (one read
+                // per PER MFMAs), so a wave never waits on LDS with an empty matrix pipe.  0x100 = DS read, 0x008 = MFMA.
+                constexpr int PER = (MI * NI) / (MI + NI) > 0 ? (MI * NI) / (MI + NI) : 1;
+                constexpr int GROUPS = (MI * NI) / PER < MI + NI ? (MI * NI) / PER : MI + NI;
+#pragma unroll
+                for (int n = 0; n < GROUPS; ++n) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x100, MI + NI - GROUPS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - GROUPS * PER, 0);
             }
-        } else {
+        }
+    };
+    // The same without a second fragment set: every step's fragments are read just before its MFMAs.
+    auto k_tile_single = [&](const char* tile_a, const char* tile_b) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int ca = ((2 * (ks0 + ks) + g) ^ asw) * 16, cb = ((2 * (ks0 + ks) + g) ^ bsw) * 16;
-                bf16x8 fa[MI], fb[NI];
-#pragma unroll
-                for (int i = 0; i < MI; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * ROWB + ca);
-#pragma unroll
-                for (int j = 0; j < NI; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * ROWB + cb);
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-                        acc[i][j] = RD ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, MI * NI, 0);
-            }
+        for (int ks = 0; ks < KS; ++ks) {
+            fetch(tile_a, tile_b, ks, 0);
+            multiply(0);
+            __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, MI * NI, 0);
         }
     };
 
     constexpr bool BLOCK = WN % 64 != 0 || KG > 1;            // small tiles: a wave does not hold whole 64-column groups, or only partial sums
-    float lncs[NI];                                           // their column sums; the others fetch them pass by pass
-    if constexpr (BLOCK) {
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int c = n0 + wn * WN + j * 32 + li;
-            lncs[j] = p.ln_stats && c < p.N ? p.ln_colsum[c] : 0.0f;
-        }
-    }
 
-    // --- main loop: S LDS stages.  Iteration kt: wait until tile kt has landed (the S - 2 younger
-    // tiles may still be in flight), barrier (which also tells everyone that the stage read in
-    // iteration kt - 1 is free), issue the loads of tile kt + S - 1 into that free stage, multiply
-    // tile kt.  Prefetches are unconditional (clamped index): every path has the same loads in flight.
+    // --- main loop over the k-tiles
     const int KT = p.K / BK;
-    auto last = [&](int kt) { return kt < KT ? kt : KT - 1; };
-    float mean = 0.0f, rstd = 0.0f;
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, KS & 1> odd{};                  // (an even number of steps: every tile begins on the same set)
+    auto none = [] {};
     if constexpr (RING) {
         // Two whole stages of a 256 x 256 tile leave 32 KB of the LDS unused and give a load one tile time to arrive (about
-        // 2100 clocks, as long as the loads of a tile take by themselves).  Five units of 32 KB instead: during tile kt the A
-        // operand of tile kt + 1 is already on its way when B's is issued, then A's of tile kt + 2 between the MFMAs.
+        // 2100 clocks, as long as the loads of a tile take by themselves).  Five units of 32 KB instead, A and B of a tile one each:
+        // during tile kt A of tile kt + 2 is issued between the MFMAs, B of kt + 2 behind the tile's barrier.
         char* unit[5] = {smem, smem + A_BYTES, smem + 2 * A_BYTES, smem + 3 * A_BYTES, smem + 4 * A_BYTES};
         dma_a(unit[0], 0);
         dma_b(unit[1], 0);
         __builtin_amdgcn_sched_barrier(0);                    // (the counted waits go by the order of issue)
-        dma_a(unit[2], last(1));
+        dma_a(unit[2], KT > 1 ? 1 : 0);
+        dma_b(unit[3], KT > 1 ? 1 : 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (p.ln_stats && tid < BM) ln_tile_row(p, m0, n0, tid, mean, rstd);
-        for (int kt = 0; kt < KT; ++kt) {
-            pipeline_barrier<A_SLOTS>();                      // A and B of tile kt are here; A of kt + 1 may be on its way
-            dma_b(unit[3], last(kt + 1));
-            __builtin_amdgcn_sched_barrier(0);
-            compute(unit[0], unit[1], [&] {
-                __builtin_amdgcn_sched_barrier(0);
-                dma_a(unit[4], last(kt + 2));
-                __builtin_amdgcn_sched_barrier(0);
-            });
+        pipeline_barrier<A_SLOTS + B_SLOTS>();
+        fetch(unit[0], unit[1], 0, 0);
+        auto tile = [&](int kt, auto PAR) {
+            k_tile(unit[0], unit[1], unit[2], unit[3], PAR,
+                   [&] { __builtin_amdgcn_sched_barrier(0); if (kt + 2 < KT) dma_a(unit[4], kt + 2); __builtin_amdgcn_sched_barrier(0); },
+                   [&](auto&& reads) {
+                       if (kt + 2 < KT) {
+                           pipeline_barrier<A_SLOTS>();
+                           dma_b(unit[0], kt + 2);
+                       } else {
+                           pipeline_barrier<0>();
+                       }
+                       __builtin_amdgcn_sched_barrier(0);
+                       reads();
+                   });
             char* const u0 = unit[0];
             char* const u1 = unit[1];
             unit[0] = unit[2]; unit[1] = unit[3]; unit[2] = unit[4]; unit[3] = u0; unit[4] = u1;
+        };
+        static_assert(KS >= 2 && KS % 2 == 0, "A is issued in the second step, tiles begin on set 0");
+        for (int kt = 0; kt < KT; ++kt) tile(kt, even);
+    } else if constexpr (FRAG_DB || ESZ == 4) {
+        // S stages: the tile's barrier waits for tile kt + 1 (kt + 2 ... kt + S - 1 may be on their way), the loads of tile kt + S go
+        // into the stage that tile kt leaves.
+        constexpr int L = A_SLOTS + B_SLOTS;
+#pragma unroll
+        for (int s = 0; s < PD; ++s) {
+            dma(s, s < KT ? s : KT - 1);                      // (unconditional, so that the wait for older loads can be counted)
+            __builtin_amdgcn_sched_barrier(0);                // (the counted waits go by the order of issue)
+        }
+        pipeline_barrier<(PD - 1) * L>();
+        fetch(smem, smem + A_BYTES, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (PD < KT) dma(PD, PD);                             // (the last stage is filled behind the first reads)
+        __builtin_amdgcn_sched_barrier(0);
+        int cur = 0;                                          // stage of tile kt
+        auto tile = [&](auto PAR, auto&& turn) {
+            const int nxt = cur + 1 == S ? 0 : cur + 1;
+            const char* a = smem + cur * STAGE;
+            const char* n = smem + nxt * STAGE;
+            k_tile(a, a + A_BYTES, n, n + A_BYTES, PAR, none, turn);
+            cur = nxt;
+        };
+        auto full = [&](int kt, auto PAR) {                   // a tile with all loads in flight
+            tile(PAR, [&](auto&& reads) {
+                pipeline_barrier<(S - 2) * L>();
+                dma(cur, kt + S);
+                __builtin_amdgcn_sched_barrier(0);
+                reads();
+            });
+        };
+        auto tail = [&](int kt, auto PAR) {                   // one of the last S or S + 1
+            tile(PAR, [&](auto&& reads) {
+                if (kt + 1 == KT) return;
+                if (kt + S <= KT) pipeline_barrier<(S - 2) * L>();
+                else pipeline_barrier<0>();
+                if (kt + S < KT) dma(cur, kt + S);
+                __builtin_amdgcn_sched_barrier(0);
+                reads();
+            });
+        };
+        int kt = 0;
+        for (; kt + 1 + S < KT; kt += 2) { full(kt, even); full(kt + 1, odd); }
+        for (; kt < KT; kt += 2) {
+            tail(kt, even);
+            if (kt + 1 < KT) tail(kt + 1, odd);
         }
     } else {
+        // Tile kt + S - 1 is issued when tile kt has landed and everyone is done with the stage of tile kt - 1.
+        auto last = [&](int kt) { return kt < KT ? kt : KT - 1; };     // (prefetches are unconditional: every path has the same loads in flight)
 #pragma unroll
         for (int s = 0; s < PD; ++s) {
             dma(s, last(s));
-            __builtin_amdgcn_sched_barrier(0);                // (the counted waits go by the order of issue)
-        }
-        // behind the first tile loads, ordered before the epilogue by the loop's barriers
-        if (p.ln_stats && tid < BM) {
-            ln_tile_row(p, m0, n0, tid, mean, rstd);
-            *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
+            __builtin_amdgcn_sched_barrier(0);
         }
         int cur = 0, nxt = PD;                                // stages of tiles kt and kt + PD
         for (int kt = 0; kt < KT; ++kt) {
             pipeline_barrier<(PD - 1) * (A_SLOTS + B_SLOTS)>();
             dma(nxt, last(kt + PD));
             __builtin_amdgcn_sched_barrier(0);
-            compute(smem + cur * STAGE, smem + cur * STAGE + A_BYTES, [] {});
+            k_tile_single(smem + cur * STAGE, smem + cur * STAGE + A_BYTES);
             cur = cur + 1 == S ? 0 : cur + 1;
             nxt = nxt + 1 == S ? 0 : nxt + 1;
         }
@@ -625,7 +645,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         const int any = __any(all != all);
         if (lane == 0) redo_flags[wave] = any;
     }
-    pipeline_barrier<0>();                                    // drain the clamped tail prefetches before LDS is reused
+    pipeline_barrier<0>();                                    // everyone is done with the operands: LDS is reused
     if constexpr (ESZ == 4) {
         // The split holds neither infinities nor finite values above 3.396e38 (they round to infinity in bf16): their rests, and
         // with them every sum that they enter, are NaN.  A tile with such a sum is computed again on the fp32
@@ -649,45 +669,43 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
             }
         }
     }
-    if (RING && p.ln_stats) {
-        if (tid < BM) *reinterpret_cast<f32x2*>(lnrow + 2 * tid) = f32x2{mean, rstd};
-        __syncthreads();
-    }
-
     if constexpr (BLOCK) {                                    // (whole tile staged in LDS)
-        static_assert(KG > 1 || BM * BN * 4 <= S * STAGE, "accumulator tile must fit the stage buffers");
-        block_epilogue<T, BM, BN, WGM, WGN, KG>(p, acc, smem, lnrow, lncs, m0, n0);
-        return;
+        block_epilogue<T, EPI, BM, BN, WGM, WGN, KG>(p, acc, smem, lnrow, m0, n0);
+    } else if constexpr (EPI == EPI_ROWDOT) {
+        rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
+    } else {
+        wave_tile_epilogue<T, EPI, BM, MI, NI, WM, WN, false, (OCC * NW > 8 ? 1 : 4)>(p, acc, smem, lnrow, wave, wm, wn, tid, m0, n0);
     }
-
-    if constexpr (RD) rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
-    else wave_tile_epilogue<T, MI, NI, WM, WN, AMODE == A_CONV3, false, (OCC * NW > 8 ? 1 : 4)>(p, acc, smem, lnrow, wave, wm, wn, lane, m0, n0);
 }
 
-template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, bool RD = false, int KG = 1, bool RING = false>
+template <typename T, int BN, int BK, int S, int WGM = 2, int WGN = 2, int OCC = 1, int BM = 256, int KG = 1, bool RING = false>
 static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     constexpr int nt = 64 * WGM * WGN * KG;
     constexpr int stage_b = (RING ? 5 * BM : S * (BM + BN)) * BK * (int)sizeof(T);
-    constexpr int epi_b = KG > 1 ? KG * BM * BN * 4 : BN / WGN % 64 ? BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4;
-    constexpr int ln_b = BM * 8 + (sizeof(T) == 4 ? 64 : 0);              // (mean, rstd) of the tile's rows; fp32: a flag per wave
-    constexpr int lds = RING ? (stage_b > epi_b + ln_b ? stage_b : epi_b + ln_b) : (stage_b > epi_b ? stage_b : epi_b) + ln_b;
+    constexpr int epi_b = (KG > 1 ? KG * BM * BN * 4 : BN / WGN % 64 ? BM * BN * 4 : WGM * WGN * 32 * (BN / WGN) * 4) + BM * 8;   // and (mean, rstd) of the rows
+    constexpr int lds = (stage_b > epi_b ? stage_b : epi_b) + (sizeof(T) == 4 ? 64 : 0);        // fp32: a flag per wave
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
-    auto plain = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_PLAIN, BM, false, KG, RING>;
-    auto conv = &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, A_CONV3, BM, RD, KG, RING>;
+    typedef void (*Kernel)(const GemmArgs);
+#define VPE_KERNEL(mode, epi) &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, mode, epi, BM, KG, RING>
+    static const Kernel plain[] = {VPE_KERNEL(A_PLAIN, EPI_STORE), VPE_KERNEL(A_PLAIN, EPI_RESID), VPE_KERNEL(A_PLAIN, EPI_SWIGLU),
+                                   VPE_KERNEL(A_PLAIN, EPI_QKV), VPE_KERNEL(A_PLAIN, EPI_PATCH)};
+    static const Kernel conv[] = {VPE_KERNEL(A_CONV3, EPI_STORE), VPE_KERNEL(A_CONV3, EPI_ROWDOT)};
+#undef VPE_KERNEL
     static bool configured = false;
     if (!configured) {
+        auto opt_in = [&](Kernel k) { return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
         hipError_t rc = hipSuccess;
-        if (!RD) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(plain), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (rc == hipSuccess) rc = hipFuncSetAttribute(reinterpret_cast<const void*>(conv), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        for (Kernel k : plain) if (rc == hipSuccess) rc = opt_in(k);
+        for (Kernel k : conv) if (rc == hipSuccess) rc = opt_in(k);
         if (rc != hipSuccess) return rc;
         configured = true;
     }
     if (configure_only) return hipSuccess;
-    // the projection-only instantiation exists for convolutions (the only users of that epilogue on these tiles)
-    if (RD && (amode != A_CONV3 || a.epi != EPI_ROWDOT || a.ln_stats)) return hipErrorInvalidValue;
-    const int tiles = cdiv(a.M - a.m_begin, BM) * cdiv(a.N, BN), nz = a.nz > 1 ? a.nz : 1;
-    if (!RD && amode == A_PLAIN) hipLaunchKernelGGL(plain, dim3(tiles, nz), dim3(nt), lds, s, a);
-    else hipLaunchKernelGGL(conv, dim3(tiles, nz), dim3(nt), lds, s, a);
+    if (amode == A_CONV3 ? a.epi != EPI_STORE && a.epi != EPI_ROWDOT : a.epi < EPI_STORE || a.epi > EPI_PATCH) return hipErrorInvalidValue;
+    const Kernel k = amode == A_CONV3 ? conv[a.epi == EPI_ROWDOT] : plain[a.epi];
+    GemmArgs args = a;
+    args.map = TileMap::make(cdiv(a.M - a.m_begin, BM), cdiv(a.N, BN));
+    hipLaunchKernelGGL(k, dim3(args.map.tiles, a.nz > 1 ? a.nz : 1), dim3(nt), lds, s, args);
     return hipGetLastError();
 }
 

@@ -26,15 +26,14 @@ namespace vpe {
 // The one-per-CU shapes run in lockstep rounds, so they pay for a partly filled last round in full; which
 // shape wins depends on how the tile count divides by the 256 CUs (see launch_gemm_bf16).
 hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStream_t s) {
-    const bool rd = amode == A_CONV3 && a.epi == EPI_ROWDOT && !a.ln_stats;   // projection epilogue from transposed accumulators
     switch (kind) {
-        case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, false, 4>(a, amode, s);
-        case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, amode, s);
+        case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, amode, s);
+        case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, amode, s);
         case 64: return launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, amode, s);
         case 65: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, amode, s);
         case 129: return launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, amode, s);
-        case 384: return rd ? launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s);
-        case 256: return rd ? launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, amode, s) : launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, amode, s);
+        case 384: return launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s);
+        case 256: return launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, 1, true>(a, amode, s);
         default: return launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, amode, s);
     }
 }
@@ -76,12 +75,10 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, true>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, false>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384, true>(a, A_CONV3, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, true, 1, true>(a, A_CONV3, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, false, 1, true>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, 1, true>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, false, 4>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, false, 2>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, A_PLAIN, nullptr, true);
+    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
     if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
     return rc != hipSuccess ? rc : launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, A_PLAIN, nullptr, true);

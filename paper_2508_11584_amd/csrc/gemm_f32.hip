@@ -28,9 +28,9 @@ constexpr Cand kCands[] = {{64, 64, 2, 5.25f, 6.325f}, {64, 128, 1, 6.75f, 2.649
 
 hipError_t launch_f32(int kind, const GemmArgs& a, int amode, hipStream_t s, bool configure_only = false) {
     switch (kind) {
-        case 0: return launch_gemm_dma<float, 64, 64, 2, 1, 2, 2, 64, false, 4>(a, amode, s, configure_only);
-        case 1: return launch_gemm_dma<float, 128, 64, 2, 1, 2, 1, 64, false, 4>(a, amode, s, configure_only);
-        case 2: return launch_gemm_dma<float, 128, 32, 3, 1, 2, 2, 64, false, 2>(a, amode, s, configure_only);
+        case 0: return launch_gemm_dma<float, 64, 64, 2, 1, 2, 2, 64, 4>(a, amode, s, configure_only);
+        case 1: return launch_gemm_dma<float, 128, 64, 2, 1, 2, 1, 64, 4>(a, amode, s, configure_only);
+        case 2: return launch_gemm_dma<float, 128, 32, 3, 1, 2, 2, 64, 2>(a, amode, s, configure_only);
         default: return launch_gemm_dma<float, 128, 32, 2, 2, 2, 2, 128>(a, amode, s, configure_only);
     }
 }
