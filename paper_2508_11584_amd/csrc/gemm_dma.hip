@@ -1,40 +1,44 @@
-// Instantiations of the large-tile direct-to-LDS GEMM.
+// Instantiations of the bf16 direct-to-LDS GEMM and of the strip convolution.
 #include <cstdlib>
 
 #include "conv_strip.h"
 #include "gemm_dma.h"
 #include "kernels.h"
 namespace vpe {
-// Tilings, all with 64-deep k-tiles (128-byte rows: a k-tile of 64-byte rows loads at half the rate, 20 against 43 bytes
-// per clock and CU in a load-only probe) but for 384, whose two 64-deep stages would not fit the LDS, and 129:
-//   384: 384 x 256, 32-deep k-tiles, 8 waves (96 x 128 wave tiles), one workgroup per CU
+// Tilings, with 64-deep k-tiles (128-byte rows: a k-tile of 64-byte rows loads at half the rate, 20 against 43 bytes
+// per clock and CU in a load-only probe) except where said:
+//   384: 384 x 256, 32-deep k-tiles (two 64-deep stages would not fit the LDS), 8 waves (96 x 128 wave tiles), one workgroup per CU
 //   256: 256 x 256, 8 waves (64 x 128), operand tiles in a ring of five units, one workgroup per CU
-//   128: 256 x 128, 8 waves (64 x 64), three stages, one workgroup per CU
-//   129: the same with 32-deep k-tiles, two workgroups per CU: a large convolution of 128 channels has no wider tile to fall back on,
-//        and products of many rows with short k loops are mostly epilogue, which has the other workgroup's k loop beside it (us, best
-//        of the others / 129: 128 -> 128 on 320x320 57.8 / 50.6, on 480x520 118.7 / 100.2; ViT-S 25000 tokens fc1 78 / 71,
-//        33000 QKV 61 / 54, out-projection 37 / 34.5)
-//    65:  64 x 128, 4 waves (32 x 64),  two stages, two workgroups per CU;  64: 64 x 64, 4 waves (32 x 32), two stages
+//    20: 128 x 128, 4 waves (64 x 64), ring, two workgroups per CU;  2: the same with 8 waves (32 x 64).  One workgroup's epilogue has
+//        the other's k loop beside it; fewer operand bytes through LDS per product than any 64-row tile.  8 waves have the shorter
+//        epilogue, 4 read fewer operands (us, best of the others / 2 / 20): ViT-S 4110 tokens fc1 15.4 / 14.5 / 15.9, ViT-L 2748 fc1
+//        38.1 / 34.5 / 36.8, ViT-L 5496 fc2 63.1 / 67.6 / 61.7, ViT-g 4110 fc2 67.4 / 71.4 / 63.9.  (They also took the place of 256 x 128 tiles.)
+//    65:  64 x 128, 4 waves (32 x 64), two stages, three workgroups per CU;  64: 64 x 64, 4 waves (32 x 32), two stages
 //     5:  64 x 128, 8 waves in two groups that halve the k-steps of every k-tile (32 x 64 wave tiles), three stages
-//     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages
-// 4 and 5 are for problems with few tiles per CU, where a workgroup's own loop is the time: what it waits for is the LDS
-// (operand reads + landing loads) and the loads in flight.  Two groups at 64 x 64 read 32 KB of fragments per 16 KB k-tile, four
-// groups of twice as wide wave tiles 24 KB.  Against the register-staged two-group kernel that served these problems (us, its
-// old / new): ViT-S 1531 tokens fc2 12.2 / 8.4, out-projection 6.8 / 5.6; 257 tokens QKV 6.1 / 5.6, fc2 11.3 / 7.5; 3x3 convolutions
-// 34 x 45 256 -> 256 17.3 / 15.3, towers 24.3 / 21.2.  5 against the register-staged 64 x 128 tiles: ViT-B 1370 tokens fc2
-// 30.4 / 20.8, ViT-L 1374 tokens fc2 38.2 / 27.1; against 64: 68 x 90 convolution 23.7 / 20.4.
+//     6:  64 x 128, 8 waves in four groups (64 x 64 wave tiles), four stages, one workgroup per CU: long k loops on up to 256 tiles
+//     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages;  43: the same with 128-deep k-tiles, three stages, one
+//        workgroup per CU: half the barriers
+//     3:  32 x 64, 4 waves in four groups (32 x 64 wave tiles), four stages, three per CU;  33: 128-deep k-tiles, three stages, two per CU
+// 3 to 6 are for problems with few tiles per CU, where a workgroup's own loop is the time: fixed cost (3.1 us of alpha for the
+// 32-row tiles, 3.7 for 64 x 64, 5.5 for 64 x 128) and the rate at which one CU loads (40-56 bytes a clock).  us, 64 x 64 in four
+// groups (4) / 32 x 64 (33): ViT-S 257 tokens QKV 5.2 / 4.9, out-projection 4.6 / 3.8, fc1 5.3 / 4.8, fc2 7.4 / 6.0; 3x3 convolution of
+// 256 channels on 34 x 45 12.4 / 9.1; ViT-S detection towers there 17.4, with 43 14.9; ViT-L 1370 tokens fc2 22.6 with 5, 21.1 with 6.
 // The one-per-CU shapes run in lockstep rounds, so they pay for a partly filled last round in full; which
 // shape wins depends on how the tile count divides by the 256 CUs (see launch_gemm_bf16).
-hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStream_t s) {
+hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStream_t s, bool configure_only) {
     switch (kind) {
-        case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, amode, s);
-        case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, amode, s);
-        case 64: return launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, amode, s);
-        case 65: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, amode, s);
-        case 129: return launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, amode, s);
-        case 384: return launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s);
-        case 256: return launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, 1, true>(a, amode, s);
-        default: return launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, amode, s);
+        case 384: return launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, amode, s, configure_only);
+        case 256: return launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, 1, true>(a, amode, s, configure_only);
+        case 20: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 128, 1, true>(a, amode, s, configure_only);
+        case 65: return launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 3, 64>(a, amode, s, configure_only);
+        case 64: return launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 4, 64>(a, amode, s, configure_only);
+        case 6: return launch_gemm_dma<bf16, 128, 64, 4, 1, 2, 1, 64, 4>(a, amode, s, configure_only);
+        case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, amode, s, configure_only);
+        case 43: return launch_gemm_dma<bf16, 64, 128, 3, 1, 2, 1, 64, 4>(a, amode, s, configure_only);
+        case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, amode, s, configure_only);
+        case 33: return launch_gemm_dma<bf16, 64, 128, 3, 1, 1, 2, 32, 4>(a, amode, s, configure_only);
+        case 3: return launch_gemm_dma<bf16, 64, 64, 4, 1, 1, 2, 32, 4>(a, amode, s, configure_only);
+        default: return launch_gemm_dma<bf16, 128, 64, 2, 4, 2, 2, 128, 1, true>(a, amode, s, configure_only);
     }
 }
 // 3x3 convolution from an input strip in LDS (conv_strip.h), 96 x 128 wave tiles: 768 x 128 tiles (eight waves on top
@@ -74,13 +78,8 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_conv_strip<384, 256, 4, 2, 1, false>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, true>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, false>(a, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 32, 2, 4, 2, 1, 384>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 256, 64, 2, 4, 2, 1, 256, 1, true>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 32, 3, 4, 2, 2>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 64, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
-    if (rc == hipSuccess) rc = launch_gemm_dma<bf16, 128, 64, 2, 2, 2, 2, 64>(a, A_PLAIN, nullptr, true);
-    return rc != hipSuccess ? rc : launch_gemm_dma<bf16, 128, 64, 3, 4, 2, 1>(a, A_PLAIN, nullptr, true);
+    for (int kind : {384, 256, 20, 2, 65, 64, 6, 5, 43, 4, 33, 3})
+        if (rc == hipSuccess) rc = launch_gemm_dma_bf16(kind, a, A_PLAIN, nullptr, true);
+    return rc;
 }
 }  // namespace vpe

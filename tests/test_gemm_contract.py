@@ -47,3 +47,37 @@ def test_gemm_launcher_refuses_what_its_kernels_do_not_have(tmp_path):
     # no device: the refusal must come from the arguments alone, with a device as without one
     r = subprocess.run([str(exe)], capture_output=True, text=True, env={**os.environ, "HIP_VISIBLE_DEVICES": ""})
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+MAP_PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace vpe;
+int main() {
+    // every tile of a launch exactly once: the map's divisions by reciprocals, as the kernel does them, against divisions
+    int bad = 0;
+    for (int tiles_m : {1, 2, 5, 7, 8, 9, 15, 16, 17, 43, 250, 1023, 5000})
+        for (int tiles_n : {1, 2, 3, 6, 18, 64, 129}) {
+            const TileMap t = TileMap::make(tiles_m, tiles_n);
+            auto quotient = [](uint32_t x, uint32_t d, uint32_t inv) { return inv ? (uint32_t)(((uint64_t)x * inv) >> 32) : x / d; };
+            for (int lin = 0; lin < t.tiles; ++lin) {
+                const int group = quotient(lin, t.per_group, t.inv_group), rem = lin - group * t.per_group, rows = tiles_m - group * TileMap::GM;
+                if (group != lin / t.per_group) ++bad;
+                if (rows > 1 && rows < TileMap::GM && (int)quotient(rem, rows, t.inv_last) != rem / rows) ++bad;
+            }
+        }
+    if (TileMap::make(1 << 20, 1 << 10).inv_group) ++bad;      // (products past 32 bits: the kernel divides)
+    printf("%d\n", bad);
+    return bad != 0;
+}
+"""
+
+
+def test_tile_map_reciprocals_are_exact(tmp_path):
+    vpe.load_library()
+    src, exe = tmp_path / "map.cpp", tmp_path / "map"
+    src.write_text(MAP_PROGRAM)
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-w", "-I" + os.path.join(PKG, "csrc"), str(src),
+                    "-x", "none", os.path.join(PKG, "libvpe.so"), "-Wl,-rpath," + PKG, "-o", str(exe)], check=True, capture_output=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, env={**os.environ, "HIP_VISIBLE_DEVICES": ""})
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -227,6 +227,30 @@ def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
                            img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 141, 241)
 
 
+@pytest.mark.parametrize("tile", ["20", "2", "6", "43", "33", "3"])
+def test_gemm_tilings_for_few_and_for_many_tiles_per_cu(tile, monkeypatch):
+    # 128 x 128 tiles with four and eight waves ("20", "2"), 64 x 128 in four wave groups ("6"), 64 x 64 and 32 x 64 with 128-deep
+    # k-tiles ("43", "33") and 32 x 64 ("3"), forced for every GEMM of the models of the two tests above: every epilogue, whole and
+    # ragged tiles, 8-row groups that straddle two views, one to nine k-tiles (widths of an odd multiple of 64: the 128-deep ones hand
+    # over to "4" and "3").  The gates are those of every bf16 model
+    monkeypatch.setenv("VPE_GEMM_TILE", tile)
+    check_all(vi.ModelSpec("medium_bf16_tile" + tile, dtype="bf16", **MEDIUM), 102, 202)
+    spec = vi.ModelSpec("swiglu_tile" + tile, dtype="bf16", **{**MEDIUM, "mlp_kind": vi.MLP_SWIGLU, "registers": 4,
+                                                                "batch": 3, "img_h": 70, "img_w": 98})
+    check_all(spec, 103, 203)
+    check_all(vi.ModelSpec("short_k_tile" + tile, dtype="bf16", dim=64, depth=4, heads=1, mlp_hidden=192, registers=2, batch=2,
+                           img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 141, 241)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("width", [320, 1600])
+def test_layernorm_statistics_of_odd_and_of_many_groups(width, dtype):
+    # 5 and 25 groups of 64 columns: an odd last group, and more than the 24 that are fetched in one batch; the gates are
+    # those of every model of the type
+    check_all(vi.ModelSpec("groups_%s_%d" % (dtype, width), dtype=dtype, dim=width, depth=4, heads=width // 64, mlp_hidden=320, registers=1,
+                           img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 148, 248, kinds=("seg",))
+
+
 @pytest.mark.parametrize("variant", ["114", "122", "141"])
 def test_fp32_attention_shapes(variant, monkeypatch):
     # every workgroup shape of the fp32 attention: 38 tokens a view (one ragged key tile, fewer than the key waves), and 166
@@ -260,6 +284,20 @@ def test_fp32_gemm_tilings(tile, monkeypatch):
     for width in (64, 192):
         check_all(vi.ModelSpec("short_f32_tile%s_%d" % (tile, width), dtype="f32", **{**MEDIUM, **small, "dim": width, "heads": width // 64,
                                                                                       "mlp_hidden": 192}), 147, 247)
+
+
+@pytest.mark.parametrize("tile", ["4", "5"])
+def test_fp32_tilings_of_32_rows(tile, monkeypatch):
+    # 32 x 64 tiles in four wave groups, three stages and two, as above: every epilogue, one and three k-tiles, ragged edges, and the
+    # second computation of tiles with values that bf16 terms cannot hold (an infinite weight in one row); fp32 gates (1e-4)
+    monkeypatch.setenv("VPE_GEMM_TILE_F32", tile)
+    small = {"registers": 2, "batch": 2, "img_h": 70, "img_w": 98}
+    check_all(vi.ModelSpec("medium_f32_tile" + tile, dtype="f32", **MEDIUM), 145, 245)
+    check_all(vi.ModelSpec("swiglu_f32_tile" + tile, dtype="f32", **{**MEDIUM, **small, "mlp_kind": vi.MLP_SWIGLU}), 146, 246, kinds=("seg", "dpt"))
+    for width in (64, 192):
+        check_all(vi.ModelSpec("short_f32_tile%s_%d" % (tile, width), dtype="f32", **{**MEDIUM, **small, "dim": width, "heads": width // 64,
+                                                                                      "mlp_hidden": 192}), 147, 247)
+    test_fp32_head_weights_beyond_the_range_of_bf16(tile, monkeypatch)
 
 
 @pytest.mark.parametrize("shape", ["1", "2"])
