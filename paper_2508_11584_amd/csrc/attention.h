@@ -90,17 +90,21 @@ template <> struct AttnMma<bf16> {
     // v = 8 s + kk of score block kb sits, so P needs no shuffle, and a lane's eight keys are one 16-byte chunk of
     // a V^T row (one conflict-free ds_read_b128 per accumulator and step).  The reads of step + 1 are issued before
     // the MFMAs of step.
-    // Row sums on the matrix pipe (LM): ones[32 x 16] P^T adds the 16 keys of a k-step for every query, in every
-    // row of the accumulator (lane halves included), using the same rounded probabilities as the numerator; four
-    // of these per tile replace 32 VALU additions per lane.
-    static constexpr bool MFMA_ROWSUM = true;
+    // Row sums (sum2) take the same rounded probabilities as the numerator, two keys per instruction.  On the matrix pipe,
+    // as a product with ones, they were a fifth of its work and 20 registers: without them the four-wave shapes fit 128
+    // registers, four waves per SIMD (ViT-g x 8 122.2 -> 116.6 us, with the vector work before, between and behind the
+    // MFMAs below instead of behind each of them 116.1).
     // `sc` holds the raw scores; element e becomes 2^(sc[e] * scale - ref).  The exponentials of step + 1 are issued
-    // behind the MFMAs of step, so the vector pipe works on them while the matrix pipe runs.  psum (LM == false)
+    // behind the MFMAs of step, so the vector pipe works on them while the matrix pipe runs.  psum
     // receives the lane's sum of probabilities.
-    template <bool LM>
-    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, f32x16& l, float& psum, const char* sV, int li,
+    static __device__ __forceinline__ float sum2(bf16x8 b, float sum) {
+        const bf16x2 one = {(bf16)1.0f, (bf16)1.0f};
+#pragma unroll
+        for (int kk = 0; kk < 8; kk += 2) sum = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{b[kk], b[kk + 1]}, one, sum, false);
+        return sum;
+    }
+    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, float& psum, const char* sV, int li,
                                                    f32x16* sc, float scale, float ref, int g) {
-        const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
         const int sw = (li >> 1) & 7;                      // rows li and li + 32 share the swizzle term
         const char* r0 = sV + li * 128;
         const char* r1 = r0 + 32 * 128;
@@ -109,9 +113,9 @@ template <> struct AttnMma<bf16> {
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 const float e = __builtin_amdgcn_exp2f(fmaf(sc[st >> 1][8 * (st & 1) + kk], scale, -ref));
-                if (!LM) psum += e;
                 b[kk] = (bf16)e;
             }
+            psum = sum2(b, psum);
             return b;
         };
         bf16x8 a[2][2], b[2];
@@ -127,11 +131,11 @@ template <> struct AttnMma<bf16> {
             __builtin_amdgcn_sched_barrier(0);
             o0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st & 1][0], b[st & 1], o0, 0, 0, 0);
             o1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st & 1][1], b[st & 1], o1, 0, 0, 0);
-            if (LM) l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, b[st & 1], l, 0, 0, 0);
             if (st < 3) b[(st + 1) & 1] = probs(st + 1);
-            // one MFMA, then a third of the next step's exponentials and conversions, three times
+            // the next step's exponentials, conversions and sums before, between and behind the two MFMAs
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < 2; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x402, 4, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x402, 8, 0);
             }
@@ -171,9 +175,7 @@ template <> struct AttnMma<float> {
         }
     }
     static __device__ __forceinline__ int key_of(int v, int g) { return 16 * (v >> 3) + 8 * g + (v & 7); }
-    static constexpr bool MFMA_ROWSUM = false;
-    template <bool LM>
-    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, f32x16&, float& psum, const char* sV, int li,
+    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, float& psum, const char* sV, int li,
                                                    f32x16* sc, float scale, float ref, int g) {
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
@@ -218,8 +220,7 @@ struct AttnMmaF32 : AttnMma<float> {
             }
         }
     }
-    template <bool LM>
-    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, f32x16&, float& psum, const char* sV, int li,
+    static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, float& psum, const char* sV, int li,
                                                    f32x16* sc, float scale, float ref, int g) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -246,7 +247,8 @@ struct AttnMmaF32 : AttnMma<float> {
 // allowed it places them in the accumulation-register file, and since the softmax works on the scores with
 // vector instructions every tile then pays ~190 register-file moves per lane (measured on the four-wave shapes:
 // 158 + 48 registers and 300 vector instructions per tile without the bound, 164 + 0 and 105 with it).  Two
-// shapes would spill under the bound and keep the old one.
+// shapes would spill under the bound and keep the old one.  The bf16 (1,4,1) shape has LDS for five workgroups on a CU and
+// is held to 128 registers, four waves per SIMD.
 template <typename T, int KW>
 constexpr bool attn_double_buffered() { return 2 * KW * 2 * 64 * AttnMma<T>::ROWB <= 128 * 1024; }
 
@@ -258,7 +260,9 @@ constexpr int attn_lds() {
 }
 
 template <typename T, int QB, int QW, int KW>
-constexpr int attn_min_waves() { return (QW * KW == 4 && (QB == 2 || (sizeof(T) == 4 && KW == 4))) ? 1 : 2; }
+constexpr int attn_min_waves() {
+    return QW * KW == 4 && (QB == 2 || (sizeof(T) == 4 && KW == 4)) ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 4 : 2;
+}
 
 template <typename T, int QB, int QW, int KW>
 __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) void attention_kernel(const AttnArgs p) {
@@ -274,7 +278,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     static_assert((KW * 2 * 64 * CPR) % NT == 0 && NT % CPR == 0, "loader mapping");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qw = wave % QW, kw = wave / QW;
     const int g = lane >> 5, li = lane & 31;
     // One-dimensional grid, (image, head)-major: the hardware deals consecutive workgroups round-robin to the 8 XCDs,
@@ -291,12 +295,8 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     const T* __restrict__ kbase = qk + p.dim;
     const T* __restrict__ vt = reinterpret_cast<const T*>(p.vt) + ((int64_t)b * p.dim + h * 64) * p.npad;
 
-    // denominators: on the matrix pipe where the type and the register budget allow it (complete sums, every
-    // accumulator row the same), else per lane half in l_run
-    constexpr bool LMFMA = AttnMma<T>::MFMA_ROWSUM && QB == 1;
-    f32x16 lacc[LMFMA ? QB : 1];
     f32x16 o[QB][2];
-    float m_run[QB], l_run[QB];
+    float m_run[QB], l_run[QB];                        // (denominators: per lane half)
 
     const int KT = p.npad / 64;
     const int NIT = (KT + KW - 1) / KW;
@@ -346,15 +346,16 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     static_assert(!DB || (G % NW == 0 && (NW * RPI) % 16 == 0) || NW == G, "loader mapping of the direct-to-LDS path");
     const int drow = wave * RPI + lane / CPR;
     const int dlc = AttnMma<T>::chunk_at(drow, lane % CPR);          // (exclusive or with the row's term: its own inverse)
-    const T* kdma = kbase + (int64_t)drow * ld + dlc * CE;
-    const T* vdma = vt + (int64_t)drow * p.npad + dlc * CE;
+    // (scalar addresses of the rows and 32 bits of a lane's own offset)
+    const uint32_t koff = (uint32_t)(drow * ld + dlc * CE) * sizeof(T), voff = (uint32_t)(drow * p.npad + dlc * CE) * (uint32_t)sizeof(T);
     auto dma = [&](char* base, int it) {               // tiles of iteration `it` into the stage at `base`
         const int64_t ka = (int64_t)it * KW * 64 * ld;
         const int va = it * KW * 64;
 #pragma unroll
         for (int i = 0; i < (DB ? NDMA : 0); ++i) {
             const int ti = i / PPT, pass = i % PPT, j = ti >> 1, which = ti & 1, r0 = pass * NW * RPI;
-            const T* src = which ? vdma + (int64_t)r0 * p.npad + j * 64 + va : kdma + (int64_t)(j * 64 + r0) * ld + ka;
+            const T* row = which ? vt + (int64_t)r0 * p.npad + j * 64 + va : kbase + (int64_t)(j * 64 + r0) * ld + ka;
+            const char* src = reinterpret_cast<const char*>(row) + (which ? voff : koff);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                              (__attribute__((address_space(3))) void*)(base + (wave + NW * i) * 1024), 16, 0, 0);
         }
@@ -378,10 +379,6 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         for (int qb = 0; qb < QB; ++qb) {
             m_run[qb] = -INFINITY;
             l_run[qb] = 0.0f;
-            if (LMFMA) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) lacc[qb][v] = 0.0f;
-            }
 #pragma unroll
             for (int d = 0; d < 2; ++d)
 #pragma unroll
@@ -418,16 +415,23 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                         for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
+                    // Waves of a SIMD are in different phases: the one with products to issue goes first, the second products with
+                    // the exponentials among them before the first (no priorities / these, us: ViT-B 518x518 18.3 / 17.3,
+                    // ViT-L 19.2 / 18.4, x 4 49.2 / 47.8, ViT-g x 8 136.7 / 137.6, fp32 ViT-S 518x518 x 4 128.9 / 121.5).
+                    __builtin_amdgcn_s_setprio(1);
                     M::qk2(s[0], s[1], sK, li, q[qb], g);
                     if (last) {
+                        // (opaque: the 32 comparisons with it stay here and do not hold 64 scalar registers through the loop)
+                        int left = p.N - t * 64;
+                        asm volatile("" : "+s"(left));
 #pragma unroll
                         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                             for (int v = 0; v < 16; ++v) {
-                                const int key = t * 64 + kb * 32 + M::key_of(v, g);
-                                if (key >= p.N) s[kb][v] = -INFINITY;
+                                if (kb * 32 + M::key_of(v, g) >= left) s[kb][v] = -INFINITY;
                             }
                     }
+                    __builtin_amdgcn_s_setprio(0);
                     float mx = s[0][0];
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -446,18 +450,16 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
                         const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
                         l_run[qb] *= alpha;
                         m_run[qb] = m_new;
-                        if (LMFMA) {
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) lacc[qb][v] *= alpha;
-                        }
 #pragma unroll
                         for (int d = 0; d < 2; ++d)
 #pragma unroll
                             for (int v = 0; v < 16; ++v) o[qb][d][v] *= alpha;
                     }
                     float psum = 0.0f;
-                    M::template pv_tile<LMFMA>(o[qb][0], o[qb][1], lacc[LMFMA ? qb : 0], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
-                    if (!LMFMA) l_run[qb] += psum;
+                    __builtin_amdgcn_s_setprio(2);
+                    M::pv_tile(o[qb][0], o[qb][1], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
+                    l_run[qb] += psum;
+                    __builtin_amdgcn_s_setprio(0);
                 }
             }
             if constexpr (DB) {
@@ -488,12 +490,6 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
 #pragma unroll
         for (int w = 0; w < NW; ++w) redo |= flags[w];
         if (__builtin_amdgcn_readfirstlane(redo)) sweep(AttnMmaF32{});
-    }
-
-    if (LMFMA) {
-        // the matrix-pipe sums are complete in both lane halves; the code below adds the halves, so each takes half
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) l_run[qb] = 0.5f * lacc[qb][0];
     }
 
     if constexpr (KW > 2) {

@@ -46,22 +46,30 @@ hipError_t configure_attention() {
 
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     const int forced = g_forced_variant;
-    // Workgroup shapes measured on MI355X (QB, QW, KW = query blocks per wave, query waves, key waves), us:
-    //                                         (1,2,4) (1,2,2) (2,2,4) (1,4,1) (1,4,2) (1,8,1)
-    //   ViT-S 476x630   (6 x N 1531)            14.0    15.1    22.3    23.5    19.6      -
-    //   ViT-B 518x518   (12 x N 1370)           25.9    20.3    22.4    22.7      -     31.1
-    //   ViT-L 518x518 x4 (64 x N 1374)          80.2    59.0    67.6    50.9      -     76.2
-    //   ViT-g 518x518 x8 (192 x N 1374)        217.0   153.6   190.7   145.0   164.3   182.0
-    // Few (head, 32-query block) pairs want the key axis split over waves to fill the chip; many want four
-    // query waves sharing each key tile and no merge.  Wider workgroups (eight query waves, or two query blocks per
-    // wave) halve the L2 -> LDS traffic and are slower all the same; narrower ones (two waves) double it and are
-    // slower too.
-    // Beside other streams' kernels the footprint counts for more than the time alone: (1,2,4) holds a CU's LDS
-    // (128 KB) for itself, (1,2,2) takes half and four waves.  ViT-S 476x630, three encoder lanes + heads: 1968 against
-    // 1888 frames/s with (1,2,2), although the kernel alone takes 14.3 against 13.0 us (and frame latency 1.069
-    // against 1.058 ms); even (1,4,1) -- 32 KB, 22.5 us alone -- gives 1941.
-    const int64_t qblocks = (int64_t)cdiv(a.N, 32) * a.B * a.heads;
-    int variant = qblocks >= 2048 ? 141 : (qblocks >= 400 || a.shared_gpu) ? 122 : 124;
+    // Workgroup shapes measured on MI355X (QB, QW, KW = query blocks per wave, query waves, key waves), us, by pairs of a head
+    // and a block of 32 queries:
+    //                                        (1,1,4) (1,2,4) (1,2,2) (1,4,1)
+    //     54  ViT-S 224x224  (N  257)             5.8     6.9     6.3     7.3
+    //    108  ViT-B 224x224                       5.9     6.9     6.4
+    //    150  ViT-S 392x392  (N  785)             8.1     9.5     9.7
+    //    222  ViT-S 476x476  (N 1157)             9.5    11.4    12.3
+    //    288  ViT-S 476x630  (N 1531)                    12.7    14.5    22.0
+    //    348  ViT-S 602x602  (N 1850)            24.2    15.7    17.3
+    //    444  ViT-B 476x476                      17.8    12.1    13.0
+    //    516  ViT-B 518x518  (N 1370)                    23.8    17.2    20.9
+    //    696  ViT-B 602x602                      36.2    29.7    23.9
+    //   2752  ViT-L 518x518 x 4                          68.6    51.9    42.7
+    //   8256  ViT-g 518x518 x 8                         191     139     118
+    // The first two hold a CU each, the longest-running split of the keys that one round of the 256 CUs has room for wins
+    // (and a merge that four waves share beats one by a single wave); then half a CU each; many pairs want four query
+    // waves sharing each key tile and no merge.  Wider workgroups (eight query waves, or two query blocks per wave) halve the
+    // L2 -> LDS traffic and are slower all the same; narrower ones (two waves) double it and are slower too.
+    // Beside another encoder lane's kernels the footprint counts for more than the time alone.  Frames of two lanes, us, in the
+    // order of the table: ViT-S 224x224 243 248 247, 308x308 251 258 258, 476x476 with a depth head 495 477 481, ViT-B 308x308 (192
+    // pairs) 371 370 371, 476x476 844 772 764; so (1,1,4) where both lanes' workgroups find a CU each, (1,2,2) up to the line
+    // of (1,4,1).
+    const int64_t heads = (int64_t)a.B * a.heads, qblocks = cdiv(a.N, 32) * heads;
+    int variant = qblocks >= 2048 ? 141 : qblocks <= (a.shared_gpu ? 128 : 256) ? 114 : a.shared_gpu || cdiv(a.N, 64) * heads > 256 ? 122 : 124;
     if (forced) variant = forced;
     if (dtype) return launch_variant<bf16>(variant, a, s);
     // fp32: a workgroup of any shape fills a CU's LDS, or half of it with (1,4,1), so what counts is whole rounds of the 256 CUs.
