@@ -246,8 +246,8 @@ struct AttnMmaF32 : AttnMma<float> {
 // is what makes the compiler keep the MFMA accumulators in ordinary vector registers: with up to 512 registers
 // allowed it places them in the accumulation-register file, and since the softmax works on the scores with
 // vector instructions every tile then pays ~190 register-file moves per lane (measured on the four-wave shapes:
-// 158 + 48 registers and 300 vector instructions per tile without the bound, 164 + 0 and 105 with it).  Two
-// shapes would spill under the bound and keep the old one.  The bf16 (1,4,1) shape has LDS for five workgroups on a CU and
+// 158 + 48 registers and 300 vector instructions per tile without the bound, 164 + 0 and 105 with it).  (2,1,4)
+// would spill under the bound and keeps the old one.  The bf16 (1,4,1) shape has LDS for five workgroups on a CU and
 // is held to 128 registers, four waves per SIMD.
 template <typename T, int KW>
 constexpr bool attn_double_buffered() { return 2 * KW * 2 * 64 * AttnMma<T>::ROWB <= 128 * 1024; }
@@ -261,7 +261,7 @@ constexpr int attn_lds() {
 
 template <typename T, int QB, int QW, int KW>
 constexpr int attn_min_waves() {
-    return QW * KW == 4 && (QB == 2 || (sizeof(T) == 4 && KW == 4)) ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 4 : 2;
+    return QW * KW == 4 && QB == 2 ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 4 : 2;
 }
 
 template <typename T, int QB, int QW, int KW>
@@ -272,10 +272,8 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     constexpr int CPR = 64 / CE;                 // 16-byte chunks per 64-element row
     constexpr int ROWB = AttnMma<T>::ROWB;
     constexpr int TILE = 64 * ROWB;
-    constexpr int CH = KW * 2 * 64 * CPR / NT;   // chunks per thread per iteration
     constexpr int STAGE = KW * 2 * TILE;         // K and V tiles of one iteration
     constexpr bool DB = attn_double_buffered<T, KW>();
-    static_assert((KW * 2 * 64 * CPR) % NT == 0 && NT % CPR == 0, "loader mapping");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -300,41 +298,7 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
 
     const int KT = p.npad / 64;
     const int NIT = (KT + KW - 1) / KW;
-    const int lchunk = tid % CPR;
-    u32x4 rg[DB ? 1 : CH];                             // register staging: single-buffer shapes only
-    // chunk i of this thread: linear index tid + i NT over (tile j, K|V, row, chunk).  Its address advances by a
-    // fixed step per iteration (KW tiles), so the loader keeps one running pointer per chunk instead of
-    // recomputing tile, row and clamps each time.  Nothing is clamped: tiles past the last one and key rows past
-    // N are read from whatever follows (the next image's keys, the buffers' padding -- see AttnArgs) and never
-    // used: scores of keys >= N are overwritten with -inf, waves skip tiles >= KT.
-    // Thread part of the address (its row within a pass and its chunk) in two pointers; tile, K|V and pass of
-    // chunk i are compile-time constants, the advance per iteration is wave-uniform: scalar arithmetic only.
-    constexpr int RPP = NT / CPR;                      // rows per loader pass
-    static_assert(64 % RPP == 0, "a pass must not straddle tiles");
-    const T* kthr = kbase + (int64_t)(tid / CPR) * ld + lchunk * CE;
-    const T* vthr = vt + (int64_t)(tid / CPR) * p.npad + lchunk * CE;
-    int64_t kadv = 0, vadv = 0;
-    auto gload = [&]() {                               // loads the next iteration's tiles
-#pragma unroll
-        for (int i = 0; i < (DB ? 0 : CH); ++i) {
-            const int r0 = (i * RPP) & 63, which = ((i * RPP) >> 6) & 1, j = (i * RPP) >> 7;
-            const T* src = which ? vthr + (int64_t)r0 * p.npad + j * 64 + vadv
-                                 : kthr + (int64_t)(j * 64 + r0) * ld + kadv;
-            rg[i] = ld_global_16(src);
-        }
-        kadv += (int64_t)KW * 64 * ld;
-        vadv += KW * 64;
-    };
-    auto sstore = [&](char* base) {
-#pragma unroll
-        for (int i = 0; i < (DB ? 0 : CH); ++i) {
-            const int idx = (tid + i * NT) / CPR;
-            const int row = idx & 63;
-            *reinterpret_cast<u32x4*>(base + (idx >> 6) * TILE + (row * CPR + AttnMma<T>::chunk_at(row, lchunk)) * 16) = rg[i];
-        }
-    };
-
-    // Double-buffered shapes load straight into LDS (global_load_lds_dwordx4: no staging registers, no ds_write).
+    // Tiles are loaded straight into LDS (global_load_lds_dwordx4: no staging registers, no ds_write).
     // One instruction of a wave fills 1 KB = RPI consecutive rows of a tile; lane l lands on row l / CPR, physical
     // chunk l % CPR of that row group, so it fetches the logical chunk that belongs there under the swizzle.
     // Instruction i of wave w fills slot w + NW i of the stage (tile i / PPT, pass i % PPT over its row groups):
@@ -343,17 +307,19 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     constexpr int RPI = 1024 / ROWB, G = TILE / 1024;  // rows per instruction, instructions per tile
     constexpr int PPT = G / NW > 0 ? G / NW : 1;       // passes of the workgroup over one tile
     constexpr int NDMA = KW * 2 * G / NW;              // instructions per wave per iteration
-    static_assert(!DB || (G % NW == 0 && (NW * RPI) % 16 == 0) || NW == G, "loader mapping of the direct-to-LDS path");
+    constexpr int KEYS = 1, VALUES = 2;
+    static_assert((G % NW == 0 && (NW * RPI) % 16 == 0) || NW == G, "loader mapping");
     const int drow = wave * RPI + lane / CPR;
     const int dlc = AttnMma<T>::chunk_at(drow, lane % CPR);          // (exclusive or with the row's term: its own inverse)
     // (scalar addresses of the rows and 32 bits of a lane's own offset)
     const uint32_t koff = (uint32_t)(drow * ld + dlc * CE) * sizeof(T), voff = (uint32_t)(drow * p.npad + dlc * CE) * (uint32_t)sizeof(T);
-    auto dma = [&](char* base, int it) {               // tiles of iteration `it` into the stage at `base`
+    auto dma = [&](char* base, int it, int kinds) {    // tiles of iteration `it` into the stage at `base`: KEYS, VALUES or both
         const int64_t ka = (int64_t)it * KW * 64 * ld;
         const int va = it * KW * 64;
 #pragma unroll
-        for (int i = 0; i < (DB ? NDMA : 0); ++i) {
+        for (int i = 0; i < NDMA; ++i) {
             const int ti = i / PPT, pass = i % PPT, j = ti >> 1, which = ti & 1, r0 = pass * NW * RPI;
+            if (!((kinds >> which) & 1)) continue;
             const T* row = which ? vt + (int64_t)r0 * p.npad + j * 64 + va : kbase + (int64_t)(j * 64 + r0) * ld + ka;
             const char* src = reinterpret_cast<const char*>(row) + (which ? voff : koff);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
@@ -362,8 +328,9 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     };
     // Two buffers: the loads of iteration it + 1 are issued at the top of iteration it into the buffer that was read
     // in iteration it - 1, and one barrier per iteration is enough (everyone has finished reading buffer b, and the
-    // loads into buffer b ^ 1 have landed).  Shapes whose two buffers would not fit the CU's LDS keep one buffer,
-    // register staging and two barriers.
+    // loads into buffer b ^ 1 have landed).  Shapes whose two buffers would not fit the CU's LDS have one, and each half of it
+    // is loaded while the other is multiplied: behind the barrier that ends the scores the next keys, behind the one that
+    // ends the values the next values (staged in registers, 128 of a lane's 422, fp32 ViT-S 224x224 took 13.85 us, now 12.65).
     // All tiles from the start: scores, softmax and values with the product blocks of M.
     auto sweep = [&](auto mma) {
         using M = decltype(mma);
@@ -384,87 +351,95 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[qb][d][v] = 0.0f;
         }
-        kadv = vadv = 0;
-        if constexpr (DB) {
-            dma(smem, 0);
-            __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the loads into LDS have landed
-            __syncthreads();
-        } else {
-            gload();
-        }
+        if constexpr (DB) dma(smem, 0, KEYS | VALUES); else dma(smem, 0, KEYS);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): the loads into LDS have landed
+        __syncthreads();
+        if constexpr (!DB) dma(smem, 0, VALUES);
+        // Scores of query block qb against tile t, and the reference that their exponentials are taken against
+        auto scores = [&](f32x16* s, int qb, int t, const char* sK) {
+            const bool last = t == KT - 1;                 // keys past N only exist in the last tile
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
+            // Waves of a SIMD are in different phases: the one with products to issue goes first, the second products with
+            // the exponentials among them before the first (no priorities / these, us: ViT-B 518x518 18.3 / 17.3,
+            // ViT-L 19.2 / 18.4, x 4 49.2 / 47.8, ViT-g x 8 136.7 / 137.6, fp32 ViT-S 518x518 x 4 128.9 / 121.5).
+            __builtin_amdgcn_s_setprio(1);
+            M::qk2(s[0], s[1], sK, li, q[qb], g);
+            if (last) {
+                // (opaque: the 32 comparisons with it stay here and do not hold registers through the loop)
+                int left = p.N - t * 64 - M::key_of(0, g);
+                asm volatile("" : "+v"(left));
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        if (kb * 32 + M::key_of(v, 0) >= left) s[kb][v] = -INFINITY;
+                    }
+            }
+            __builtin_amdgcn_s_setprio(0);
+            float mx = s[0][0];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
+            mx = halves_max(mx);
+            // Lazy rescaling: m_run is the reference the exponentials are taken against (in log2 units), not
+            // necessarily the running maximum.  It only moves when a query's maximum has grown by more than 8
+            // (probabilities stay <= 2^8, exact in fp32 and harmless in bf16), which after the first tile is
+            // rare -- and then the whole wave skips the 32 multiplications of the accumulator.  On the first
+            // tile the reference is -inf, alpha = 0 and the (zero) accumulators are overwritten.
+            const float mxs = mx * p.scale_log2e;
+            const bool grow = mxs > m_run[qb] + 8.0f;
+            if (__any(grow)) {
+                const float m_new = grow ? mxs : m_run[qb];
+                const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+                l_run[qb] *= alpha;
+                m_run[qb] = m_new;
+#pragma unroll
+                for (int d = 0; d < 2; ++d)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o[qb][d][v] *= alpha;
+            }
+        };
+        auto values = [&](f32x16* s, int qb, const char* sV) {
+            float psum = 0.0f;
+            __builtin_amdgcn_s_setprio(2);
+            M::pv_tile(o[qb][0], o[qb][1], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
+            l_run[qb] += psum;
+            __builtin_amdgcn_s_setprio(0);
+        };
         for (int it = 0; it < NIT; ++it) {
-            const char* stage = smem;
+            // (a wave without a tile in the last iteration still takes part in the barriers)
             if constexpr (DB) {
-                if (it + 1 < NIT) dma(smem + ((it + 1) & 1) * STAGE, it + 1);
-                stage = smem + (it & 1) * STAGE;
-            } else {
-                __syncthreads();           // everyone is done reading the previous tiles
-                sstore(smem);
-                __syncthreads();
-                if (it + 1 < NIT) gload();
-            }
-            const int t = it * KW + kw;
-            if (t < KT) {                  // (a wave without a tile in the last iteration still takes part in the barriers)
-                const char* sK = stage + (kw * 2) * TILE;
-                const char* sV = sK + TILE;
-                const bool last = t == KT - 1;     // keys past N only exist in the last tile
+                const char* stage = smem + (it & 1) * STAGE;
+                if (it + 1 < NIT) dma(smem + ((it + 1) & 1) * STAGE, it + 1, KEYS | VALUES);
+                const int t = it * KW + kw;
+                if (t < KT) {
+                    const char* sK = stage + (kw * 2) * TILE;
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    f32x16 s[2];
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
-                    // Waves of a SIMD are in different phases: the one with products to issue goes first, the second products with
-                    // the exponentials among them before the first (no priorities / these, us: ViT-B 518x518 18.3 / 17.3,
-                    // ViT-L 19.2 / 18.4, x 4 49.2 / 47.8, ViT-g x 8 136.7 / 137.6, fp32 ViT-S 518x518 x 4 128.9 / 121.5).
-                    __builtin_amdgcn_s_setprio(1);
-                    M::qk2(s[0], s[1], sK, li, q[qb], g);
-                    if (last) {
-                        // (opaque: the 32 comparisons with it stay here and do not hold 64 scalar registers through the loop)
-                        int left = p.N - t * 64;
-                        asm volatile("" : "+s"(left));
-#pragma unroll
-                        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                if (kb * 32 + M::key_of(v, g) >= left) s[kb][v] = -INFINITY;
-                            }
+                    for (int qb = 0; qb < QB; ++qb) {
+                        f32x16 s[2];
+                        scores(s, qb, t, sK);
+                        values(s, qb, sK + TILE);
                     }
-                    __builtin_amdgcn_s_setprio(0);
-                    float mx = s[0][0];
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
-                    mx = halves_max(mx);
-                    // Lazy rescaling: m_run is the reference the exponentials are taken against (in log2 units), not
-                    // necessarily the running maximum.  It only moves when a query's maximum has grown by more than 8
-                    // (probabilities stay <= 2^8, exact in fp32 and harmless in bf16), which after the first tile is
-                    // rare -- and then the whole wave skips the 32 multiplications of the accumulator.  On the first
-                    // tile the reference is -inf, alpha = 0 and the (zero) accumulators are overwritten.
-                    const float mxs = mx * p.scale_log2e;
-                    const bool grow = mxs > m_run[qb] + 8.0f;
-                    if (__any(grow)) {
-                        const float m_new = grow ? mxs : m_run[qb];
-                        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-                        l_run[qb] *= alpha;
-                        m_run[qb] = m_new;
-#pragma unroll
-                        for (int d = 0; d < 2; ++d)
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) o[qb][d][v] *= alpha;
-                    }
-                    float psum = 0.0f;
-                    __builtin_amdgcn_s_setprio(2);
-                    M::pv_tile(o[qb][0], o[qb][1], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
-                    l_run[qb] += psum;
-                    __builtin_amdgcn_s_setprio(0);
                 }
-            }
-            if constexpr (DB) {
+            } else {
+                static_assert(DB || QB == 1, "the scores of a query block wait for the values");
+                const int t = it * KW + kw;
+                const char* sK = smem + (kw * 2) * TILE;
+                f32x16 s[2];
+                if (t < KT) scores(s, 0, t, sK);
                 __builtin_amdgcn_s_waitcnt(0x0F70);
                 __syncthreads();
+                if (it + 1 < NIT) dma(smem, it + 1, KEYS);
+                if (t < KT) values(s, 0, sK + TILE);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            __syncthreads();
+            if constexpr (!DB) {
+                if (it + 1 < NIT) dma(smem, it + 1, VALUES);
             }
         }
     };

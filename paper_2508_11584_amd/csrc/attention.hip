@@ -10,13 +10,13 @@ static hipError_t launch_variant(int variant, const AttnArgs& a, hipStream_t s, 
     switch (variant) {
         case 114: return launch_attention_variant<T, 1, 1, 4>(a, s, cfg);
         case 141: return launch_attention_variant<T, 1, 4, 1>(a, s, cfg);
-        case 122: return launch_attention_variant<T, 1, 2, 2>(a, s, cfg);
+        case 124: return launch_attention_variant<T, 1, 2, 4>(a, s, cfg);
         default: break;
     }
     if constexpr (sizeof(T) == 2) {
         switch (variant) {
             case 214: return launch_attention_variant<T, 2, 1, 4>(a, s, cfg);
-            case 124: return launch_attention_variant<T, 1, 2, 4>(a, s, cfg);
+            case 122: return launch_attention_variant<T, 1, 2, 2>(a, s, cfg);
             case 224: return launch_attention_variant<T, 2, 2, 4>(a, s, cfg);
             default: break;
         }
@@ -37,7 +37,7 @@ hipError_t configure_attention() {
         hipError_t rc = launch_variant<bf16>(v, a, nullptr, true);
         if (rc != hipSuccess) return rc;
     }
-    for (int v : {114, 122, 141}) {
+    for (int v : {114, 124, 141}) {
         hipError_t rc = launch_variant<float>(v, a, nullptr, true);
         if (rc != hipSuccess) return rc;
     }
@@ -72,12 +72,15 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     int variant = qblocks >= 2048 ? 141 : qblocks <= (a.shared_gpu ? 128 : 256) ? 114 : a.shared_gpu || cdiv(a.N, 64) * heads > 256 ? 122 : 124;
     if (forced) variant = forced;
     if (dtype) return launch_variant<bf16>(variant, a, s);
-    // fp32: a workgroup of any shape fills a CU's LDS, or half of it with (1,4,1), so what counts is whole rounds of the 256 CUs.
-    // us, the kernel on fp32 instructions / (1,1,4) (1,2,2) (1,4,1) here:
-    //   54 pairs (ViT-S 224x224)  15.8 / 14.1 15.2 20.9      288 (ViT-S 476x630) 79.0 / 66.9 51.1 86.2
-    //   516 (ViT-B 518x518)      116.3 / 100.5 91.1 84.5    1032 (ViT-S 518x518 x4) 192 / 167 139 143     2064 (ViT-B x4) 280 / 293 237 215
-    int v32 = qblocks <= 256 ? 114 : qblocks <= 512 ? 122 : 141;
-    if (forced == 114 || forced == 122 || forced == 141) v32 = forced;
+    // fp32: a workgroup fills a CU's LDS ((1,4,1): half of it), so what counts is whole rounds of the 256 CUs and waves to overlap:
+    // a wave alone on its SIMD splits values and multiplies in turn, of eight waves two share a SIMD.  us, the kernel on fp32
+    // instructions / (1,1,4) (1,2,4) (1,4,1), and (1,2,2), which is no longer there, before its masks and addresses changed:
+    //   54 pairs (ViT-S 224x224)  15.8 / 12.7 15.5 21.1, 15.2    288 (ViT-S 476x630)  79.0 / 55.7 42.2 83.5, 47.5
+    //   348 (ViT-S 602x602)       72.4 53.8 99.9, 58.3           516 (ViT-B 518x518) 116.3 / 84 77 80.6, 91.1
+    //   1032 (ViT-S 518x518 x4) 192 / 139 115.5 122.5, 129       2064 (ViT-B 518x518 x4) 280 / 252 196 203, 237
+    //   3096 (ViT-S 896x896 x4) 973 763 704
+    int v32 = qblocks <= 256 ? 114 : qblocks <= 2560 ? 124 : 141;
+    if (forced == 114 || forced == 124 || forced == 141) v32 = forced;
     return launch_variant<float>(v32, a, s);
 }
 }  // namespace vpe

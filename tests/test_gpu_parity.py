@@ -251,7 +251,7 @@ def test_layernorm_statistics_of_odd_and_of_many_groups(width, dtype):
                            img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 148, 248, kinds=("seg",))
 
 
-@pytest.mark.parametrize("variant", ["114", "122", "141"])
+@pytest.mark.parametrize("variant", ["114", "122", "141", "124"])        # (122 is a bf16 shape: the choice by size)
 def test_fp32_attention_shapes(variant, monkeypatch):
     # every workgroup shape of the fp32 attention: 38 tokens a view (one ragged key tile, fewer than the key waves), and 166
     # (three tiles, the last of 38 keys: key waves with unequal numbers of tiles); fp32 gates
@@ -444,7 +444,7 @@ def _sharpen(scale):
 @pytest.mark.parametrize("dtype,variant,scale", [("bf16", "124", 16.0), ("bf16", "224", 16.0), ("bf16", "141", 16.0),
                                                  ("bf16", "114", 16.0), ("bf16", "214", 16.0), ("bf16", "122", 16.0),
                                                  ("bf16", "", 16.0),
-                                                 ("f32", "114", 32.0), ("f32", "122", 32.0), ("f32", "141", 32.0)])
+                                                 ("f32", "114", 32.0), ("f32", "122", 32.0), ("f32", "141", 32.0), ("f32", "124", 32.0)])
 def test_attention_with_peaked_softmax(dtype, variant, scale, monkeypatch):
     # 361 tokens = six key tiles of 64 (the last with 41 keys): with four key waves two of them own two tiles.
     # With the benchmark's weights every score lies within a fraction of a unit of the others, so the running
@@ -545,7 +545,7 @@ def test_fp32_head_weights_beyond_the_range_of_bf16(tile, monkeypatch):
     assert relerr(outs[1][0][0][..., :spec.det_classes].transpose(2, 0, 1), o["logits"]) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("variant", ["114", "122", "141"])
+@pytest.mark.parametrize("variant", ["114", "122", "141", "124"])
 def test_fp32_attention_keys_beyond_the_range_of_bf16(variant, monkeypatch):
     # one channel of every key at 3.4e38 against 1e-37 in the queries: the same 4.25 in every score, which the softmax does not see
     monkeypatch.setenv("VPE_ATTN_VARIANT", variant)
