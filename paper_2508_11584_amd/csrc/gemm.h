@@ -121,20 +121,25 @@ __device__ __forceinline__ float gelu_erf(float v) {
 }
 
 // The same function for results that are rounded to bf16: v Phi(v) with the normal distribution function as a logistic one,
-// Phi(v) = 1 / (1 + 2^(v q(v^2))), q of degree 4 (least maximum error of Phi on |v| <= 5, linear program; beyond 5 the value at
-// 5, 2.9e-7 from 0 or 1).  The result differs from the exact form by at most 1.6e-6 |v| (rms, before rounding: 2.7e-6 on
-// 2 < |v| < 3, 3.3e-6 up to 3.5, 4.5e-6 up to 4.25; 4.5 % of the result at -4), a sixth of what erf as an odd polynomial on
-// |x| <= 3 had (1.04e-5 |v|), in 13 issue slots (8 clocks for v_exp_f32 and v_rcp_f32, 4 for the others) instead of 18 (us, before / now: ViT-B 1569 tokens
-// fc1 17.8 / 17.1, ViT-L 1374 21.4 / 20.7): an epilogue has the vector ALU to itself while the matrix pipes of
-// its workgroup idle, at 64 values a clock and CU.  -inf gives -inf, as that form did.
-__device__ __forceinline__ float gelu_erf_bf16(float v) {
-    const float x = __builtin_amdgcn_fmed3f(v, -5.0f, 5.0f);
+// Phi(v) = 1 / (1 + 2^(v q(v^2))), q of degree 5 on |v| <= 5.5; beyond 5.5 the value there, 1.6e-7 from 0 or 1.  Least maximum
+// error of Phi (linear program) relative to an envelope that is 1.6e-8 at 0, where most of fc1's results lie, 1e-6 from 2 on: a fit of
+// degree 4 without it had 1.7e-7 rms on |v| < 0.25.  The result differs from the exact form by at most 6.4e-7 |v| (rms, before
+// rounding: 1.1e-8 on |v| < 0.25, 1.8e-7 up to 1, 6.4e-7 up to 2, 1.7e-6 beyond; 1.2 % of the result at -4), less on every interval
+// than erf as an odd polynomial of degree 19 on |x| <= 3 (1.7e-8, 4.0e-7, 3.1e-6, 9.3e-6 up to 4) in 14 issue slots (8 clocks for
+// v_exp_f32 and v_rcp_f32, 4 for the others) instead of 18: an epilogue has the vector ALU to itself while the matrix pipes of its
+// workgroup idle, at 64 values a clock and CU.  -inf gives -inf, +inf +inf (the exact form gives NaN for -inf).
+constexpr float GELU_LIMIT = 5.5f;
+__host__ __device__ __forceinline__ float gelu_exponent(float x) {        // x q(x^2), |x| <= GELU_LIMIT
     const float t = x * x;
-    float q = fmaf(-4.1093172e-06f, t, 1.0581483e-04f);
-    q = fmaf(q, t, 2.5373331e-04f);
-    q = fmaf(q, t, -1.0500616e-01f);
-    q = fmaf(q, t, -2.3021653e+00f);
-    return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(q * x));
+    float q = fmaf(1.61200518e-07f, t, -8.30406134e-06f);
+    q = fmaf(q, t, 1.41446319e-04f);
+    q = fmaf(q, t, 1.36013434e-04f);
+    q = fmaf(q, t, -1.04866788e-01f);
+    q = fmaf(q, t, -2.30220509e+00f);
+    return q * x;
+}
+__device__ __forceinline__ float gelu_erf_bf16(float v) {
+    return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(gelu_exponent(__builtin_amdgcn_fmed3f(v, -GELU_LIMIT, GELU_LIMIT))));
 }
 template <typename T>
 __device__ __forceinline__ float gelu_for(float v) { return sizeof(T) == 2 ? gelu_erf_bf16(v) : gelu_erf(v); }

@@ -1,5 +1,5 @@
-"""Host-side checks of the GEMM launcher: k extents that its kernels' loops cannot do, and epilogues that its convolution kernels do
-not carry, are refused before anything is launched."""
+"""Host-side checks of the GEMMs: k extents that the kernels' loops cannot do, and epilogues that the convolution kernels do
+not carry, are refused before anything is launched; tile maps; the GELU of results that are rounded to bf16."""
 import os
 import subprocess
 
@@ -38,15 +38,20 @@ int main() {
 """
 
 
-def test_gemm_launcher_refuses_what_its_kernels_do_not_have(tmp_path):
+def run_host_program(tmp_path, program, optimize="-O1"):
+    """Compiles the host side of `program` against the kernels' headers, links it with the library and runs it: exit code 0."""
     vpe.load_library()                                   # (built already, or an error that says so)
-    src, exe = tmp_path / "contract.cpp", tmp_path / "contract"
-    src.write_text(PROGRAM)
-    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O0", "-w", "-I" + os.path.join(PKG, "csrc"), str(src),
+    src, exe = tmp_path / "program.cpp", tmp_path / "program"
+    src.write_text(program)
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", optimize, "-w", "-I" + os.path.join(PKG, "csrc"), str(src),
                     "-x", "none", os.path.join(PKG, "libvpe.so"), "-Wl,-rpath," + PKG, "-o", str(exe)], check=True, capture_output=True)
-    # no device: the refusal must come from the arguments alone, with a device as without one
+    # no device: what is checked must come from the arguments alone, with a device as without one
     r = subprocess.run([str(exe)], capture_output=True, text=True, env={**os.environ, "HIP_VISIBLE_DEVICES": ""})
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_gemm_launcher_refuses_what_its_kernels_do_not_have(tmp_path):
+    run_host_program(tmp_path, PROGRAM, "-O0")
 
 
 MAP_PROGRAM = r"""
@@ -74,10 +79,47 @@ int main() {
 
 
 def test_tile_map_reciprocals_are_exact(tmp_path):
-    vpe.load_library()
-    src, exe = tmp_path / "map.cpp", tmp_path / "map"
-    src.write_text(MAP_PROGRAM)
-    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-w", "-I" + os.path.join(PKG, "csrc"), str(src),
-                    "-x", "none", os.path.join(PKG, "libvpe.so"), "-Wl,-rpath," + PKG, "-o", str(exe)], check=True, capture_output=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True, env={**os.environ, "HIP_VISIBLE_DEVICES": ""})
-    assert r.returncode == 0, r.stdout + r.stderr
+    run_host_program(tmp_path, MAP_PROGRAM)
+
+
+GELU_PROGRAM = r"""
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include "gemm.h"
+// the GELU of bf16 results as the kernel evaluates it (v_exp_f32 and v_rcp_f32: 1 ulp), and the form before it, erf as an odd
+// polynomial on |x| <= 3, both in fp32
+static float logistic(float v) {
+    const float x = fminf(fmaxf(v, -vpe::GELU_LIMIT), vpe::GELU_LIMIT);
+    return v * (1.0f / (1.0f + exp2f(vpe::gelu_exponent(x))));
+}
+static float polynomial(float v) {
+    const float c[10] = {-4.469939086e-09f, 2.302152922e-07f, -5.322654488e-06f, 7.394709974e-05f, -7.009955007e-04f,
+                         4.897189327e-03f, -2.645343542e-02f, 1.125671491e-01f, -3.760564327e-01f, 1.128376126e+00f};
+    const float x = fminf(fabsf(v) * 0.70710678118654752f, 3.0f), t = x * x;
+    float p = c[0];
+    for (int i = 1; i < 10; ++i) p = fmaf(p, t, c[i]);
+    return 0.5f * v * (1.0f + copysignf(fminf(p * x, 1.0f), v));
+}
+int main() {
+    int bad = 0;
+    for (int k = 0; k < 28; ++k) {                       // intervals of 0.25 up to 7, both signs
+        const int n = 20000;
+        double now = 0.0, before = 0.0, most = 0.0;
+        for (int i = 0; i < 2 * n; ++i) {
+            const float v = (i & 1 ? -1.0f : 1.0f) * (float)(0.25 * (k + (i / 2 + 0.5) / n));
+            const double exact = 0.5 * v * erfc(-v / sqrt(2.0)), e = logistic(v) - exact, f = polynomial(v) - exact;
+            now += e * e; before += f * f; most = fmax(most, fabs(e / v));
+        }
+        if (now > before || most > 6.5e-7) { printf("|v| from %g: rms %.2e, before %.2e, largest %.2e |v|\n", 0.25 * k, sqrt(now / (2 * n)), sqrt(before / (2 * n)), most); ++bad; }
+    }
+    const float inf = INFINITY;
+    if (logistic(inf) != inf || logistic(-inf) != -inf || !std::isnan(logistic(NAN))) { printf("infinities or NaN\n"); ++bad; }
+    return bad;
+}
+"""
+
+
+def test_gelu_of_bf16_results_loses_nothing_on_any_interval(tmp_path):
+    # rms error against 64 bits, before rounding to bf16: no larger than the polynomial's on any interval; 6.4e-7 |v| at most
+    run_host_program(tmp_path, GELU_PROGRAM)
