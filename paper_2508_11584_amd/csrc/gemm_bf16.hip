@@ -55,38 +55,39 @@ constexpr TileModel kConv[] = {
 constexpr float kConvShared = 1.12f;
 }  // namespace
 
+// Can (and, with the tuning aids, may) a tiling take this problem?
+static bool admissible(const TileModel& c, const GemmArgs& a, int amode) {
+    // k-tiles of 128 need whole ones (in a convolution within a tap); where there are, the 64-deep 32 x 64 shape is never faster
+    const bool deep = amode == A_CONV3 ? a.cC % 128 == 0 : a.K % 128 == 0;
+    if (g_no_small && (c.kind == 64 || c.kind == 65)) return false;
+    if (g_no_splitk && c.bm <= 64 && c.kind != 64 && c.kind != 65) return false;
+    if ((c.kind == 33 || c.kind == 43) && !deep) return false;
+    return !(c.kind == 3 && deep);
+}
+
 // The model's pick for rows m_begin .. M - 1 of `a` and its predicted time in us.
 template <int NC>
 static int pick_tile(const TileModel (&cands)[NC], const GemmArgs& a, int amode, float& best_cost) {
     int best = 2;
     best_cost = 0.0f;
-    // k-tiles of 128 need whole ones (in a convolution within a tap); where there are, the 64-deep 32 x 64 shape is never faster
-    const bool deep = amode == A_CONV3 ? a.cC % 128 == 0 : a.K % 128 == 0;
     for (const TileModel& c : cands) {
-        if (g_no_small && (c.kind == 64 || c.kind == 65)) continue;
-        if (g_no_splitk && c.bm <= 64 && c.kind != 64 && c.kind != 65) continue;
-        if ((c.kind == 33 || c.kind == 43) && !deep) continue;
-        if (c.kind == 3 && deep) continue;
+        if (!admissible(c, a, amode)) continue;
         const float cost = tile_time(c, tile_count(c, a), a.K, epilogue_weight(a)) * (amode == A_CONV3 && c.bm <= 64 ? kConvShared : 1.0f);
         if (best_cost == 0.0f || cost < best_cost) { best_cost = cost; best = c.kind; }
     }
     return best;
 }
 
-static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best);
-
 template <int NC>
-static hipError_t launch_chosen(const TileModel (&cands)[NC], const GemmArgs& a, int amode, hipStream_t s) {
-    float whole_cost;
-    const int whole = pick_tile(cands, a, amode, whole_cost);
+static GemmPlan plan_among(const TileModel (&cands)[NC], const GemmArgs& a, int amode) {
+    float cost;
+    GemmPlan plan{0, 0, pick_tile(cands, a, amode, cost)};
     // The one-per-CU tiles run in lockstep rounds of 256 and pay for a partly filled last round in full (ViT-g, 8
     // views: fc2 and the out-projection have 43 x 6 = 258 tiles of 256 x 256, QKV 774).  Two launches instead: whole
     // rounds of the large tile over the leading rows, then the remaining rows with whatever the model picks for them.
     if (g_forced_tile == 0 && !g_no_split && a.nz <= 1 && a.m_begin == 0) {
-        float split_cost = whole_cost;
-        int split_kind = 0, split_rows = 0;
         for (const TileModel& c : cands) {
-            if (c.held != 1) continue;
+            if (c.held != 1 || !admissible(c, a, amode)) continue;
             const int tn = cdiv(a.N, c.bn), tm = cdiv(a.M, c.bm);
             const int64_t tiles = (int64_t)tm * tn;
             const int rounds = (int)(tiles / 256);
@@ -97,28 +98,27 @@ static hipError_t launch_chosen(const TileModel (&cands)[NC], const GemmArgs& a,
             GemmArgs tail = a;
             tail.m_begin = tm_main * c.bm;
             float tail_cost;
-            pick_tile(cands, tail, amode, tail_cost);
-            if (main_cost + tail_cost < 0.93f * split_cost) {   // a second launch costs a few us the model does not see
-                split_cost = main_cost + tail_cost;
-                split_kind = c.kind;
-                split_rows = tm_main * c.bm;
+            const int tail_kind = pick_tile(cands, tail, amode, tail_cost);
+            if (main_cost + tail_cost < 0.93f * cost) {         // a second launch costs a few us the model does not see
+                cost = main_cost + tail_cost;
+                plan = GemmPlan{c.kind, tail.m_begin, tail_kind};
             }
         }
-        if (split_kind) {
-            GemmArgs main = a, tail = a;
-            main.M = split_rows;
-            tail.m_begin = split_rows;
-            hipError_t rc = launch_gemm_dma_bf16(split_kind, main, amode, s);
-            if (rc != hipSuccess) return rc;
-            float unused;
-            return launch_picked(tail, amode, s, pick_tile(cands, tail, amode, unused));
-        }
     }
-    return launch_picked(a, amode, s, whole);
+    return plan;
 }
 
+GemmPlan plan_gemm_bf16(const GemmArgs& a, int amode) { return amode == A_CONV3 ? plan_among(kConv, a, amode) : plan_among(kPlain, a, amode); }
+
+static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best);
+
 hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
-    return amode == A_CONV3 ? launch_chosen(kConv, a, amode, s) : launch_chosen(kPlain, a, amode, s);
+    const GemmPlan plan = plan_gemm_bf16(a, amode);
+    if (!plan.lead_kind) return launch_picked(a, amode, s, plan.kind);
+    GemmArgs lead = a, tail = a;
+    lead.M = tail.m_begin = plan.lead_rows;
+    const hipError_t rc = launch_gemm_dma_bf16(plan.lead_kind, lead, amode, s);
+    return rc != hipSuccess ? rc : launch_picked(tail, amode, s, plan.kind);
 }
 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best) {

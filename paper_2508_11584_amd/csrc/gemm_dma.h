@@ -701,6 +701,7 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
         configured = true;
     }
     if (configure_only) return hipSuccess;
+    if (a.K < BK || a.K % BK || (amode == A_CONV3 && a.cC % BK)) return hipErrorInvalidValue;      // the k loop has no remainder
     if (amode == A_CONV3 ? a.epi != EPI_STORE && a.epi != EPI_ROWDOT : a.epi < EPI_STORE || a.epi > EPI_PATCH) return hipErrorInvalidValue;
     const Kernel k = amode == A_CONV3 ? conv[a.epi == EPI_ROWDOT] : plain[a.epi];
     GemmArgs args = a;

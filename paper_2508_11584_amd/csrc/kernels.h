@@ -10,6 +10,10 @@
 namespace vpe {
 
 hipError_t launch_gemm(int dtype, const GemmArgs& a, int amode, hipStream_t s);
+// How launch_gemm takes a bf16 problem: one launch of the tiling `kind`, or, with lead_kind != 0, that tiling over the rows in front of
+// lead_rows and `kind` over the others (host arithmetic only; the strip convolution may still take a whole problem's place).
+struct GemmPlan { int lead_kind, lead_rows, kind; };
+GemmPlan plan_gemm_bf16(const GemmArgs& a, int amode);
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t configure_attention();
 hipError_t configure_gemm();

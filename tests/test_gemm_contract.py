@@ -82,6 +82,42 @@ def test_tile_map_reciprocals_are_exact(tmp_path):
     run_host_program(tmp_path, MAP_PROGRAM)
 
 
+PLAN_PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace vpe;
+int main() {
+    int bad = 0, two = 0;
+    auto check = [&](const GemmArgs& a, int amode) {
+        const GemmPlan p = plan_gemm_bf16(a, amode);
+        const int per_tile = amode == A_CONV3 ? a.cC : a.K;                 // what a k-tile has to divide
+        for (int kind : {p.lead_kind, p.kind})
+            if ((kind == 43 || kind == 33) && per_tile % 128) { printf("mode %d K %d cC %d N %d M %d: kind %d\n", amode, a.K, a.cC, a.N, a.M, kind); ++bad; }
+        two += p.lead_kind != 0;
+        if (p.lead_kind && (p.lead_rows <= 0 || p.lead_rows >= a.M || p.lead_rows % 32)) { printf("M %d: lead of %d rows\n", a.M, p.lead_rows); ++bad; }
+    };
+    for (int k = 64; k <= 4096; k += 64)
+        for (int n : {21, 64, 128, 192, 256, 320, 576, 960, 1536, 3072})
+            for (double m = 40; m < 3e5; m *= 1.07) {
+                GemmArgs a{};
+                a.M = (int)m; a.N = n; a.K = k; a.nz = 1;
+                for (int epi : {EPI_STORE, EPI_RESID}) { a.epi = epi; check(a, A_PLAIN); }
+                if (k > 1536) continue;
+                a.epi = EPI_STORE; a.cC = k; a.K = 9 * k;
+                check(a, A_CONV3);
+            }
+    printf("%d problems in two launches\n", two);
+    return bad ? 1 : two == 0;
+}
+"""
+
+
+def test_plans_use_tilings_whose_k_tiles_divide_the_problem(tmp_path):
+    # 128-deep k-tiles (kinds 43 and 33) only where they divide K, of a convolution its channels, as the leading part of a
+    # two-launch form, too; over k extents of odd and even multiples of 64
+    run_host_program(tmp_path, PLAN_PROGRAM)
+
+
 GELU_PROGRAM = r"""
 #include <cmath>
 #include <cstdio>
