@@ -65,6 +65,11 @@ static bool admissible(const TileModel& c, const GemmArgs& a, int amode) {
     return !(c.kind == 3 && deep);
 }
 
+// What `tiles` tiles of a tiling count as, in us: a whole launch, a leading part and a tail by the same measure.
+static float tile_cost(const TileModel& c, const GemmArgs& a, int amode, int64_t tiles) {
+    return tile_time(c, tiles, a.K, epilogue_weight(a)) * (amode == A_CONV3 && c.bm <= 64 ? kConvShared : 1.0f);
+}
+
 // The model's pick for rows m_begin .. M - 1 of `a` and its predicted time in us.
 template <int NC>
 static int pick_tile(const TileModel (&cands)[NC], const GemmArgs& a, int amode, float& best_cost) {
@@ -72,7 +77,7 @@ static int pick_tile(const TileModel (&cands)[NC], const GemmArgs& a, int amode,
     best_cost = 0.0f;
     for (const TileModel& c : cands) {
         if (!admissible(c, a, amode)) continue;
-        const float cost = tile_time(c, tile_count(c, a), a.K, epilogue_weight(a)) * (amode == A_CONV3 && c.bm <= 64 ? kConvShared : 1.0f);
+        const float cost = tile_cost(c, a, amode, tile_count(c, a));
         if (best_cost == 0.0f || cost < best_cost) { best_cost = cost; best = c.kind; }
     }
     return best;
@@ -94,7 +99,7 @@ static GemmPlan plan_among(const TileModel (&cands)[NC], const GemmArgs& a, int 
             if (rounds < 1 || tiles % 256 == 0) continue;
             const int tm_main = rounds * 256 / tn;              // whole tile rows in `rounds` rounds
             if (tm_main < 1 || tm_main >= tm) continue;
-            const float main_cost = tile_time(c, (int64_t)tm_main * tn, a.K, epilogue_weight(a));
+            const float main_cost = tile_cost(c, a, amode, (int64_t)tm_main * tn);
             GemmArgs tail = a;
             tail.m_begin = tm_main * c.bm;
             float tail_cost;

@@ -118,6 +118,31 @@ def test_plans_use_tilings_whose_k_tiles_divide_the_problem(tmp_path):
     run_host_program(tmp_path, PLAN_PROGRAM)
 
 
+CONV_PLAN_PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace vpe;
+int main() {
+    int bad = 0;
+    struct { int cC, N, M; bool two; } towers[] = {{768, 512, 4216, false}, {768, 512, 4 * 33 * 33, false}, {1024, 512, 4 * 46 * 46, false},
+                                                   {1536, 512, 5776, false}, {1536, 256, 8 * 39 * 39, false}, {1024, 512, 4232, true}};
+    for (auto& t : towers) {
+        GemmArgs a{};
+        a.M = t.M; a.N = t.N; a.cC = t.cC; a.K = 9 * t.cC; a.nz = 1; a.epi = EPI_STORE; a.act = ACT_RELU;
+        const GemmPlan p = plan_gemm_bf16(a, A_CONV3);
+        if ((p.lead_kind != 0) != t.two) { printf("%d -> %d channels, %d pixels: lead %d of %d rows, rest %d\n", t.cC, t.N, t.M, p.lead_kind, p.lead_rows, p.kind); ++bad; }
+    }
+    return bad;
+}
+"""
+
+
+def test_leading_parts_of_convolutions_count_what_a_whole_launch_counts(tmp_path):
+    # detection towers just above a round of 64 x 128 tiles: their leading part carries the factor that tiles of up to 64
+    # rows carry beside an encoder, so that two launches are taken only where they win by it
+    run_host_program(tmp_path, CONV_PLAN_PROGRAM)
+
+
 GELU_PROGRAM = r"""
 #include <cmath>
 #include <cstdio>
