@@ -45,7 +45,7 @@ struct GemmArgs {
     int a_rpi, a_istride, a_off;
     int cH, cW, cC;      // CONV3 grid and channels (K = 9 cC, cC multiple of 64)
     const void* zeros;   // CONV3: >= 16 bytes of zeros, read in place of out-of-image taps
-    int epi, act, out_f32;         // (CONV3: STORE or ROWDOT, without a folded LayerNorm)
+    int epi, act, out_f32;         // (CONV3: STORE or ROWDOT, without a folded LayerNorm; PLAIN: all but ROWDOT)
     void* out;           // T or float (out_f32); RESID/PATCH: float residual stream
     int64_t ldo;
     int o_rpi, o_istride, o_off;   // output row map, as for A
@@ -59,7 +59,7 @@ struct GemmArgs {
     // been scaled by the LayerNorm gain along k and bias holds b + beta W; the accumulator of (row r, column c)
     // becomes rstd_r * (acc - mean_r * ln_colsum[c]) before bias / activation, with ln_colsum[c] = sum_k W[c][k].
     // ln_stats [M][ln_groups][2]: (mean, sum of squared deviations from it) of every 64-column group of row r,
-    // as written by the producer below; both sides work with differences, never with raw squares.
+    // as written by the producer below; both sides work with differences, never with raw squares.  Not with RESID or PATCH.
     const float* ln_stats;     // null: no LayerNorm
     const float* ln_colsum;
     int ln_groups;             // = K / 64

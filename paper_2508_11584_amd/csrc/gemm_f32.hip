@@ -51,7 +51,10 @@ hipError_t launch_f32(int kind, const GemmArgs& a, int amode, hipStream_t s, boo
 hipError_t launch_gemm(int dtype, const GemmArgs& a, int amode, hipStream_t s) {
     // the k loops have no remainder, and a k-tile of a convolution belongs to one tap
     if (a.K < 64 || a.K % 64 || (amode == A_CONV3 && (a.cC % 64 || a.K != 9 * a.cC))) return hipErrorInvalidValue;
-    // convolution kernels carry the epilogues that convolutions have
+    // convolution kernels carry the epilogues that convolutions have, the others all but the projection; the folded LayerNorm belongs to
+    // the epilogues without a residual stream
+    if (amode == A_PLAIN && (a.epi < EPI_STORE || a.epi > EPI_PATCH)) return hipErrorInvalidValue;
+    if (a.ln_stats && (a.epi == EPI_RESID || a.epi == EPI_PATCH)) return hipErrorInvalidValue;
     if (amode == A_CONV3 && ((a.epi != EPI_STORE && a.epi != EPI_ROWDOT) || a.ln_stats)) return hipErrorInvalidValue;
     if (dtype) return launch_gemm_bf16(a, amode, s);
     int best = 3;

@@ -33,6 +33,17 @@ int main() {
         const hipError_t rc = launch_gemm(1, a, A_CONV3, nullptr);
         if (rc != hipErrorInvalidValue) { printf("convolution with epilogue %d: %d\n", epi, (int)rc); ++bad; }
     }
+    // the projection epilogue belongs to convolutions, the folded LayerNorm to the epilogues without a residual stream
+    const float stats[2] = {0.0f, 1.0f};
+    for (int epi : {EPI_RESID, EPI_PATCH, EPI_ROWDOT})
+        for (int dtype = 0; dtype < 2; ++dtype) {
+            GemmArgs a{};
+            a.M = a.N = a.K = 64;
+            a.lda = a.ldo = 64; a.a_rpi = a.o_rpi = 64; a.nz = 1; a.epi = epi;
+            if (epi != EPI_ROWDOT) { a.ln_stats = stats; a.ln_groups = 1; }
+            const hipError_t rc = launch_gemm(dtype, a, A_PLAIN, nullptr);
+            if (rc != hipErrorInvalidValue) { printf("dtype %d, epilogue %d of a plain product: %d\n", dtype, epi, (int)rc); ++bad; }
+        }
     return bad;
 }
 """
