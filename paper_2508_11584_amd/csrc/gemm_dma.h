@@ -83,7 +83,7 @@ struct EpilogueRows {
 // each block (row lane % 32, columns 8 (v / 4) + 4 (lane / 32) + v % 4 of every 32), so a block is staged with 16-byte writes, a quarter of
 // the instructions of a layout with a column per lane, and the folded LayerNorm is applied where the chunks are read.
 // lnrow: LDS for (mean, rstd) per tile row.
-template <typename T, int EPI, int BM, int MI, int NI, int WM, int WN, bool PADDED = false, int BATCH = 4>
+template <typename T, int EPI, int BM, int MI, int NI, int WM, int WN, bool PADDED = false>
 __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, float* lnrow,
                                                    int wave, int wm, int wn, int tid, int m0, int n0) {
     const int lane = tid & 63, g = lane >> 5, li = lane & 31;
@@ -109,8 +109,10 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
     };
     auto row_stats = [&](int row) { return *reinterpret_cast<const f32x2*>(lnrow + 2 * row); };     // (of a tile row)
     // The row-chunk paths: a lane keeps one 8-column chunk (64 is a multiple of the chunks per row) for all its rows
-    // (96 x 128 wave tiles have registers for two rows at a time, and none for the columns while all blocks wait)
-    constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < BATCH ? ITS : BATCH;
+    // Four rows at a time (one at a time cost 128 x 128 tiles of eight waves 1.2-2.1 us a launch, 64 x 128 ones 1.2-2.2: ViT-L 1370 tokens
+    // out-projection 14.9 / 12.8 and 11.7 / 10.3; their k loops need more registers than the rows do).  96 x 128 wave
+    // tiles have registers for two, and none for the columns while all blocks wait.
+    constexpr int CG = WN / 8, ITS = 32 * CG / 64, NB = MI * NI >= 12 ? 2 : ITS < 4 ? ITS : 4;
     static_assert(64 % CG == 0 && ITS % NB == 0, "a lane keeps its column chunk");
     // One pass per 32-row block of the wave tile; the block index is a compile-time constant of each pass (a loop over the
     // blocks turns the accumulators into an indexed array in scratch, or spills them).
@@ -674,7 +676,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
     } else if constexpr (EPI == EPI_ROWDOT) {
         rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
     } else {
-        wave_tile_epilogue<T, EPI, BM, MI, NI, WM, WN, false, (OCC * NW > 8 ? 1 : 4)>(p, acc, smem, lnrow, wave, wm, wn, tid, m0, n0);
+        wave_tile_epilogue<T, EPI, BM, MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, tid, m0, n0);
     }
 }
 
