@@ -223,7 +223,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC * WGM * WGN / 4) void conv_stri
     if constexpr (ROWDOT) {
         rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, true>(p, acc, smem, wm, wn, tid, m0, n0);
     } else {
-        wave_tile_epilogue<bf16, EPI_STORE, BM, MI, NI, WM, WN, true>(p, acc, smem, nullptr, wave, wm, wn, tid, m0, n0);
+        wave_tile_epilogue<bf16, EPI_STORE, BM, MI, NI, WM, WN, false, true>(p, acc, smem, nullptr, wave, wm, wn, tid, m0, n0);
     }
 }
 

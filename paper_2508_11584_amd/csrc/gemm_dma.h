@@ -82,14 +82,14 @@ struct EpilogueRows {
 // read of them) and leaves with 8-column chunks per lane.  The MFMAs took the W operand first: a lane holds one row of
 // each block (row lane % 32, columns 8 (v / 4) + 4 (lane / 32) + v % 4 of every 32), so a block is staged with 16-byte writes, a quarter of
 // the instructions of a layout with a column per lane, and the folded LayerNorm is applied where the chunks are read.
-// lnrow: LDS for (mean, rstd) per tile row.
-template <typename T, int EPI, int BM, int MI, int NI, int WM, int WN, bool PADDED = false>
+// lnrow: LDS for (mean, rstd) per tile row.  LN: a folded LayerNorm is possible (convolutions have none).
+template <typename T, int EPI, int BM, int MI, int NI, int WM, int WN, bool LN, bool PADDED = false>
 __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&acc)[MI][NI], char* smem, float* lnrow,
                                                    int wave, int wm, int wn, int tid, int m0, int n0) {
     const int lane = tid & 63, g = lane >> 5, li = lane & 31;
     float* sC = reinterpret_cast<float*>(smem) + wave * (32 * WN);
     const int wrow0 = m0 + wm * WM, wcol0 = n0 + wn * WN;
-    const bool has_ln = EPI != EPI_RESID && EPI != EPI_PATCH && p.ln_stats;
+    const bool has_ln = LN && EPI != EPI_RESID && EPI != EPI_PATCH && p.ln_stats;
     // 4-column groups of a row are exchanged by the row: 16 consecutive rows writing one group, and the four 8-row blocks
     // that a transposed value read takes at once, fall on different banks
     auto at = [&](int row, int col) { return row * WN + (col ^ ((((row & 15) ^ ((row >> 3) << 2)) & 15) << 2)); };
@@ -222,9 +222,12 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
         }
     };
     if (has_ln) {
+        // (the statistics of 96 x 128 wave tiles find registers when the first block has left its own; before it, 68 bytes a lane went to
+        // scratch: 384 x 256 tiles, QKV of ViT-L 5496 tokens 60.8 us, now 58.5, ViT-g 10992 225 / 216)
         LnTile<BM> ln;
-        ln.ask(p, m0, tid);
+        if (MI * NI < 12) ln.ask(p, m0, tid);
         stage(std::integral_constant<int, 0>{});
+        if (MI * NI >= 12) ln.ask(p, m0, tid);
         ln.leave(p, lnrow, m0, n0, tid);
         __syncthreads();
     } else {
@@ -672,11 +675,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, OCC * WGM * WGN * KG / 4) void
         }
     }
     if constexpr (BLOCK) {                                    // (whole tile staged in LDS)
-        block_epilogue<T, EPI, BM, BN, WGM, WGN, KG>(p, acc, smem, lnrow, m0, n0);
+        block_epilogue<T, EPI, BM, BN, WGM, WGN, KG, AMODE == A_PLAIN>(p, acc, smem, lnrow, m0, n0);
     } else if constexpr (EPI == EPI_ROWDOT) {
         rowdot_epilogue_transposed<MI, NI, WM, WN, BN, 64 * NW, false>(p, acc, smem, wm, wn, tid, m0, n0);
     } else {
-        wave_tile_epilogue<T, EPI, BM, MI, NI, WM, WN>(p, acc, smem, lnrow, wave, wm, wn, tid, m0, n0);
+        wave_tile_epilogue<T, EPI, BM, MI, NI, WM, WN, AMODE == A_PLAIN>(p, acc, smem, lnrow, wave, wm, wn, tid, m0, n0);
     }
 }
 
