@@ -308,22 +308,54 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     constexpr int PPT = G / NW > 0 ? G / NW : 1;       // passes of the workgroup over one tile
     constexpr int NDMA = KW * 2 * G / NW;              // instructions per wave per iteration
     constexpr int KEYS = 1, VALUES = 2;
-    static_assert((G % NW == 0 && (NW * RPI) % 16 == 0) || NW == G, "loader mapping");
+    static_assert(G % NW == 0 && (NW * RPI) % 16 == 0, "loader mapping: a tile is whole passes of the workgroup");
     const int drow = wave * RPI + lane / CPR;
     const int dlc = AttnMma<T>::chunk_at(drow, lane % CPR);          // (exclusive or with the row's term: its own inverse)
-    // (scalar addresses of the rows and 32 bits of a lane's own offset)
+    // Scalar addresses of the rows and 32 bits of a lane's own offset.  As constants of the key loop the compiler keeps an iteration's
+    // row addresses and places in LDS in scalar registers; of 16 and more instructions it spills up to 149 of them, 64 moves an
+    // iteration of fp32 (1,1,4).  There they run (RUN): keys down their rows, values down a tile's rows and on to the next tile,
+    // opaque after every step (us, held / running: fp32 54 pairs 12.6 / 11.9, 288 41.8 / 41.4, 1032 117.2 / 115.9; bf16 54 pairs
+    // 5.9 / 5.6).  Shapes of up to eight are faster with held ones (fp32 (1,4,1) 3096 pairs 716 / 721, bf16 (1,2,2) 516 16.6 / 16.7).
+    constexpr bool RUN = NDMA > 8;
+    typedef __attribute__((address_space(3))) char LdsChar;
     const uint32_t koff = (uint32_t)(drow * ld + dlc * CE) * sizeof(T), voff = (uint32_t)(drow * p.npad + dlc * CE) * (uint32_t)sizeof(T);
+    auto load = [&](const char* src, LdsChar* dst) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    };
     auto dma = [&](char* base, int it, int kinds) {    // tiles of iteration `it` into the stage at `base`: KEYS, VALUES or both
         const int64_t ka = (int64_t)it * KW * 64 * ld;
         const int va = it * KW * 64;
+        if constexpr (RUN) {
+            const int64_t kstep = (int64_t)NW * RPI * ld, vstep = (int64_t)NW * RPI * p.npad;
+            const T* krow = kbase + ka;
+            const T* vtile = vt + va;
+            const T* vrow = vtile;
+            LdsChar* dst = (LdsChar*)(base + wave * 1024);
 #pragma unroll
-        for (int i = 0; i < NDMA; ++i) {
-            const int ti = i / PPT, pass = i % PPT, j = ti >> 1, which = ti & 1, r0 = pass * NW * RPI;
-            if (!((kinds >> which) & 1)) continue;
-            const T* row = which ? vt + (int64_t)r0 * p.npad + j * 64 + va : kbase + (int64_t)(j * 64 + r0) * ld + ka;
-            const char* src = reinterpret_cast<const char*>(row) + (which ? voff : koff);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(base + (wave + NW * i) * 1024), 16, 0, 0);
+            for (int i = 0; i < NDMA; ++i, dst += NW * 1024) {
+                const int which = (i / PPT) & 1, pass = i % PPT;
+                if (!((kinds >> which) & 1)) continue;
+                asm("" : "+s"(dst));
+                load(reinterpret_cast<const char*>(which ? vrow : krow) + (which ? voff : koff), dst);
+                if (!which) {
+                    krow += kstep;
+                    asm("" : "+s"(krow));
+                } else if (pass + 1 < PPT) {
+                    vrow += vstep;
+                    asm("" : "+s"(vrow));
+                } else {
+                    vtile += 64;
+                    vrow = vtile;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NDMA; ++i) {
+                const int ti = i / PPT, j = ti >> 1, which = ti & 1, r0 = (i % PPT) * NW * RPI;
+                if (!((kinds >> which) & 1)) continue;
+                const T* row = which ? vt + (int64_t)r0 * p.npad + j * 64 + va : kbase + (int64_t)(j * 64 + r0) * ld + ka;
+                load(reinterpret_cast<const char*>(row) + (which ? voff : koff), (LdsChar*)(base + (wave + NW * i) * 1024));
+            }
         }
     };
     // Two buffers: the loads of iteration it + 1 are issued at the top of iteration it into the buffer that was read

@@ -35,3 +35,10 @@ def test_no_kernel_keeps_registers_in_scratch_memory():
     spilled = [(k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in found
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
     assert not spilled, spilled
+
+
+def test_scalar_registers_of_the_kernels():
+    # (what a spilled scalar register costs depends on where it is read: the attention kernels may keep up to 32 for what follows
+    # their key loop; with an iteration's load addresses among them they kept 67 and 149, read back in every iteration)
+    spilled = {k[".name"]: k[".sgpr_spill_count"] for k in kernels() if k[".sgpr_spill_count"]}
+    assert all("attention_kernel" in name and n <= 32 for name, n in spilled.items()), spilled
