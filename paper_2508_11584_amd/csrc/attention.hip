@@ -79,7 +79,11 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     //   348 (ViT-S 602x602)       72.4 53.8 99.9, 58.3           516 (ViT-B 518x518) 116.3 / 84 77 80.6, 91.1
     //   1032 (ViT-S 518x518 x4) 192 / 139 115.5 122.5, 129       2064 (ViT-B 518x518 x4) 280 / 252 196 203, 237
     //   3096 (ViT-S 896x896 x4) 973 763 704
-    int v32 = qblocks <= 256 ? 114 : qblocks <= 2560 ? 124 : 141;
+    // Beside another lane's kernels (1,4,1) leaves half a CU.  Frames of two lanes, us, (1,2,4) / (1,4,1), without and with a depth head:
+    //   288 1038 / 1366, 2003 / 2273   516 2317 / 2319   576 - , 3395 / 3435   696 2169 / 2187   774 2176 / 2165, 4786 / 4773
+    //   864 2390 / 2262   1032 2799 / 2678, 5803 / 5944   1152 3169 / 3077, 6767 / 6634   1290 3300 / 3161, 7292 / 7181   1548
+    //   (ViT-B) 5944 / 5771, 8391 / 8267   2064 8084 / 7866, 11510 / 11377
+    int v32 = qblocks <= 256 ? 114 : qblocks <= (a.shared_gpu ? 768 : 2560) ? 124 : 141;
     if (forced == 114 || forced == 124 || forced == 141) v32 = forced;
     return launch_variant<float>(v32, a, s);
 }

@@ -458,12 +458,17 @@ def test_attention_with_peaked_softmax(dtype, variant, scale, monkeypatch):
     assert rep["b0.feat3"] > 0.0
 
 
-@pytest.mark.parametrize("gh,gw,batch,lanes", [(7, 9, 1, 1), (8, 8, 1, 1), (16, 16, 7, 1), (16, 16, 8, 1), (16, 16, 13, 1), (16, 16, 3, 2), (16, 16, 4, 2)])
-def test_attention_on_both_sides_of_its_shape_lines(gh, gw, batch, lanes):
-    # 64, 65 and 257 tokens of a view: a whole key tile, a key more, one more than a round of four key waves.  252, 288 and 468
-    # pairs of a head and a block of 32 queries: below the line of 256, above it, and above 256 workgroups of 64 queries; 108
-    # and 144 beside a second lane (line 128).  Sharp scores, so a lost or doubled key shows; the gates of every bf16 model.
-    spec = vi.ModelSpec("attn_line_%d_%d_%d" % (gh, gw, batch), dtype="bf16",
+@pytest.mark.parametrize("dtype,gh,gw,batch,lanes", [
+    ("bf16", 7, 9, 1, 1), ("bf16", 8, 8, 1, 1), ("bf16", 16, 16, 7, 1), ("bf16", 16, 16, 8, 1), ("bf16", 16, 16, 13, 1), ("bf16", 16, 16, 3, 2),
+    ("bf16", 16, 16, 4, 2), ("bf16", 16, 16, 56, 1), ("bf16", 16, 16, 57, 1), ("bf16", 16, 16, 57, 2), ("f32", 16, 16, 7, 1), ("f32", 16, 16, 8, 1),
+    ("f32", 16, 16, 21, 2), ("f32", 16, 16, 22, 2), ("f32", 8, 8, 213, 1), ("f32", 8, 8, 214, 1)])
+def test_attention_on_both_sides_of_its_shape_lines(dtype, gh, gw, batch, lanes):
+    # 64, 65 and 257 tokens of a view: a whole key tile, a key more, one more than a round of four key waves.  Pairs of a head and a
+    # block of 32 queries, bf16: 252, 288 and 468: below the line of 256, above it, and above 256 workgroups of 64 queries; 108
+    # and 144 beside a second lane (line 128); 2016 and 2052 (line 2048, with and without a second lane).  fp32: 252 and 288 (256),
+    # 756 and 792 beside a second lane (768), 2556 and 2568 (2560).  Sharp scores, so a lost or doubled key shows; the gates
+    # of every model of the type.
+    spec = vi.ModelSpec("attn_line_%s_%d_%d_%d" % (dtype, gh, gw, batch), dtype=dtype,
                         **{**SHARP, "dim": 256, "heads": 4, "img_h": 14 * gh, "img_w": 14 * gw, "batch": batch})
     rep = check_all(spec, 151, 251, kinds=("seg",), batch_check=sorted({0, batch - 1}), weights_edit=_sharpen(16.0),
                     encoder_lanes=lanes, ring_slots=lanes + 1)
