@@ -143,6 +143,14 @@ int main() {
         const GemmPlan p = plan_gemm_bf16(a, A_CONV3);
         if ((p.lead_kind != 0) != t.two) { printf("%d -> %d channels, %d pixels: lead %d of %d rows, rest %d\n", t.cC, t.N, t.M, p.lead_kind, p.lead_rows, p.kind); ++bad; }
     }
+    // the two products that tests/test_gpu_parity.py runs in two launches
+    for (int conv = 0; conv < 2; ++conv) {
+        GemmArgs a{};
+        a.M = conv ? 4232 : 2180; a.N = conv ? 512 : 1024; a.cC = 1024; a.K = conv ? 9 * 1024 : 4096; a.nz = 1;
+        a.epi = conv ? EPI_STORE : EPI_RESID; a.act = conv ? ACT_RELU : ACT_NONE;
+        const GemmPlan p = plan_gemm_bf16(a, conv ? A_CONV3 : A_PLAIN);
+        if (p.lead_kind != 6 || p.lead_rows != (conv ? 4096 : 2048) || p.kind != 33) { printf("conv %d: lead %d of %d rows, rest %d\n", conv, p.lead_kind, p.lead_rows, p.kind); ++bad; }
+    }
     return bad;
 }
 """

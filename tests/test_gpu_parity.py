@@ -203,10 +203,11 @@ def test_cfg2_in_the_pipelined_configuration_the_benchmark_times():
     check_all(spec, *vi.SEEDS["cfg2"], flags=vpe.VPE_FLAG_GRAPHS, lead_frames=6, ring_slots=4, encoder_lanes=3)
 
 
-@pytest.mark.parametrize("tile", ["384", "256", "128", "129", "65", "64", "5", "4"])
+@pytest.mark.parametrize("tile", ["384", "256", "128", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_variant(tile, monkeypatch):
-    # each bf16 GEMM shape (384 x 256, 256 x 256, 256 x 128, 64 x 128, 64 x 64 tiles; "5" and "4": 64 x 128 and 64 x 64 whose two and
-    # four wave groups share the k-steps of every k-tile), forced for every GEMM of the model,
+    # each bf16 GEMM shape (384 x 256, 256 x 256, 64 x 128, 64 x 64 tiles; "5" and "4": 64 x 128 and 64 x 64 whose two and four wave
+    # groups share the k-steps of every k-tile; "128": the name of a former shape, which stands for 128 x 128 tiles, "2"), forced
+    # for every GEMM of the model,
     # through every epilogue: folded LayerNorm + QKV with transposed values, LayerScale residual with row
     # statistics, GELU and SwiGLU, patch embedding, 1x1 and 3x3 convolutions, the fused 1-channel projection
     monkeypatch.setenv("VPE_GEMM_TILE", tile)
@@ -216,7 +217,7 @@ def test_direct_to_lds_gemm_variant(tile, monkeypatch):
     check_all(spec, 103, 203)
 
 
-@pytest.mark.parametrize("tile", ["384", "256", "128", "129", "65", "64", "5", "4"])
+@pytest.mark.parametrize("tile", ["384", "256", "65", "64", "5", "4"])
 def test_direct_to_lds_gemm_with_fewer_k_tiles_than_stages(tile, monkeypatch):
     # one k-tile (width 64), three (MLP of 192) and nine (3x3 convolutions of 64 channels): pipelines whose first loads
     # already run past the last k-tile; 35 + 3 tokens a view, so that tiles and 8-row groups straddle two views; QKV width
@@ -251,7 +252,7 @@ def test_layernorm_statistics_of_odd_and_of_many_groups(width, dtype):
                            img_h=70, img_w=98, taps=(1, 2, 3, 4), head_ch=64), 148, 248, kinds=("seg",))
 
 
-@pytest.mark.parametrize("variant", ["114", "122", "141", "124"])        # (122 is a bf16 shape: the choice by size)
+@pytest.mark.parametrize("variant", ["114", "141", "124"])
 def test_fp32_attention_shapes(variant, monkeypatch):
     # every workgroup shape of the fp32 attention: 38 tokens a view (one ragged key tile, fewer than the key waves), and 166
     # (three tiles, the last of 38 keys: key waves with unequal numbers of tiles); fp32 gates
@@ -425,6 +426,35 @@ def test_eight_detection_heads_in_the_pipelined_configuration():
               encoder_lanes=3)
 
 
+# ---------------------------------------------------------------- products in two launches
+@pytest.mark.parametrize("gh,gw,batch,kinds", [(33, 33, 2, ("seg",)), (46, 46, 2, ("det",))])
+def test_two_launches_with_a_leading_part_of_64_row_tiles(gh, gw, batch, kinds, monkeypatch):
+    # width 1024: fc2 of 2180 tokens and a detection tower on 4232 cells (tests/test_gemm_contract.py holds that these shapes go out as
+    # 64 x 128 tiles in four wave groups over 2048 and 4096 rows and 32 x 64 tiles over the others).  Against an engine
+    # with one launch per product: the gates of every bf16 model, and bit-equal repeats
+    spec = vi.ModelSpec("two_launches_%d" % gh, dtype="bf16", dim=1024, depth=4, heads=16, mlp_hidden=4096, img_h=14 * gh, img_w=14 * gw,
+                        batch=batch, taps=(1, 2, 3, 4), head_ch=256)
+    weights, images = vi.make_backbone_weights(spec, 161), vi.make_batch(spec, 261)
+    results = []
+    for one_launch in (False, True):
+        if one_launch:
+            monkeypatch.setenv("VPE_NO_ROW_SPLIT", "1")
+        eng, _, _ = make_engine(spec, 161, kinds=kinds, weights=weights)
+        got = []
+        for _ in range(1 if one_launch else 2):
+            _, feats = run_gpu(eng, images, 1)
+            got.append((feats[3], head_outputs(eng, kinds)[0][0]))
+        eng.close()
+        assert all(np.array_equal(a, b) for a, b in zip(got[0], got[-1]))
+        results.append(got[0])
+    (f2, o2), (f1, o1) = results
+    print("features", relerr(f2, f1), "head", relerr(o2, o1), flush=True)
+    assert relerr(f2, f1) <= TOL["bf16"] and relerr(o2, o1) <= TOL["bf16"]
+    for rows in (slice(0, 64), slice(-64, None)):                # (a lost tail would hide in a maximum over everything)
+        a, b = f2.reshape(-1, spec.dim)[rows], f1.reshape(-1, spec.dim)[rows]
+        assert relerr(a, b) <= TOL["bf16"]
+
+
 # ---------------------------------------------------------------- attention far from uniform
 SHARP = dict(dim=128, depth=4, heads=2, mlp_hidden=256, img_h=14 * 18, img_w=14 * 20, taps=(1, 2, 3, 4), head_ch=64)
 
@@ -444,7 +474,7 @@ def _sharpen(scale):
 @pytest.mark.parametrize("dtype,variant,scale", [("bf16", "124", 16.0), ("bf16", "224", 16.0), ("bf16", "141", 16.0),
                                                  ("bf16", "114", 16.0), ("bf16", "214", 16.0), ("bf16", "122", 16.0),
                                                  ("bf16", "", 16.0),
-                                                 ("f32", "114", 32.0), ("f32", "122", 32.0), ("f32", "141", 32.0), ("f32", "124", 32.0)])
+                                                 ("f32", "114", 32.0), ("f32", "141", 32.0), ("f32", "124", 32.0)])
 def test_attention_with_peaked_softmax(dtype, variant, scale, monkeypatch):
     # 361 tokens = six key tiles of 64 (the last with 41 keys): with four key waves two of them own two tiles.
     # With the benchmark's weights every score lies within a fraction of a unit of the others, so the running
@@ -480,13 +510,13 @@ def _gelu_exact(v):
     return np.array([0.5 * x * math.erfc(-x / math.sqrt(2.0)) for x in np.asarray(v, dtype=np.float64)])
 
 
-@pytest.mark.parametrize("lo,hi,gate", [(-3.5, -3.0, 1.1e-5), (-4.2, -3.5, 1.3e-5)])
+@pytest.mark.parametrize("lo,hi,gate", [(-3.5, -3.0, 5.5e-6), (-4.2, -3.5, 3.5e-6)])
 def test_gelu_of_bf16_results_where_it_is_nearly_zero(lo, hi, gate):
     # One block whose second MLP product is the identity, fed by biases alone: the residual stream is GELU(v) of 256 known
     # v, beside 256 exact anchors between 0 and -0.005 whose straight-line fit undoes the final LayerNorm.  Gate: rms error of
-    # the rounded value.  Its polynomial gives 6.5e-6 and 1.0e-5, rounding to bf16 3.6e-6 and 0.6e-6, the features' own
-    # rounding (2^-9 / sqrt 3 of values up to 2e-3 from the mean) up to 2e-6: 7.7e-6 and 1.05e-5 together.  A fit with the
-    # same largest error over all v that is worse on these intervals gave 1.8e-5 on both.
+    # the rounded value.  The form itself gives 8e-7 and 1.6e-6, rounding to bf16 3.6e-6 and 0.6e-6, the features' own rounding
+    # (2^-9 / sqrt 3 of values up to 2e-3 from the mean) up to 2e-6: 4.2e-6 and 2.6e-6 together, and 1.3 times that as the
+    # gate.  erf as an odd polynomial, 6.5e-6 and 1.0e-5 before rounding, gives 7.7e-6 and 1.05e-5 and fails both.
     D = 512
     spec = vi.ModelSpec("gelu_tail", dtype="bf16", dim=D, depth=4, heads=8, mlp_hidden=D, img_h=14, img_w=14, taps=(1, 2, 3, 4))
     w = vi.make_backbone_weights(spec, 1)
@@ -550,7 +580,7 @@ def test_fp32_head_weights_beyond_the_range_of_bf16(tile, monkeypatch):
     assert relerr(outs[1][0][0][..., :spec.det_classes].transpose(2, 0, 1), o["logits"]) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("variant", ["114", "122", "141", "124"])
+@pytest.mark.parametrize("variant", ["114", "141", "124"])
 def test_fp32_attention_keys_beyond_the_range_of_bf16(variant, monkeypatch):
     # one channel of every key at 3.4e38 against 1e-37 in the queries: the same 4.25 in every score, which the softmax does not see
     monkeypatch.setenv("VPE_ATTN_VARIANT", variant)
