@@ -18,7 +18,9 @@ bool g_no_small = false, g_no_splitk = false, g_no_strip = false, g_no_split = f
 // The tilings (launch_gemm_dma_bf16 describes them) with their time models (tile_model.h).
 // Plain GEMMs: fitted to QKV, out-projection, fc1 and fc2 of widths 384, 768, 1024 and 1536 (SwiGLU) with 145 ... 26000 tokens: 264
 // shapes, over which the picks cost 1.0 % more than the measured best in the geometric mean, more than 5 % on 23 of them and 15 % at
-// most (a model without the epilogue's weight, fitted to launches of one shape with its weights in the L2s: 7 %).
+// most (a model without the epilogue's weight, fitted to launches of one shape with its weights in the L2s: 7 %).  Fitted before the
+// residual epilogue of 2 and 65 had four rows in flight and before 384 and 5 kept their LayerNorm statistics in registers: the third
+// alpha of 2 and 65 is 1.2-2.4 us high, the first of 384 2, the second of 5 0.4-1.
 constexpr TileModel kPlain[] = {
     {256, 256, 256, 1, {13.69f, 16.34f, 20.09f}, 0.0f, 0.01249f, 0.00100f, 40.28f},
     {384, 384, 256, 1, {18.55f, 21.79f, 25.72f}, 0.0f, 0.02775f, 0.01000f, 52.75f},
@@ -49,8 +51,8 @@ constexpr TileModel kConv[] = {
     {33, 32, 64, 2, {3.59f, 3.59f, 3.59f}, 0.0f, 0.00225f, 0.00179f, 0.00f},
     {3, 32, 64, 3, {3.60f, 3.60f, 3.60f}, 0.0f, 0.00242f, 0.00188f, 0.00f},
 };
-// What a convolution's tile of up to 64 rows has to be faster by, alone, to be taken over a larger one: a head's convolutions run beside
-// encoder kernels, where operand traffic costs more than the time alone shows (ViT-S 476x630 frames of two lanes:
+// What a convolution's tile of up to 64 rows has to be faster by, alone, to be taken over a larger one, whatever else runs (the launcher
+// does not know): a head's convolutions run beside encoder kernels, where operand traffic costs more than the time alone shows (ViT-S 476x630 frames of two lanes:
 // 609 us without this, 591 with it; 256 -> 256 on 136x180 takes 37.7 us with 64 x 128 tiles and 40.5 with 128 x 128).
 constexpr float kConvShared = 1.12f;
 }  // namespace

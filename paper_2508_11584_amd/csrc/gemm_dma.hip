@@ -19,8 +19,8 @@ namespace vpe {
 //     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages;  43: the same with 128-deep k-tiles, three stages, one
 //        workgroup per CU: half the barriers
 //     3:  32 x 64, 4 waves in four groups (32 x 64 wave tiles), four stages, three per CU;  33: 128-deep k-tiles, three stages, two per CU
-// 3 to 6 are for problems with few tiles per CU, where a workgroup's own loop is the time: fixed cost (3.1 us of alpha for the
-// 32-row tiles, 3.7 for 64 x 64, 5.5 for 64 x 128) and the rate at which one CU loads (40-56 bytes a clock).  us, 64 x 64 in four
+// 3 to 6 are for problems with few tiles per CU, where a workgroup's own loop is the time: fixed cost (alpha of the time models in
+// gemm_bf16.hip, by epilogue: 3.1-4.0 us for the 32-row tiles, 3.7-4.3 for 64 x 64, 5.1-5.6 for 64 x 128) and the rate at which one CU loads (40-56 bytes a clock).  us, 64 x 64 in four
 // groups (4) / 32 x 64 (33): ViT-S 257 tokens QKV 5.2 / 4.9, out-projection 4.6 / 3.8, fc1 5.3 / 4.8, fc2 7.4 / 6.0; 3x3 convolution of
 // 256 channels on 34 x 45 12.4 / 9.1; ViT-S detection towers there 17.4, with 43 14.9; ViT-L 1370 tokens fc2 22.6 with 5, 21.1 with 6.
 // The one-per-CU shapes run in lockstep rounds, so they pay for a partly filled last round in full; which
