@@ -3,15 +3,29 @@ memory, and nothing in a result shows it."""
 import os
 import struct
 
-import msgpack
-
 import paper_2508_11584_amd as vpe
 
 LIB = os.path.join(os.path.dirname(os.path.abspath(vpe.__file__)), "libvpe.so")
+SIZES = {0xCC: ">B", 0xCD: ">H", 0xCE: ">I", 0xD9: ">B", 0xDA: ">H"}        # MessagePack: unsigned integers, strings
+
+
+def values(code, key):
+    """What follows every occurrence of a key in the AMDGPU note's MessagePack: a small unsigned integer or a string."""
+    out, at = [], 0
+    while (at := code.find(key, at)) >= 0:
+        at += len(key)
+        tag, p = code[at], at + 1
+        if tag in SIZES:
+            number, = struct.unpack_from(SIZES[tag], code, p)
+            p += struct.calcsize(SIZES[tag])
+        else:
+            number = tag & (0x1F if tag >= 0xA0 else 0x7F)
+        out.append(code[p:p + number].decode() if tag in (0xD9, 0xDA) or 0xA0 <= tag < 0xC0 else number)
+    return out
 
 
 def kernels():
-    """The metadata of every gfx950 kernel: the offload bundles' code objects, each with one AMDGPU note in msgpack."""
+    """(symbol, vector spills, scalar spills, bytes of scratch a lane) of every gfx950 kernel, from the offload bundles' code objects."""
     vpe.load_library()
     with open(LIB, "rb") as f:
         data = f.read()
@@ -22,8 +36,9 @@ def kernels():
             offset, size, length = struct.unpack_from("<QQQ", data, p)
             if b"gfx950" in data[p + 24:p + 24 + length]:
                 code = data[at + offset:at + offset + size]
-                note = code.find(b"AMDGPU\0\0")
-                out += msgpack.unpackb(code[note + 8:note + 8 + struct.unpack_from("<I", code, note - 8)[0]])["amdhsa.kernels"]
+                columns = [values(code, k) for k in (b".symbol", b".vgpr_spill_count", b".sgpr_spill_count", b".private_segment_fixed_size")]
+                assert columns[0] and len({len(c) for c in columns}) == 1
+                out += zip(*columns)
             p += 24 + length
         at += len(magic)
     return out
@@ -31,14 +46,13 @@ def kernels():
 
 def test_no_kernel_keeps_registers_in_scratch_memory():
     found = kernels()
-    assert sum("gemm_dma_kernel" in k[".name"] for k in found) > 50 and any("attention_kernel" in k[".name"] for k in found)
-    spilled = [(k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in found
-               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
+    assert sum("gemm_dma_kernel" in name for name, *_ in found) > 50 and any("attention_kernel" in name for name, *_ in found)
+    spilled = [(name, vector, scratch) for name, vector, _, scratch in found if vector or scratch]
     assert not spilled, spilled
 
 
 def test_scalar_registers_of_the_kernels():
     # (what a spilled scalar register costs depends on where it is read: the attention kernels may keep up to 32 for what follows
     # their key loop; with an iteration's load addresses among them they kept 67 and 149, read back in every iteration)
-    spilled = {k[".name"]: k[".sgpr_spill_count"] for k in kernels() if k[".sgpr_spill_count"]}
+    spilled = {name: scalar for name, _, scalar, _ in kernels() if scalar}
     assert all("attention_kernel" in name and n <= 32 for name, n in spilled.items()), spilled
