@@ -11,6 +11,8 @@
 //   vt  [B*dim][npad] values transposed, npad = N rounded up to 64, padding columns zero
 //   out [B*N][dim]
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "gemm.h"
 #include "split3.h"
@@ -28,7 +30,7 @@ struct AttnArgs {
     const void* vt;
     void* out;
     int B, N, npad, dim, heads;
-    float scale_log2e;   // (1 / sqrt(64)) * log2(e)
+    float scale_log2e;   // (1 / sqrt(64)) * log2(e): factor of the raw scores; 1 where the queries carry it already (bf16: GemmArgs::q_scale)
     int pad;             // readable rows of qk / elements of vt past their ends
     int shared_gpu;      // the launch runs beside other streams' kernels (several encoder lanes): prefer a shape that
                          // leaves room on its CUs over the fastest one on an empty GPU
@@ -94,7 +96,7 @@ template <> struct AttnMma<bf16> {
     // as a product with ones, they were a fifth of its work and 20 registers: without them the four-wave shapes fit 128
     // registers, four waves per SIMD (ViT-g x 8 122.2 -> 116.6 us, with the vector work before, between and behind the
     // MFMAs below instead of behind each of them 116.1).
-    // `sc` holds the raw scores; element e becomes 2^(sc[e] * scale - ref).  The exponentials of step + 1 are issued
+    // `sc` holds the raw scores; element e becomes 2^(sc[e] * scale - ref), DONE: 2^sc[e].  The exponentials of step + 1 are issued
     // behind the MFMAs of step, so the vector pipe works on them while the matrix pipe runs.  psum
     // receives the lane's sum of probabilities.
     static __device__ __forceinline__ float sum2(bf16x8 b, float sum) {
@@ -103,6 +105,7 @@ template <> struct AttnMma<bf16> {
         for (int kk = 0; kk < 8; kk += 2) sum = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{b[kk], b[kk + 1]}, one, sum, false);
         return sum;
     }
+    template <bool DONE = false>
     static __device__ __forceinline__ void pv_tile(f32x16& o0, f32x16& o1, float& psum, const char* sV, int li,
                                                    f32x16* sc, float scale, float ref, int g) {
         const int sw = (li >> 1) & 7;                      // rows li and li + 32 share the swizzle term
@@ -112,7 +115,8 @@ template <> struct AttnMma<bf16> {
             bf16x8 b;
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
-                const float e = __builtin_amdgcn_exp2f(fmaf(sc[st >> 1][8 * (st & 1) + kk], scale, -ref));
+                const float x = sc[st >> 1][8 * (st & 1) + kk];
+                const float e = __builtin_amdgcn_exp2f(DONE ? x : fmaf(x, scale, -ref));
                 b[kk] = (bf16)e;
             }
             psum = sum2(b, psum);
@@ -248,7 +252,8 @@ struct AttnMmaF32 : AttnMma<float> {
 // vector instructions every tile then pays ~190 register-file moves per lane (measured on the four-wave shapes:
 // 158 + 48 registers and 300 vector instructions per tile without the bound, 164 + 0 and 105 with it).  (2,1,4)
 // would spill under the bound and keeps the old one.  The bf16 (1,4,1) shape has LDS for five workgroups on a CU and
-// is held to 128 registers, four waves per SIMD.
+// is held to 168 registers, three waves per SIMD (at 128 a query block's references have to be subtracted from the scores: ViT-L x 4
+// 42.4 us against 39.3, ViT-g x 8 113 against 108).
 template <typename T, int KW>
 constexpr bool attn_double_buffered() { return 2 * KW * 2 * 64 * AttnMma<T>::ROWB <= 128 * 1024; }
 
@@ -259,12 +264,16 @@ constexpr int attn_lds() {
     return kv > red ? kv : red;
 }
 
-template <typename T, int QB, int QW, int KW>
-constexpr int attn_min_waves() {
-    return QW * KW == 4 && QB == 2 ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 4 : 2;
-}
+// Do a query's exponentials keep the reference of its wave's first tile (bf16; two blocks of queries have no registers for it)?
+template <typename T, int QB>
+constexpr bool attn_fixed_reference() { return sizeof(T) == 2 && QB == 1; }
 
 template <typename T, int QB, int QW, int KW>
+constexpr int attn_min_waves() {
+    return QW * KW == 4 && QB == 2 ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 3 : 2;
+}
+
+template <typename T, int QB, int QW, int KW, bool FIXED = attn_fixed_reference<T, QB>()>
 __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) void attention_kernel(const AttnArgs p) {
     constexpr int NW = QW * KW, NT = 64 * NW;
     static_assert(KW <= ATTN_MAX_KW, "the loader's overshoot is budgeted for at most ATTN_MAX_KW key waves");
@@ -290,8 +299,8 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     const int ld = 2 * p.dim;
 
     const T* __restrict__ qk = reinterpret_cast<const T*>(p.qk) + (int64_t)b * p.N * ld + h * 64;
-    const T* __restrict__ kbase = qk + p.dim;
-    const T* __restrict__ vt = reinterpret_cast<const T*>(p.vt) + ((int64_t)b * p.dim + h * 64) * p.npad;
+    const T* kbase = qk + p.dim;
+    const T* vt = reinterpret_cast<const T*>(p.vt) + ((int64_t)b * p.dim + h * 64) * p.npad;
 
     f32x16 o[QB][2];
     float m_run[QB], l_run[QB];                        // (denominators: per lane half)
@@ -364,8 +373,16 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     // is loaded while the other is multiplied: behind the barrier that ends the scores the next keys, behind the one that
     // ends the values the next values (staged in registers, 128 of a lane's 422, fp32 ViT-S 224x224 took 13.85 us, now 12.65).
     // All tiles from the start: scores, softmax and values with the product blocks of M.
-    auto sweep = [&](auto mma) {
+    // FIXED (the kernel's first sweep; `fixed` here): every query's reference is the maximum of its wave's first tile and stays.  A probability only has to be
+    // representable: up to 2^64 above the reference fp32 sums and bf16 probabilities are as precise as at 2^0, so no later tile looks for a
+    // maximum, and the reference is what its products start from (-reference in the accumulators: the scores leave the matrix pipe as
+    // exponents).  A workgroup that met more than that starts again with references that move.  Of a tile's 126
+    // vector instructions a lane 64 are left, all of them among the second products (us, references that move / that stay: ViT-S
+    // 1531 tokens 12.4 / 11.5, ViT-B 1370 17.0 / 15.6, ViT-L 1374 17.8 / 16.8, x 4 43.1 / 39.3, ViT-g x 8 118 / 108).
+    auto sweep = [&](auto mma, auto fixed) {
         using M = decltype(mma);
+        constexpr bool FIRST = decltype(fixed)::value;
+        f32x16 start[FIRST ? QB : 1];                   // -reference, what a score block's products start from
         typename M::QFrag q[QB][4];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -378,6 +395,10 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         for (int qb = 0; qb < QB; ++qb) {
             m_run[qb] = -INFINITY;
             l_run[qb] = 0.0f;
+            if constexpr (FIRST) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) start[qb][v] = 0.0f;
+            }
 #pragma unroll
             for (int d = 0; d < 2; ++d)
 #pragma unroll
@@ -390,10 +411,14 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         // Scores of query block qb against tile t, and the reference that their exponentials are taken against
         auto scores = [&](f32x16* s, int qb, int t, const char* sK) {
             const bool last = t == KT - 1;                 // keys past N only exist in the last tile
+            if constexpr (FIRST) {
+                s[0] = s[1] = start[qb];
+            } else {
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
+                    for (int v = 0; v < 16; ++v) s[kb][v] = 0.0f;
+            }
             // Waves of a SIMD are in different phases: the one with products to issue goes first, the second products with
             // the exponentials among them before the first (no priorities / these, us: ViT-B 518x518 18.3 / 17.3,
             // ViT-L 19.2 / 18.4, x 4 49.2 / 47.8, ViT-g x 8 136.7 / 137.6, fp32 ViT-S 518x518 x 4 128.9 / 121.5).
@@ -411,12 +436,23 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
                     }
             }
             __builtin_amdgcn_s_setprio(0);
+            if (FIRST && t >= KW) return;                  // (a wave's first tile is tile kw)
             float mx = s[0][0];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[kb][v]);
             mx = halves_max(mx);
+            if constexpr (FIRST) {
+                m_run[qb] = mx;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    start[qb][v] = -mx;
+                    s[0][v] -= mx;
+                    s[1][v] -= mx;
+                }
+                return;
+            }
             // Lazy rescaling: m_run is the reference the exponentials are taken against (in log2 units), not
             // necessarily the running maximum.  It only moves when a query's maximum has grown by more than 8
             // (probabilities stay <= 2^8, exact in fp32 and harmless in bf16), which after the first tile is
@@ -438,15 +474,20 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         auto values = [&](f32x16* s, int qb, const char* sV) {
             float psum = 0.0f;
             __builtin_amdgcn_s_setprio(2);
-            M::pv_tile(o[qb][0], o[qb][1], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
+            if constexpr (FIRST) M::template pv_tile<true>(o[qb][0], o[qb][1], psum, sV, li, s, 1.0f, 0.0f, g);
+            else M::pv_tile(o[qb][0], o[qb][1], psum, sV, li, s, p.scale_log2e, m_run[qb], g);
             l_run[qb] += psum;
             __builtin_amdgcn_s_setprio(0);
         };
+        // Eight waves issue 64 loads an iteration, 1024 clocks of the CU's address unit: keys and values apart, so that waves multiply
+        // meanwhile (1531 tokens, 288 pairs 12.0 -> 11.6 us; shapes of four waves are faster with all loads ahead: 516 pairs 15.8 / 16.3)
+        constexpr bool APART = NW > 4;
         for (int it = 0; it < NIT; ++it) {
             // (a wave without a tile in the last iteration still takes part in the barriers)
             if constexpr (DB) {
                 const char* stage = smem + (it & 1) * STAGE;
-                if (it + 1 < NIT) dma(smem + ((it + 1) & 1) * STAGE, it + 1, KEYS | VALUES);
+                char* const next = smem + ((it + 1) & 1) * STAGE;
+                if (it + 1 < NIT) dma(next, it + 1, APART ? KEYS : KEYS | VALUES);
                 const int t = it * KW + kw;
                 if (t < KT) {
                     const char* sK = stage + (kw * 2) * TILE;
@@ -454,8 +495,11 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
                     for (int qb = 0; qb < QB; ++qb) {
                         f32x16 s[2];
                         scores(s, qb, t, sK);
+                        if (APART && qb == 0 && it + 1 < NIT) dma(next, it + 1, VALUES);
                         values(s, qb, sK + TILE);
                     }
+                } else if (APART && it + 1 < NIT) {
+                    dma(next, it + 1, VALUES);
                 }
             } else {
                 static_assert(DB || QB == 1, "the scores of a query block wait for the values");
@@ -475,50 +519,73 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
             }
         }
     };
-    sweep(AttnMma<T>{});
-    if constexpr (sizeof(T) == 4) {
-        // The split holds neither infinities nor finite values above 3.396e38: NaN among their terms, and with them in the sums.
-        // A workgroup with an infinite or NaN sum starts again on the fp32 instructions (the check: ViT-S 224x224 13.6 -> 14.1 us
-        // a launch, 476x630 and larger no difference).
-        float t = 0.0f;
+    sweep(AttnMma<T>{}, std::integral_constant<bool, FIXED>{});
+    // A workgroup with a sum that the first sweep does not hold starts again.  FIXED: a row sum above 2^64 (a later tile's score
+    // far above the reference) or an infinite or NaN one.  fp32: the split holds neither infinities nor finite values above
+    // 3.396e38, NaN among their terms and with them in the sums; it starts again on the fp32 instructions.
+    // Every wave leaves a flag; with four key waves their merge's barrier stands behind it (a barrier of its own: ViT-S 224x224
+    // 5.6 -> 5.8 us).
+    constexpr bool CHECKED = FIXED || sizeof(T) == 4;
+    constexpr int PER = QB * (32 + 2) * 64;              // floats per wave that a merge takes: O (32 per lane), m, l
+    constexpr int FLAGS = sizeof(T) == 4 ? attn_lds<T, QB, QW, KW>() : KW > 2 ? KW * QW * PER * 4 : 0;
+    static_assert(!FIXED || FLAGS + 4 * NW <= attn_lds<T, QB, QW, KW>(), "flags lie behind what a merge writes");
+    int* flags = reinterpret_cast<int*>(smem + FLAGS);
+    auto leave_flag = [&] {
+        float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};            // NaN if any of the lane's sums is infinite or NaN
+        bool again = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            t = fmaf(l_run[qb], 0.0f, t);
+            t[0] = fmaf(l_run[qb], 0.0f, t[0]);
+            if (FIXED) again |= l_run[qb] > 0x1p64f;
 #pragma unroll
             for (int d = 0; d < 2; ++d)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) t = fmaf(o[qb][d][v], 0.0f, t);
+                for (int v = 0; v < 16; ++v) t[v & 3] = fmaf(o[qb][d][v], 0.0f, t[v & 3]);
         }
-        const int any = __any(t != t);
-        int* flags = reinterpret_cast<int*>(smem + attn_lds<T, QB, QW, KW>());
+        const float all = (t[0] + t[1]) + (t[2] + t[3]);
+        const int any = __any(again || all != all);
         if (lane == 0) flags[wave] = any;
-        __syncthreads();
+    };
+    auto flagged = [&] {                                  // (behind a barrier)
         int redo = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) redo |= flags[w];
-        if (__builtin_amdgcn_readfirstlane(redo)) sweep(AttnMmaF32{});
-    }
+        return __builtin_amdgcn_readfirstlane(redo) != 0;
+    };
+    auto sweep_again = [&] {
+        asm volatile("" : "+s"(kbase), "+s"(vt));         // (nothing of the first sweep's addresses is held for this one)
+        __syncthreads();                                  // everyone has read the flags
+        if constexpr (sizeof(T) == 4) sweep(AttnMmaF32{}, std::false_type{});
+        else sweep(AttnMma<T>{}, std::false_type{});
+    };
 
     if constexpr (KW > 2) {
         // Merge the KW partial (max, sum, O) triples of each query group, lane by lane and in a fixed order.  Every wave
         // leaves its triple in LDS and finishes 1 / KW of the group's output (one wave merging and storing it all left the
         // others idle; us, before / now: ViT-S 224x224 7.3 / 6.9, 476x630 13.7 / 13.3, fp32 224x224 13.9 / 13.3).
-        constexpr int PER = QB * (32 + 2) * 64;          // floats per wave: O (32 per lane), m, l
         constexpr int SL = 32 / KW;
         static_assert(SL % 4 == 0, "a wave's share is whole groups of four channels");
         float* red = reinterpret_cast<float*>(smem) + lane;
-        __syncthreads();
         float* own = red + (kw * QW + qw) * PER;
+        auto leave_triple = [&] {                         // (every wave is done with the tiles: a sweep ends with a barrier)
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
+            for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
-            for (int d = 0; d < 2; ++d)
+                for (int d = 0; d < 2; ++d)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) own[(qb * 34 + d * 16 + v) * 64] = o[qb][d][v];
-            own[(qb * 34 + 32) * 64] = m_run[qb];
-            own[(qb * 34 + 33) * 64] = l_run[qb];
-        }
+                    for (int v = 0; v < 16; ++v) own[(qb * 34 + d * 16 + v) * 64] = o[qb][d][v];
+                own[(qb * 34 + 32) * 64] = m_run[qb];
+                own[(qb * 34 + 33) * 64] = l_run[qb];
+            }
+        };
+        if (CHECKED) leave_flag();
+        leave_triple();
         __syncthreads();
+        if (CHECKED && __builtin_expect(flagged(), 0)) {
+            sweep_again();
+            leave_triple();
+            __syncthreads();
+        }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const float* src = red + qw * PER + qb * 34 * 64;          // wave k's triple: + k QW PER
@@ -552,9 +619,14 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
         return;
     }
 
+    if constexpr (CHECKED) {
+        leave_flag();
+        __syncthreads();
+        if (__builtin_expect(flagged(), 0)) sweep_again();
+    }
+
     if constexpr (KW == 2) {
         // two triples: the second wave's through LDS, merged and stored by the first (shared as above: ViT-B 20.0 against 19.7 us)
-        constexpr int PER = QB * (32 + 2) * 64;          // floats per wave: O (32 per lane), m, l
         float* red = reinterpret_cast<float*>(smem);
         __syncthreads();
         if (kw > 0) {
@@ -611,19 +683,19 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     }
 }
 
-template <typename T, int QB, int QW, int KW>
+template <typename T, int QB, int QW, int KW, bool FIXED = attn_fixed_reference<T, QB>()>
 static inline hipError_t launch_attention_variant(const AttnArgs& a, hipStream_t s, bool configure_only) {
     constexpr int lds = attn_lds<T, QB, QW, KW>() + (sizeof(T) == 4 ? 64 : 0);
     static bool configured = false;       // opt in to more than 64 KB of LDS once per instantiation
     if (!configured) {
-        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<T, QB, QW, KW>),
+        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<T, QB, QW, KW, FIXED>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (rc != hipSuccess) return rc;
         configured = true;
     }
     if (configure_only) return hipSuccess;
     if (a.pad < 2 * KW * 64 || a.npad % 64 || a.npad < a.N || a.dim != a.heads * 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attention_kernel<T, QB, QW, KW>), dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads),
+    hipLaunchKernelGGL((attention_kernel<T, QB, QW, KW, FIXED>), dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads),
                        dim3(64 * QW * KW), lds, s, a);
     return hipGetLastError();
 }

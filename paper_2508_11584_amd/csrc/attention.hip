@@ -7,6 +7,12 @@ namespace vpe {
 // variant = QB * 100 + QW * 10 + KW
 template <typename T>
 static hipError_t launch_variant(int variant, const AttnArgs& a, hipStream_t s, bool cfg = false) {
+    // With up to two tiles a wave the check of references that stay costs more than the maxima (257 tokens, 54 pairs: 5.62 us with
+    // references that move, 5.76 with others; 577 tokens 6.74 / 6.71)
+    if (sizeof(T) == 2 && variant == 114 && (cfg || a.npad <= 2 * 4 * 64)) {
+        const hipError_t rc = launch_attention_variant<T, 1, 1, 4, false>(a, s, cfg);
+        if (!cfg || rc != hipSuccess) return rc;
+    }
     switch (variant) {
         case 114: return launch_attention_variant<T, 1, 1, 4>(a, s, cfg);
         case 141: return launch_attention_variant<T, 1, 4, 1>(a, s, cfg);
@@ -49,27 +55,30 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     // Workgroup shapes measured on MI355X (QB, QW, KW = query blocks per wave, query waves, key waves), us, by pairs of a head
     // and a block of 32 queries:
     //                                        (1,1,4) (1,2,4) (1,2,2) (1,4,1)
-    //     54  ViT-S 224x224  (N  257)             5.8     6.9     6.3     7.3
-    //    108  ViT-B 224x224                       5.9     6.9     6.4
-    //    150  ViT-S 392x392  (N  785)             8.1     9.5     9.7
-    //    222  ViT-S 476x476  (N 1157)             9.5    11.4    12.3
-    //    288  ViT-S 476x630  (N 1531)                    12.7    14.5    22.0
-    //    348  ViT-S 602x602  (N 1850)            24.2    15.7    17.3
-    //    444  ViT-B 476x476                      17.8    12.1    13.0
-    //    516  ViT-B 518x518  (N 1370)                    23.8    17.2    20.9
-    //    696  ViT-B 602x602                      36.2    29.7    23.9
-    //   2752  ViT-L 518x518 x 4                          68.6    51.9    42.7
-    //   8256  ViT-g 518x518 x 8                         191     139     118
+    //     54  ViT-S 224x224  (N  257)             5.6     7.0     6.3     7.1
+    //    108  ViT-B 224x224                       5.7     7.0     6.4     7.2
+    //    222  ViT-S 476x476  (N 1157)             8.9    10.4    11.3    15.7
+    //    288  ViT-S 476x630  (N 1531)            17.9    11.6    12.9    18.8
+    //    348  ViT-S 602x602  (N 1850)            21.5    13.7    15.3    21.9
+    //    444  ViT-B 476x476                      16.5    11.1    12.0    15.9
+    //    516  ViT-B 518x518  (N 1370)            26.0    21.4    15.6    17.7
+    //    612  ViT-B 252x406 x 3                  17.9    15.4    10.5    10.1
+    //    696  ViT-B 602x602                      31.8    26.0    20.5    22.4
+    //    928  ViT-L 602x602                      41.9    27.0    22.2    23.1
+    //   1548  ViT-B 518x518 x 3                  60.2    42.0    31.0    25.7
+    //   2752  ViT-L 518x518 x 4                  95.8    64.8    48.2    39.3
     // The first two hold a CU each, the longest-running split of the keys that one round of the 256 CUs has room for wins
-    // (and a merge that four waves share beats one by a single wave); then half a CU each; many pairs want four query
-    // waves sharing each key tile and no merge.  Wider workgroups (eight query waves, or two query blocks per wave) halve the
+    // (and a merge that four waves share beats one by a single wave); then half a CU each, as long as one round of two to a CU
+    // holds them (512 workgroups of 64 queries; beyond, whole frames are 1-4 % faster with (1,4,1): ViT-B 518x518 x 3 on two lanes
+    // 11891 / 11611 us, ViT-S 476x630 x 4 1655 / 1610, ViT-L 518x518 x 2 4912 / 4804); more want four query waves sharing each key
+    // tile, three to a CU, and no merge.  Wider workgroups (eight query waves, or two query blocks per wave) halve the
     // L2 -> LDS traffic and are slower all the same; narrower ones (two waves) double it and are slower too.
     // Beside another encoder lane's kernels the footprint counts for more than the time alone.  Frames of two lanes, us, in the
     // order of the table: ViT-S 224x224 243 248 247, 308x308 251 258 258, 476x476 with a depth head 495 477 481, ViT-B 308x308 (192
     // pairs) 371 370 371, 476x476 844 772 764; so (1,1,4) where both lanes' workgroups find a CU each, (1,2,2) up to the line
-    // of (1,4,1).
+    // of (1,4,1).  (Two-lane figures from before references that stay, attention.h.)
     const int64_t heads = (int64_t)a.B * a.heads, qblocks = cdiv(a.N, 32) * heads;
-    int variant = qblocks >= 2048 ? 141 : qblocks <= (a.shared_gpu ? 128 : 256) ? 114 : a.shared_gpu || cdiv(a.N, 64) * heads > 256 ? 122 : 124;
+    int variant = cdiv(a.N, 64) * heads > 512 ? 141 : qblocks <= (a.shared_gpu ? 128 : 256) ? 114 : a.shared_gpu || cdiv(a.N, 64) * heads > 256 ? 122 : 124;
     if (forced) variant = forced;
     if (dtype) return launch_variant<bf16>(variant, a, s);
     // fp32: a workgroup fills a CU's LDS ((1,4,1): half of it), so what counts is whole rounds of the 256 CUs and waves to overlap:

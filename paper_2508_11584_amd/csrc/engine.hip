@@ -675,6 +675,11 @@ GemmArgs ln_gemm(const vpe_engine& e, const vpe_engine::Lane& L, const void* W, 
     return a;
 }
 
+// Scores of 64-wide heads in log2 units: 1 / sqrt(64) * log2(e).  bf16 engines put the factor into the queries, ahead of their only
+// rounding, so that the attention kernel's products are exponents as they come.
+constexpr float SCORE_SCALE = 0.125f * 1.4426950408889634f;
+float q_scale(int bf) { return bf ? SCORE_SCALE : 1.0f; }
+
 // A GEMM whose epilogue updates the residual stream: also refreshes its copy (against `level`) and its row
 // statistics.
 void produce_stats(const vpe_engine& e, const vpe_engine::Lane& L, GemmArgs& a, const float* level) {
@@ -704,11 +709,11 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
         {
             GemmArgs a = ln_gemm(e, L, w.qkv_w, w.qkv_b, w.qkv_s, 3 * D, level, L.lev[nxt]);
             level = L.lev[nxt]; nxt ^= 1;
-            a.epi = EPI_QKV; a.out = L.qk; a.ldo = 2 * D; a.out2 = L.vt; a.ntok = e.N; a.npad = e.npad; a.dim = D;
+            a.epi = EPI_QKV; a.out = L.qk; a.ldo = 2 * D; a.out2 = L.vt; a.ntok = e.N; a.npad = e.npad; a.dim = D; a.q_scale = q_scale(dt);
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
         }
         {
-            AttnArgs a{L.qk, L.vt, L.att, e.B, e.N, e.npad, D, e.nh, 0.125f * 1.4426950408889634f, ATTN_PAD, e.lanes > 1};
+            AttnArgs a{L.qk, L.vt, L.att, e.B, e.N, e.npad, D, e.nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e.lanes > 1};
             HIPCHK(&e, launch_attention(dt, a, s));
         }
         {
@@ -1412,10 +1417,10 @@ int vpe_time_kernel(vpe_engine* e, int which, int reps, float* ms_per_launch, do
         for (int i = 0; i < (timed ? reps : 1); ++i) {
             if (which == 0) {
                 GemmArgs a = ln_gemm(*e, L0, e->blk[0].qkv_w, e->blk[0].qkv_b, e->blk[0].qkv_s, 3 * D, L0.lev[1], nullptr);
-                a.epi = EPI_QKV; a.out = L0.qk; a.ldo = 2 * D; a.out2 = L0.vt; a.ntok = e->N; a.npad = e->npad; a.dim = D;
+                a.epi = EPI_QKV; a.out = L0.qk; a.ldo = 2 * D; a.out2 = L0.vt; a.ntok = e->N; a.npad = e->npad; a.dim = D; a.q_scale = q_scale(dt);
                 HIPCHK(e, launch_gemm(dt, a, A_PLAIN, s));
             } else if (which == 1) {
-                AttnArgs a{L0.qk, L0.vt, L0.att, e->B, e->N, e->npad, D, e->nh, 0.125f * 1.4426950408889634f, ATTN_PAD, e->lanes > 1};
+                AttnArgs a{L0.qk, L0.vt, L0.att, e->B, e->N, e->npad, D, e->nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e->lanes > 1};
                 HIPCHK(e, launch_attention(dt, a, s));
             } else if (which == 5 || which == 7) {
                 // out-projection / fc2 of block 0 with the LayerScale residual epilogue (the residual stream of lane 0

@@ -55,6 +55,7 @@ struct GemmArgs {
     const float* pos;    // PATCH: positional rows [o_rpi][N]
     void* out2;          // QKV: transposed values  vt[(b * dim + c)][npad]
     int ntok, npad, dim; // QKV
+    float q_scale;       // QKV: factor of the query columns (after the bias, before they are rounded)
     // LayerNorm folded into this GEMM (consumer side): A holds the UN-normalised rows (plain row map), W has
     // been scaled by the LayerNorm gain along k and bias holds b + beta W; the accumulator of (row r, column c)
     // becomes rstd_r * (acc - mean_r * ln_colsum[c]) before bias / activation, with ln_colsum[c] = sum_k W[c][k].
@@ -315,6 +316,9 @@ __device__ __forceinline__ void epilogue_chunk(const GemmArgs& p, const EpiCols&
             store8(reinterpret_cast<T*>(p.xb_out) + (int64_t)e.orow * p.ldo + k.c, rel);
         }
     } else {   // EPI_QKV, query / key columns
+        const float f = k.c < p.dim ? p.q_scale : 1.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] *= f;
         store8(reinterpret_cast<T*>(p.out) + (int64_t)e.orow * p.ldo + k.c, v);
     }
 }

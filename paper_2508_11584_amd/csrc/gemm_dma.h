@@ -174,6 +174,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
             }
         } else if constexpr (EPI == EPI_QKV) {
             const EpiCols cols = epilogue_cols<EPI>(p, wcol0 + (lane % CG) * 8);
+            const float f = cols.c < p.dim ? p.q_scale : 1.0f;
 #pragma unroll
             for (int n = 0; n < ITS; ++n) {
                 const int rr = lane / CG + n * (64 / CG), r = epilogue_row<PADDED>(p, rblk + rr);
@@ -181,7 +182,7 @@ __device__ __forceinline__ void wave_tile_epilogue(const GemmArgs& p, f32x16 (&a
                 chunk8(rr, (lane % CG) * 8, v);
                 if (has_ln) ln_apply(row_stats(tblk + rr), cols.g0, cols.g1, v);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { v[e] += cols.b0[e]; v[4 + e] += cols.b1[e]; }
+                for (int e = 0; e < 4; ++e) { v[e] = (v[e] + cols.b0[e]) * f; v[4 + e] = (v[4 + e] + cols.b1[e]) * f; }
                 if (r < p.M && cols.nv > 0) store8(reinterpret_cast<T*>(p.out) + (int64_t)r * p.ldo + cols.c, v);
             }
         } else if (batched) {

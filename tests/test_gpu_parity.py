@@ -505,6 +505,39 @@ def test_attention_on_both_sides_of_its_shape_lines(dtype, gh, gw, batch, lanes)
     assert rep["b0.feat3"] > 0.0
 
 
+@pytest.mark.parametrize("variant", ["114", "124", "122", "141"])
+@pytest.mark.parametrize("product", [16.0, 48.0])
+def test_attention_to_one_key_of_a_later_tile(variant, product, monkeypatch):
+    # 361 tokens; the last one (tile 5 of 6, no wave's first) stands out in one channel, which the keys of every head show to a constant
+    # query channel: its score is 2 x product (log2 units: 46 and 138) above the others', which the references of the first tiles know
+    # nothing of: within the 2^64 that sums taken against them hold, and beyond, where a workgroup starts again.  Every
+    # query's result is that token's value (the next share is below e^-20), whatever rounding does to the scores.
+    monkeypatch.setenv("VPE_ATTN_VARIANT", variant)
+    D = SHARP["dim"]
+    where, big = 5, 300.0
+
+    def edit(w):
+        w["pos"][:, where] *= 0.1
+        w["pos"][-1, where] = big
+        for l in range(SHARP["depth"]):
+            for h in range(SHARP["heads"]):
+                c = 64 * h + 9
+                w["blk%d.qkv_w" % l][:, c] = 0.0
+                w["blk%d.qkv_w" % l][:, D + c] = 0.0
+                w["blk%d.qkv_w" % l][where, D + c] = product / math.sqrt(D) * 16.0 / 8.0
+                w["blk%d.qkv_b" % l][c] = 8.0
+                w["blk%d.qkv_b" % l][D + c] = 0.0
+    rep = check_all(vi.ModelSpec("one_key_" + variant, dtype="bf16", **SHARP), 161, 261, kinds=("seg",), weights_edit=edit)
+    assert rep["b0.feat3"] > 0.0
+
+
+@pytest.mark.parametrize("batch,lanes", [(25, 1), (26, 1), (26, 2)])
+def test_bf16_attention_beside_one_round_of_two_key_waves(batch, lanes):
+    # 500 and 520 workgroups of 64 queries: the line is 512
+    spec = vi.ModelSpec("attn_round_%d" % batch, dtype="bf16", **{**SHARP, "dim": 256, "heads": 4, "img_h": 224, "img_w": 224, "batch": batch})
+    check_all(spec, 153, 253, kinds=("seg",), batch_check=[0, batch - 1], weights_edit=_sharpen(16.0), encoder_lanes=lanes, ring_slots=lanes + 1)
+
+
 # ---------------------------------------------------------------- GELU of bf16 results
 def _gelu_exact(v):
     return np.array([0.5 * x * math.erfc(-x / math.sqrt(2.0)) for x in np.asarray(v, dtype=np.float64)])
