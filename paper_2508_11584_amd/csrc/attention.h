@@ -15,6 +15,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "layernorm.h"
 #include "split3.h"
 
 namespace vpe {
@@ -25,6 +26,17 @@ namespace vpe {
 // rows of qk / elements of vt past their ends the caller made readable; a launch whose shape needs more is refused.
 constexpr int ATTN_MAX_KW = 4;                        // widest key split of any instantiation
 constexpr int ATTN_PAD = 2 * ATTN_MAX_KW * 64;        // rows / elements a caller has to provide for any shape
+// LayerNorm of rows that the launch normalises beside the attention, with workgroups of its own behind the others (x null: none):
+// a feature map is tapped between two blocks, and the residual stream stands still until the next block's out-projection.
+struct RowNorm {
+    const float* x;      // [rows][D]
+    const float* gain;
+    const float* bias;
+    void* out;           // T [rows][D]
+    int rows, D;
+    float eps;
+    int blocks;          // (filled in by the launcher)
+};
 struct AttnArgs {
     const void* qk;
     const void* vt;
@@ -34,6 +46,7 @@ struct AttnArgs {
     int pad;             // readable rows of qk / elements of vt past their ends
     int shared_gpu;      // the launch runs beside other streams' kernels (several encoder lanes): prefer a shape that
                          // leaves room on its CUs over the fastest one on an empty GPU
+    RowNorm norm;
 };
 
 // Exchange between the two halves of a wave without going through LDS (v_permlane32_swap): both operands are the
@@ -273,7 +286,8 @@ constexpr int attn_min_waves() {
     return QW * KW == 4 && QB == 2 ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 3 : 2;
 }
 
-template <typename T, int QB, int QW, int KW, bool FIXED = attn_fixed_reference<T, QB>()>
+// NORM: with a RowNorm's workgroups (an instantiation of its own: the look at their number is 0.25 us of every launch).
+template <typename T, int QB, int QW, int KW, bool FIXED, bool NORM>
 __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) void attention_kernel(const AttnArgs p) {
     constexpr int NW = QW * KW, NT = 64 * NW;
     static_assert(KW <= ATTN_MAX_KW, "the loader's overshoot is budgeted for at most ATTN_MAX_KW key waves");
@@ -292,8 +306,13 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     // so ids are remapped to give each XCD one contiguous range -- all query blocks of an (image, head) pair then run
     // on the same XCD and its keys and values are fetched into that L2 once, not into all eight (measured at ViT-g x8:
     // 615 MB fetched per launch against 135 MB of operands before the remapping).
-    const int nqb = cdiv(p.N, 32 * QB * QW);
-    const int lin = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int nqb = cdiv(p.N, 32 * QB * QW), tasks = gridDim.x - (NORM ? p.norm.blocks : 0);
+    if (NORM && (int)blockIdx.x >= tasks) {
+        for (int row = (blockIdx.x - tasks) * NW + wave; row < p.norm.rows; row += p.norm.blocks * NW)
+            layernorm_row(p.norm.x, row, p.norm.D, p.norm.gain, p.norm.bias, p.norm.eps, reinterpret_cast<T*>(p.norm.out), lane);
+        return;
+    }
+    const int lin = xcd_contiguous(blockIdx.x, tasks);
     const int bh = lin / nqb, b = bh / p.heads, h = bh % p.heads;
     const int q0 = (lin % nqb) * (32 * QB * QW) + qw * 32 * QB;
     const int ld = 2 * p.dim;
@@ -686,17 +705,21 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
 template <typename T, int QB, int QW, int KW, bool FIXED = attn_fixed_reference<T, QB>()>
 static inline hipError_t launch_attention_variant(const AttnArgs& a, hipStream_t s, bool configure_only) {
     constexpr int lds = attn_lds<T, QB, QW, KW>() + (sizeof(T) == 4 ? 64 : 0);
+    typedef void (*Kernel)(const AttnArgs);
+    static const Kernel kernels[] = {&attention_kernel<T, QB, QW, KW, FIXED, false>, &attention_kernel<T, QB, QW, KW, FIXED, true>};
     static bool configured = false;       // opt in to more than 64 KB of LDS once per instantiation
     if (!configured) {
-        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<T, QB, QW, KW, FIXED>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (rc != hipSuccess) return rc;
+        for (Kernel k : kernels) {
+            hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (rc != hipSuccess) return rc;
+        }
         configured = true;
     }
     if (configure_only) return hipSuccess;
     if (a.pad < 2 * KW * 64 || a.npad % 64 || a.npad < a.N || a.dim != a.heads * 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attention_kernel<T, QB, QW, KW, FIXED>), dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads),
-                       dim3(64 * QW * KW), lds, s, a);
+    AttnArgs args = a;
+    args.norm.blocks = !a.norm.x ? 0 : cdiv(a.norm.rows, QW * KW) < 512 ? cdiv(a.norm.rows, QW * KW) : 512;       // a row per wave up to two per CU
+    hipLaunchKernelGGL(kernels[args.norm.blocks > 0], dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads + args.norm.blocks), dim3(64 * QW * KW), lds, s, args);
     return hipGetLastError();
 }
 

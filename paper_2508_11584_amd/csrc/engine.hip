@@ -704,6 +704,7 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
     const float* level = e.lev0;
     int nxt = 0;
     int tap = 0;
+    RowNorm norm{};                              // the tapped rows that the next attention launch normalises
     for (int l = 0; l < e.L; ++l) {
         const BlockW& w = e.blk[l];
         {
@@ -713,8 +714,9 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
         }
         {
-            AttnArgs a{L.qk, L.vt, L.att, e.B, e.N, e.npad, D, e.nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e.lanes > 1};
+            AttnArgs a{L.qk, L.vt, L.att, e.B, e.N, e.npad, D, e.nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e.lanes > 1, norm};
             HIPCHK(&e, launch_attention(dt, a, s));
+            norm = RowNorm{};
         }
         {
             GemmArgs a = plain_gemm(L.att, D, w.proj_w, w.proj_b, T, D, D);
@@ -737,7 +739,12 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
         }
         if (tap < 4 && l + 1 == e.cfg.taps[tap]) {
-            HIPCHK(&e, launch_layernorm(dt, L.x, T, D, e.norm_g, e.norm_b, e.cfg.ln_eps, e.feat[slot * 4 + tap], s));
+            // Up to 2048 rows in the next block's attention launch, which reads other buffers and leaves room on the chip: a launch of its
+            // own is 3.3-4.8 us of the chain.  us a pass, launches of their own / so: ViT-S 224x224 362.5 / 358.4, fp32 659 / 645, 476x630
+            // 558 / 546, ViT-B 518x518 907 / 893, 252x406 x 3 870 / 864, ViT-L 518x518 2499 / 2488.  Behind an attention that fills the chip
+            // they take longer than a launch (ViT-L x 4, 5496 rows, 5295 / 5345; ViT-g x 8 29780 / 29940).
+            if (l + 1 < e.L && T <= 2048) norm = RowNorm{L.x, e.norm_g, e.norm_b, e.feat[slot * 4 + tap], T, D, e.cfg.ln_eps, 0};
+            else HIPCHK(&e, launch_layernorm(dt, L.x, T, D, e.norm_g, e.norm_b, e.cfg.ln_eps, e.feat[slot * 4 + tap], s));
             ++tap;
         }
     }

@@ -3,6 +3,7 @@
 // contiguous (channel) axis; one wavefront owns one row.
 #pragma once
 #include "common.h"
+#include "layernorm.h"
 
 namespace vpe {
 
@@ -33,53 +34,14 @@ __global__ __launch_bounds__(256) void activation_kernel(T* __restrict__ h, int6
 }
 
 
-// LayerNorm over the last axis of the fp32 residual stream: y = g (x - mean) / sqrt(var + eps) + b
-// with the biased variance; statistics in fp32 (mean first, then centred second moment, both
-// from registers).  One wave per row, 4 rows per workgroup.  D multiple of 64, D <= 64 * 32.
+// LayerNorm of the rows of the fp32 residual stream (layernorm.h), 4 rows per workgroup.
 template <typename T>
 __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict__ x, int rows, int D,
                                                         const float* __restrict__ gam,
                                                         const float* __restrict__ bet, float eps,
                                                         T* __restrict__ y) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= rows) return;
-    constexpr int MAXV = 16;                     // float2 per lane -> D <= 2048
-    const int nv = D >> 7;                       // full float2 passes (128 elements each)
-    const bool tail = (D & 64) != 0;             // one extra pass of single floats
-    const float* xr = x + (int64_t)row * D;
-    f32x2 v[MAXV];
-    float t = 0.0f, sum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (i < nv) {
-            v[i] = *reinterpret_cast<const f32x2*>(xr + i * 128 + 2 * lane);
-            sum += v[i][0] + v[i][1];
-        }
-    if (tail) { t = xr[nv * 128 + lane]; sum += t; }
-    const float mean = wave_sum(sum) / D;
-    float sq = 0.0f;
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (i < nv) {
-            const float a = v[i][0] - mean, b = v[i][1] - mean;
-            sq += a * a + b * b;
-        }
-    if (tail) sq += (t - mean) * (t - mean);
-    const float rstd = 1.0f / sqrtf(wave_sum(sq) / D + eps);
-    T* yr = y + (int64_t)row * D;
-#pragma unroll
-    for (int i = 0; i < MAXV; ++i)
-        if (i < nv) {
-            const int c = i * 128 + 2 * lane;
-            const f32x2 gg = *reinterpret_cast<const f32x2*>(gam + c);
-            const f32x2 bb = *reinterpret_cast<const f32x2*>(bet + c);
-            yr[c] = from_f32<T>(gg[0] * (v[i][0] - mean) * rstd + bb[0]);
-            yr[c + 1] = from_f32<T>(gg[1] * (v[i][1] - mean) * rstd + bb[1]);
-        }
-    if (tail) {
-        const int c = nv * 128 + lane;
-        yr[c] = from_f32<T>(gam[c] * (t - mean) * rstd + bet[c]);
-    }
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row < rows) layernorm_row(x, row, D, gam, bet, eps, y, threadIdx.x & 63);
 }
 
 // Patch gathering for the 14x14 stride-14 embedding: row (b, p) of `cols` receives the 588
