@@ -165,6 +165,7 @@ struct vpe_engine {
     void* static_ptr = nullptr;          // that GPU's copy of the library's static scratch array
     int D = 0, L = 0, nh = 0, Mh = 0, F = 0, R = 0, B = 0, H = 0, W = 0, gh = 0, gw = 0, P = 0, N = 0, T = 0;
     int npad = 0, esz = 2, S = 1;
+    int proj_group = 64, fc2_group = 64;  // columns per group of the statistics that out-projection and fc2 leave (stats_columns)
     char* ws = nullptr;
     uint64_t ws_bytes = 0;
     // backbone weights
@@ -179,7 +180,7 @@ struct vpe_engine {
     // kernels are too small to fill 256 CUs on their own); results per frame are unchanged.
     struct Lane {
         // x: fp32 residual stream; u: its copy in the engine dtype (the A operand of the LayerNorm-folded
-        // GEMMs; unused by fp32 engines, which read x); stats: per row and 64-column group (mean, sum of squared deviations) of x
+        // GEMMs; unused by fp32 engines, which read x); stats: per row and group of 64 or 32 columns (mean, sum of squared deviations) of x
         void *apatch = nullptr, *u = nullptr, *qk = nullptr, *vt = nullptr, *att = nullptr, *hid = nullptr;
         float *x = nullptr, *stats = nullptr;
         float* lev[2] = {nullptr, nullptr};   // [T] row levels the copy u is stored against, alternating (see ln_gemm)
@@ -390,7 +391,7 @@ void layout(vpe_engine& e, Bump& b) {
         vpe_engine::Lane& L = e.lane[l];
         L.apatch = b.take(B * P * KPATCH_PAD * esz);
         L.x = f32(T * D);
-        L.stats = f32(T * (D / 64) * 2);
+        L.stats = f32(T * (D / 32) * 2);
         L.lev[0] = f32(T); L.lev[1] = f32(T);
         L.u = b.take(T * D * esz);
         // + ATTN_PAD rows / elements that the attention loader may prefetch past the end (never used)
@@ -667,10 +668,11 @@ GemmArgs plain_gemm(const void* A, int64_t lda, const void* W, const float* bias
 // of x in the engine dtype (x itself for fp32 engines), statistics come from the producers' epilogues.
 // The 16-bit copy is stored relative to a per-row level: `level` is the one the current copy was written
 // against, `next_level` receives the rows' means for the next copy (fp32 engines read x itself: no levels).
+// `group`: columns per group of the statistics, as the producer left them (GemmArgs::st_group).
 GemmArgs ln_gemm(const vpe_engine& e, const vpe_engine::Lane& L, const void* W, const float* bias, const float* colsum, int N,
-                 const float* level, float* next_level) {
+                 const float* level, float* next_level, int group = 64) {
     GemmArgs a = plain_gemm(e.bf ? (const void*)L.u : (const void*)L.x, e.D, W, bias, e.T, N, e.D);
-    a.ln_stats = L.stats; a.ln_colsum = colsum; a.ln_groups = e.D / 64; a.ln_eps = e.cfg.ln_eps;
+    a.ln_stats = L.stats; a.ln_colsum = colsum; a.ln_groups = e.D / group; a.ln_width = (float)group; a.ln_eps = e.cfg.ln_eps;
     if (e.bf) { a.ln_level = level; a.ln_level_out = next_level; }
     return a;
 }
@@ -689,6 +691,13 @@ void produce_stats(const vpe_engine& e, const vpe_engine::Lane& L, GemmArgs& a, 
     a.xb_level = e.bf ? level : nullptr;
 }
 
+// Columns per group of the statistics that the residual product over k is to leave.
+int residual_group(const vpe_engine& e, int k) {
+    GemmArgs a = plain_gemm(nullptr, k, nullptr, nullptr, e.T, e.D, k);
+    a.epi = EPI_RESID;
+    return stats_columns(e.bf, a);
+}
+
 int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
     const int D = e.D, T = e.T, dt = e.bf;
     const vpe_engine::Lane& L = e.lane[lane];
@@ -704,11 +713,12 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
     const float* level = e.lev0;
     int nxt = 0;
     int tap = 0;
+    int group = 64;
     RowNorm norm{};                              // the tapped rows that the next attention launch normalises
     for (int l = 0; l < e.L; ++l) {
         const BlockW& w = e.blk[l];
         {
-            GemmArgs a = ln_gemm(e, L, w.qkv_w, w.qkv_b, w.qkv_s, 3 * D, level, L.lev[nxt]);
+            GemmArgs a = ln_gemm(e, L, w.qkv_w, w.qkv_b, w.qkv_s, 3 * D, level, L.lev[nxt], group);
             level = L.lev[nxt]; nxt ^= 1;
             a.epi = EPI_QKV; a.out = L.qk; a.ldo = 2 * D; a.out2 = L.vt; a.ntok = e.N; a.npad = e.npad; a.dim = D; a.q_scale = q_scale(dt);
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
@@ -722,10 +732,11 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
             GemmArgs a = plain_gemm(L.att, D, w.proj_w, w.proj_b, T, D, D);
             a.epi = EPI_RESID; a.gamma = w.ls1;
             produce_stats(e, L, a, level);
+            group = a.st_group = e.proj_group;
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
         }
         {
-            GemmArgs a = ln_gemm(e, L, w.fc1_w, w.fc1_b, w.fc1_s, e.F, level, L.lev[nxt]);
+            GemmArgs a = ln_gemm(e, L, w.fc1_w, w.fc1_b, w.fc1_s, e.F, level, L.lev[nxt], group);
             level = L.lev[nxt]; nxt ^= 1;
             a.out = L.hid; a.ldo = e.Mh;
             if (e.cfg.mlp_kind == VPE_MLP_SWIGLU) a.epi = EPI_SWIGLU;
@@ -736,6 +747,7 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
             GemmArgs a = plain_gemm(L.hid, e.Mh, w.fc2_w, w.fc2_b, T, D, e.Mh);
             a.epi = EPI_RESID; a.gamma = w.ls2;
             produce_stats(e, L, a, level);
+            group = a.st_group = e.fc2_group;
             HIPCHK(&e, launch_gemm(dt, a, A_PLAIN, s));
         }
         if (tap < 4 && l + 1 == e.cfg.taps[tap]) {
@@ -1010,6 +1022,8 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
     if (hip(configure_gemm(), "configure_gemm")) return bail(VPE_EHIP);
     if (hip(configure_gemm_bf16(), "configure_gemm_bf16")) return bail(VPE_EHIP);
     if (hip(configure_gemm_f32(), "configure_gemm_f32")) return bail(VPE_EHIP);
+    e->proj_group = residual_group(*e, e->D);
+    e->fc2_group = residual_group(*e, e->Mh);
     Bump real;
     real.base = e->ws;
     layout(*e, real);
@@ -1437,6 +1451,7 @@ int vpe_time_kernel(vpe_engine* e, int which, int reps, float* ms_per_launch, do
                                         : plain_gemm(L0.hid, e->Mh, w.fc2_w, w.fc2_b, T, D, e->Mh);
                 a.epi = EPI_RESID; a.gamma = which == 5 ? w.ls1 : w.ls2;
                 produce_stats(*e, L0, a, L0.lev[1]);
+                a.st_group = which == 5 ? e->proj_group : e->fc2_group;
                 HIPCHK(e, launch_gemm(dt, a, A_PLAIN, s));
             } else if (which == 6 || which == 9) {
                 GemmArgs a = ln_gemm(*e, L0, e->blk[0].fc1_w, e->blk[0].fc1_b, e->blk[0].fc1_s, e->F, L0.lev[1], nullptr);

@@ -59,11 +59,12 @@ struct GemmArgs {
     // LayerNorm folded into this GEMM (consumer side): A holds the UN-normalised rows (plain row map), W has
     // been scaled by the LayerNorm gain along k and bias holds b + beta W; the accumulator of (row r, column c)
     // becomes rstd_r * (acc - mean_r * ln_colsum[c]) before bias / activation, with ln_colsum[c] = sum_k W[c][k].
-    // ln_stats [M][ln_groups][2]: (mean, sum of squared deviations from it) of every 64-column group of row r,
+    // ln_stats [M][ln_groups][2]: (mean, sum of squared deviations from it) of every group of K / ln_groups columns of row r,
     // as written by the producer below; both sides work with differences, never with raw squares.  Not with RESID or PATCH.
     const float* ln_stats;     // null: no LayerNorm
     const float* ln_colsum;
-    int ln_groups;             // = K / 64
+    int ln_groups;             // groups of a row and their width: K / 64 of 64 columns, or K / 32 of 32 (the producer's st_group)
+    float ln_width;
     float ln_eps;
     // A may hold the rows minus a per-row level (LayerNorm does not see a level common to a row, and a 16-bit
     // copy of x - level keeps its precision when the row sits far from zero): ln_level[r] is that level (null:
@@ -73,9 +74,11 @@ struct GemmArgs {
     const float* ln_level;
     float* ln_level_out;
     // Producer side (RESID / PATCH, N a multiple of 64): besides the fp32 rows, write their copy in T
-    // (xb_out, [rows][N], may be null) and the group statistics of the updated rows (st_out, may be null)
+    // (xb_out, [rows][N], may be null) and the group statistics of the updated rows (st_out, [rows][N / group][2], may be null:
+    // groups of 64 columns, or, with st_group = 32, of 32: RESID alone, in tiles of 32 columns)
     void* xb_out;
     float* st_out;
+    int st_group;
     const float* xb_level;     // xb_out holds x - xb_level[row] (null: 0); statistics are of x itself
     // STORE only (N and ldo multiples of 8): fp32 tensors added after the activation, read through the output
     // row map with the output's row pitch (null: none); and a second copy of the result in T, optionally
@@ -376,12 +379,12 @@ __device__ __forceinline__ void store_tokens8(const GemmArgs& p, T* vt, int r, i
 // (mean, rstd) of a row from its group statistics (mean_g, M2_g = sum of squared deviations from mean_g, of
 // each 64-column group), one thread per tile row.  Groups are merged around the first group's mean, so a level common to
 // the whole row cancels before anything is squared:
-//   mean = m_0 + avg_g (m_g - m_0),   M2 = sum_g M2_g + 64 (sum_g (m_g - m_0)^2 - G (mean - m_0)^2).
+//   mean = m_0 + avg_g (m_g - m_0),   M2 = sum_g M2_g + W (sum_g (m_g - m_0)^2 - G (mean - m_0)^2),  G groups of W columns.
 // In two parts, so that the loads are under way while the accumulators are staged: `fetch` asks for the statistics, `merge`
 // uses them.  Both belong to the epilogue: while loads into LDS are in flight the compiler waits for all of them before it
 // uses any other loaded value, so in front of the k loop the statistics cost a drained pipeline (us before the first
 // barrier with / without them, ViT-S 1.9 / 1.0, ViT-g 3.7 / 1.3).
-// Rows of up to 24 groups (width 1536) go in one batch; more follow in `merge`.
+// Rows of up to 24 groups (width 1536; 768 in groups of 32) go in one batch; more follow in `merge`.
 struct LnRow {
     f32x4 v[12];                    // two groups each
     float odd_mean, odd_m2, level;  // the last group of an odd number; what A was stored against
@@ -424,8 +427,8 @@ struct LnRow {
         }
         const float G = (float)p.ln_groups, dm = sd / G;
         mean = m0 + dm;
-        const float m2 = sm2 + 64.0f * fmaxf(sdd - G * dm * dm, 0.0f);
-        rstd = 1.0f / sqrtf(m2 / (64.0f * G) + p.ln_eps);
+        const float m2 = sm2 + p.ln_width * fmaxf(sdd - G * dm * dm, 0.0f);
+        rstd = 1.0f / sqrtf(m2 / (p.ln_width * G) + p.ln_eps);
     }
 };
 
@@ -438,12 +441,12 @@ __device__ __forceinline__ float lane_across(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, true));
 }
 
-// Statistics (mean, sum of squared deviations) of a 64-column group of the row of `e`, for the LayerNorm that follows.
-// Called by all 8 lanes that hold the group's chunks (consecutive lanes, chunk index = lane % 8).  Each lane takes its
+// Statistics (mean, sum of squared deviations) of a W-column group (64 or 32) of the row of `e`, for the LayerNorm that follows.
+// Called by all W / 8 lanes that hold the group's chunks (consecutive lanes, chunk index = lane % (W / 8)).  Each lane takes its
 // eight values around the first of them, then the lanes' means and sums are merged pairwise: only differences are
 // squared, so the level of the data cancels.
-template <typename T>
-__device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k, const EpiRow& e, const float* v, bool active, int lane8) {
+template <typename T, int W = 64>
+__device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k, const EpiRow& e, const float* v, bool active, int chunk) {
     if (!p.st_out) return;
     float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
@@ -459,11 +462,13 @@ __device__ __forceinline__ void group_stats(const GemmArgs& p, const EpiCols& k,
     d = lane_across<2>(mean) - mean;
     m2 += lane_across<2>(m2) + 8.0f * d * d;
     mean += 0.5f * d;
-    d = lane_across<4>(mean) - mean;
-    m2 += lane_across<4>(m2) + 16.0f * d * d;
-    mean += 0.5f * d;
-    if (active && lane8 == 0)
-        *reinterpret_cast<f32x2*>(p.st_out + ((int64_t)e.orow * (p.N >> 6) + (k.c >> 6)) * 2) = f32x2{mean, m2};
+    if constexpr (W == 64) {
+        d = lane_across<4>(mean) - mean;
+        m2 += lane_across<4>(m2) + 16.0f * d * d;
+        mean += 0.5f * d;
+    }
+    if (active && chunk == 0)
+        *reinterpret_cast<f32x2*>(p.st_out + ((int64_t)e.orow * (p.N >> (W == 64 ? 6 : 5)) + (k.c >> (W == 64 ? 6 : 5))) * 2) = f32x2{mean, m2};
 }
 
 // The folded LayerNorm's (mean, rstd) of the tile's rows into lnrow[2 row] (LDS), one thread per row: `ask` in front of other
@@ -514,8 +519,11 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
     LnTile<BM> ln;
     if (has_ln) ln.ask(p, m0, tid);
     // the lane's columns for the row-chunk paths, and its first rows' operands: on their way while the tile is staged
-    constexpr int CG = BN / 8, RPASS = NT / CG, PASSES = BM / RPASS, NB = PASSES < 4 ? PASSES : 4;
+    // (32 x 32 tiles have fewer chunks than the workgroup threads: the others stand by)
+    constexpr int CG = BN / 8, RPASS = NT / CG < BM ? NT / CG : BM, PASSES = BM / RPASS, NB = PASSES < 4 ? PASSES : 4;
+    constexpr bool SPARE = NT / CG > BM;
     static_assert(BM % RPASS == 0 && PASSES % NB == 0, "whole passes over the tile's rows");
+    static_assert(BN % 64 == 0 || EPI == EPI_RESID, "tiles of 32 columns are for the residual epilogue");
     const int cg = tid % CG, rr0 = tid / CG;
     const bool values = EPI == EPI_QKV && n0 >= 2 * p.dim;            // value columns of QKV
     const bool chunks = EPI != EPI_SWIGLU && EPI != EPI_ROWDOT && !values;
@@ -525,7 +533,7 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
             const int r = m0 + rr0 + n * RPASS;
-            rows[n] = epilogue_row_operands<EPI>(p, cols, r, r < p.M && cols.nv > 0);
+            rows[n] = epilogue_row_operands<EPI>(p, cols, r, r < p.M && cols.nv > 0 && !(SPARE && rr0 >= BM));
         }
     };
     if (chunks) {
@@ -534,7 +542,8 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
     }
     // 4-column groups of a row are exchanged by the row: 16 consecutive rows writing one group, and eight lanes reading one
     // column of eight 8-row blocks (the transposed value store), fall on different banks
-    auto at = [&](int row, int col) { return row * BN + (col ^ (((row ^ (row >> 3)) & 15) << 2)); };
+    constexpr int GROUPS = BN / 4 < 16 ? BN / 4 : 16;
+    auto at = [&](int row, int col) { return row * BN + (col ^ (((row ^ (row >> 3)) & (GROUPS - 1)) << 2)); };
     {
         float* own = sC + kg * BM * BN;
 #pragma unroll
@@ -641,6 +650,7 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
         }
         return;
     }
+    if (SPARE && rr0 >= BM) return;
 #pragma unroll 1
     for (int b = 0; b < PASSES; b += NB) {
         EpiRow now[NB];
@@ -661,7 +671,7 @@ __device__ __forceinline__ void block_epilogue(const GemmArgs& p, f32x16 (&acc)[
             tile8(rr, cg * 8, v);
             if (has_ln) ln_apply(row_stats(rr), cols.g0, cols.g1, v);
             if (active) epilogue_chunk<T, EPI>(p, cols, now[n], v);
-            if (EPI == EPI_RESID || EPI == EPI_PATCH) group_stats<T>(p, cols, now[n], v, active, cg & 7);
+            if (EPI == EPI_RESID || EPI == EPI_PATCH) group_stats<T, BN % 64 ? 32 : 64>(p, cols, now[n], v, active, cg & (BN % 64 ? 3 : 7));
         }
     }
 }

@@ -51,11 +51,18 @@ constexpr TileModel kConv[] = {
     {33, 32, 64, 2, {3.59f, 3.59f, 3.59f}, 0.0f, 0.00225f, 0.00179f, 0.00f},
     {3, 32, 64, 3, {3.60f, 3.60f, 3.60f}, 0.0f, 0.00242f, 0.00188f, 0.00f},
 };
+// 32 x 32 tiles, for the residual epilogue alone (GemmArgs::st_group = 32): faster than 33 exactly where a CU has one of them (us, 33 / 34,
+// out-projection and fc2: ViT-S 257 tokens, 108 tiles, 3.69 5.41 / 3.41 4.52, 485, 192, 3.76 5.48 / 3.49 4.63, 785, 300, 3.86 5.66 / 4.02 6.52;
+// ViT-B 257, 216, 4.42 8.74 / 3.98 7.31; ViT-L 261, 288, 4.87 10.33 / 5.46 13.71; launches with their weights in the L2s, in a frame
+// both take longer).
+constexpr TileModel kNarrow = {34, 32, 32, 2, {3.10f, 3.10f, 3.10f}, 0.0f, 0.00105f, 0.00115f, 1.50f};
 // What a convolution's tile of up to 64 rows has to be faster by, alone, to be taken over a larger one, whatever else runs (the launcher
 // does not know): a head's convolutions run beside encoder kernels, where operand traffic costs more than the time alone shows (ViT-S 476x630 frames of two lanes:
 // 609 us without this, 591 with it; 256 -> 256 on 136x180 takes 37.7 us with 64 x 128 tiles and 40.5 with 128 x 128).
 constexpr float kConvShared = 1.12f;
 }  // namespace
+
+static bool narrow_fits(const GemmArgs& a) { return a.epi == EPI_RESID && a.m_begin == 0 && a.K % 128 == 0; }
 
 // Can (and, with the tuning aids, may) a tiling take this problem?
 static bool admissible(const TileModel& c, const GemmArgs& a, int amode) {
@@ -120,12 +127,20 @@ GemmPlan plan_gemm_bf16(const GemmArgs& a, int amode) { return amode == A_CONV3 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best);
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, int amode, hipStream_t s) {
+    if (a.st_group == 32) return amode == A_PLAIN && narrow_fits(a) ? launch_gemm_dma_bf16(34, a, amode, s) : hipErrorInvalidValue;
     const GemmPlan plan = plan_gemm_bf16(a, amode);
     if (!plan.lead_kind) return launch_picked(a, amode, s, plan.kind);
     GemmArgs lead = a, tail = a;
     lead.M = tail.m_begin = plan.lead_rows;
     const hipError_t rc = launch_gemm_dma_bf16(plan.lead_kind, lead, amode, s);
     return rc != hipSuccess ? rc : launch_picked(tail, amode, s, plan.kind);
+}
+
+int stats_columns_bf16(const GemmArgs& a) {
+    if (!narrow_fits(a) || (g_forced_tile && g_forced_tile != 34) || g_no_splitk) return 64;
+    float cost = 0.0f;
+    pick_tile(kPlain, a, A_PLAIN, cost);
+    return g_forced_tile == 34 || tile_cost(kNarrow, a, A_PLAIN, tile_count(kNarrow, a)) < cost ? 32 : 64;
 }
 
 static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int best) {
@@ -140,7 +155,7 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
     }
     if (forced && forced != 9) {
         const bool deep = amode == A_CONV3 ? a.cC % 128 == 0 : a.K % 128 == 0;
-        best = forced == 33 && !deep ? 3 : forced == 43 && !deep ? 4 : forced;
+        best = forced == 33 && !deep ? 3 : forced == 43 && !deep ? 4 : forced == 34 ? (deep ? 33 : 3) : forced;
     }
     return launch_gemm_dma_bf16(best, a, amode, s);
 }
@@ -149,7 +164,7 @@ static hipError_t launch_picked(const GemmArgs& a, int amode, hipStream_t s, int
 hipError_t configure_gemm_bf16() {
     const char* env = getenv("VPE_GEMM_TILE");
     g_forced_tile = 0;
-    for (int kind : {384, 256, 20, 2, 65, 64, 6, 5, 43, 4, 33, 3, 9}) if (env && atoi(env) == kind) g_forced_tile = kind;      // (anything else: no tile forced)
+    for (int kind : {384, 256, 20, 2, 65, 64, 6, 5, 43, 4, 33, 3, 34, 9}) if (env && atoi(env) == kind) g_forced_tile = kind;      // (anything else: no tile forced)
     if (env && (atoi(env) == 128 || atoi(env) == 129)) g_forced_tile = 2;                     // (the 256 x 128 shapes that 128 x 128 replaced)
     g_no_small = getenv("VPE_NO_SMALL_DMA") != nullptr;
     g_no_splitk = getenv("VPE_NO_SPLITK") != nullptr;

@@ -692,14 +692,21 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     constexpr int lds = (stage_b > epi_b ? stage_b : epi_b) + (sizeof(T) == 4 ? 64 : 0);        // fp32: a flag per wave
     static_assert(lds * OCC <= 160 * 1024 && nt <= 1024 && lds % 16 == 0, "LDS budget of one CU, workgroup size");
     typedef void (*Kernel)(const GemmArgs);
-#define VPE_KERNEL(mode, epi) &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, mode, epi, BM, KG, RING>
+    // (tiles of 32 columns: the residual epilogue only)
+    constexpr auto kernel_for = [](auto mode, auto epi) -> Kernel {
+        if constexpr (BN % 64 && !(mode == A_PLAIN && epi == EPI_RESID)) return nullptr;
+        else return &gemm_dma_kernel<T, BN, BK, S, WGM, WGN, OCC, decltype(mode)::value, decltype(epi)::value, BM, KG, RING>;
+    };
+#define VPE_KERNEL(mode, epi) kernel_for(std::integral_constant<int, mode>{}, std::integral_constant<int, epi>{})
     static const Kernel plain[] = {VPE_KERNEL(A_PLAIN, EPI_STORE), VPE_KERNEL(A_PLAIN, EPI_RESID), VPE_KERNEL(A_PLAIN, EPI_SWIGLU),
                                    VPE_KERNEL(A_PLAIN, EPI_QKV), VPE_KERNEL(A_PLAIN, EPI_PATCH)};
     static const Kernel conv[] = {VPE_KERNEL(A_CONV3, EPI_STORE), VPE_KERNEL(A_CONV3, EPI_ROWDOT)};
 #undef VPE_KERNEL
     static bool configured = false;
     if (!configured) {
-        auto opt_in = [&](Kernel k) { return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+        auto opt_in = [&](Kernel k) {
+            return k ? hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds) : hipSuccess;
+        };
         hipError_t rc = hipSuccess;
         for (Kernel k : plain) if (rc == hipSuccess) rc = opt_in(k);
         for (Kernel k : conv) if (rc == hipSuccess) rc = opt_in(k);
@@ -710,6 +717,7 @@ static inline hipError_t launch_gemm_dma(const GemmArgs& a, int amode, hipStream
     if (a.K < BK || a.K % BK || (amode == A_CONV3 && a.cC % BK)) return hipErrorInvalidValue;      // the k loop has no remainder
     if (amode == A_CONV3 ? a.epi != EPI_STORE && a.epi != EPI_ROWDOT : a.epi < EPI_STORE || a.epi > EPI_PATCH) return hipErrorInvalidValue;
     const Kernel k = amode == A_CONV3 ? conv[a.epi == EPI_ROWDOT] : plain[a.epi];
+    if (!k) return hipErrorInvalidValue;
     GemmArgs args = a;
     args.map = TileMap::make(cdiv(a.M - a.m_begin, BM), cdiv(a.N, BN));
     hipLaunchKernelGGL(k, dim3(args.map.tiles, a.nz > 1 ? a.nz : 1), dim3(nt), lds, s, args);

@@ -18,6 +18,7 @@ namespace vpe {
 //     6:  64 x 128, 8 waves in four groups (64 x 64 wave tiles), four stages, one workgroup per CU: long k loops on up to 256 tiles
 //     4:  64 x 64, 8 waves in four groups (64 x 32 wave tiles), four stages;  43: the same with 128-deep k-tiles, three stages, one
 //        workgroup per CU: half the barriers
+//    34:  32 x 32, 4 waves in four groups, 128-deep k-tiles, four stages, two per CU: residual epilogue only, one tile per CU (gemm_bf16.hip)
 //     3:  32 x 64, 4 waves in four groups (32 x 64 wave tiles), four stages, three per CU;  33: 128-deep k-tiles, three stages, two per CU
 // 3 to 6 are for problems with few tiles per CU, where a workgroup's own loop is the time: fixed cost (alpha of the time models in
 // gemm_bf16.hip, by epilogue: 3.1-4.0 us for the 32-row tiles, 3.7-4.3 for 64 x 64, 5.1-5.6 for 64 x 128) and the rate at which one CU loads (40-56 bytes a clock).  us, 64 x 64 in four
@@ -36,6 +37,7 @@ hipError_t launch_gemm_dma_bf16(int kind, const GemmArgs& a, int amode, hipStrea
         case 5: return launch_gemm_dma<bf16, 128, 64, 3, 2, 2, 2, 64, 2>(a, amode, s, configure_only);
         case 43: return launch_gemm_dma<bf16, 64, 128, 3, 1, 2, 1, 64, 4>(a, amode, s, configure_only);
         case 4: return launch_gemm_dma<bf16, 64, 64, 4, 1, 2, 2, 64, 4>(a, amode, s, configure_only);
+        case 34: return launch_gemm_dma<bf16, 32, 128, 4, 1, 1, 2, 32, 4>(a, amode, s, configure_only);
         case 33: return launch_gemm_dma<bf16, 64, 128, 3, 1, 1, 2, 32, 4>(a, amode, s, configure_only);
         case 3: return launch_gemm_dma<bf16, 64, 64, 4, 1, 1, 2, 32, 4>(a, amode, s, configure_only);
         default: return launch_gemm_dma<bf16, 128, 64, 2, 4, 2, 2, 128, 1, true>(a, amode, s, configure_only);
@@ -78,7 +80,7 @@ hipError_t configure_gemm() {
     if (rc == hipSuccess) rc = launch_conv_strip<384, 256, 4, 2, 1, false>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, true>(a, nullptr, true);
     if (rc == hipSuccess) rc = launch_conv_strip<768, 128, 8, 1, 1, false>(a, nullptr, true);
-    for (int kind : {384, 256, 20, 2, 65, 64, 6, 5, 43, 4, 33, 3})
+    for (int kind : {384, 256, 20, 2, 65, 64, 6, 5, 43, 4, 33, 3, 34})
         if (rc == hipSuccess) rc = launch_gemm_dma_bf16(kind, a, A_PLAIN, nullptr, true);
     return rc;
 }

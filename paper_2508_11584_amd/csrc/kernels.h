@@ -14,6 +14,9 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, int amode, hipStream_t s);
 // lead_rows and `kind` over the others (host arithmetic only; the strip convolution may still take a whole problem's place).
 struct GemmPlan { int lead_kind, lead_rows, kind; };
 GemmPlan plan_gemm_bf16(const GemmArgs& a, int amode);
+// Columns per group of the statistics that a residual product had best leave (GemmArgs::st_group): 32 where tiles of 32 columns are the
+// fastest, else 64.  Asked once, when an engine is created: producer and consumers of the statistics have to agree.
+int stats_columns(int dtype, const GemmArgs& a);
 hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s);
 hipError_t configure_attention();
 hipError_t configure_gemm();

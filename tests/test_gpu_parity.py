@@ -301,6 +301,24 @@ def test_fp32_tilings_of_32_rows(tile, monkeypatch):
     test_fp32_head_weights_beyond_the_range_of_bf16(tile, monkeypatch)
 
 
+@pytest.mark.parametrize("dtype,name,tile", [("bf16", "VPE_GEMM_TILE", "34"), ("f32", "VPE_GEMM_TILE_F32", "6")])
+def test_tilings_of_32_columns(dtype, name, tile, monkeypatch):
+    # 32 x 32 tiles wherever they are allowed (out-projection and fc2; 32 x 64 elsewhere): the LayerNorms that follow read
+    # statistics of 32-column groups.  166 tokens, then 38 + 38 (the last row tile holds 12 rows); widths of one, two, three and four
+    # groups of 64, with k extents that 128-deep k-tiles do and do not divide (bf16: then one of the two leaves groups of 64); a
+    # level of +30 common to every token; SwiGLU.  The gates of every model of the type
+    monkeypatch.setenv(name, tile)
+    small = {"registers": 2, "batch": 2, "img_h": 70, "img_w": 98}
+    check_all(vi.ModelSpec("narrow_%s" % dtype, dtype=dtype, **MEDIUM), 148, 248, kinds=("seg",))
+    check_all(vi.ModelSpec("narrow_swiglu_%s" % dtype, dtype=dtype, **{**MEDIUM, **small, "mlp_kind": vi.MLP_SWIGLU}), 149, 249, kinds=("seg",))
+
+    def lift(w):
+        w["pos"][:] += np.float32(30.0)
+    for width, hidden in ((64, 128), (192, 384), (256, 192)):
+        check_all(vi.ModelSpec("narrow_%s_%d" % (dtype, width), dtype=dtype, **{**MEDIUM, **small, "dim": width, "heads": width // 64,
+                                                                               "mlp_hidden": hidden}), 150, 250, kinds=("seg",), weights_edit=lift)
+
+
 @pytest.mark.parametrize("shape", ["1", "2"])
 def test_strip_convolution_kernel(shape, monkeypatch):
     # the 3x3 convolution that forms its nine taps from one input strip in LDS, in both of its tile shapes (1: 384 x 256,
