@@ -19,17 +19,18 @@
  *   - "device" pointers are HIP device addresses on the current device; "host" pointers
  *     are ordinary process memory.
  *   - streams are hipStream_t passed as void*; NULL selects the engine's own stream for
-  *     that call (one stream per encoder lane, one stream per head, all at default priority).
+  *     that call (one stream per encoder lane and the head streams, see head_streams and vpe_run_head; all at
+ *     default priority).
  *   - vpe_encode and vpe_run_head only enqueue work; vpe_sync blocks until it is done.
  *   - an engine may be driven from one host thread at a time.
  *
  * Throughput.  With the defaults (encoder_lanes = 1) frames pass through the encoder one after another and a
- * ViT-S pass leaves most of the 256 compute units idle (about 1100 frames/s at 476x630 with three heads).  The
+ * ViT-S pass leaves most of the 256 compute units idle (about 1340 frames/s at 476x630 with three heads).  The
  * pipelined rate the benchmark reports (about 2100 frames/s) needs encoder_lanes = 3 and ring_slots = 4 (lanes + 1),
  * which makes the engine use 3 encoder streams + 1 head stream, AND a process that may use five hardware queues:
  * export GPU_MAX_HW_QUEUES=5 before the HIP runtime initialises (the runtime's default of 4 leaves three for the
  * engine beside the default stream's, and the fourth engine stream then shares a queue and serialises; with the
- * default limit the best choice is encoder_lanes = 2, ring_slots = 3: about 1650 frames/s).  The batched
+ * default limit the best choice is encoder_lanes = 2, ring_slots = 3: about 1900 frames/s).  The batched
  * configurations (4 or 8 views per step) want encoder_lanes = 2, ring_slots = 3.
  */
 #ifndef VPE_H
@@ -100,8 +101,9 @@ typedef struct {
                               encoder passes of k consecutive frames overlap on the GPU -- throughput pipelining,
                               per-frame results are unchanged */
     int32_t head_streams; /* streams the heads are spread over (heaviest head first, onto the least loaded);
-                              0 = as many as heads, within the four hardware queues a process gets by default
-                              minus the encoder lanes (at least 1).  Heads sharing a stream run in call order */
+                              0 = as many as heads whose runs take at least half as long as the longest's, within the
+                              four hardware queues a process gets by default minus the encoder lanes (at least 1).
+                              Heads sharing a stream run in call order */
     int32_t reserved;
     const void* weights;  /* host, fp32 */
     uint64_t weights_bytes;
@@ -199,8 +201,10 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
 
 /* A head module's step (paper, Sec. "Head Module": each head reads the middle buffer asynchronously, by
  * reference, runs its model and leaves its post-processed result in its output buffer; Sec. "Dynamic Frequency
- * Control" for the rate).  Enqueues head `head` on the features of frame fh, in place, on `stream` (NULL = the
- * head's own stream) after the frame's encoder pass and the head's previous run.  Returns VPE_SKIPPED when
+ * Control" for the rate).  Enqueues head `head` on the features of frame fh, in place, on `stream` (NULL = an
+ * engine stream: the head's, or with head_streams = 0 that of the frame's encoder lane, right behind the newest frame's
+ * encode -- for heads that are short beside an encoder pass, and for a single long one when the previous frame is done)
+ * after the frame's encoder pass and the head's previous run.  Returns VPE_SKIPPED when
  * fh.frame % every_n != 0 or a limit in Hz says the frame is not due, VPE_ESTALE when the slot has been reused by
  * a later frame, VPE_EINVAL for an unknown head or a handle this engine did not produce, VPE_EHIP. */
 int vpe_run_head(vpe_engine* e, int head, vpe_feat fh, void* stream);

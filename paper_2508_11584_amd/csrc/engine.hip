@@ -140,6 +140,8 @@ struct Head {
     // scheduling
     hipStream_t stream = nullptr;     // one of the engine's head streams (shared when heads outnumber them)
     hipEvent_t last_done = nullptr;   // completion of the most recent run (any slot)
+    bool light = false;               // all heads' runs together are shorter than what a waiting stream costs an encoder pass
+    bool heavy = false;               // the only one that is long: no other's run is half as long
     hipEvent_t t_begin = nullptr, t_end = nullptr;   // around the most recent run (engines created with VPE_FLAG_TIMING)
     bool ran = false;
     int64_t runs = 0, skips = 0;
@@ -186,6 +188,7 @@ struct vpe_engine {
         float* lev[2] = {nullptr, nullptr};   // [T] row levels the copy u is stored against, alternating (see ln_gemm)
         hipStream_t stream = nullptr;
         hipEvent_t done = nullptr;      // completion of the lane's most recent encode
+        bool own = false;               // that encode ran on the lane's own stream
         hipEvent_t t_begin = nullptr, t_end = nullptr;   // around it (engines created with VPE_FLAG_TIMING)
         bool used = false;
     };
@@ -349,6 +352,13 @@ double head_flops(const vpe_engine& e, const Head& h) {
         }
         default: return P * (4.0 * e.D * h.ch + 85.0 * 9 * h.ch * h.ch);   // four 3x3 stages on 1 + 4 + 16 + 64 grids
     }
+}
+
+// About what a head's run takes by itself, in us: its launches (about 5 us each when they are small) and its operations at 600
+// TFLOP/s (fp32: a tenth); head_flops counts multiply-adds.
+double head_us(const vpe_engine& e, const Head& h) {
+    const int launches = h.kind == VPE_HEAD_SEG ? 2 : h.kind == VPE_HEAD_DET ? 3 : h.kind == VPE_HEAD_DPT ? 35 : 10;
+    return 5.0 * launches + 2.0 * head_flops(e, h) / (e.bf ? 600e6 : 60e6);
 }
 
 // Hands out the intermediate buffers of a seg / det / DPT-lite head (see HeadScratch) from `b`.
@@ -1052,7 +1062,22 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
         if (hip(hipEventCreateWithFlags(&e->lane[l].done, hipEventDisableTiming), "hipEventCreate")) return bail(VPE_EHIP);
     }
     if (nh > 0) {
-        int ns = cfg->head_streams > 0 ? cfg->head_streams : std::max(1, HW_QUEUES - e->lanes);
+        // A stream that waits for a frame slows every kernel of the encoder stream down, by 0.4-0.7 us a launch and waiting
+        // stream (60 launches of 3.2 us 195 us a frame, with one stream waiting for their end 239, with two 263): heads share a stream
+        // unless several of them are about as heavy as the heaviest (us a frame, three streams / one: ViT-S 476x630 with
+        // segmentation, depth and detection 792 / 762, with the full DPT head 772 / 694, on two lanes 580 / 535, ViT-L 518x518
+        // 2807 / 2753).  All heads are light when their runs together are shorter than what one waiting stream costs a pass.
+        double heaviest = 0.0, total_us = 0.0;
+        for (const Head& h : e->heads) { heaviest = std::max(heaviest, head_us(*e, h)); total_us += head_us(*e, h); }
+        int heavy = 0;
+        for (Head& h : e->heads) heavy += h.heavy = 2.0 * head_us(*e, h) >= heaviest;
+        // (several heavy ones run side by side on streams of their own, and a number of streams that the caller chose is what heads get)
+        const bool chosen = cfg->head_streams > 0;
+        for (Head& h : e->heads) {
+            h.heavy = h.heavy && heavy == 1 && !chosen;
+            h.light = !chosen && total_us <= 0.7 * (5 * e->L + 3);
+        }
+        int ns = cfg->head_streams > 0 ? cfg->head_streams : std::min(heavy, std::max(1, HW_QUEUES - e->lanes));
         ns = std::min(ns, nh);
         e->head_streams.assign(ns, nullptr);
         for (auto& hs : e->head_streams)
@@ -1150,6 +1175,7 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
         if (e->timing) HIPCHK(e, hipEventRecord(L.t_end, s));
         HIPCHK(e, hipEventRecord(L.done, s));
         L.used = true;
+        L.own = s == L.stream;
         e->last_lane = ln;
         HIPCHK(e, hipEventRecord(e->ready[slot], s));
     }
@@ -1176,6 +1202,26 @@ bool hz_allows(Head& h, double t) {
     h.due = h.due_set && t - h.due < h.period ? h.due + h.period : t + h.period;
     h.due_set = true;
     return true;
+}
+
+// The stream of a run whose caller names none.  Right behind the frame's own encode, in its stream, nothing has to wait for another
+// stream: light heads run there, and where the host waits for every frame (the previous frame and the head's previous run are
+// done) the heavy ones, beside the light ones on the head stream.  Otherwise the head's stream, beside the next frames' encodes.
+// us a frame, streams of their own / this: ViT-S 224x224 segmentation 434 / 377, fp32 717 / 677; waited for, ViT-S 476x630 three
+// heads 876 / 821, full DPT 948 / 911, ViT-L 518x518 2887 / 2831.
+hipStream_t stream_for(vpe_engine* e, const Head& h, int64_t frame) {
+    const vpe_engine::Lane& L = e->lane[frame % e->lanes];
+    if (frame + 1 != e->frames || !L.own) return h.stream;
+    if (h.light) return L.stream;
+    if (!h.heavy) return h.stream;
+    // (a query is not a call that another thread's capture forbids, whatever that thread's mode)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return h.stream;
+    const bool idle = (!h.ran || hipEventQuery(h.last_done) == hipSuccess) &&
+                      (frame == 0 || (e->S > 1 && hipEventQuery(e->ready[(frame - 1) % e->S]) == hipSuccess));
+    if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();      // (no error of a later call)
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return idle ? L.stream : h.stream;
 }
 
 // Enqueue one run of a head on the frame in `slot` (already checked to be current and due).
@@ -1220,6 +1266,7 @@ int vpe_run_head(vpe_engine* e, int head, vpe_feat fh, void* stream) {
     if (fh.frame % h.every_n != 0) { ++h.skips; return VPE_SKIPPED; }
     if (e->slot_frame[fh.slot] != fh.frame) return e->fail(VPE_ESTALE, "slot has been reused by a later frame");
     if (!hz_allows(h, e->slot_time[fh.slot])) { ++h.skips; return VPE_SKIPPED; }
+    if (!stream && !e->host_only) stream = stream_for(e, h, fh.frame);
     return start_head(e, head, fh.slot, fh.frame, stream, h.sc, true);
 }
 

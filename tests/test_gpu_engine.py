@@ -145,6 +145,58 @@ def test_unsynchronised_stream_of_frames_ends_in_the_right_state(lanes, slots, h
     eng.close()
 
 
+@pytest.mark.parametrize("kinds", [("seg",), ("seg", "det"), ("seg", "depth", "det"), ("depth", "depth")])
+@pytest.mark.parametrize("lanes", [1, 2])
+def test_runs_on_whichever_stream_the_engine_picks_give_the_same_results(kinds, lanes):
+    # heads in the encoder lane's stream or on head streams: waited-for frames, frames pushed without waiting, runs on a frame
+    # that is no longer the newest, encodes and runs on a caller's stream, in turn on one engine; every frame's last run against
+    # an engine that takes that frame alone
+    fs = frames(3, seed=510)
+    alone = []
+    for f in fs:
+        eng, _, _ = make_engine(SPEC, 18, kinds=kinds)
+        fh = eng.encode(f)
+        for h in range(len(kinds)):
+            eng.run_head(h, fh)
+        eng.sync()
+        alone.append([eng.head_output(h, 0).clone() for h in range(len(kinds))])
+        eng.close()
+    eng, _, _ = make_engine(SPEC, 18, kinds=kinds, flags=vpe.VPE_FLAG_GRAPHS, ring_slots=3, encoder_lanes=lanes)
+    mine = torch.cuda.Stream()
+
+    def check(f):
+        eng.sync()
+        torch.cuda.synchronize()
+        for h, want in enumerate(alone[f]):
+            assert torch.equal(eng.head_output(h, 0), want), (f, h)
+
+    for turn in range(3):
+        for f in range(3):                                   # waited for
+            fh = eng.encode(fs[f])
+            for h in range(len(kinds)):
+                eng.run_head(h, fh)
+            check(f)
+        for i in range(12):                                  # without waiting
+            fh = eng.encode(fs[i % 3])
+            for h in range(len(kinds)):
+                eng.run_head(h, fh)
+        check(2)
+        older = eng.encode(fs[0])                            # no longer the newest, then the newest again
+        fh = eng.encode(fs[1])
+        for h in range(len(kinds)):
+            eng.run_head(h, older)
+        check(0)
+        for h in range(len(kinds)):
+            eng.run_head(h, fh)
+        check(1)
+        mine.wait_stream(torch.cuda.current_stream())
+        fh = eng.encode(fs[2], stream=mine)                  # a caller's stream for the encode, then for the runs, too
+        for h in range(len(kinds)):
+            eng.run_head(h, fh, None if turn % 2 else mine)
+        check(2)
+    eng.close()
+
+
 def test_no_device_allocation_after_create():
     eng, _, _ = make_engine(SPEC, 16, flags=vpe.VPE_FLAG_GRAPHS)
     fs = frames(2)
