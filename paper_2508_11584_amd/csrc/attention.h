@@ -37,6 +37,13 @@ struct RowNorm {
     float eps;
     int blocks;          // (filled in by the launcher)
 };
+// Memory that the launch reads once for the sake of the memory-side cache, with workgroups of its own: the weights of the products that
+// follow, of models whose weights do not stay there from frame to frame.  Whole KB each (the rest of a KB is not read).
+struct Touch {
+    const void* at[3];
+    uint32_t kb[3];
+    int blocks;          // 0: none
+};
 struct AttnArgs {
     const void* qk;
     const void* vt;
@@ -47,6 +54,7 @@ struct AttnArgs {
     int shared_gpu;      // the launch runs beside other streams' kernels (several encoder lanes): prefer a shape that
                          // leaves room on its CUs over the fastest one on an empty GPU
     RowNorm norm;
+    Touch touch;
 };
 
 // Exchange between the two halves of a wave without going through LDS (v_permlane32_swap): both operands are the
@@ -286,8 +294,8 @@ constexpr int attn_min_waves() {
     return QW * KW == 4 && QB == 2 ? 1 : sizeof(T) == 2 && QB == 1 && KW == 1 ? 3 : 2;
 }
 
-// NORM: with a RowNorm's workgroups (an instantiation of its own: the look at their number is 0.25 us of every launch).
-template <typename T, int QB, int QW, int KW, bool FIXED, bool NORM>
+// RIDERS: with a RowNorm's or a Touch's workgroups (an instantiation of its own: the look at their number is 0.25 us of every launch).
+template <typename T, int QB, int QW, int KW, bool FIXED, bool RIDERS>
 __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) void attention_kernel(const AttnArgs p) {
     constexpr int NW = QW * KW, NT = 64 * NW;
     static_assert(KW <= ATTN_MAX_KW, "the loader's overshoot is budgeted for at most ATTN_MAX_KW key waves");
@@ -306,9 +314,20 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     // so ids are remapped to give each XCD one contiguous range -- all query blocks of an (image, head) pair then run
     // on the same XCD and its keys and values are fetched into that L2 once, not into all eight (measured at ViT-g x8:
     // 615 MB fetched per launch against 135 MB of operands before the remapping).
-    const int nqb = cdiv(p.N, 32 * QB * QW), tasks = gridDim.x - (NORM ? p.norm.blocks : 0);
-    if (NORM && (int)blockIdx.x >= tasks) {
-        for (int row = (blockIdx.x - tasks) * NW + wave; row < p.norm.rows; row += p.norm.blocks * NW)
+    const int nqb = cdiv(p.N, 32 * QB * QW), tasks = gridDim.x - (RIDERS ? p.touch.blocks + p.norm.blocks : 0);
+    if (RIDERS && (int)blockIdx.x >= tasks) {
+        const int rider = blockIdx.x - tasks;
+        if (rider < p.touch.blocks) {
+            // straight to LDS, one KB of it a wave: no registers, up to 63 loads of a wave on their way
+#pragma unroll 1
+            for (int s = 0; s < 3; ++s)
+                for (uint32_t k = rider * NW + wave; k < p.touch.kb[s]; k += p.touch.blocks * NW)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(p.touch.at[s]) + k * 1024ull + lane * 16),
+                                                     (__attribute__((address_space(3))) void*)(smem + wave * 1024), 16, 0, 0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);            // (the LDS is this workgroup's until the loads have landed)
+            return;
+        }
+        for (int row = (rider - p.touch.blocks) * NW + wave; row < p.norm.rows; row += p.norm.blocks * NW)
             layernorm_row(p.norm.x, row, p.norm.D, p.norm.gain, p.norm.bias, p.norm.eps, reinterpret_cast<T*>(p.norm.out), lane);
         return;
     }
@@ -719,7 +738,8 @@ static inline hipError_t launch_attention_variant(const AttnArgs& a, hipStream_t
     if (a.pad < 2 * KW * 64 || a.npad % 64 || a.npad < a.N || a.dim != a.heads * 64) return hipErrorInvalidValue;
     AttnArgs args = a;
     args.norm.blocks = !a.norm.x ? 0 : cdiv(a.norm.rows, QW * KW) < 512 ? cdiv(a.norm.rows, QW * KW) : 512;       // a row per wave up to two per CU
-    hipLaunchKernelGGL(kernels[args.norm.blocks > 0], dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads + args.norm.blocks), dim3(64 * QW * KW), lds, s, args);
+    const int riders = args.norm.blocks + args.touch.blocks;
+    hipLaunchKernelGGL(kernels[riders > 0], dim3(cdiv(a.N, 32 * QB * QW) * a.B * a.heads + riders), dim3(64 * QW * KW), lds, s, args);
     return hipGetLastError();
 }
 

@@ -708,6 +708,25 @@ int residual_group(const vpe_engine& e, int k) {
     return stats_columns(e.bf, a);
 }
 
+// The weights of the three products behind block l's attention, which its launch reads ahead of them (Touch), for models whose weights
+// do not stay in the 256 MB of memory-side cache from frame to frame.  The first tiles of a product wait for every line of theirs, and
+// every page's translation, from memory: of a ViT-L pass at 518x518 330 of 2490 us (all blocks on one block's weights: 2160).  us a pass, without / with:
+// ViT-L 518x518 2487 / 2175 (with heads 2710 / 2438), x 2 4135 / 3590, 224x224 1220 / 1110, two lanes 1736 / 1708; ViT-g 518x518
+// 7070 / 6340, two lanes 5132 / 5144, 224x224 2810 / 2680.  With the next block's QKV weights as well ViT-g 6530, two lanes 5360.  64
+// workgroups are too few for 224x224 of ViT-g (3000), 16 and 32 slow every size down.
+constexpr int64_t TOUCH_BYTES = 200 << 20;      // of block weights, from which on they are read ahead
+constexpr int TOUCH_ROWS = 4096;                // more rows than that: the products are long, the attention leaves no room (ViT-L x 4 5845 / 6038)
+constexpr int TOUCH_BLOCKS = 128;
+Touch next_weights(const vpe_engine& e, int l) {
+    const BlockW& w = e.blk[l];
+    auto kb = [&](int64_t elements) { return (uint32_t)(elements * e.esz / 1024); };
+    return Touch{{w.proj_w, w.fc1_w, w.fc2_w}, {kb((int64_t)e.D * e.D), kb((int64_t)e.D * e.F), kb((int64_t)e.D * e.Mh)}, TOUCH_BLOCKS};
+}
+// (fp32 products take six times as long: ViT-B, 344 MB, 19.0 ms a rate cycle either way)
+bool reads_ahead(const vpe_engine& e) {
+    return e.bf && e.T <= TOUCH_ROWS && (int64_t)e.L * e.D * (4 * e.D + e.F + e.Mh) * e.esz > TOUCH_BYTES;
+}
+
 int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
     const int D = e.D, T = e.T, dt = e.bf;
     const vpe_engine::Lane& L = e.lane[lane];
@@ -724,6 +743,7 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
     int nxt = 0;
     int tap = 0;
     int group = 64;
+    const bool ahead = reads_ahead(e);
     RowNorm norm{};                              // the tapped rows that the next attention launch normalises
     for (int l = 0; l < e.L; ++l) {
         const BlockW& w = e.blk[l];
@@ -735,6 +755,7 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
         }
         {
             AttnArgs a{L.qk, L.vt, L.att, e.B, e.N, e.npad, D, e.nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e.lanes > 1, norm};
+            if (ahead) a.touch = next_weights(e, l);
             HIPCHK(&e, launch_attention(dt, a, s));
             norm = RowNorm{};
         }
