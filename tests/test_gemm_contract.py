@@ -129,6 +129,47 @@ def test_plans_use_tilings_whose_k_tiles_divide_the_problem(tmp_path):
     run_host_program(tmp_path, PLAN_PROGRAM)
 
 
+NARROW_PROGRAM = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace vpe;
+int main() {
+    int bad = 0, narrow = 0, wide = 0;
+    for (int dtype = 0; dtype < 2; ++dtype)
+        for (int k = 64; k <= 4096; k += 64)
+            for (int n : {64, 192, 384, 768, 1024, 1536})
+                for (double m = 1; m < 2e4; m *= 1.3) {
+                    GemmArgs a{};
+                    a.M = (int)m; a.N = n; a.K = k; a.nz = 1; a.epi = EPI_RESID;
+                    const int group = stats_columns(dtype, a);
+                    if (group != 32 && group != 64) ++bad;
+                    if (group == 32 && ((dtype && k % 128) || (int64_t)cdiv(a.M, 32) * (n / 32) > 512)) { printf("dtype %d M %d N %d K %d\n", dtype, a.M, n, k); ++bad; }
+                    (group == 32 ? narrow : wide) += 1;
+                    for (int epi : {EPI_STORE, EPI_PATCH, EPI_QKV}) { a.epi = epi; if (stats_columns(dtype, a) != 64) { printf("epilogue %d\n", epi); ++bad; } }
+                }
+    // groups of 32 columns are refused where no tile leaves them
+    for (int dtype = 0; dtype < 2; ++dtype)
+        for (int kind = 0; kind < 3; ++kind) {
+            GemmArgs a{};
+            a.M = a.N = 64; a.K = kind == 1 ? 192 : 256; a.lda = a.ldo = 64; a.a_rpi = a.o_rpi = 64; a.nz = 1;
+            a.epi = kind == 0 ? EPI_STORE : EPI_RESID; a.st_group = 32;
+            if (kind == 2) { a.epi = EPI_STORE; a.cC = 64; a.K = 576; a.cH = a.cW = 8; }
+            if (kind == 1 && !dtype) continue;                              // (fp32 k-tiles are 64 deep)
+            const hipError_t rc = launch_gemm(dtype, a, kind == 2 ? A_CONV3 : A_PLAIN, nullptr);
+            if (rc != hipErrorInvalidValue) { printf("dtype %d kind %d: %d\n", dtype, kind, (int)rc); ++bad; }
+        }
+    printf("%d narrow, %d wide\n", narrow, wide);
+    return bad ? 1 : !narrow || !wide;
+}
+"""
+
+
+def test_statistics_of_32_columns_only_where_a_tile_leaves_them(tmp_path):
+    # residual products of both types over k extents of odd and even multiples of 64, one row to 20000: 32-column groups only for
+    # whole k-tiles and up to two 32 x 32 tiles per CU, never for another epilogue; asked for elsewhere they are refused
+    run_host_program(tmp_path, NARROW_PROGRAM)
+
+
 CONV_PLAN_PROGRAM = r"""
 #include <cstdio>
 #include "kernels.h"
