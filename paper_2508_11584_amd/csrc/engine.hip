@@ -141,7 +141,6 @@ struct Head {
     hipStream_t stream = nullptr;     // one of the engine's head streams (shared when heads outnumber them)
     hipEvent_t last_done = nullptr;   // completion of the most recent run (any slot)
     bool light = false;               // all heads' runs together are shorter than what a waiting stream costs an encoder pass
-    bool heavy = false;               // the only one that is long: no other's run is half as long
     hipEvent_t t_begin = nullptr, t_end = nullptr;   // around the most recent run (engines created with VPE_FLAG_TIMING)
     bool ran = false;
     int64_t runs = 0, skips = 0;
@@ -1091,13 +1090,9 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
         double heaviest = 0.0, total_us = 0.0;
         for (const Head& h : e->heads) { heaviest = std::max(heaviest, head_us(*e, h)); total_us += head_us(*e, h); }
         int heavy = 0;
-        for (Head& h : e->heads) heavy += h.heavy = 2.0 * head_us(*e, h) >= heaviest;
+        for (const Head& h : e->heads) heavy += 2.0 * head_us(*e, h) >= heaviest;
         // (several heavy ones run side by side on streams of their own, and a number of streams that the caller chose is what heads get)
-        const bool chosen = cfg->head_streams > 0;
-        for (Head& h : e->heads) {
-            h.heavy = h.heavy && heavy == 1 && !chosen;
-            h.light = !chosen && total_us <= 0.7 * (5 * e->L + 3);
-        }
+        for (Head& h : e->heads) h.light = cfg->head_streams <= 0 && total_us <= 0.7 * (5 * e->L + 3);
         int ns = cfg->head_streams > 0 ? cfg->head_streams : std::min(heavy, std::max(1, HW_QUEUES - e->lanes));
         ns = std::min(ns, nh);
         e->head_streams.assign(ns, nullptr);
@@ -1225,24 +1220,13 @@ bool hz_allows(Head& h, double t) {
     return true;
 }
 
-// The stream of a run whose caller names none.  Right behind the frame's own encode, in its stream, nothing has to wait for another
-// stream: light heads run there, and where the host waits for every frame (the previous frame and the head's previous run are
-// done) the heavy ones, beside the light ones on the head stream.  Otherwise the head's stream, beside the next frames' encodes.
-// us a frame, streams of their own / this: ViT-S 224x224 segmentation 434 / 377, fp32 717 / 677; waited for, ViT-S 476x630 three
-// heads 876 / 821, full DPT 948 / 911, ViT-L 518x518 2887 / 2831.
-hipStream_t stream_for(vpe_engine* e, const Head& h, int64_t frame) {
+// The stream of a run whose caller names none.  Right behind the newest frame's own encode, in its stream, nothing has to wait for
+// another stream: light heads run there (us a frame, a stream of its own / this: ViT-S 224x224 segmentation 434 / 377, fp32 717 /
+// 677).  A long head does not, not even on an idle engine: the next encode would wait for it, whenever the host waited for
+// something else than this head.
+hipStream_t stream_for(const vpe_engine* e, const Head& h, int64_t frame) {
     const vpe_engine::Lane& L = e->lane[frame % e->lanes];
-    if (frame + 1 != e->frames || !L.own) return h.stream;
-    if (h.light) return L.stream;
-    if (!h.heavy) return h.stream;
-    // (a query is not a call that another thread's capture forbids, whatever that thread's mode)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return h.stream;
-    const bool idle = (!h.ran || hipEventQuery(h.last_done) == hipSuccess) &&
-                      (frame == 0 || (e->S > 1 && hipEventQuery(e->ready[(frame - 1) % e->S]) == hipSuccess));
-    if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();      // (no error of a later call)
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    return idle ? L.stream : h.stream;
+    return h.light && frame + 1 == e->frames && L.own ? L.stream : h.stream;
 }
 
 // Enqueue one run of a head on the frame in `slot` (already checked to be current and due).

@@ -1,0 +1,63 @@
+"""Which of an engine's calls wait for which, by what is done when: heads and encodes beside a depth head of tens of milliseconds.
+
+In a process of its own: it may use four hardware queues, one stream each for the default stream, the encoder and two heads, and
+streams that share one run in turn whatever the engine does (the other tests' process has made dozens of streams)."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+import json, sys
+import numpy as np
+import torch
+import paper_2508_11584_amd as vpe
+import vpe_inputs as vi
+from paper_2508_11584_amd.synthetic import make_engine
+
+SPEC = vi.ModelSpec("long_head", dim=64, depth=4, heads=1, mlp_hidden=64, img_h=518, img_w=518, taps=(1, 2, 3, 4), head_ch=1024,
+                    dtype="bf16", batch=12)
+image = torch.from_numpy(vi.make_batch(SPEC, 31)).cuda()
+
+def engine(kinds, **kw):
+    eng, _, _ = make_engine(SPEC, 30, kinds=kinds, **kw)
+    for _ in range(2):                                   # (the first launches load code)
+        fh = eng.encode(image)
+        for h in range(len(kinds)):
+            eng.run_head(h, fh)
+        eng.sync()
+    return eng
+
+def ready(eng, fh):
+    while eng.frame_ready(fh) == vpe.VPE_BUSY:
+        pass
+
+found = {}
+
+# a long head on an idle engine, then the next frame
+eng = engine(("depth",))
+eng.run_head(0, eng.encode(image))
+ready(eng, eng.encode(image))
+found["long head done when the next encode was"] = eng.head_done(0)
+eng.sync()
+eng.close()
+print(json.dumps(found))
+"""
+
+
+@pytest.fixture(scope="module")
+def found():
+    r = subprocess.run([sys.executable, "-c", PROGRAM], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+    print(r.stdout, flush=True)
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+def test_a_long_head_does_not_hold_the_next_encode(found):
+    assert not found["long head done when the next encode was"]
