@@ -187,7 +187,6 @@ struct vpe_engine {
         float* lev[2] = {nullptr, nullptr};   // [T] row levels the copy u is stored against, alternating (see ln_gemm)
         hipStream_t stream = nullptr;
         hipEvent_t done = nullptr;      // completion of the lane's most recent encode
-        bool own = false;               // that encode ran on the lane's own stream
         hipEvent_t t_begin = nullptr, t_end = nullptr;   // around it (engines created with VPE_FLAG_TIMING)
         bool used = false;
     };
@@ -207,6 +206,7 @@ struct vpe_engine {
     std::vector<hipGraphExec_t> enc_graphs;   // [S][lanes]
     std::vector<Head> heads;
     std::vector<hipStream_t> head_streams;
+    bool private_streams = true;         // no call has named a stream or asked for one: all that runs on the engine's is its own
     int64_t frames = 0;
     std::string err;
 
@@ -1145,6 +1145,7 @@ int vpe_preprocess_u8(const uint8_t* frames, int batch, int src_h, int src_w, fl
 int vpe_next_encode_stream(vpe_engine* e, void** stream) {
     if (!e) return VPE_EINVAL;
     if (!stream) return e->fail(VPE_EINVAL, "stream is null");
+    e->private_streams = false;
     *stream = e->host_only ? nullptr : (void*)e->lane[e->frames % e->lanes].stream;
     return VPE_OK;
 }
@@ -1172,6 +1173,7 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
         const int ln = (int)(frame % e->lanes);
         vpe_engine::Lane& L = e->lane[ln];
         hipStream_t s = stream ? (hipStream_t)stream : L.stream;
+        if (stream) e->private_streams = false;
         // the slot's previous frame may still be read by heads (or still be written): wait on the GPU
         for (int h = 0; h < nh; ++h)
             if (e->done_set[(size_t)slot * nh + h]) HIPCHK(e, hipStreamWaitEvent(s, e->done[(size_t)slot * nh + h], 0));
@@ -1191,7 +1193,6 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
         if (e->timing) HIPCHK(e, hipEventRecord(L.t_end, s));
         HIPCHK(e, hipEventRecord(L.done, s));
         L.used = true;
-        L.own = s == L.stream;
         e->last_lane = ln;
         HIPCHK(e, hipEventRecord(e->ready[slot], s));
     }
@@ -1223,20 +1224,21 @@ bool hz_allows(Head& h, double t) {
 // The stream of a run whose caller names none.  Right behind the newest frame's own encode, in its stream, nothing has to wait for
 // another stream: light heads run there (us a frame, a stream of its own / this: ViT-S 224x224 segmentation 434 / 377, fp32 717 /
 // 677).  A long head does not, not even on an idle engine: the next encode would wait for it, whenever the host waited for
-// something else than this head.
+// something else than this head.  Nor does any head once a caller has put work of its own among the engine's (on a borrowed encoder
+// stream, or in front of a call on a stream it named): the head would wait for that work, or an encode for the head that does.
 hipStream_t stream_for(const vpe_engine* e, const Head& h, int64_t frame) {
-    const vpe_engine::Lane& L = e->lane[frame % e->lanes];
-    return h.light && frame + 1 == e->frames && L.own ? L.stream : h.stream;
+    return h.light && e->private_streams && frame + 1 == e->frames ? e->lane[frame % e->lanes].stream : h.stream;
 }
 
-// Enqueue one run of a head on the frame in `slot` (already checked to be current and due).
+// Enqueue one run of a head on the frame in `slot` (already checked to be current and due), on the caller's stream or else on `own`.
 // `sc` = the intermediate buffers to use; `replay` = false launches the kernels one by one even on an engine with
 // graphs (a replay is tied to the buffers it was captured with, and the first one instantiates a graph, which allocates).
-int start_head(vpe_engine* e, int head, int slot, int64_t frame, void* stream, const HeadScratch& sc, bool replay) {
+int start_head(vpe_engine* e, int head, int slot, int64_t frame, void* stream, hipStream_t own, const HeadScratch& sc, bool replay) {
     Head& h = e->heads[head];
     const int nh = (int)e->heads.size();
     if (!e->host_only) {
-        hipStream_t s = stream ? (hipStream_t)stream : h.stream;
+        hipStream_t s = stream ? (hipStream_t)stream : own;
+        if (stream) e->private_streams = false;
         HIPCHK(e, hipStreamWaitEvent(s, e->ready[slot], 0));
         // the head's scratch and outputs are single-instance: order after its previous run
         if (h.ran) HIPCHK(e, hipStreamWaitEvent(s, h.last_done, 0));
@@ -1271,8 +1273,7 @@ int vpe_run_head(vpe_engine* e, int head, vpe_feat fh, void* stream) {
     if (fh.frame % h.every_n != 0) { ++h.skips; return VPE_SKIPPED; }
     if (e->slot_frame[fh.slot] != fh.frame) return e->fail(VPE_ESTALE, "slot has been reused by a later frame");
     if (!hz_allows(h, e->slot_time[fh.slot])) { ++h.skips; return VPE_SKIPPED; }
-    if (!stream && !e->host_only) stream = stream_for(e, h, fh.frame);
-    return start_head(e, head, fh.slot, fh.frame, stream, h.sc, true);
+    return start_head(e, head, fh.slot, fh.frame, stream, stream_for(e, h, fh.frame), h.sc, true);
 }
 
 int vpe_run_head_static(vpe_engine* e, int head, vpe_feat fh, void* stream) {
@@ -1302,7 +1303,7 @@ int vpe_run_head_static(vpe_engine* e, int head, vpe_feat fh, void* stream) {
     if (fh.frame % h.every_n != 0) { ++h.skips; return VPE_SKIPPED; }
     if (e->slot_frame[fh.slot] != fh.frame) return e->fail(VPE_ESTALE, "slot has been reused by a later frame");
     if (!hz_allows(h, e->slot_time[fh.slot])) { ++h.skips; return VPE_SKIPPED; }
-    return start_head(e, head, fh.slot, fh.frame, stream, sc, false);
+    return start_head(e, head, fh.slot, fh.frame, stream, h.stream, sc, false);
 }
 
 int vpe_run_head_latest(vpe_engine* e, int head, void* stream, vpe_feat* ran_on) {
@@ -1333,7 +1334,7 @@ int vpe_run_head_latest(vpe_engine* e, int head, void* stream, vpe_feat* ran_on)
     const int slot = (int)(newest % e->S);
     if (h.last_run_frame >= 0 && newest - h.last_run_frame < h.every_n) { ++h.skips; return VPE_SKIPPED; }
     if (!hz_allows(h, e->slot_time[slot])) { ++h.skips; return VPE_SKIPPED; }
-    const int rc = start_head(e, head, slot, newest, stream, h.sc, true);
+    const int rc = start_head(e, head, slot, newest, stream, h.stream, h.sc, true);
     if (rc == VPE_OK && ran_on) { ran_on->slot = slot; ran_on->reserved = 0; ran_on->frame = newest; }
     return rc;
 }

@@ -1,4 +1,5 @@
-"""Which of an engine's calls wait for which, by what is done when: heads and encodes beside a depth head of tens of milliseconds.
+"""Which of an engine's calls wait for which, by what is done when: heads and encodes beside a depth head, or a caller's kernel, of tens of
+milliseconds.
 
 In a process of its own: it may use four hardware queues, one stream each for the default stream, the encoder and two heads, and
 streams that share one run in turn whatever the engine does (the other tests' process has made dozens of streams)."""
@@ -47,6 +48,40 @@ ready(eng, eng.encode(image))
 found["long head done when the next encode was"] = eng.head_done(0)
 eng.sync()
 eng.close()
+
+# a short head beside 20 ms or more of the caller's own work on the borrowed encoder stream (the next frame's copy, say), asked for
+# again or kept from before
+def borrowed_work(stream):
+    with torch.cuda.stream(torch.cuda.ExternalStream(stream)):
+        torch.cuda._sleep(50_000_000)
+        done = torch.cuda.Event()
+        done.record()
+    return done
+
+eng = engine(("seg",), ring_slots=4)
+kept = eng.next_encode_stream()
+for name, ask in (("asked for again", eng.next_encode_stream), ("kept", lambda: kept)):
+    fh = eng.encode(image)
+    work = borrowed_work(ask())
+    eng.run_head(0, fh)
+    eng.wait_head(0)
+    found["caller's work done when the head was, stream " + name] = work.query()
+    eng.sync()
+    torch.cuda.synchronize()
+eng.close()
+
+# a run behind the caller's work on a stream it named; the head's next run waits for that run, the encode behind must not
+eng = engine(("seg",), ring_slots=4)
+mine = torch.cuda.Stream()
+fh = eng.encode(image)
+work = borrowed_work(mine.cuda_stream)
+eng.run_head(0, fh, mine)
+eng.run_head(0, eng.encode(image))
+ready(eng, eng.encode(image))
+found["caller's work done when the second next encode was"] = work.query()
+eng.sync()
+torch.cuda.synchronize()
+eng.close()
 print(json.dumps(found))
 """
 
@@ -61,3 +96,12 @@ def found():
 
 def test_a_long_head_does_not_hold_the_next_encode(found):
     assert not found["long head done when the next encode was"]
+
+
+def test_heads_do_not_wait_for_the_callers_work_on_a_borrowed_stream(found):
+    assert not found["caller's work done when the head was, stream asked for again"]
+    assert not found["caller's work done when the head was, stream kept"]
+
+
+def test_encodes_do_not_wait_for_the_callers_work_in_front_of_a_head(found):
+    assert not found["caller's work done when the second next encode was"]
