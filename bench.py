@@ -317,8 +317,7 @@ def main() -> None:
         spec = vi.with_(spec, head_ch=args.head_ch)
     flags = 0 if args.no_graphs else vpe.VPE_FLAG_GRAPHS
     eng, w, hw = make_engine(spec, wseed, kinds=kinds, ring_slots=args.ring_slots, flags=flags, encoder_lanes=args.encoder_lanes)
-    heavy = max(1, sum(k in ("depth", "dpt") for k in kinds))           # (a depth head outweighs the others)
-    head_streams = min(heavy, max(1, 4 - args.encoder_lanes))           # the engine's rule (include/vpe.h, head_streams = 0)
+    head_streams = min(len(kinds), max(1, 4 - args.encoder_lanes))      # the engine's rule (include/vpe.h, head_streams = 0)
     images_np = vi.make_batch(spec, iseed)
     # two distinct resident frames, alternated, so no step can reuse the previous step's result
     frames = [torch.from_numpy(images_np).cuda(), torch.from_numpy(np.ascontiguousarray(images_np[..., ::-1])).cuda()]

@@ -101,9 +101,8 @@ typedef struct {
                               encoder passes of k consecutive frames overlap on the GPU -- throughput pipelining,
                               per-frame results are unchanged */
     int32_t head_streams; /* streams the heads are spread over (heaviest head first, onto the least loaded);
-                              0 = as many as heads whose runs take at least half as long as the longest's, within the
-                              four hardware queues a process gets by default minus the encoder lanes (at least 1).
-                              Heads sharing a stream run in call order */
+                              0 = as many as heads, within the four hardware queues a process gets by default
+                              minus the encoder lanes (at least 1).  Heads sharing a stream run in call order */
     int32_t reserved;
     const void* weights;  /* host, fp32 */
     uint64_t weights_bytes;

@@ -140,7 +140,7 @@ struct Head {
     // scheduling
     hipStream_t stream = nullptr;     // one of the engine's head streams (shared when heads outnumber them)
     hipEvent_t last_done = nullptr;   // completion of the most recent run (any slot)
-    bool light = false;               // all heads' runs together are shorter than what a waiting stream costs an encoder pass
+    bool light = false;               // its run, with those of shorter heads, is shorter than what a waiting stream costs an encoder pass
     hipEvent_t t_begin = nullptr, t_end = nullptr;   // around the most recent run (engines created with VPE_FLAG_TIMING)
     bool ran = false;
     int64_t runs = 0, skips = 0;
@@ -1082,18 +1082,7 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
         if (hip(hipEventCreateWithFlags(&e->lane[l].done, hipEventDisableTiming), "hipEventCreate")) return bail(VPE_EHIP);
     }
     if (nh > 0) {
-        // A stream that waits for a frame slows every kernel of the encoder stream down, by 0.4-0.7 us a launch and waiting
-        // stream (60 launches of 3.2 us 195 us a frame, with one stream waiting for their end 239, with two 263): heads share a stream
-        // unless several of them are about as heavy as the heaviest (us a frame, three streams / one: ViT-S 476x630 with
-        // segmentation, depth and detection 792 / 762, with the full DPT head 772 / 694, on two lanes 580 / 535, ViT-L 518x518
-        // 2807 / 2753).  All heads are light when their runs together are shorter than what one waiting stream costs a pass.
-        double heaviest = 0.0, total_us = 0.0;
-        for (const Head& h : e->heads) { heaviest = std::max(heaviest, head_us(*e, h)); total_us += head_us(*e, h); }
-        int heavy = 0;
-        for (const Head& h : e->heads) heavy += 2.0 * head_us(*e, h) >= heaviest;
-        // (several heavy ones run side by side on streams of their own, and a number of streams that the caller chose is what heads get)
-        for (Head& h : e->heads) h.light = cfg->head_streams <= 0 && total_us <= 0.7 * (5 * e->L + 3);
-        int ns = cfg->head_streams > 0 ? cfg->head_streams : std::min(heavy, std::max(1, HW_QUEUES - e->lanes));
+        int ns = cfg->head_streams > 0 ? cfg->head_streams : std::max(1, HW_QUEUES - e->lanes);
         ns = std::min(ns, nh);
         e->head_streams.assign(ns, nullptr);
         for (auto& hs : e->head_streams)
@@ -1107,6 +1096,15 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
             e->heads[i].stream = e->head_streams[k];
             load[k] += head_flops(*e, e->heads[i]);
         }
+        // A stream that waits for a frame slows every kernel of the encoder stream down, by 0.4-0.7 us a launch and waiting stream
+        // (60 launches of 3.2 us 195 us a frame, with one stream waiting for their end 239, with two 263).  The shortest heads are
+        // light (stream_for) as long as their runs together are shorter than that of a pass, us a frame, all heads on head streams /
+        // so: ViT-S 224x224 segmentation 404 / 351, 476x630 with segmentation, depth and detection 803 / 776, with the full DPT head
+        // 741 / 721, ViT-L 518x518 2643 / 2610.  One head stream for all of them would be 763, 684 and 2596, but a short head would
+        // wait for a long one.  A number of streams that the caller chose is what heads get.
+        std::sort(order.begin(), order.end(), [&](int a, int b) { return head_us(*e, e->heads[a]) < head_us(*e, e->heads[b]); });
+        double total_us = 0.0;
+        for (int i : order) e->heads[i].light = (total_us += head_us(*e, e->heads[i])) <= 0.7 * (5 * e->L + 3) && cfg->head_streams <= 0;
     }
     e->ready.assign(e->S, nullptr);
     e->done.assign((size_t)e->S * std::max(nh, 1), nullptr);
@@ -1222,8 +1220,7 @@ bool hz_allows(Head& h, double t) {
 }
 
 // The stream of a run whose caller names none.  Right behind the newest frame's own encode, in its stream, nothing has to wait for
-// another stream: light heads run there (us a frame, a stream of its own / this: ViT-S 224x224 segmentation 434 / 377, fp32 717 /
-// 677).  A long head does not, not even on an idle engine: the next encode would wait for it, whenever the host waited for
+// another stream: light heads run there (vpe_create has the rule and its figures).  A long head does not, not even on an idle engine: the next encode would wait for it, whenever the host waited for
 // something else than this head.  Nor does any head once a caller has put work of its own among the engine's (on a borrowed encoder
 // stream, or in front of a call on a stream it named): the head would wait for that work, or an encode for the head that does.
 hipStream_t stream_for(const vpe_engine* e, const Head& h, int64_t frame) {

@@ -49,6 +49,22 @@ found["long head done when the next encode was"] = eng.head_done(0)
 eng.sync()
 eng.close()
 
+# a short head behind a long one: called on the same frame, then polled on the next
+eng = engine(("depth", "det"), ring_slots=4)
+fh = eng.encode(image)
+eng.run_head(0, fh)
+eng.run_head(1, fh)
+eng.wait_head(1)
+found["long head done when the short one called behind it was"] = eng.head_done(0)
+eng.sync()
+eng.run_head(0, eng.encode(image))
+ready(eng, eng.encode(image))
+assert eng.run_head_latest(1)[0] == vpe.VPE_OK
+eng.wait_head(1)
+found["long head done when the polled one was"] = eng.head_done(0)
+eng.sync()
+eng.close()
+
 # a short head beside 20 ms or more of the caller's own work on the borrowed encoder stream (the next frame's copy, say), asked for
 # again or kept from before
 def borrowed_work(stream):
@@ -96,6 +112,11 @@ def found():
 
 def test_a_long_head_does_not_hold_the_next_encode(found):
     assert not found["long head done when the next encode was"]
+
+
+def test_short_heads_do_not_wait_for_a_long_one(found):
+    assert not found["long head done when the short one called behind it was"]
+    assert not found["long head done when the polled one was"]
 
 
 def test_heads_do_not_wait_for_the_callers_work_on_a_borrowed_stream(found):
