@@ -1483,28 +1483,33 @@ int vpe_time_kernel(vpe_engine* e, int which, int reps, float* ms_per_launch, do
     int launches = reps, rc = 0;
     Head* dh = nullptr;
     for (auto& h : e->heads) if (h.kind == VPE_HEAD_DEPTH) dh = &h;
+    // out-projection / fc2 of block 0 with the LayerScale residual epilogue (the residual stream of lane 0 accumulates over the
+    // repetitions; the next encode rewrites it)
+    auto residual = [&](bool proj) {
+        const BlockW& w = e->blk[0];
+        GemmArgs a = proj ? plain_gemm(L0.att, D, w.proj_w, w.proj_b, T, D, D) : plain_gemm(L0.hid, e->Mh, w.fc2_w, w.fc2_b, T, D, e->Mh);
+        a.epi = EPI_RESID; a.gamma = proj ? w.ls1 : w.ls2;
+        produce_stats(*e, L0, a, L0.lev[1]);
+        a.st_group = proj ? e->proj_group : e->fc2_group;
+        return launch_gemm(dt, a, A_PLAIN, s);
+    };
     auto body = [&](bool timed) -> int {
+        // QKV and fc1 read the statistics of the product in front of them
+        if (!timed && which == 0) HIPCHK(e, residual(false));
+        if (!timed && (which == 6 || which == 9)) HIPCHK(e, residual(true));
         if (timed) HIPCHK(e, hipEventRecord(t0, s));
         for (int i = 0; i < (timed ? reps : 1); ++i) {
             if (which == 0) {
-                GemmArgs a = ln_gemm(*e, L0, e->blk[0].qkv_w, e->blk[0].qkv_b, e->blk[0].qkv_s, 3 * D, L0.lev[1], nullptr);
+                GemmArgs a = ln_gemm(*e, L0, e->blk[0].qkv_w, e->blk[0].qkv_b, e->blk[0].qkv_s, 3 * D, L0.lev[1], nullptr, e->fc2_group);
                 a.epi = EPI_QKV; a.out = L0.qk; a.ldo = 2 * D; a.out2 = L0.vt; a.ntok = e->N; a.npad = e->npad; a.dim = D; a.q_scale = q_scale(dt);
                 HIPCHK(e, launch_gemm(dt, a, A_PLAIN, s));
             } else if (which == 1) {
                 AttnArgs a{L0.qk, L0.vt, L0.att, e->B, e->N, e->npad, D, e->nh, SCORE_SCALE / q_scale(dt), ATTN_PAD, e->lanes > 1};
                 HIPCHK(e, launch_attention(dt, a, s));
             } else if (which == 5 || which == 7) {
-                // out-projection / fc2 of block 0 with the LayerScale residual epilogue (the residual stream of lane 0
-                // accumulates over the repetitions; the next encode rewrites it)
-                const BlockW& w = e->blk[0];
-                GemmArgs a = which == 5 ? plain_gemm(L0.att, D, w.proj_w, w.proj_b, T, D, D)
-                                        : plain_gemm(L0.hid, e->Mh, w.fc2_w, w.fc2_b, T, D, e->Mh);
-                a.epi = EPI_RESID; a.gamma = which == 5 ? w.ls1 : w.ls2;
-                produce_stats(*e, L0, a, L0.lev[1]);
-                a.st_group = which == 5 ? e->proj_group : e->fc2_group;
-                HIPCHK(e, launch_gemm(dt, a, A_PLAIN, s));
+                HIPCHK(e, residual(which == 5));
             } else if (which == 6 || which == 9) {
-                GemmArgs a = ln_gemm(*e, L0, e->blk[0].fc1_w, e->blk[0].fc1_b, e->blk[0].fc1_s, e->F, L0.lev[1], nullptr);
+                GemmArgs a = ln_gemm(*e, L0, e->blk[0].fc1_w, e->blk[0].fc1_b, e->blk[0].fc1_s, e->F, L0.lev[1], nullptr, e->proj_group);
                 a.out = L0.hid; a.ldo = e->Mh;
                 if (which == 9) { a.N = e->Mh; }             // plain store of the first mlp_hidden columns: no activation
                 else if (e->cfg.mlp_kind == VPE_MLP_SWIGLU) a.epi = EPI_SWIGLU;

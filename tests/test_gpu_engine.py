@@ -7,7 +7,7 @@ import torch
 
 import paper_2508_11584_amd as vpe
 import vpe_inputs as vi
-from helpers import make_engine
+from helpers import make_engine, relerr
 
 pytestmark = pytest.mark.gpu
 
@@ -374,6 +374,36 @@ def test_head_completion_query_and_stage_times():
     eng.sync()
     assert torch.equal(eng.head_output(0, 1), seg)
     eng.close()
+
+
+@pytest.mark.parametrize("dtype,name,tiles", [("bf16", "VPE_GEMM_TILE", ("3", "34")), ("f32", "VPE_GEMM_TILE_F32", ("4", "6"))])
+def test_timed_products_read_the_statistics_as_the_frame_does(dtype, name, tiles, monkeypatch):
+    # QKV and fc1 timed on one frame's activations, with LayerNorm statistics of 64 and of 32 columns: the same results up to rounding
+    # (statistics of 32 columns read as of 64 are half the variance of other rows).  The buffers lie in front of the feature ring
+    spec = vi.with_(SPEC, dtype=dtype, batch=2)
+    esz, rows = (2 if dtype == "bf16" else 4), spec.batch * spec.tokens
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    image = torch.from_numpy(vi.make_batch(spec, 310)).cuda()
+    got = []
+    for tile in tiles:
+        monkeypatch.setenv(name, tile)
+        eng, _, _ = make_engine(spec, 24, kinds=("seg",))
+        fh = eng.encode(image)
+        eng.sync()
+        hid = eng.feat_ptr(fh, 0) - eng._ws.data_ptr() - up(rows * spec.mlp_hidden * esz)
+        npad = (spec.tokens + 63) // 64 * 64
+        qk = hid - up(rows * spec.dim * esz) - up((spec.batch * spec.dim * npad + 512) * esz) - up((rows + 512) * 2 * spec.dim * esz)
+        for which, at, count in ((0, qk, rows * 2 * spec.dim), (6, hid, rows * spec.mlp_hidden)):
+            eng._ws[at:at + count * esz].fill_(0)
+            torch.cuda.synchronize()
+            eng.time_kernel(which, 1)
+            torch.cuda.synchronize()
+            got.append(eng._ws[at:at + count * esz].clone().view(torch.bfloat16 if dtype == "bf16" else torch.float32).float().cpu().numpy())
+        eng.close()
+    for wide, narrow in zip(got[:2], got[2:]):
+        err = relerr(narrow, wide)
+        print("timed", dtype, err, flush=True)
+        assert np.max(np.abs(wide)) > 0 and err <= (2e-2 if dtype == "bf16" else 1e-4)
 
 
 def test_sync_waits_for_work_on_caller_streams_too():
