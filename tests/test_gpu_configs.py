@@ -73,6 +73,15 @@ def test_cfg5_shapes_vitg_swiglu_batch8_four_blocks():
     check_all(spec, 1005, 2008, batch_check=(0, 7))
 
 
+@pytest.mark.parametrize("cfg,grid,batch,depth", [("cfg4", 8, 1, 10), ("cfg4", 37, 1, 10), ("cfg5", 8, 1, 4), ("cfg5", 37, 2, 4)])
+def test_attention_launches_that_read_the_following_weights_ahead(cfg, grid, batch, depth):
+    # more than 200 MiB of block weights and at most 4096 rows: the attention launches read out-projection, fc1 (SwiGLU: twice the rows)
+    # and fc2 ahead, up to 2048 rows (69, 1374 and 69 here, 2748 in the last case) beside the tapped rows of the block before
+    spec = vi.with_(vi.CONFIGS[cfg], name="ahead_%s_%d" % (cfg, grid), depth=depth, taps=(1, 2, 3, depth), img_h=14 * grid, img_w=14 * grid, batch=batch)
+    assert spec.depth * spec.dim * (4 * spec.dim + spec.fc1_out + spec.mlp_hidden) * 2 > 200 << 20 and spec.batch * spec.tokens <= 4096
+    check_all(spec, 1004, 2004, kinds=("seg",), batch_check=(batch - 1,))
+
+
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("cfg", ["cfg4", "cfg5"])
 def test_full_depth_large_configs_match_the_oracle_and_are_consistent(cfg):
