@@ -203,7 +203,8 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
  * Control" for the rate).  Enqueues head `head` on the features of frame fh, in place, on `stream` (NULL = an
  * engine stream: the head's, or with head_streams = 0 that of the frame's encoder lane, right behind the newest frame's
  * encode, for heads that are short beside an encoder pass, as long as no call on this engine has named a stream or asked
- * for one with vpe_next_encode_stream: never behind work of the caller's)
+ * for one with vpe_next_encode_stream: never behind work of the caller's; nor where its last run, on an older frame or
+ * polled, may still be behind a longer head's in the stream that the two share)
  * after the frame's encoder pass and the head's previous run.  Returns VPE_SKIPPED when
  * fh.frame % every_n != 0 or a limit in Hz says the frame is not due, VPE_ESTALE when the slot has been reused by
  * a later frame, VPE_EINVAL for an unknown head or a handle this engine did not produce, VPE_EHIP. */

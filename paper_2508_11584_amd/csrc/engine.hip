@@ -141,6 +141,8 @@ struct Head {
     hipStream_t stream = nullptr;     // one of the engine's head streams (shared when heads outnumber them)
     hipEvent_t last_done = nullptr;   // completion of the most recent run (any slot)
     bool light = false;               // its run, with those of shorter heads, is shorter than what a waiting stream costs an encoder pass
+    bool beside_long = false;         // a head that is not light has the same head stream
+    bool held = false;                // its last run may be behind one of that head's (until the host has seen it done)
     hipEvent_t t_begin = nullptr, t_end = nullptr;   // around the most recent run (engines created with VPE_FLAG_TIMING)
     bool ran = false;
     int64_t runs = 0, skips = 0;
@@ -1105,6 +1107,8 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
         std::sort(order.begin(), order.end(), [&](int a, int b) { return head_us(*e, e->heads[a]) < head_us(*e, e->heads[b]); });
         double total_us = 0.0;
         for (int i : order) e->heads[i].light = (total_us += head_us(*e, e->heads[i])) <= 0.7 * (5 * e->L + 3) && cfg->head_streams <= 0;
+        for (Head& h : e->heads)
+            for (const Head& other : e->heads) h.beside_long |= !other.light && other.stream == h.stream;
     }
     e->ready.assign(e->S, nullptr);
     e->done.assign((size_t)e->S * std::max(nh, 1), nullptr);
@@ -1221,10 +1225,11 @@ bool hz_allows(Head& h, double t) {
 
 // The stream of a run whose caller names none.  Right behind the newest frame's own encode, in its stream, nothing has to wait for
 // another stream: light heads run there (vpe_create has the rule and its figures).  A long head does not, not even on an idle engine: the next encode would wait for it, whenever the host waited for
-// something else than this head.  Nor does any head once a caller has put work of its own among the engine's (on a borrowed encoder
+// something else than this head.  Nor does a light head whose previous run, on an older frame or polled, is behind a long one's on their
+// head stream.  Nor does any head once a caller has put work of its own among the engine's (on a borrowed encoder
 // stream, or in front of a call on a stream it named): the head would wait for that work, or an encode for the head that does.
 hipStream_t stream_for(const vpe_engine* e, const Head& h, int64_t frame) {
-    return h.light && e->private_streams && frame + 1 == e->frames ? e->lane[frame % e->lanes].stream : h.stream;
+    return h.light && !h.held && e->private_streams && frame + 1 == e->frames ? e->lane[frame % e->lanes].stream : h.stream;
 }
 
 // Enqueue one run of a head on the frame in `slot` (already checked to be current and due), on the caller's stream or else on `own`.
@@ -1251,6 +1256,7 @@ int start_head(vpe_engine* e, int head, int slot, int64_t frame, void* stream, h
         hipEvent_t ev = e->done[(size_t)slot * nh + head];
         HIPCHK(e, hipEventRecord(ev, s));
         h.last_done = ev;
+        h.held = s == h.stream && h.beside_long;
     }
     e->done_set[(size_t)slot * nh + head] = 1;
     h.ran = true;
@@ -1411,28 +1417,32 @@ int vpe_sync(vpe_engine* e) {
     // vpe_frame_ready answer VPE_OK for every frame as soon as this returns)
     for (int sl = 0; sl < e->S; ++sl)
         if (e->slot_frame[sl] >= 0) HIPCHK(e, hipEventSynchronize(e->ready[sl]));
-    for (Head& h : e->heads)
+    for (Head& h : e->heads) {
         if (h.ran) HIPCHK(e, hipEventSynchronize(h.last_done));
+        h.held = false;
+    }
     return VPE_OK;
 }
 
 int vpe_head_done(vpe_engine* e, int head) {
     if (!e) return VPE_EINVAL;
     if (head < 0 || head >= (int)e->heads.size()) return e->fail(VPE_EINVAL, "unknown head");
-    const Head& h = e->heads[head];
+    Head& h = e->heads[head];
     if (e->host_only || !h.ran) return VPE_OK;
     const hipError_t q = hipEventQuery(h.last_done);
     if (q == hipErrorNotReady) return VPE_BUSY;
     HIPCHK(e, q);
+    h.held = false;
     return VPE_OK;
 }
 
 int vpe_wait_head(vpe_engine* e, int head) {
     if (!e) return VPE_EINVAL;
     if (head < 0 || head >= (int)e->heads.size()) return e->fail(VPE_EINVAL, "unknown head");
-    const Head& h = e->heads[head];
+    Head& h = e->heads[head];
     if (e->host_only || !h.ran) return VPE_OK;
     HIPCHK(e, hipEventSynchronize(h.last_done));
+    h.held = false;
     return VPE_OK;
 }
 

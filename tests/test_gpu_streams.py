@@ -1,8 +1,8 @@
 """Which of an engine's calls wait for which, by what is done when: heads and encodes beside a depth head, or a caller's kernel, of tens of
 milliseconds.
 
-In a process of its own: it may use four hardware queues, one stream each for the default stream, the encoder and two heads, and
-streams that share one run in turn whatever the engine does (the other tests' process has made dozens of streams)."""
+In a process of its own, with five hardware queues: one each for the default stream and an engine's four, since streams that share
+one run in turn whatever the engine does (the other tests' process has made dozens of streams)."""
 import json
 import os
 import subprocess
@@ -65,6 +65,20 @@ found["long head done when the polled one was"] = eng.head_done(0)
 eng.sync()
 eng.close()
 
+# a short head that shares a long one's stream: behind it on an older frame, then called on the newest, whose lane encodes on
+eng = engine(("depth", "seg"), encoder_lanes=3, ring_slots=8)
+older = eng.encode(image)
+eng.run_head(0, older)
+newest = eng.encode(image)
+eng.run_head(1, older)
+eng.run_head(1, newest)
+for _ in range(3):
+    fh = eng.encode(image)
+ready(eng, fh)
+found["long head done when the lanes' next encodes were"] = eng.head_done(0)
+eng.sync()
+eng.close()
+
 # a short head beside 20 ms or more of the caller's own work on the borrowed encoder stream (the next frame's copy, say), asked for
 # again or kept from before
 def borrowed_work(stream):
@@ -104,7 +118,7 @@ print(json.dumps(found))
 
 @pytest.fixture(scope="module")
 def found():
-    r = subprocess.run([sys.executable, "-c", PROGRAM], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    r = subprocess.run([sys.executable, "-c", PROGRAM], cwd=ROOT, env={**os.environ, "GPU_MAX_HW_QUEUES": "5"}, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stdout + r.stderr
     print(r.stdout, flush=True)
     return json.loads(r.stdout.splitlines()[-1])
@@ -117,6 +131,10 @@ def test_a_long_head_does_not_hold_the_next_encode(found):
 def test_short_heads_do_not_wait_for_a_long_one(found):
     assert not found["long head done when the short one called behind it was"]
     assert not found["long head done when the polled one was"]
+
+
+def test_a_short_head_behind_a_long_one_does_not_hold_the_next_encodes(found):
+    assert not found["long head done when the lanes' next encodes were"]
 
 
 def test_heads_do_not_wait_for_the_callers_work_on_a_borrowed_stream(found):
