@@ -25,7 +25,7 @@
  *   - an engine may be driven from one host thread at a time.
  *
  * Throughput.  With the defaults (encoder_lanes = 1) frames pass through the encoder one after another and a
- * ViT-S pass leaves most of the 256 compute units idle (about 1340 frames/s at 476x630 with three heads).  The
+ * ViT-S pass leaves most of the 256 compute units idle (about 1300 frames/s at 476x630 with three heads).  The
  * pipelined rate the benchmark reports (about 2100 frames/s) needs encoder_lanes = 3 and ring_slots = 4 (lanes + 1),
  * which makes the engine use 3 encoder streams + 1 head stream, AND a process that may use five hardware queues:
  * export GPU_MAX_HW_QUEUES=5 before the HIP runtime initialises (the runtime's default of 4 leaves three for the

@@ -114,9 +114,8 @@ template <> struct AttnMma<bf16> {
     // a V^T row (one conflict-free ds_read_b128 per accumulator and step).  The reads of step + 1 are issued before
     // the MFMAs of step.
     // Row sums (sum2) take the same rounded probabilities as the numerator, two keys per instruction.  On the matrix pipe,
-    // as a product with ones, they were a fifth of its work and 20 registers: without them the four-wave shapes fit 128
-    // registers, four waves per SIMD (ViT-g x 8 122.2 -> 116.6 us, with the vector work before, between and behind the
-    // MFMAs below instead of behind each of them 116.1).
+    // as a product with ones, they were a fifth of its work and 20 registers (ViT-g x 8, references that move: 122.2 -> 116.6 us, with the
+    // vector work before, between and behind the MFMAs below instead of behind each of them 116.1).
     // `sc` holds the raw scores; element e becomes 2^(sc[e] * scale - ref), DONE: 2^sc[e].  The exponentials of step + 1 are issued
     // behind the MFMAs of step, so the vector pipe works on them while the matrix pipe runs.  psum
     // receives the lane's sum of probabilities.
@@ -414,9 +413,15 @@ __global__ __launch_bounds__(64 * QW * KW, (attn_min_waves<T, QB, QW, KW>())) vo
     // FIXED (the kernel's first sweep; `fixed` here): every query's reference is the maximum of its wave's first tile and stays.  A probability only has to be
     // representable: up to 2^64 above the reference fp32 sums and bf16 probabilities are as precise as at 2^0, so no later tile looks for a
     // maximum, and the reference is what its products start from (-reference in the accumulators: the scores leave the matrix pipe as
-    // exponents).  A workgroup that met more than that starts again with references that move.  Of a tile's 126
-    // vector instructions a lane 64 are left, all of them among the second products (us, references that move / that stay: ViT-S
+    // exponents).  A workgroup that met more than that starts again with references that move.  A wave of ViT-g (22 tiles) issues
+    // 2717 vector instructions instead of 3710, its 352 products included (us, references that move / that stay: ViT-S
     // 1531 tokens 12.4 / 11.5, ViT-B 1370 17.0 / 15.6, ViT-L 1374 17.8 / 16.8, x 4 43.1 / 39.3, ViT-g x 8 118 / 108).
+    // Not further than 2^64: waves' sums meet in a merge whose factors, 2^(difference of references), underflow from 2^-126 on, and
+    // a sum that is dropped there has to be nothing beside the other's.
+    // Starting again costs the launch a second sweep, as long as a workgroup of every round of the CUs does it (us, flat scores / one query
+    // of every head above 2^64 / all; with references that move always: ViT-S 476x476 9.0 / 15.6 / 16.1; 9.3, 476x630 11.9 / 20.9 / 21.3; 12.6,
+    // ViT-B 518x518 16.1 / 25.1 / 29.6; 17.3, ViT-L x 4 39.9 / 54.0 / 74.3; 43.3, ViT-g x 8 108 / 130 / 219; 120).  It takes a score 44
+    // (64 in log2 units) above all of a wave's first 64 keys.
     auto sweep = [&](auto mma, auto fixed) {
         using M = decltype(mma);
         constexpr bool FIRST = decltype(fixed)::value;

@@ -73,10 +73,15 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
     // 11891 / 11611 us, ViT-S 476x630 x 4 1655 / 1610, ViT-L 518x518 x 2 4912 / 4804); more want four query waves sharing each key
     // tile, three to a CU, and no merge.  Wider workgroups (eight query waves, or two query blocks per wave) halve the
     // L2 -> LDS traffic and are slower all the same; narrower ones (two waves) double it and are slower too.
-    // Beside another encoder lane's kernels the footprint counts for more than the time alone.  Frames of two lanes, us, in the
-    // order of the table: ViT-S 224x224 243 248 247, 308x308 251 258 258, 476x476 with a depth head 495 477 481, ViT-B 308x308 (192
-    // pairs) 371 370 371, 476x476 844 772 764; so (1,1,4) where both lanes' workgroups find a CU each, (1,2,2) up to the line
-    // of (1,4,1).  (Two-lane figures from before references that stay, attention.h.)
+    // Beside another encoder lane's kernels the footprint counts for more than the time alone.  Encoder passes on two lanes, us, in the
+    // order of the table:
+    //     54  ViT-S 224x224   196  199  201  205        222  ViT-S 476x476       331  306  305  325      1032  ViT-B 518x518 x 2  1275 1163 1102 1075
+    //     96  ViT-S 308x308   229  223  228  239        288  ViT-S 476x630       407  362  348  371      1152  ViT-S 476x630 x 4  1033  898  845  812
+    //    150  ViT-S 392x392   270  266  269  283        444  ViT-B 476x476       637  560  539  556      1376  ViT-L 518x518 x 2  3410 3085 2955 2855
+    //    192  ViT-B 308x308   341  331  334  331        516  ViT-B 518x518       720  636  614  604
+    //    688  ViT-L 518x518  1975 1823 1731 1744        696  ViT-B 602x602       935  826  778  772
+    // so (1,1,4) where both lanes' workgroups find a CU each, then (1,2,2) up to the line of (1,4,1), above which the last column is.  At 96,
+    // 150 and 516 pairs another shape is 1-2.5 % faster.
     const int64_t heads = (int64_t)a.B * a.heads, qblocks = cdiv(a.N, 32) * heads;
     int variant = cdiv(a.N, 64) * heads > 512 ? 141 : qblocks <= (a.shared_gpu ? 128 : 256) ? 114 : a.shared_gpu || cdiv(a.N, 64) * heads > 256 ? 122 : 124;
     if (forced) variant = forced;

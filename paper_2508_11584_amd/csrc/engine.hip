@@ -716,7 +716,10 @@ int residual_group(const vpe_engine& e, int k) {
 // 7070 / 6340, two lanes 5132 / 5144, 224x224 2810 / 2680.  With the next block's QKV weights as well ViT-g 6530, two lanes 5360.  64
 // workgroups are too few for 224x224 of ViT-g (3000), 16 and 32 slow every size down.
 constexpr int64_t TOUCH_BYTES = 200 << 20;      // of block weights, from which on they are read ahead
-constexpr int TOUCH_ROWS = 4096;                // more rows than that: the products are long, the attention leaves no room (ViT-L x 4 5845 / 6038)
+// Rows up to which they are: 1854 of ViT-L 2808 / 2650, 2088 (224x224 x 8) 3420 / 2900, 3708 (602x602 x 2) 4545 / 4320, two lanes
+// 4562 / 4350, 3912 (308x308 x 8) 4283 / 3948, ViT-g 2748 10300 / 10200, two lanes 10250 / 10160, 3708 12190 / 12180; 5496 (ViT-L x 4) 5845 / 6038:
+// the products are long, the attention leaves no room.
+constexpr int TOUCH_ROWS = 4096;
 constexpr int TOUCH_BLOCKS = 128;
 Touch next_weights(const vpe_engine& e, int l) {
     const BlockW& w = e.blk[l];
@@ -785,7 +788,8 @@ int enqueue_encoder_body(vpe_engine& e, int slot, int lane, hipStream_t s) {
         if (tap < 4 && l + 1 == e.cfg.taps[tap]) {
             // Up to 2048 rows in the next block's attention launch, which reads other buffers and leaves room on the chip: a launch of its
             // own is 3.3-4.8 us of the chain.  us a pass, launches of their own / so: ViT-S 224x224 362.5 / 358.4, fp32 659 / 645, 476x630
-            // 558 / 546, ViT-B 518x518 907 / 893, 252x406 x 3 870 / 864, ViT-L 518x518 2499 / 2488.  Behind an attention that fills the chip
+            // 558 / 546, 602x602 627 / 619, fp32 1673 / 1664, 224x224 x 7 560 / 558, ViT-B 518x518 907 / 893, 252x406 x 3 870 / 864, 602x602 1043 / 1035,
+            // ViT-L 518x518 2499 / 2488, 602x602 2626 / 2626; two lanes ViT-S 476x630 621 / 609, ViT-B 518x518 636 / 629.  Behind an attention that fills the chip
             // they take longer than a launch (ViT-L x 4, 5496 rows, 5295 / 5345; ViT-g x 8 29780 / 29940).
             if (l + 1 < e.L && T <= 2048) norm = RowNorm{L.x, e.norm_g, e.norm_b, e.feat[slot * 4 + tap], T, D, e.cfg.ln_eps, 0};
             else HIPCHK(&e, launch_layernorm(dt, L.x, T, D, e.norm_g, e.norm_b, e.cfg.ln_eps, e.feat[slot * 4 + tap], s));

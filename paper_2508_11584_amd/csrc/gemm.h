@@ -377,7 +377,7 @@ __device__ __forceinline__ void store_tokens8(const GemmArgs& p, T* vt, int r, i
 }
 
 // (mean, rstd) of a row from its group statistics (mean_g, M2_g = sum of squared deviations from mean_g, of
-// each 64-column group), one thread per tile row.  Groups are merged around the first group's mean, so a level common to
+// each group of 64 or 32 columns), one thread per tile row.  Groups are merged around the first group's mean, so a level common to
 // the whole row cancels before anything is squared:
 //   mean = m_0 + avg_g (m_g - m_0),   M2 = sum_g M2_g + W (sum_g (m_g - m_0)^2 - G (mean - m_0)^2),  G groups of W columns.
 // In two parts, so that the loads are under way while the accumulators are staged: `fetch` asks for the statistics, `merge`
