@@ -202,7 +202,7 @@ int vpe_encode_at(vpe_engine* e, const float* images, void* stream, double t_sec
  * reference, runs its model and leaves its post-processed result in its output buffer; Sec. "Dynamic Frequency
  * Control" for the rate).  Enqueues head `head` on the features of frame fh, in place, on `stream` (NULL = an
  * engine stream: the head's, or with head_streams = 0 that of the frame's encoder lane, right behind the newest frame's
- * encode, for heads that are short beside an encoder pass, as long as no call on this engine has named a stream or asked
+ * encode, for heads that are short beside an encoder pass (several lanes: if all are), as long as no call on this engine has named a stream or asked
  * for one with vpe_next_encode_stream: never behind work of the caller's; nor where its last run, on an older frame or
  * polled, may still be behind a longer head's in the stream that the two share)
  * after the frame's encoder pass and the head's previous run.  Returns VPE_SKIPPED when

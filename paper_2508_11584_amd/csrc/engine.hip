@@ -1107,15 +1107,16 @@ int vpe_create(const vpe_backbone_cfg* cfg, const vpe_head_cfg* heads, int n_hea
         // light (stream_for) as long as their runs together are shorter than that of a pass, us a frame, all heads on head streams /
         // so: ViT-S 224x224 segmentation 405 / 352, with a depth head 458 / 433, 476x630 with segmentation, depth and detection 763 / 762,
         // fp32 2390 / 2368, 602x602 838 / 823, with the full DPT head 703 / 720 in a process of its own, 740 / 715 in one that has
-        // had other engines, ViT-L 518x518 2512 / 2493; three lanes 476x630 482 / 477, full DPT 508 / 459.  Two lanes and a long head are faster
-        // with all on head streams (224x224 239 / 257, 476x630 534 / 552, ViT-B 518x518 844 / 861, at rates 1, 2, 3 4963 / 5036), without one as
-        // above (224x224 240 / 210).  One head stream for all would be faster still, but a short head would wait for a long
-        // one.  A number of streams that the caller chose is what heads get.
+        // had other engines, ViT-L 518x518 2512 / 2493, two lanes 224x224 240 / 210.  With several lanes and a long head none is: a
+        // short head then waits for its previous run in another lane's stream, behind an encode that may wait for the long head (its
+        // slot is read), and the lane's next encode with it (two lanes are faster so, 476x630 534 / 552, ViT-B 518x518 844 / 861; three
+        // 476 / 476, 224x224 with a depth head 177 / 185, with the full DPT head 511 / 464).  One head stream for all would be faster still, but a short head would wait for a
+        // long one.  A number of streams that the caller chose is what heads get.
         std::sort(order.begin(), order.end(), [&](int a, int b) { return head_us(*e, e->heads[a]) < head_us(*e, e->heads[b]); });
         const double limit = 0.7 * (5 * e->L + 3);
         double total_us = 0.0;
         for (int i : order) e->heads[i].light = (total_us += head_us(*e, e->heads[i])) <= limit && cfg->head_streams <= 0;
-        if (e->lanes == 2 && total_us > limit)
+        if (e->lanes > 1 && total_us > limit)
             for (Head& h : e->heads) h.light = false;
         for (Head& h : e->heads)
             for (const Head& other : e->heads) h.beside_long |= !other.light && other.stream == h.stream;
